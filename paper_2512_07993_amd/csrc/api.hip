@@ -52,7 +52,7 @@ int check_params(const skipkv_cache *c, const skipkv_params *p, RowLayout *rl) {
   const int n = c->n_kv_heads > 0 ? c->n_q_heads / c->n_kv_heads : 1;
   if (!make_row_layout(n, p->obs_window, rl)) return SKIPKV_ECAPACITY;
   if (c->dtype == SKIPKV_F32 && rl->rows > 160) return SKIPKV_ECAPACITY;  // fp32 query tile would not fit in LDS
-  rl->rows = scan_two_pass_rows(*rl, c->dtype);
+  rl->rows2 = scan_two_pass_rows(*rl, c->dtype);
   return SKIPKV_OK;
 }
 
@@ -69,6 +69,7 @@ Workspace carve(const skipkv_cache *c, const RowLayout &rl, void *base) {
   w.ni_max = (int32_t)std::min<size_t>(spans_max / kItemSpans + B + 1, (size_t)0x7FFFFFFF);
   w.fits = w.nc_max <= kHdrMaxChunks && spans_max / kItemSpans + B + 1 <= (size_t)kHdrMaxItems && w.nrb_max <= kHdrMaxRowBlocks;
   w.rows = rl.rows;
+  w.rows2 = rl.rows2;
   size_t off = 0;
   char *p = static_cast<char *>(base);
   auto take = [&](size_t bytes) {
@@ -86,9 +87,9 @@ Workspace carve(const skipkv_cache *c, const RowLayout &rl, void *base) {
   w.item_rec = static_cast<int32_t *>(take((size_t)w.ni_max * kItemRecInts * 4));
   w.chunks = static_cast<Chunk *>(take((size_t)w.nc_max * sizeof(Chunk)));
   w.rowblocks = static_cast<RowBlock *>(take((size_t)w.nrb_max * sizeof(RowBlock)));
-  w.stat_part = static_cast<float2 *>(take(LH * w.nc_max * rl.rows * sizeof(float2)));
+  w.stat_part = static_cast<float2 *>(take(LH * w.nc_max * rl.rows2 * sizeof(float2)));
   w.item_stat = static_cast<float2 *>(take(LH * w.ni_max * rl.rows * sizeof(float2)));
-  w.row_norm = static_cast<float *>(take(LH * B * rl.rows * sizeof(float)));
+  w.row_norm = static_cast<float *>(take(LH * B * rl.rows2 * sizeof(float)));
   w.vhat_hi = static_cast<uint16_t *>(take(LH * S * kD * 2));
   w.vhat_lo = static_cast<uint16_t *>(take(LH * S * kD * 2));
   w.sent_imp = static_cast<float *>(take(LH * S * 4));

@@ -87,14 +87,14 @@ struct Workspace {
   int32_t *item_rec;     // [ni_max][kItemRecInts] one record per item of the single-pass scan (ItemRec)
   Chunk *chunks;         // [nc_max]
   RowBlock *rowblocks;   // [nrb_max]
-  float2 *stat_part;     // [LH, nc_max, R]  two-pass scan: per-chunk (max, sum) of every query row, log2 domain
+  float2 *stat_part;     // [LH, nc_max, R2]  two-pass scan: per-chunk (max, sum) of every query row, log2 domain
   float2 *item_stat;     // [LH, ni_max, R]  single-pass scan: per-item (reference, sum) of every query row; the plan presets .x of the used records to kRowNormUnset
-  float *row_norm;       // [LH, B, R]       two-pass scan: log2 of the softmax normaliser of every query row
+  float *row_norm;       // [LH, B, R2]      two-pass scan: log2 of the softmax normaliser of every query row
   uint16_t *vhat_hi;     // [LH, S_total, 128] bf16 high part of the unit sentence embedding
   uint16_t *vhat_lo;     // [LH, S_total, 128] bf16 low part (residual)
   float *sent_imp;       // [LH, S_total]    mean token importance over the candidate span
   float *sent_red;       // [LH, S_total]    mean token redundancy over the candidate span
-  int32_t nc_max, ni_max, nrb_max, rows;  // rows = R, padded query rows per head
+  int32_t nc_max, ni_max, nrb_max, rows, rows2;  // rows = R, padded query rows per head; rows2 = R2, the same for the two-pass scan
   bool fits;                      // the counts fit the packed range counters of the plan header
   size_t bytes;
 };
@@ -108,6 +108,7 @@ struct RowLayout {
   int al;    // window queries per lane group = ceil(alpha / 4)
   int nt;    // row tiles of 16 rows
   int rows;  // nt * 16
+  int rows2; // rows of the two-pass scan's statistics arrays (scan_two_pass_rows)
 };
 
 inline bool make_row_layout(int n, int alpha, RowLayout *out) {
@@ -119,7 +120,7 @@ inline bool make_row_layout(int n, int alpha, RowLayout *out) {
   out->np = np;
   out->al = al;
   out->nt = (np * al + 3) / 4;
-  out->rows = out->nt * 16;
+  out->rows = out->rows2 = out->nt * 16;
   return true;
 }
 
@@ -202,10 +203,12 @@ struct ScanArgs {
 };
 bool scan_fused_supported(const RowLayout &rl, int64_t row_pitch_bytes);
 hipError_t launch_scan_fused(const ScanArgs &a, hipStream_t st);    // single pass over K (sequences the plan marked fused)
-int scan_two_pass_rows(const RowLayout &rl, int dtype);  // rows of the statistics arrays that the two-pass scan of this shape needs (>= rl.rows)
+int scan_two_pass_rows(const RowLayout &rl, int dtype);  // rows of the statistics arrays that the two-pass scan of this shape has
 hipError_t launch_scan_stats(const ScanArgs &a, hipStream_t st);    // pass A: row statistics + sentence embeddings
-hipError_t launch_row_norm(const ScanArgs &a, hipStream_t st);      // combine the per-chunk statistics
+hipError_t launch_row_norm(const ScanArgs &a, hipStream_t st);      // combine the records of pass A
 hipError_t launch_scan_scores(const ScanArgs &a, hipStream_t st);   // pass B: token importance, sentence means
+hipError_t launch_rows_stats(const ScanArgs &a, hipStream_t st);    // ... passes A and B for bf16 caches (scan_rows.hip)
+hipError_t launch_rows_scores(const ScanArgs &a, hipStream_t st);
 
 struct CosineArgs {
   int32_t n_lh, batch, total_sentences, protect;

@@ -25,29 +25,18 @@ struct Tr<SKIPKV_F32> {
 // pieces.
 template <int DT, int NT>
 __device__ __forceinline__ void tile_logits(const char *qt, const char *krow, int c16, int g, f32x4 (&acc)[NT]) {
+  static_assert(DT == SKIPKV_F32, "the bf16 scans keep their query fragments in registers");
   constexpr int LSTR = Tr<DT>::LSTR;
-  if constexpr (DT == SKIPKV_BF16) {
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk) {
-      const bf16x8 bfrag = *reinterpret_cast<const bf16x8 *>(krow + g * 64 + kk * 16);
+  for (int c = 0; c < 8; ++c) {
+    const float4 bfrag = *reinterpret_cast<const float4 *>(krow + c * 64 + g * 16);
 #pragma unroll
-      for (int T = 0; T < NT; ++T) {
-        const bf16x8 afrag = *reinterpret_cast<const bf16x8 *>(qt + (16 * T + c16) * LSTR + g * 64 + kk * 16);
-        acc[T] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(afrag, bfrag, acc[T], 0, 0, 0);
-      }
-    }
-  } else {
-#pragma unroll
-    for (int c = 0; c < 8; ++c) {
-      const float4 bfrag = *reinterpret_cast<const float4 *>(krow + c * 64 + g * 16);
-#pragma unroll
-      for (int T = 0; T < NT; ++T) {
-        const float4 afrag = *reinterpret_cast<const float4 *>(qt + (16 * T + c16) * LSTR + c * 64 + g * 16);
-        acc[T] = __builtin_amdgcn_mfma_f32_16x16x4f32(afrag.x, bfrag.x, acc[T], 0, 0, 0);
-        acc[T] = __builtin_amdgcn_mfma_f32_16x16x4f32(afrag.y, bfrag.y, acc[T], 0, 0, 0);
-        acc[T] = __builtin_amdgcn_mfma_f32_16x16x4f32(afrag.z, bfrag.z, acc[T], 0, 0, 0);
-        acc[T] = __builtin_amdgcn_mfma_f32_16x16x4f32(afrag.w, bfrag.w, acc[T], 0, 0, 0);
-      }
+    for (int T = 0; T < NT; ++T) {
+      const float4 afrag = *reinterpret_cast<const float4 *>(qt + (16 * T + c16) * LSTR + c * 64 + g * 16);
+      acc[T] = __builtin_amdgcn_mfma_f32_16x16x4f32(afrag.x, bfrag.x, acc[T], 0, 0, 0);
+      acc[T] = __builtin_amdgcn_mfma_f32_16x16x4f32(afrag.y, bfrag.y, acc[T], 0, 0, 0);
+      acc[T] = __builtin_amdgcn_mfma_f32_16x16x4f32(afrag.z, bfrag.z, acc[T], 0, 0, 0);
+      acc[T] = __builtin_amdgcn_mfma_f32_16x16x4f32(afrag.w, bfrag.w, acc[T], 0, 0, 0);
     }
   }
 }

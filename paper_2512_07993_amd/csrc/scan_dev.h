@@ -92,4 +92,38 @@ __device__ __forceinline__ float row16_sum_fast(float v) {
 }
 #undef SKIPKV_DPP_STEP
 
+typedef __attribute__((__vector_size__(4 * sizeof(short)))) short i16x4;
+typedef const __attribute__((address_space(4))) int32_t *ConstIntPtr;  // constant while the kernel runs: scalar loads
+
+// Swizzle of 256-byte rows in LDS: the 16-byte piece p of row r is kept at piece position p ^ swz16(r).  Bits (r0, r1, r2, r3) of the row number go to
+// bits (1, 2, 0, 3) of the piece number.  A permutation of bits, hence linear over XOR:
+// swz(a ^ b) = swz(a) ^ swz(b).
+__host__ __device__ constexpr int swz16(int r) { return ((r & 3) << 1) | ((r >> 2) & 1) | (r & 8); }
+
+// Transposing LDS read: the 16 lanes of a group hand in 16 addresses of 4 consecutive 16-bit
+// elements each, read as a 4 x 16 matrix (lanes 4i .. 4i+3 hold row i); lane n gets column n.
+__device__ __forceinline__ i16x4 lds_read_tr16(uint32_t addr) {
+  return __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) i16x4 *)(uintptr_t)addr);
+}
+
+// A uniform 64-bit address as a scalar register pair (the compiler may hold it in vector registers).
+__device__ __forceinline__ uint64_t scalar64(const void *p_) {
+  const uint64_t p = (uint64_t)(uintptr_t)p_;
+  return ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(p >> 32)) << 32) | (uint32_t)__builtin_amdgcn_readfirstlane((int)p);
+}
+// Direct HBM -> LDS load with a scalar base and a 32-bit offset per lane.  The base may come straight from a
+// v_readfirstlane or v_readlane: a vector-memory instruction may read such a register 5 wait states later at
+// the earliest, and the compiler, which keeps that distance for its own instructions, does not look into this
+// one; hence the s_nop.
+__device__ __forceinline__ void load_to_lds_16_sbase(uint64_t sbase, uint32_t voff, void *wave_lds_base) {
+  const uint32_t l = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)wave_lds_base;
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(l), "v"(voff), "s"(sbase) : "memory");
+}
+
+// The same for one dword per lane: 256 bytes at wave_lds_base + lane * 4.
+__device__ __forceinline__ void load_to_lds_4_sbase(uint64_t sbase, uint32_t voff, void *wave_lds_base) {
+  const uint32_t l = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)wave_lds_base;
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tglobal_load_lds_dword %1, %2" ::"s"(l), "v"(voff), "s"(sbase) : "memory");
+}
+
 }  // namespace skipkv

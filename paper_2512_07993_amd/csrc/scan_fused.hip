@@ -70,8 +70,6 @@ constexpr int kStageRows = 16;                      // rows per pipeline stage =
 constexpr int kSpanStages = kSpanCap / kStageRows;  // stages per span
 constexpr int kMergeDepth = 8;                      // records a lane has in flight while merging
 
-typedef __attribute__((__vector_size__(4 * sizeof(short)))) short i16x4;
-
 struct Item {  // one item as seen by one wave
   uint32_t item;  // >= n_items: none
   int lh, b, nsp, rec, n_tok, tok0, np, first, soff_idx, ns_item;
@@ -79,28 +77,6 @@ struct Item {  // one item as seen by one wave
   int w0, w1, nst;  // the wave's span: token range (relative to the sequence) and number of stages
   int ns, sb;       // ... its sentences: count, and index of the first one among the item's sentences
 };
-
-// Swizzle of 256-byte rows (see "Data movement" above): bits (r0, r1, r2, r3) of the row number go to
-// bits (1, 2, 0, 3) of the piece number.  A permutation of bits, hence linear over XOR:
-// swz(a ^ b) = swz(a) ^ swz(b).
-__host__ __device__ constexpr int swz16(int r) { return ((r & 3) << 1) | ((r >> 2) & 1) | (r & 8); }
-
-// Transposing LDS read: the 16 lanes of a group hand in 16 addresses of 4 consecutive 16-bit
-// elements each, read as a 4 x 16 matrix (lanes 4i .. 4i+3 hold row i); lane n gets column n.
-__device__ __forceinline__ i16x4 lds_read_tr16(uint32_t addr) {
-  return __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) i16x4 *)(uintptr_t)addr);
-}
-
-// A uniform 64-bit address as a scalar register pair (the compiler may hold it in vector registers).
-__device__ __forceinline__ uint64_t scalar64(const void *p_) {
-  const uint64_t p = (uint64_t)(uintptr_t)p_;
-  return ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(p >> 32)) << 32) | (uint32_t)__builtin_amdgcn_readfirstlane((int)p);
-}
-// Direct HBM -> LDS load with a scalar base and a 32-bit offset per lane.
-__device__ __forceinline__ void load_to_lds_16_sbase(uint64_t sbase, uint32_t voff, void *wave_lds_base) {
-  const uint32_t l = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)wave_lds_base;
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(l), "v"(voff), "s"(sbase) : "memory");
-}
 
 template <int DT, int NP, int AL>
 __global__ void __launch_bounds__(256, (DT == SKIPKV_BF16 ? 2 : 1)) k_scan_fused(ScanArgs a) {
@@ -143,7 +119,6 @@ __global__ void __launch_bounds__(256, (DT == SKIPKV_BF16 ? 2 : 1)) k_scan_fused
   if (a.force_two_pass) return;
   // The plan is constant while this kernel runs: reading it through the constant address space
   // lets the compiler use scalar loads, which do not queue behind the key loads in flight.
-  typedef const __attribute__((address_space(4))) int32_t *ConstIntPtr;
   const ConstIntPtr item_rec_c = (ConstIntPtr)a.ws.item_rec;
   const ConstIntPtr row_map_c = (ConstIntPtr)a.row_map;  // written by an earlier kernel, constant here
 

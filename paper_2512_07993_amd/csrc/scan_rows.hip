@@ -1,0 +1,629 @@
+// Two-pass key scan of bf16 caches (Sec. 4.1 "Token Importance Score", Eq. 4, and the sentence embedding of
+// Eq. 2 over the head's keys), for shapes whose logits cannot wait in registers for the head's normalisers
+// (more than 64 query rows) and for whatever else the single-pass scan cannot take:
+//   pass A   (reference, sum exp2) of every query row over a run of chunks, and the unit key mean of every
+//            sentence;
+//   k_row_norm   merges a head's records into log2 of each row's normaliser;
+//   pass B   the logits again, I[t] = (1/alpha) sum_a max_i softmax, and its mean over every sentence.
+//
+// What bounds it.  With 160 query rows a 256-byte key costs 41 KFLOP and 160 exponentials: both passes are bound by
+// the instructions that a SIMD can issue (pass A at 160 rows: about 1240 VALU and 205 MFMA instructions per 64-key
+// tile and CU; the kernel's time is close to the sum of their issue times), not by HBM.  Hence:
+//   - a workgroup takes a RUN of up to kMaxRunChunks consecutive chunks of a sequence, so that its query fragments,
+//     loaded once, stay in registers for it (no query tile in LDS);
+//   - 8 waves; the rows are split over RS of them (2, 4, 8 for up to 16, 40, 64 slots per lane group) and a tile's
+//     tokens over the other 8 / RS: 40 slots are four waves' ten, 10 of 12 in whole 16-row products;
+//   - keys go HBM -> LDS directly in tiles of 64 rows, three tiles deep, two tiles ahead of the compute, one barrier
+//     per tile; a chunk's sentence offsets travel with its tiles;
+//   - sentence sums are matrix products of a 0/2 indicator with the transposed key tile, 32 dimensions and 16
+//     sentences per wave, so that no wave waits for another one's sentences;
+//   - pass A's row sums are relative to a reference that the wave's first 16 tokens fix: one fma, one exponential and
+//     one add per logit, with an exact second try where that reference did not fit.
+// Measured, pass A / pass B / k_row_norm in us, against one workgroup of 256 threads per chunk with the query tile in
+// LDS and a running maximum per row, which this replaces:
+//   48 layers x 8 heads, 4 x 32 K tokens, 160 rows (50 M keys, 12.9 GB):    7327 / 3926 / 196  ->  4189 / 3193 / 14
+//   32 layers x 8 heads, 4 x 3-9 K tokens, 1 % long sentences, 64 rows:      995 /  711 /  23  ->   407 /  347 /  9
+// Half the waves with twice the rows each (256 threads): 4445 / 3110.  32x32x16 products with the rows in two halves:
+// 5675 / 2936, the logits of a tile no longer fit beside the fragments in pass A.
+#include "scan_dev.h"
+
+#include <algorithm>
+
+namespace skipkv {
+
+namespace {
+
+constexpr int kWaves = 8;
+constexpr int kTileRows = 64;           // keys per tile: 8 per wave
+constexpr int kTileSlots = 3;           // tiles in LDS
+constexpr int kAhead = kTileSlots - 1;  // tiles that are loaded ahead of the one computed on
+constexpr int kTileLoads = 3;           // direct loads of a wave per tile: 2 x 4 rows and the chunk's offsets
+constexpr int kGroupTok = 256;    // pass B: tokens whose importance is summed over the waves at a time
+constexpr int kMaxRunChunks = 16;  // per run: the query fragments' loads and a record per run are then under 2 % of it
+
+template <int NP, int AL>
+struct RowsShape {
+  static constexpr int SL = NP * AL;                             // (window query, head) slots of a lane group
+  static constexpr int RS = SL <= 16 ? 2 : (SL <= 40 ? 4 : 8);   // waves that share the rows
+  static constexpr int TH = kWaves / RS;                         // waves that share the tokens
+  static constexpr int ALW = AL / RS;                            // window-query slots per wave
+  static constexpr int SPW = NP * ALW;                           // used slots per wave
+  static constexpr int NTW = (SPW + 3) / 4;                      // row tiles per wave
+  static constexpr int RW = 16 * NTW;                            // query rows per wave
+  static constexpr int R = RS * RW;                              // rows of the statistics arrays
+  static constexpr int NSUB = 4 / TH;                            // 16-token sub-tiles of a tile per wave
+  static constexpr int PG = RS == 8 ? 1 : 4;                     // pass B: lane groups whose parts of the importance go to LDS
+  static_assert(AL % RS == 0, "whole window queries per wave");
+};
+
+// Where the rows of a head are: contiguous from base, or through a row map.
+struct KeyRows {
+  const char *base;
+  ConstIntPtr map;      // paged cache, else nullptr
+  int64_t pitch;        // bytes from a row to the next (of the same block)
+  int64_t map_pitch;    // bytes per unit of the map
+  int page_size;        // > 0: a power of two >= 16, consecutive slots of a block are one pitch apart
+};
+
+// Rows r0 .. r0+3 from token t0 of a sequence of which `last` + 1 rows (from t0) may be read (the others re-read row
+// `last`) -> 1 KB at dst, swizzled as rows tile_row + r0 .. of their tile.  (Contiguous caches with a row pitch below
+// 16 MB do this in place.)
+__device__ __forceinline__ void issue_rows4(const KeyRows &kr, int t0, int last, int r0, int tile_row, int lane, char *dst) {
+  const int sub = lane >> 4, r = min(r0 + sub, last);
+  const uint32_t piece = (uint32_t)((lane & 15) ^ swz16((tile_row + r0 + sub) & 15)) << 4;
+  if (kr.map == nullptr) {
+    load_to_lds_16(kr.base + (int64_t)(t0 + r) * kr.pitch + piece, dst);
+  } else if (kr.page_size > 0) {  // at most two blocks, consecutive slots in each
+    const int jb = kr.page_size - (t0 & (kr.page_size - 1));  // rows before the next block begins
+    const char *b0 = kr.base + (int64_t)kr.map[t0] * kr.map_pitch;
+    const char *b1 = kr.base + (int64_t)kr.map[t0 + min(jb, last)] * kr.map_pitch - (int64_t)jb * kr.pitch;
+    load_to_lds_16((r >= jb ? b1 : b0) + (int64_t)r * kr.pitch + piece, dst);
+  } else {  // blocks of any size: every row is looked up, with scalar reads
+    int m[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) m[u] = kr.map[t0 + min(r0 + u, last)];
+    const int mine = sub == 0 ? m[0] : (sub == 1 ? m[1] : (sub == 2 ? m[2] : m[3]));
+    load_to_lds_16(kr.base + (int64_t)mine * kr.map_pitch + piece, dst);
+  }
+}
+
+// ((1 << width) - 1) << offset, both taken modulo 32.
+__device__ __forceinline__ uint32_t bitfield_mask(int width, int offset) { return ((1u << (width & 31)) - 1u) << (offset & 31); }
+__device__ __forceinline__ bf16x8 join_tr(i16x4 lo, i16x4 hi) {
+  const uint2 l = __builtin_bit_cast(uint2, lo), h = __builtin_bit_cast(uint2, hi);
+  return __builtin_bit_cast(bf16x8, make_uint4(l.x, l.y, h.x, h.y));
+}
+
+// Fields of a Chunk record as seen through ConstIntPtr.
+enum ChunkRec : int { kChB = 0, kChS0, kChNs, kChT, kChLen, kChSoff, kChTok0, kChNTok, kChInts };
+static_assert(sizeof(Chunk) == kChInts * 4, "a chunk is read as eight words");
+
+template <int NP, int AL, bool PASSB, bool SIMPLE>
+__global__ void __launch_bounds__(64 * kWaves, 4) k_scan_rows(ScanArgs a, int run_chunks) {
+  using SH = RowsShape<NP, AL>;
+  constexpr int RS = SH::RS, TH = SH::TH, ALW = SH::ALW, SPW = SH::SPW, NTW = SH::NTW, RW = SH::RW, R = SH::R, NSUB = SH::NSUB, PG = SH::PG;
+  constexpr int GT = kGroupTok;
+  // pass A: sums of squares of the sentence sums [32][4 waves], row statistics [waves][RW][2], references [waves][RW]
+  // pass B: importance parts [row part and lane group][GT], importance [GT]
+  constexpr int NPART = PG * RS;
+  constexpr int NF = PASSB ? (NPART + 1) * GT : 128 + 3 * kWaves * RW;
+  __shared__ __align__(256) char kt[kTileSlots][kTileRows * 256];
+  __shared__ int soffb[kTileSlots][64];  // offsets of the tile's chunk, the last one repeated (every wave loads the same)
+  __shared__ __align__(16) float fbuf[NF];
+
+  const int tid = threadIdx.x, lane = tid & 63, c16 = lane & 15, g = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int rh = wave % RS, th = wave / RS;  // the wave's share of the rows and of a tile's tokens
+  // Fallback: only sequences and heads that the single-pass scan left, unless everything goes this way.
+  if (!a.force_two_pass && a.ws.hdr->n_unfused == 0) return;
+  const int n_lh = a.n_layers * a.n_kv_heads;
+  const int n_chunks = hdr_chunks(a.ws.hdr->ranges);
+  const int n_runs = (n_chunks + run_chunks - 1) / run_chunks;
+  const uint32_t n_items = (uint32_t)n_lh * (uint32_t)n_runs;
+  const int n = a.n_q_heads / a.n_kv_heads;
+  const ConstIntPtr chunks_c = (ConstIntPtr) reinterpret_cast<const int32_t *>(a.ws.chunks);
+
+  // lane constants of the LDS addressing, as in the single-pass scan
+  const uint32_t b_off = c16 * 256 + (((4 * g) ^ swz16(c16)) << 4);
+  const int tr_row = 4 * g + (c16 >> 2);
+  const uint32_t tr_off = tr_row * 256 + (((((c16 >> 1) & 1) ^ swz16(tr_row)) & 15) << 4) + ((c16 & 1) << 3);
+
+  for (uint32_t item = blockIdx.x; item < n_items; item += gridDim.x) {
+  const int lh = item / n_runs;
+  const int run_end = min(n_chunks, (int)(item % n_runs + 1) * run_chunks);
+  int c1 = (int)(item % n_runs) * run_chunks;
+  while (c1 < run_end) {
+    // ---- a segment: the run's chunks of one sequence
+    const int c0 = c1;
+    const ConstIntPtr ch0 = chunks_c + (int64_t)c0 * kChInts;
+    const int b = ch0[kChB];
+    int n_tiles = 0;
+    do {
+      n_tiles += (chunks_c[(int64_t)c1 * kChInts + kChLen] + kTileRows - 1) / kTileRows;
+      ++c1;
+    } while (c1 < run_end && chunks_c[(int64_t)c1 * kChInts + kChB] == b);
+    if (!a.force_two_pass && a.ws.seq_fused[b] && !a.ws.head_redo[(int64_t)lh * a.batch + b]) continue;  // done by the single-pass scan
+    const int l = lh / a.n_kv_heads, h = lh % a.n_kv_heads;
+    const int tok0 = ch0[kChTok0], n_tok = ch0[kChNTok], t_first = ch0[kChT];
+    const int last_free = n_tok - a.alpha;  // keys t <= last_free are visible to every window query
+    KeyRows kr;
+    kr.map = !SIMPLE && a.row_map ? (ConstIntPtr)a.row_map + tok0 : nullptr;
+    kr.base = static_cast<const char *>(a.k) + ((int64_t)l * a.stride_layer + (int64_t)h * a.stride_head + (!SIMPLE && a.row_map ? 0 : (int64_t)tok0 * a.stride_tok)) * 2;
+    kr.pitch = a.stride_tok * 2;
+    kr.map_pitch = a.map_stride * 2;
+    kr.page_size = (a.page_size >= 16 && (a.page_size & (a.page_size - 1)) == 0) ? a.page_size : 0;
+
+    // ---- load stream: tiles of the segment in order, chunk by chunk.  A tile's loads come in two parts (part j: rows
+    // 4j .. 4j+3 of the wave's eight; the second one also the chunk's offsets, and on to the next tile), so that they
+    // can be spread over the compute: issued in one go by all waves they queue up at the CU's address unit.  Rows past
+    // a chunk's end re-read its last row, and tiles past the segment its last tile's (nobody looks at either): no
+    // branch, and the same count every time.
+    int lc, lt, lend, lns;
+    const int32_t *lso;
+    const uint32_t v_piece = (uint32_t)((lane & 15) ^ swz16(8 * (wave & 1) + (lane >> 4))) << 4;
+    auto load_chunk = [&](int c) {
+      const ConstIntPtr r = chunks_c + (int64_t)c * kChInts;
+      lt = r[kChT];
+      lend = lt + r[kChLen];
+      lso = a.sent_off + r[kChSoff];
+      lns = r[kChNs];
+    };
+    auto issue = [&](int slot, int j) {
+      char *dst = kt[slot] + wave * 2048 + j * 1024;
+      const int t0 = min(lt + 8 * wave, lend - 1), last = lend - 1 - t0;
+      if constexpr (SIMPLE)
+        load_to_lds_16_sbase(scalar64(kr.base + (int64_t)t0 * kr.pitch), __umul24((uint32_t)min(4 * j + (lane >> 4), last), (uint32_t)kr.pitch) + (v_piece ^ (uint32_t)(swz16(4 * j) << 4)), dst);
+      else
+        issue_rows4(kr, t0, last, 4 * j, 8 * (wave & 1), opaque(lane), dst);
+      if (j == 1) {
+        load_to_lds_4_sbase(scalar64(lso), (uint32_t)min(lane, lns) * 4u, &soffb[slot][0]);
+        lt += kTileRows;
+        if (lt >= lend && lc + 1 < c1) load_chunk(++lc);
+      }
+    };
+    // slot q = 4 T + j of the wave: window query aq = g + 4 (rh ALW + q / NP), head q % NP
+    auto slot_aq = [&](int q) { return g + 4 * (rh * ALW + q / NP); };
+    auto slot_used = [&](int q) { return q < SPW && q % NP < n && slot_aq(q) < a.alpha; };
+    auto slot_row = [&](int q) { return 16 * (q >> 2) + 4 * g + (q & 3); };
+    [[maybe_unused]] float ref1 = kRefInit, lsum[SPW];  // pass A: the lane group's reference, the slots' sums
+    [[maybe_unused]] float cn[SPW];                     // pass B: log2 normaliser of the slot's row (+inf: unused slot)
+    float *row_ref = fbuf + 128 + 2 * kWaves * RW + wave * RW;   // pass A, mode 2: the rows' own references
+#pragma unroll
+    for (int q = 0; q < SPW; ++q) {
+      if constexpr (PASSB) {
+        const float x = a.ws.row_norm[((int64_t)lh * a.batch + b) * R + rh * RW + slot_row(q)];
+        cn[q] = slot_used(q) ? x : INFINITY;
+      } else {
+        lsum[q] = 0.f;
+      }
+    }
+    const int p_start = n_tok - min(a.protect, n_tok);  // first protected token
+
+    // Pass A keeps a row's statistics relative to a reference fixed by the wave's first 16 tokens (mode 0: one fma,
+    // one exponential, one add per logit).  Should a row's sum then lie outside what fp32 holds comfortably, the
+    // segment is done again: its row maxima (mode 1), then the sums relative to those (mode 2).
+    [[maybe_unused]] int my_first = -1;  // becomes 0 once the wave has seen a token
+    [[maybe_unused]] int t_ref = 0;      // ... and this is the first one
+    for (int mode = 0;; ++mode) {
+      lc = c0;
+      load_chunk(c0);
+      // ---- the wave's query fragments: lane (row c16 of a tile, head-dim slice g), as the A operand wants them
+      bf16x8 afr[NTW][4];
+      {
+        const char *qbase = static_cast<const char *>(a.q);
+        // layer, KV head and sequence that address the query rows (the real ones under per-head ranges)
+        int ql = l, qh = h, qb = b, q_batch = a.batch, q_heads = a.n_q_heads;
+        if (a.virt_hk > 0) {
+          const int lh_r = b / a.virt_b;
+          qb = b % a.virt_b;
+          ql = lh_r / a.virt_hk;
+          qh = lh_r % a.virt_hk;
+          q_batch = a.virt_b;
+          q_heads = a.virt_hk * n;
+        }
+#pragma unroll
+        for (int T = 0; T < NTW; ++T) {
+          // row c16 of a tile is register (c16 & 3) of lane group c16 / 4 in the output
+          const int slot = 4 * T + (c16 & 3), gq = c16 >> 2;
+          const int al = rh * ALW + slot / NP, i = slot % NP, aq = gq + 4 * al;
+          const bool used = slot < SPW && i < n && aq < a.alpha;
+          const int64_t row = (((int64_t)ql * q_batch + qb) * q_heads + (qh * n + (used ? i : 0))) * a.alpha + (used ? aq : 0);
+#pragma unroll
+          for (int kk = 0; kk < 4; ++kk) {
+            uint4 v = *reinterpret_cast<const uint4 *>(qbase + row * 256 + g * 64 + kk * 16);
+            if (!used) v = make_uint4(0, 0, 0, 0);
+            afr[T][kk] = __builtin_bit_cast(bf16x8, v);
+          }
+        }
+      }
+      // ---- compute stream
+      int cc = c0, ct = t_first, c_t0 = t_first;
+      int cend = ct + ch0[kChLen], ns = ch0[kChNs], col = ch0[kChSoff] - b;
+      f32x4 pool[2];     // pass A: sentence key sums: slots 16 (wave / 4) + 4g + r, dimensions 16 (2 (wave % 4) + jj) + c16
+      float sum_i = 0.f, sum_r = 0.f;  // pass B: thread (sentence tid / 16, part tid % 16)
+#pragma unroll
+      for (int jj = 0; jj < 2; ++jj) pool[jj] = f32x4{0.f, 0.f, 0.f, 0.f};
+      int slot = 1;  // (of the first step, which loads tile 0 into slot 0)
+      for (int i = -kAhead; i < n_tiles; ++i) {
+        if (i >= 0) {
+          wait_vm<(kAhead - 1) * kTileLoads>();
+        }
+        if (i == -kAhead || i >= 0) {
+          asm volatile("" ::: "memory");
+          lds_barrier();  // the tile's rows are there for all waves, and all are done with the tile (or segment) before it
+          asm volatile("" ::: "memory");
+        }
+        const int fill = slot == 0 ? kTileSlots - 1 : slot - 1;
+        auto prefetch = [&](int j) { issue(fill, j); };
+        if (i < 0) {
+          prefetch(0);
+          prefetch(1);
+          slot = slot + 1 == kTileSlots ? 0 : slot + 1;
+          continue;
+        }
+        const uint32_t tile_a = lds_addr(kt[slot]);
+        const int *soff = soffb[slot];
+        slot = slot + 1 == kTileSlots ? 0 : slot + 1;
+        const bool chunk_done = ct + kTileRows >= cend;
+
+        // ---- logits: acc[s][T][j] = row 4g + j of the wave's row tile T, token c16 of its sub-tile s
+        const int wt = ct + 16 * th * NSUB;  // the wave's first token
+        const uint32_t brow = tile_a + th * NSUB * 4096 + b_off;
+        f32x4 acc[NSUB][NTW];
+        auto logits = [&](int s) {
+#pragma unroll
+          for (int T = 0; T < NTW; ++T) acc[s][T] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+          for (int kk = 0; kk < 4; ++kk) {
+            const bf16x8 bfr = *reinterpret_cast<const __attribute__((address_space(3))) bf16x8 *>((uintptr_t)((brow + s * 4096) ^ (kk << 4)));
+#pragma unroll
+            for (int T = 0; T < NTW; ++T) acc[s][T] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(afr[T][kk], bfr, acc[s][T], 0, 0, 0);
+          }
+        };
+        const bool edge = wt + 16 * NSUB - 1 > last_free;  // some key is hidden from some window query
+
+        if constexpr (!PASSB) {
+          if (!edge && (mode | my_first) == 0) {
+#pragma unroll
+            for (int s = 0; s < NSUB; ++s) {
+              logits(s);
+              if (s == 0) prefetch(0);
+            }
+#pragma unroll
+            for (int s = 0; s < NSUB; ++s)
+#pragma unroll
+              for (int q = 0; q < SPW; ++q)  // rows past the chunk's end count nothing
+                lsum[q] += __builtin_amdgcn_exp2f(fmaf(acc[s][q >> 2][q & 3], kScale2, wt + 16 * s + c16 < cend ? -ref1 : -INFINITY));
+          } else {
+            prefetch(0);
+#pragma unroll
+            for (int s = 0; s < NSUB; ++s) {
+              if (wt + 16 * s >= cend) continue;
+              logits(s);
+              const int t = wt + 16 * s + c16, lf = opaque(last_free);
+              float mx = -INFINITY;
+#pragma unroll
+              for (int q = 0; q < SPW; ++q) {
+                float x = acc[s][q >> 2][q & 3] * kScale2;
+                if (!(t < cend && t <= lf + slot_aq(q))) x = -INFINITY;
+                acc[s][q >> 2][q & 3] = x;
+                mx = fmaxf(mx, x);
+              }
+              if (mode == 0 && my_first < 0) {  // the wave's first 16 tokens fix the reference: their largest logit in the lane group
+                my_first = 0;
+                t_ref = wt + 16 * s;
+                ref1 = fmaxf(row16_max_fast(mx), kRefInit);
+              }
+#pragma unroll
+              for (int q = 0; q < SPW; ++q) {
+                const float x = acc[s][q >> 2][q & 3];
+                lsum[q] = mode == 1 ? fmaxf(lsum[q], x) : lsum[q] + __builtin_amdgcn_exp2f(x - (mode == 0 ? ref1 : row_ref[slot_row(q)]));
+              }
+            }
+          }
+          prefetch(1);
+          // ---- sentence sums: [16 slots x 32 tokens] indicator (ones written as 2.0, a single bit; the unit
+          // normalisation removes the factor) times [32 tokens x 16 dimensions]: waves 0-3 take the chunk's first 16
+          // sentences, waves 4-7 the others (if there are any), each 32 of the 128 dimensions.  Lane group g brings
+          // tokens 4g .. 4g+3 of two 16-token stages.
+          const int pw = wave & 3, u = wave >> 2;
+          if (mode == 0 && !a.no_pool && ns > 16 * u) {
+            // offsets past the chunk's last one repeat it: empty slots
+            const int s_lo = soff[16 * u + c16] - ct, s_hi = soff[16 * u + c16 + 1] - ct;
+            bf16x8 trv[2][2];
+#pragma unroll
+            for (int w = 0; w < 2; ++w)
+#pragma unroll
+              for (int jj = 0; jj < 2; ++jj) {
+                const uint32_t ta = ((tile_a + tr_off) ^ ((2 * pw + jj) << 5)) + w * 8192;
+                trv[w][jj] = join_tr(lds_read_tr16(ta), lds_read_tr16(ta + 4096));
+              }
+#pragma unroll
+            for (int w = 0; w < 2; ++w) {
+              uint32_t ind[4];
+#pragma unroll
+              for (int s = 0; s < 2; ++s) {  // the lane's sentence over its 4 tokens of stage 2w + s
+                const int t0 = 32 * w + 16 * s;
+                const int ra = min(max(s_lo, t0), t0 + 16), rb = min(max(s_hi, t0), t0 + 16);
+                const uint32_t x = __builtin_amdgcn_ubfe(bitfield_mask(rb - ra, ra), 4 * g + 16 * s, 4);
+                ind[2 * s] = ((x << 14) | (x << 29)) & 0x40004000u;
+                ind[2 * s + 1] = ((x << 12) | (x << 27)) & 0x40004000u;
+              }
+              const bf16x8 av = __builtin_bit_cast(bf16x8, make_uint4(ind[0], ind[1], ind[2], ind[3]));
+#pragma unroll
+              for (int jj = 0; jj < 2; ++jj) pool[jj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, trv[w][jj], pool[jj], 0, 0, 0);
+            }
+          }
+          if (mode == 0 && !a.no_pool && chunk_done) {
+            // ---- unit sentence embeddings as bf16 hi + lo.  The dimensions of a row are stored as the waves
+            // hold them: position 32 pw + 2 c + jj is dimension 16 (2 pw + jj) + c; every embedding of a head
+            // is written by this kernel, so cosines are not affected.
+            float *sq = fbuf;  // [slot][pw]
+            if (ns > 16 * u) {
+#pragma unroll
+              for (int r = 0; r < 4; ++r) {
+                const float v = row16_sum_fast(fmaf(pool[0][r], pool[0][r], pool[1][r] * pool[1][r]));
+                if (c16 == 0) sq[4 * (16 * u + 4 * g + r) + pw] = v;
+              }
+            }
+            asm volatile("" ::: "memory");
+            lds_barrier();
+            asm volatile("" ::: "memory");
+            if (ns > 16 * u) {
+              float4 ss4[4];
+              int len[4];
+#pragma unroll
+              for (int r = 0; r < 4; ++r) {
+                const int si = 16 * u + 4 * g + r;
+                ss4[r] = *reinterpret_cast<const float4 *>(sq + 4 * si);
+                len[r] = soff[si + 1] - soff[si];  // 0 past the last sentence
+              }
+              const int64_t o = ((int64_t)lh * a.total_sentences + col + 16 * u) * (kD / 2) + 16 * pw;
+              uint32_t *dhi = reinterpret_cast<uint32_t *>(a.ws.vhat_hi) + o, *dlo = reinterpret_cast<uint32_t *>(a.ws.vhat_lo) + o;
+#pragma unroll
+              for (int r = 0; r < 4; ++r) {
+                const float ss = ((ss4[r].x + ss4[r].y) + ss4[r].z) + ss4[r].w;
+                // mean / (|mean| + eps) = sum / (|sum| + eps * len), sums and eps scaled by 2
+                const float inv = __builtin_amdgcn_rcpf(__builtin_amdgcn_sqrtf(ss) + 2e-12f * (float)len[r]);
+                const float u0 = pool[0][r] * inv, u1 = pool[1][r] * inv;
+                const uint32_t hi = pack_bf16x2(u0, u1);
+                const uint32_t lo = pack_bf16x2(u0 - __uint_as_float(hi << 16), u1 - __uint_as_float(hi & 0xFFFF0000u));
+                if (len[r] > 0) {
+                  dhi[(4 * g + r) * (kD / 2) + c16] = hi;
+                  dlo[(4 * g + r) * (kD / 2) + c16] = lo;
+                }
+              }
+#pragma unroll
+              for (int jj = 0; jj < 2; ++jj) pool[jj] = f32x4{0.f, 0.f, 0.f, 0.f};
+            }
+          }
+        } else {
+          // ---- token importance: max over the group's heads in registers, exp2, sum over the wave's window queries
+          float *parts = fbuf, *imp = fbuf + NPART * GT;
+          const int goff = (ct - c_t0) % GT;  // the tile's place in its group of GT tokens
+#pragma unroll
+          for (int s = 0; s < NSUB; ++s) {
+            logits(s);
+            if (s == 0) prefetch(0);
+          }
+#pragma unroll
+          for (int s = 0; s < NSUB; ++s) {
+            float sum = 0.f;
+#pragma unroll
+            for (int al = 0; al < ALW; ++al) {
+              float gm = -INFINITY;
+#pragma unroll
+              for (int i2 = 0; i2 < NP; ++i2) {
+                const int q = al * NP + i2;
+                gm = fmaxf(gm, fmaf(acc[s][q >> 2][q & 3], kScale2, -cn[q]));
+              }
+              if (edge && wt + 16 * s + c16 > last_free + g + 4 * (rh * ALW + al)) gm = -INFINITY;
+              sum += __builtin_amdgcn_exp2f(gm);
+            }
+            if constexpr (PG == 1) {
+              sum += __shfl_xor(sum, 16);
+              sum += __shfl_xor(sum, 32);
+              if (g == 0) parts[rh * GT + goff + 16 * (th * NSUB + s) + c16] = sum;
+            } else {
+              parts[(4 * rh + g) * GT + goff + 16 * (th * NSUB + s) + c16] = sum;
+            }
+          }
+          prefetch(1);
+          if (chunk_done || goff + kTileRows == GT) {
+            // the parts of the importance are added in a fixed order, then the sentences' sums over their
+            // unprotected part
+            const int g0 = ct - goff, g1 = min(cend, g0 + GT);
+            asm volatile("" ::: "memory");
+            lds_barrier();
+            asm volatile("" ::: "memory");
+            if (tid < GT) {
+              float tot = 0.f;
+#pragma unroll
+              for (int p = 0; p < NPART; ++p) tot += parts[p * GT + tid];
+              imp[tid] = g0 + tid < g1 ? tot / (float)a.alpha : 0.f;
+            }
+            asm volatile("" ::: "memory");
+            lds_barrier();
+            asm volatile("" ::: "memory");
+            const int64_t tok_col = (int64_t)lh * a.total_tokens + tok0;
+            static_assert(kChunkMaxSent * 16 == 64 * kWaves && GT <= 64 * kWaves, "16 lanes per sentence of a chunk, one thread per token of a group");
+            const int si = tid >> 4, sub = tid & 15;
+            if (si < ns) {
+              const int lo = max(soff[si], g0), hi = min(min(soff[si + 1], p_start), g1);
+              for (int t = lo + sub; t < hi; t += 16) {
+                sum_i += imp[t - g0];
+                if (a.tok_red) sum_r += a.tok_red[tok_col + t];
+              }
+            }
+            if (a.tok_imp && tid < GT && g0 + tid < g1) a.tok_imp[tok_col + g0 + tid] = imp[tid];
+            if (chunk_done) {
+              sum_i = row16_sum_fast(sum_i);
+              if (a.tok_red) sum_r = row16_sum_fast(sum_r);
+              if (si < ns && sub == 0) {
+                const int len = min(soff[si + 1], p_start) - soff[si];
+                const int64_t o = (int64_t)lh * a.total_sentences + col + si;
+                a.ws.sent_imp[o] = len > 0 ? sum_i / (float)len : 0.f;
+                a.ws.sent_red[o] = len > 0 ? sum_r / (float)len : 0.f;
+              }
+              sum_i = sum_r = 0.f;
+            }
+          }
+        }
+        ct += kTileRows;
+        if (ct >= cend && cc + 1 < c1) {
+          ++cc;
+          const ConstIntPtr r = chunks_c + (int64_t)cc * kChInts;
+          c_t0 = ct = r[kChT];
+          cend = ct + r[kChLen];
+          ns = r[kChNs];
+          col = r[kChSoff] - b;
+        }
+      }  // tiles
+
+      if constexpr (PASSB) {
+        break;
+      } else {
+        if (mode == 1) {
+#pragma unroll
+          for (int q = 0; q < SPW; ++q) {
+            const float m = fmaxf(row16_max_fast(lsum[q]), kRefInit);
+            if (c16 == 0) row_ref[slot_row(q)] = m;
+            lsum[q] = 0.f;
+          }
+          continue;
+        }
+        bool doubt = false;
+#pragma unroll
+        for (int q = 0; q < SPW; ++q) {
+          lsum[q] = row16_sum_fast(lsum[q]);
+          // rows of padding hold zero queries, and a window query that does not see the wave's first token sees none of its tokens
+          doubt = doubt || (slot_used(q) && my_first == 0 && t_ref <= last_free + slot_aq(q) && !(lsum[q] > 1e-30f && lsum[q] < 3e38f));  // also catches NaN and infinity
+        }
+        if (mode == 0 && __syncthreads_or(doubt)) {
+#pragma unroll
+          for (int q = 0; q < SPW; ++q) lsum[q] = -INFINITY;
+          continue;
+        }
+        // ---- the segment's record, filed under its first chunk; rows of waves that shared the tokens are merged
+        float2 *out = a.ws.stat_part + ((int64_t)lh * a.ws.nc_max + c0) * R;
+        float *wstat = fbuf + 128;
+#pragma unroll
+        for (int q = 0; q < SPW; ++q) {
+          const float2 rec = make_float2(mode == 0 ? ref1 : row_ref[slot_row(q)], lsum[q]);
+          if (c16 == 0) *reinterpret_cast<float2 *>(wstat + 2 * (wave * RW + slot_row(q))) = rec;
+        }
+        asm volatile("" ::: "memory");
+        lds_barrier();
+        asm volatile("" ::: "memory");
+        if (tid < R) {  // (rows past the used slots hold whatever: nobody reads them)
+          const int w = tid / RW, r = tid % RW;
+          float m = kRefInit;
+#pragma unroll
+          for (int p = 0; p < TH; ++p) m = fmaxf(m, wstat[2 * ((w + RS * p) * RW + r)]);
+          float s = 0.f;
+#pragma unroll
+          for (int p = 0; p < TH; ++p) {
+            const float *x = wstat + 2 * ((w + RS * p) * RW + r);
+            s += x[1] * __builtin_amdgcn_exp2f(x[0] - m);
+          }
+          out[tid] = make_float2(m, s);
+        }
+        break;
+      }
+    }  // modes
+
+  }  // segments
+  }  // items
+  wait_vm<0>();  // the loads past the last tile still write LDS that the workgroup is about to give up
+}
+
+// log2 of the softmax normaliser of every query row: merge the records of a head's segments.
+__global__ void __launch_bounds__(256) k_row_norm(ScanArgs a, int R, int run_chunks) {
+  const int lhb = blockIdx.x, lh = lhb / a.batch, b = lhb % a.batch;
+  if (!a.force_two_pass && a.ws.seq_fused[b] && !a.ws.head_redo[lhb]) return;  // the single-pass scan computed these itself
+  const int cb = a.ws.chunk_base[b], ce = cb + a.ws.chunk_cnt[b];
+  const int r = threadIdx.x;
+  if (r >= R || cb >= ce) return;
+  const float2 *recs = a.ws.stat_part + (int64_t)lh * a.ws.nc_max * R + r;
+  float m = kRefInit, s = 0.f;
+  const int u1 = (ce - 1) / run_chunks;
+  for (int u = cb / run_chunks; u <= u1; u += 8) {
+    float2 p[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) p[k] = recs[(int64_t)max(cb, min(u + k, u1) * run_chunks) * R];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      if (u + k > u1) break;
+      const float nm = fmaxf(m, p[k].x);
+      s = s * __builtin_amdgcn_exp2f(m - nm) + p[k].y * __builtin_amdgcn_exp2f(p[k].x - nm);
+      m = nm;
+    }
+  }
+  a.ws.row_norm[(int64_t)lhb * R + r] = s > 0.f ? m + __builtin_amdgcn_logf(s) : INFINITY;
+}
+
+// Chunks per run: as many as leave every workgroup slot of the chip (512) at least eight runs, so that the last
+// ones to finish do not matter, and no more than kMaxRunChunks.  (One chunk per run, pass A at 160 rows: 4627 us;
+// sixteen: 4445 us, both with 256 threads.)
+int chunks_per_run(const ScanArgs &a) {
+  const int64_t chunks = (int64_t)a.n_layers * a.n_kv_heads * (a.total_tokens / kChunkCap + 1);
+  return (int)std::min<int64_t>(kMaxRunChunks, std::max<int64_t>(1, chunks / (8 * 512)));
+}
+
+template <int NP, int AL, bool PASSB>
+hipError_t launch_rows(const ScanArgs &a, hipStream_t st) {
+  static_assert(RowsShape<NP, AL>::R <= 256, "one thread per row merges the records");
+  if (a.ws.rows2 != RowsShape<NP, AL>::R) return hipErrorInvalidValue;
+  const int rc = chunks_per_run(a);
+  const int64_t items = (int64_t)a.n_layers * a.n_kv_heads * ((a.ws.nc_max + rc - 1) / rc);
+  if (items == 0) return hipSuccess;
+  const dim3 grid((unsigned)std::min<int64_t>(items, 4096));
+  if (a.row_map == nullptr && a.stride_tok * 2 < (1 << 24))  // lane offsets by a 24-bit multiply
+    hipLaunchKernelGGL((k_scan_rows<NP, AL, PASSB, true>), grid, dim3(64 * kWaves), 0, st, a, rc);
+  else
+    hipLaunchKernelGGL((k_scan_rows<NP, AL, PASSB, false>), grid, dim3(64 * kWaves), 0, st, a, rc);
+  return hipGetLastError();
+}
+
+template <bool PASSB>
+hipError_t dispatch(const ScanArgs &a, hipStream_t st) {
+#define SKIPKV_CASE(NP_, AL_) \
+  if (a.rl.np == NP_ && a.rl.al == AL_) return launch_rows<NP_, AL_, PASSB>(a, st);
+  SKIPKV_CASE(4, 2)
+  SKIPKV_CASE(4, 4)
+  SKIPKV_CASE(4, 8)
+  SKIPKV_CASE(8, 2)
+  SKIPKV_CASE(8, 4)
+  SKIPKV_CASE(8, 8)
+  SKIPKV_CASE(5, 8)
+  SKIPKV_CASE(7, 2)
+#undef SKIPKV_CASE
+  return hipErrorInvalidValue;
+}
+
+}  // namespace
+
+int scan_two_pass_rows(const RowLayout &rl, int dtype) {
+  if (dtype != SKIPKV_BF16) return rl.rows;
+#define SKIPKV_CASE(NP_, AL_) \
+  if (rl.np == NP_ && rl.al == AL_) return RowsShape<NP_, AL_>::R;
+  SKIPKV_CASE(4, 8)
+  SKIPKV_CASE(8, 4)
+  SKIPKV_CASE(8, 8)
+  SKIPKV_CASE(5, 8)
+#undef SKIPKV_CASE
+  return rl.rows;  // up to 64 rows: as the single-pass scan lays them out
+}
+
+hipError_t launch_rows_stats(const ScanArgs &a, hipStream_t st) { return dispatch<false>(a, st); }
+hipError_t launch_rows_scores(const ScanArgs &a, hipStream_t st) { return dispatch<true>(a, st); }
+
+hipError_t launch_row_norm(const ScanArgs &a, hipStream_t st) {
+  const int blocks = a.n_layers * a.n_kv_heads * a.batch;
+  if (blocks == 0) return hipSuccess;
+  const int rc = a.dtype == SKIPKV_BF16 ? chunks_per_run(a) : 1;  // the fp32 scan files a record per chunk
+  hipLaunchKernelGGL(k_row_norm, dim3(blocks), dim3(256), 0, st, a, a.ws.rows2, rc);
+  return hipGetLastError();
+}
+
+}  // namespace skipkv

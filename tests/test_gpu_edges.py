@@ -420,3 +420,32 @@ def test_lengths_around_chunk_and_stage_edges(dtype, sent_hi):
     assert int(out.dev_status.item()) == 0
     stats = _compare_all(cfg, st, out, k, v, k0, v0, q)
     assert stats["heads"] == 2 * len(lens)
+
+
+@pytest.mark.parametrize("block_size", [0, 24])
+@pytest.mark.parametrize("group,alpha", [(1, 1), (4, 16), (7, 8), (5, 32), (3, 29), (8, 32)])
+def test_two_pass_scan_shapes(group, alpha, block_size):
+    """Every split of the query rows over the waves of the two-pass bf16 scan, with odd group sizes and windows, on
+    lengths one below, at and one above its tile (64 rows) and chunk (256 tokens) after a sentence that no chunk
+    holds, and with up to 32 sentences per chunk: every head against the oracle, by the tolerances of the other
+    parity tests (fp32 sums of bf16 products, as everywhere)."""
+    from test_gpu_paged import _from_pages, _run_paged, _to_pages
+    rng = np.random.default_rng(group * 33 + alpha)
+    offsets = []
+    for i, n in enumerate([301, 363, 364, 365, 555, 556, 557, 900]):
+        off = [0, 300]
+        while off[-1] < n:
+            off.append(min(n, off[-1] + int(rng.integers(1, 5 if i % 2 else 20))))
+        offsets.append(off)
+    st = _structure(offsets)
+    cfg = W.Config("rows", 9, len(offsets), 1, 2, 2 * group, "bf16", 0, 0, 96, alpha, 40, 16.0, 0.0)
+    k0, v0, q = _random_kvq(cfg, st, 7 + group)
+    if block_size:
+        kp, vp, table = _to_pages(cfg, st, k0, v0, block_size, seed=5)
+        out = _run_paged(cfg, st, kp, vp, table, q)
+        k, v = _from_pages(cfg, st, kp, table, block_size), _from_pages(cfg, st, vp, table, block_size)
+    else:
+        k, v = k0.clone(), v0.clone()
+        out = run_step(cfg, st, k, v, q)
+    assert int(out.dev_status.item()) == 0
+    assert _compare_all(cfg, st, out, k, v, k0, v0, q)["heads"] == 2 * len(offsets)
