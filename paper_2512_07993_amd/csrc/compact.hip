@@ -16,14 +16,20 @@ namespace {
 // kept_idx[k], written by k_kept_rows below), destinations are read from the row map one coalesced
 // load per tile, issued right before the tile's row loads.  Logical positions still only move
 // forward and distinct logical rows are distinct slots, so the order argument above holds.
-template <int ROWB, bool PAGED>
+//
+// SL: bytes of a row that a wave moves.  The argument above holds for every byte column of a stream by
+// itself, so a stream may be split into ROWB / SL waves that know nothing of each other; launch_compact
+// says when.
+template <int ROWB, int SL, bool PAGED>
 __global__ void __launch_bounds__(256) k_compact(CompactArgs a) {
-  constexpr int PPR = ROWB / 16;   // 16-byte pieces per row
+  constexpr int NS = ROWB / SL;    // waves per stream
+  constexpr int PPR = SL / 16;     // 16-byte pieces per row slice
   constexpr int RPI = 64 / PPR;    // rows moved by one wave-wide instruction
   constexpr int U = 8;             // instructions in flight per tile
   constexpr int ESZ = ROWB / kD;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int64_t sid = (int64_t)blockIdx.x * 4 + wave;
+  const int64_t wid = (int64_t)blockIdx.x * (blockDim.x >> 6) + wave;
+  const int64_t sid = wid / NS;
   const int64_t n_lhb = (int64_t)a.n_layers * a.n_kv_heads * a.batch;
   if (sid >= 2 * n_lhb) return;
   const int64_t lhb = sid >> 1;
@@ -31,7 +37,7 @@ __global__ void __launch_bounds__(256) k_compact(CompactArgs a) {
   if (PAGED && a.seq_bad[b]) return;  // invalid block table: leave the sequence alone
   const int lh = (int)(lhb / a.batch), l = lh / a.n_kv_heads, h = lh % a.n_kv_heads;
   char *base = static_cast<char *>((sid & 1) ? a.v : a.k) +
-               ((int64_t)l * a.stride_layer + (int64_t)h * a.stride_head + (PAGED ? 0 : (int64_t)a.seq_off[b] * a.stride_tok)) * ESZ;
+               ((int64_t)l * a.stride_layer + (int64_t)h * a.stride_head + (PAGED ? 0 : (int64_t)a.seq_off[b] * a.stride_tok)) * ESZ + (int)(wid % NS) * SL;
   const int64_t pitch = (PAGED ? a.map_stride : a.stride_tok) * ESZ;  // paged: rows are addressed in units of the row map
   const int32_t *kept = a.kept_idx + lhb * a.kept_stride;
   const int32_t *srcs = PAGED ? a.src_rows + lhb * a.src_stride : kept;  // what the row loads are addressed with
@@ -61,7 +67,8 @@ __global__ void __launch_bounds__(256) k_compact(CompactArgs a) {
   // tile's source indices come in with one coalesced load, a tile ahead of their use.
   const int sub = lane / PPR, piece = lane % PPR;
   constexpr int TR = U * RPI;  // rows per tile
-  static_assert(TR <= 64, "one lane per row index of a tile");
+  constexpr int NI = (TR + 63) / 64;  // index loads per tile: lane i of load n holds row 64 n + i
+  static_assert(NI <= 2 && (NI == 1 || U * RPI == 128), "instructions 0..3 take their rows from the first load, 4..7 from the second");
   auto load_idx = [&](int k0) -> int {  // unconditional (clamped), so that it always counts as one outstanding load
     const int i = srcs[min(k0 + lane, nl - 1)];
     return PAGED ? i : max(0, min(i, room - 1));  // never address a row outside the sequence, whatever the indices say
@@ -77,10 +84,10 @@ __global__ void __launch_bounds__(256) k_compact(CompactArgs a) {
 #define SKIPKV_DECL(T, u) uint4 T##u;
   // always U loads per tile: rows past the end re-read the last kept row (index loads are clamped)
 #define SKIPKV_LOAD(T, u) \
-  T##u = *reinterpret_cast<const uint4 *>(base + (int64_t)__shfl(idx_##T, u * RPI + sub) * pitch + piece * 16);
+  T##u = *reinterpret_cast<const uint4 *>(base + (int64_t)__shfl(NI == 2 && u >= 4 ? idx2_##T : idx_##T, (u * RPI + sub) & 63) * pitch + piece * 16);
   // destination row of the lane's piece: position in the sequence, or (paged) its slot row; the shuffle
   // is taken by all lanes, outside any condition
-#define SKIPKV_DROW(T, u) const int64_t dr_##u = PAGED ? (int64_t)__shfl(dst_##T, u * RPI + sub) : (int64_t)(ks + u * RPI + sub);
+#define SKIPKV_DROW(T, u) const int64_t dr_##u = PAGED ? (int64_t)__shfl(NI == 2 && u >= 4 ? dst2_##T : dst_##T, (u * RPI + sub) & 63) : (int64_t)(ks + u * RPI + sub);
 #define SKIPKV_STORE(T, u) *reinterpret_cast<uint4 *>(base + dr_##u * pitch + piece * 16) = T##u;
 #define SKIPKV_STORE_TAIL(T, u) \
   if (ks + u * RPI + sub < nl) *reinterpret_cast<uint4 *>(base + dr_##u * pitch + piece * 16) = T##u;
@@ -95,30 +102,34 @@ __global__ void __launch_bounds__(256) k_compact(CompactArgs a) {
     }                                   \
   }
   // Wait until the loads of the tile about to be stored have landed.  Behind them in the queue
-  // are the previous tile's U stores (none for the first tile), one index load and the next
-  // tile's U loads (paged: plus the load of the next tile's destination rows, NX = 1).  The next tile is always loaded, also past the end (clamped, one tile of
+  // are the previous tile's U stores (none for the first tile), NI index loads and the next
+  // tile's U loads (paged: plus the NI loads of the next tile's destination rows, NX of them).  The next tile is always loaded, also past the end (clamped, one tile of
   // wasted reads per stream): unconditional loads keep the counts exact and the registers in place.
   SKIPKV_EACH(SKIPKV_DECL, A)
   SKIPKV_EACH(SKIPKV_DECL, B)
-  constexpr int NX = PAGED ? 1 : 0;
-  int idx_A = load_idx(first);
-  int idx_B = load_idx(first + TR);
-  int dst_A = load_dst(first), dst_B = 0;
+  constexpr int NX = PAGED ? NI : 0;
+  int idx_A = load_idx(first), idx2_A = NI == 2 ? load_idx(first + 64) : 0;
+  int idx_B = load_idx(first + TR), idx2_B = NI == 2 ? load_idx(first + TR + 64) : 0;
+  int dst_A = load_dst(first), dst2_A = NI == 2 ? load_dst(first + 64) : 0, dst_B = 0, dst2_B = 0;
   SKIPKV_EACH(SKIPKV_LOAD, A)
   for (int k0 = first;; k0 += 2 * TR) {
     idx_A = load_idx(k0 + 2 * TR);
+    if constexpr (NI == 2) idx2_A = load_idx(k0 + 2 * TR + 64);
     dst_B = load_dst(k0 + TR);
+    if constexpr (NI == 2) dst2_B = load_dst(k0 + TR + 64);
     SKIPKV_EACH(SKIPKV_LOAD, B)
     if (k0 != first)
-      asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * U + 1 + NX) : "memory");
+      asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * U + NI + NX) : "memory");
     else
-      asm volatile("s_waitcnt vmcnt(%0)" ::"n"(U + 1 + NX) : "memory");
+      asm volatile("s_waitcnt vmcnt(%0)" ::"n"(U + NI + NX) : "memory");
     SKIPKV_STORE_TILE(A, k0)
     if (k0 + TR >= nl) break;
     idx_B = load_idx(k0 + 3 * TR);
+    if constexpr (NI == 2) idx2_B = load_idx(k0 + 3 * TR + 64);
     dst_A = load_dst(k0 + 2 * TR);
+    if constexpr (NI == 2) dst2_A = load_dst(k0 + 2 * TR + 64);
     SKIPKV_EACH(SKIPKV_LOAD, A)
-    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * U + 1 + NX) : "memory");
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * U + NI + NX) : "memory");
     SKIPKV_STORE_TILE(B, k0 + TR)
     if (k0 + 2 * TR >= nl) break;
   }
@@ -146,24 +157,39 @@ __global__ void __launch_bounds__(256) k_kept_rows(CompactArgs a) {
   for (int k = lane; k < nl; k += 64) out[k] = rmap[max(0, min(kept[k], room - 1))];
 }
 
+template <int ROWB, int SL>
+void launch_slices(const CompactArgs &a, int64_t streams, hipStream_t st) {
+  const unsigned grid = (unsigned)((streams * (ROWB / SL) + 3) / 4);
+  if (a.row_map)
+    hipLaunchKernelGGL((k_compact<ROWB, SL, true>), dim3(grid), dim3(256), 0, st, a);
+  else
+    hipLaunchKernelGGL((k_compact<ROWB, SL, false>), dim3(grid), dim3(256), 0, st, a);
+}
+
 }  // namespace
 
+// A stream is a serial chain of tiles, so with few streams the chip waits for memory: rows are then split into
+// slices of 128 or 64 bytes (half a cache line: the least that a wave should take) as long as that makes no more
+// than 1024 waves, four per CU.  More waves than that gain nothing and the smaller pieces cost: whole step of 8 heads
+// per layer and 4224 tokens, us, with rows in 1 / 2 / 4 / 8 slices:
+//   bf16   32 streams: 154 / 116 / 97    128: 208 / 165 / 148    256: 288 / 217 / 199    512: 370 / 362 / 406
+//          768: 455 / 476 / 498    8192: 2333 / 2299 / 2573
+//   fp32   16 streams: 111 / 103 / 92 / 88    64: 333 / 235 / 191 / 176    256: 592 / 442 / 386 / 418
 hipError_t launch_compact(const CompactArgs &a, hipStream_t st) {
   const int64_t heads = (int64_t)a.n_layers * a.n_kv_heads * a.batch, streams = 2 * heads;
   if (streams == 0) return hipSuccess;
-  const unsigned grid = (unsigned)((streams + 3) / 4);
-  if (a.row_map) {
-    hipLaunchKernelGGL(k_kept_rows, dim3((unsigned)((heads + 3) / 4)), dim3(256), 0, st, a);
-    if (a.dtype == SKIPKV_BF16)
-      hipLaunchKernelGGL((k_compact<256, true>), dim3(grid), dim3(256), 0, st, a);
-    else
-      hipLaunchKernelGGL((k_compact<512, true>), dim3(grid), dim3(256), 0, st, a);
-    return hipGetLastError();
+  if (a.row_map) hipLaunchKernelGGL(k_kept_rows, dim3((unsigned)((heads + 3) / 4)), dim3(256), 0, st, a);
+  const int64_t fit = 1024 / streams;  // slices that make at most 1024 waves
+  if (a.dtype == SKIPKV_BF16) {
+    if (fit >= 4) launch_slices<256, 64>(a, streams, st);
+    else if (fit >= 2) launch_slices<256, 128>(a, streams, st);
+    else launch_slices<256, 256>(a, streams, st);
+  } else {
+    if (fit >= 8) launch_slices<512, 64>(a, streams, st);
+    else if (fit >= 4) launch_slices<512, 128>(a, streams, st);
+    else if (fit >= 2) launch_slices<512, 256>(a, streams, st);
+    else launch_slices<512, 512>(a, streams, st);
   }
-  if (a.dtype == SKIPKV_BF16)
-    hipLaunchKernelGGL((k_compact<256, false>), dim3(grid), dim3(256), 0, st, a);
-  else
-    hipLaunchKernelGGL((k_compact<512, false>), dim3(grid), dim3(256), 0, st, a);
   return hipGetLastError();
 }
 

@@ -449,3 +449,55 @@ def test_two_pass_scan_shapes(group, alpha, block_size):
         out = run_step(cfg, st, k, v, q)
     assert int(out.dev_status.item()) == 0
     assert _compare_all(cfg, st, out, k, v, k0, v0, q)["heads"] == 2 * len(offsets)
+
+
+@pytest.mark.parametrize("paged", [False, True])
+@pytest.mark.parametrize("dtype,n_layers", [("bf16", 1), ("bf16", 33), ("bf16", 65), ("f32", 1), ("f32", 17), ("f32", 33), ("f32", 65)])
+def test_compact_rows_in_slices(dtype, n_layers, paged):
+    # 16 streams per layer here: up to 256 / 512 of them move bf16 rows in slices of 64 / 128 bytes, up to
+    # 128 / 256 / 512 fp32 rows in slices of 64 / 128 / 256.  Lengths around a tile of every slice (16 to 128 rows).
+    H, n_toks = 4, [1, 150, 300]
+    st = _structure([[0, n] for n in n_toks[1:]])
+    T, bs = st.total_tokens, 16
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n_layers)
+    k0 = torch.randn((n_layers, H, T, 128), generator=g, device="cuda").to(dt)
+    v0 = torch.randn((n_layers, H, T, 128), generator=g, device="cuda").to(dt)
+    rng = np.random.default_rng(7)
+    kept = torch.full((n_layers, H, 2, T), -1, dtype=torch.int32)
+    new_len = torch.zeros((n_layers, H, 2), dtype=torch.int32)
+    rows = {}
+    for l in range(n_layers):
+        for h in range(H):
+            for b, n_tok in enumerate(n_toks[1:]):
+                n = int(rng.choice([1, 15, 17, 63, 65, 127, 128, 129, n_tok - 1]))
+                r = np.sort(rng.choice(n_tok, n, replace=False)).astype(np.int32)
+                rows[l, h, b] = r
+                kept[l, h, b, :n] = torch.from_numpy(r)
+                new_len[l, h, b] = n
+    kept, new_len = kept.cuda(), new_len.cuda()
+    cfg = W.Config("slices", 9, 2, n_layers, H, H, dtype, 0, 0, 0, 1, 1, 1.0, 0.0)
+    if paged:
+        nb = [-(-n // bs) for n in n_toks[1:]]
+        perm = torch.randperm(sum(nb), generator=g, device="cuda").to(torch.int32)
+        table = torch.full((2, max(nb)), -1, dtype=torch.int32, device="cuda")
+        table[0, :nb[0]], table[1, :nb[1]] = perm[:nb[0]], perm[nb[0]:]
+        t = [torch.arange(n, device="cuda") for n in n_toks[1:]]
+        blk = torch.cat([table[b, t[b] // bs].long() for b in range(2)])
+        slot = torch.cat([x % bs for x in t])
+        kp = torch.zeros((n_layers, sum(nb), bs, H, 128), dtype=dt, device="cuda")
+        vp = torch.zeros_like(kp)
+        kp[:, blk, slot], vp[:, blk, slot] = k0.transpose(1, 2), v0.transpose(1, 2)
+        so, sp, sf = (torch.from_numpy(x).cuda() for x in (st.seq_off, st.sent_ptr, st.sent_off))
+        cache = B.PagedCache(kp, vp, table, H, so, sp, sf, T, st.total_sentences)
+        ws = torch.empty(B.skipkv_compact_paged_workspace_bytes(cache, T), dtype=torch.uint8, device="cuda")
+        B.skipkv_compact_paged(cache, kept, new_len, T, None, ws)
+        k, v = kp[:, blk, slot].transpose(1, 2), vp[:, blk, slot].transpose(1, 2)
+    else:
+        k, v = k0.clone(), v0.clone()
+        B.skipkv_compact(make_cache(cfg, st, k, v), kept, new_len, T)
+    torch.cuda.synchronize()
+    for (l, h, b), r in rows.items():
+        t0, idx = int(st.seq_off[b]), torch.from_numpy(r).long().cuda() + int(st.seq_off[b])
+        assert torch.equal(k[l, h, t0:t0 + len(r)], k0[l, h, idx]) and torch.equal(v[l, h, t0:t0 + len(r)], v0[l, h, idx])
