@@ -8,9 +8,10 @@
 // length of {key >= K0} exceeds the room.  K0 is found bit by bit (32 score bits, then 12 index
 // bits); every step is one masked sum over the candidates.  Nothing is sorted.
 //
-// A head with at most 1024 sentences is handled by ONE wave, 16 sentences per lane in registers,
-// without any workgroup barrier; four such heads share a workgroup.  A head with more sentences
-// (up to 4096) is handled afterwards by the four waves together, with the same code.
+// A head with at most 1024 sentences is ranked by ONE wave, 2 to 16 sentences per lane in registers,
+// without any workgroup barrier; four such heads share a workgroup, or where there are few heads
+// the four waves of a workgroup rank the same one and share the writing.  A head with more sentences
+// (up to 4096) is handled by the four waves together, with the same code.
 #include <type_traits>
 
 #include "common.h"
@@ -142,10 +143,17 @@ __device__ __forceinline__ void keep_everything(const SelectArgs &a, int lhb, co
   }
 }
 
-// One head, handled by NW waves; gt = thread index inside the group, gw = wave inside the group.
-// keep_l: 1024 * NW bytes of LDS, 16-byte aligned.
-template <int NW>
-__device__ __forceinline__ void select_head(const SelectArgs &a, int lhb, const HeadShape &hs, int gt, int gw, uint8_t *keep_l, Exchange &x) {
+// One head, handled by NW waves with EPL sentences per lane; gt = thread index inside the group, gw = wave
+// inside the group.  keep_l: 64 * EPL * NW bytes of LDS, 16-byte aligned.  With NW = 1 the search may be run
+// by `parts` waves at once, each for itself with the same result; wave `part` of them then writes its share
+// of the kept indices, and wave 0 everything else.
+//
+// What bounds it: the length of one wave's instruction stream (loads of the head's shape, then of its
+// sentences, the steps of the search, the runs of kept indices), not bandwidth.  Hence all loads of a phase
+// go out before the first use, no more sentences per lane than the head needs, and four runs at a time.
+template <int NW, int EPL>
+__device__ __forceinline__ void select_head(const SelectArgs &a, int lhb, const HeadShape &hs, int gt, int gw, int part, int parts, uint8_t *keep_l, Exchange &x) {
+  static_assert(EPL == 2 || EPL % 4 == 0, "flags are read back as whole words");
   constexpr int G = 64 * NW;
   const int lane = gt & 63;
   const int lh = lhb / a.batch, b = lhb % a.batch;
@@ -156,7 +164,7 @@ __device__ __forceinline__ void select_head(const SelectArgs &a, int lhb, const 
   int32_t *noff = a.new_sent_off ? a.new_sent_off + (int64_t)lh * (a.total_sentences + a.batch) + sp : nullptr;
 
   if (hs.problem || n_tok <= budget) {  // nothing can be evicted, or the cache already fits
-    keep_everything(a, lhb, hs, gt, G, hs.problem);
+    if (part == 0) keep_everything(a, lhb, hs, gt, G, hs.problem);
     return;
   }
 
@@ -164,32 +172,41 @@ __device__ __forceinline__ void select_head(const SelectArgs &a, int lhb, const 
   const int room = budget - (n_tok - p_start);
 
   // ---- candidates, sentence s = r * G + gt: order-preserving image of the score, unprotected length
-  uint32_t hi[kEPL];
-  int len[kEPL];
+  uint32_t hi[EPL];
+  int len[EPL];
   int bad = 0;  // low half: offsets out of order, high half: NaN scores
+  {
+    int o0[EPL], o1[EPL];
+    float sc[EPL];
 #pragma unroll
-  for (int r = 0; r < kEPL; ++r) {
-    const int s = r * G + gt;
-    hi[r] = 0;
-    len[r] = 0;  // not a candidate: protected, or past the end
-    if (s < n_sent) {
-      const int o0 = off[s], o1 = off[s + 1];
-      // the ranges must run from 0 to N, strictly ascending (the scores of a head whose ranges the
-      // plan rejected were never written)
-      if (o1 <= o0 || (s == 0 && o0 != 0) || (s == n_sent - 1 && o1 != n_tok)) bad += 1;
-      if (o0 < p_start) {
-        const float sc = a.sent_score[col0 + s];
-        if (sc != sc) bad += 1 << 16;  // a NaN cannot be ranked (the scan marks scores it could not finish this way)
-        uint32_t u = __float_as_uint(sc);
-        if (u == 0x80000000u) u = 0;  // -0.0 ties with 0.0
-        hi[r] = (u & 0x80000000u) ? ~u : (u | 0x80000000u);
-        len[r] = max(0, min(o1, p_start) - o0);
+    for (int r = 0; r < EPL; ++r) {  // clamped instead of masked: all in flight together (n_sent >= 1 here)
+      const int s = min(r * G + gt, n_sent - 1);
+      o0[r] = off[s];
+      o1[r] = off[s + 1];
+      sc[r] = a.sent_score[col0 + s];
+    }
+#pragma unroll
+    for (int r = 0; r < EPL; ++r) {
+      const int s = r * G + gt;
+      hi[r] = 0;
+      len[r] = 0;  // not a candidate: protected, or past the end
+      if (s < n_sent) {
+        // the ranges must run from 0 to N, strictly ascending (the scores of a head whose ranges the
+        // plan rejected were never written)
+        if (o1[r] <= o0[r] || (s == 0 && o0[r] != 0) || (s == n_sent - 1 && o1[r] != n_tok)) bad += 1;
+        if (o0[r] < p_start) {
+          if (sc[r] != sc[r]) bad += 1 << 16;  // a NaN cannot be ranked (the scan marks scores it could not finish this way)
+          uint32_t u = __float_as_uint(sc[r]);
+          if (u == 0x80000000u) u = 0;  // -0.0 ties with 0.0
+          hi[r] = (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+          len[r] = max(0, min(o1[r], p_start) - o0[r]);
+        }
       }
     }
   }
   bad = group_sum<NW>(bad, gw, x);
   if (bad) {
-    keep_everything(a, lhb, hs, gt, G, (bad & 0xFFFF) ? SKIPKV_DEV_BAD_OFFSETS : SKIPKV_DEV_BAD_SCORES);  // scores under bad ranges were never written
+    if (part == 0) keep_everything(a, lhb, hs, gt, G, (bad & 0xFFFF) ? SKIPKV_DEV_BAD_OFFSETS : SKIPKV_DEV_BAD_SCORES);  // scores under bad ranges were never written
     return;
   }
 
@@ -198,94 +215,115 @@ __device__ __forceinline__ void select_head(const SelectArgs &a, int lhb, const 
   uint32_t H = 0;
   for (int bit = 31; bit >= 0; --bit) {
     const uint32_t th = H | (1u << bit);
-    int part = 0;
+    int sum = 0;
 #pragma unroll
-    for (int r = 0; r < kEPL; ++r) part += hi[r] >= th ? len[r] : 0;
-    if (group_sum<NW>(part, gw, x) > room) H = th;
+    for (int r = 0; r < EPL; ++r) sum += hi[r] >= th ? len[r] : 0;
+    if (group_sum<NW>(sum, gw, x) > room) H = th;
   }
   // ---- index part: among the candidates with hi == H, the largest index bound L such that those
-  // with index >= L, together with everything above H (which fits), do not fit
-  int above = 0;
-  int se[kEPL];
+  // with index >= L, together with everything above H (which fits), do not fit.  Where only one
+  // candidate has this score (the rule) that is its index.
+  int above = 0, ties = 0;
+  int se[EPL], se_sum = 0;
 #pragma unroll
-  for (int r = 0; r < kEPL; ++r) {
+  for (int r = 0; r < EPL; ++r) {
     above += hi[r] > H ? len[r] : 0;
     se[r] = (hi[r] == H && len[r] > 0) ? r * G + gt : -1;
+    ties += se[r] >= 0;
+    se_sum += max(se[r], 0);
   }
   above = group_sum<NW>(above, gw, x);
+  ties = group_sum<NW>(ties, gw, x);
   int L = 0;
-  for (int bit = 11; bit >= 0; --bit) {
-    const int tl = L | (1 << bit);
-    int part = 0;
+  if (ties == 1) {
+    L = group_sum<NW>(se_sum, gw, x);
+  } else {
+    for (int bit = 11; bit >= 0; --bit) {
+      const int tl = L | (1 << bit);
+      int sum = 0;
 #pragma unroll
-    for (int r = 0; r < kEPL; ++r) part += se[r] >= tl ? len[r] : 0;
-    if (above + group_sum<NW>(part, gw, x) > room) L = tl;
+      for (int r = 0; r < EPL; ++r) sum += se[r] >= tl ? len[r] : 0;
+      if (above + group_sum<NW>(sum, gw, x) > room) L = tl;
+    }
   }
   // ---- keep flags: key > (H, L); sentences that are not candidates keep their (protected) tokens
 #pragma unroll
-  for (int r = 0; r < kEPL; ++r) {
+  for (int r = 0; r < EPL; ++r) {
     const int s = r * G + gt;
     if (s < n_sent) {
       const uint8_t k = len[r] == 0 || hi[r] > H || (hi[r] == H && s > L);
       keep_l[s] = k;
-      if (a.sent_keep) a.sent_keep[col0 + s] = k;
+      if (a.sent_keep && part == 0) a.sent_keep[col0 + s] = k;
     }
   }
   if constexpr (NW > 1) __syncthreads();
 
-  // ---- sentences in index order, 16 consecutive ones per thread: every sentence keeps one
+  // ---- sentences in index order, EPL consecutive ones per thread: every sentence keeps one
   // contiguous run of tokens (its unprotected part if kept, followed by its protected part)
-  const int s0 = gt * kEPL;
-  const uint4 kb4 = *reinterpret_cast<const uint4 *>(keep_l + s0);
-  const uint32_t kb[4] = {kb4.x, kb4.y, kb4.z, kb4.w};
-  int run_bgn[kEPL], run_len[kEPL], run_dst[kEPL];
+  const int s0 = gt * EPL;
+  uint32_t kb[(EPL + 3) / 4];
+  if constexpr (EPL == 2) {
+    kb[0] = *reinterpret_cast<const uint16_t *>(keep_l + s0);
+  } else {
+#pragma unroll
+    for (int w = 0; w < EPL / 4; ++w) kb[w] = *reinterpret_cast<const uint32_t *>(keep_l + s0 + 4 * w);
+  }
+  int run_bgn[EPL], run_len[EPL], run_dst[EPL];
+  int end[EPL];
   int o_prev = off[min(s0, n_sent)];
+#pragma unroll
+  for (int r = 0; r < EPL; ++r) end[r] = off[min(s0 + r + 1, n_sent)];
   int tok = 0, sent = 0;
 #pragma unroll
-  for (int r = 0; r < kEPL; ++r) {
+  for (int r = 0; r < EPL; ++r) {
     const int s = s0 + r;
-    const int end = off[min(s + 1, n_sent)];
     const bool kp = (kb[r >> 2] >> (8 * (r & 3))) & 0xFF;
     const int bgn = kp ? o_prev : max(o_prev, p_start);
-    const int n = s < n_sent ? max(0, end - bgn) : 0;
+    const int n = s < n_sent ? max(0, end[r] - bgn) : 0;
     run_bgn[r] = bgn;
     run_len[r] = n;
     tok += n;
     sent += n > 0;
-    o_prev = end;
+    o_prev = end[r];
   }
   int total_tok, total_sent;
   int tok_run = group_scan_excl<NW>(tok, gw, lane, x, total_tok);
   int sent_run = group_scan_excl<NW>(sent, gw, lane, x, total_sent);
 #pragma unroll
-  for (int r = 0; r < kEPL; ++r) {
+  for (int r = 0; r < EPL; ++r) {
     run_dst[r] = tok_run;
     if (run_len[r] > 0) {
-      if (noff) noff[sent_run] = tok_run;
+      if (noff && part == 0) noff[sent_run] = tok_run;
       tok_run += run_len[r];
       ++sent_run;
     }
   }
-  if (gt == 0) {
+  if (gt == 0 && part == 0) {
     a.new_len[lhb] = total_tok;
     if (a.new_sent_cnt) a.new_sent_cnt[lhb] = total_sent;
     if (noff) noff[total_sent] = total_tok;
   }
-  // ---- ascending surviving token indices: the wave writes the runs of its lanes one after the other
+  // ---- ascending surviving token indices: sixteen lanes write the run of one lane at a time, four runs side
+  // by side (a run of 20 tokens would leave most of a whole wave idle)
+  const int g = lane >> 4, c16 = lane & 15;
+  const int lanes = min(64, max(0, (n_sent - 64 * gw * EPL + EPL - 1) / EPL));  // lanes of this wave that hold sentences
+  for (int q = 4 * part; q < lanes; q += 4 * parts) {
+    const int l = q + g;
 #pragma unroll
-  for (int r = 0; r < kEPL; ++r) {
-    unsigned long long todo = __ballot(run_len[r] > 0);
-    while (todo) {
-      const int l = __builtin_ctzll(todo);
-      todo &= todo - 1;
-      const int bgn = __builtin_amdgcn_readlane(run_bgn[r], l);
-      const int n = __builtin_amdgcn_readlane(run_len[r], l);
-      const int d = __builtin_amdgcn_readlane(run_dst[r], l);
-      for (int i = lane; i < n; i += 64) kept[d + i] = bgn + i;
+    for (int r = 0; r < EPL; ++r) {
+      const int n = __shfl(run_len[r], l), bgn = __shfl(run_bgn[r], l), d = __shfl(run_dst[r], l);
+      int32_t *out = kept + d;
+#pragma unroll
+      for (int u = 0; u < 3; ++u)
+        if (c16 + 16 * u < n) out[c16 + 16 * u] = bgn + c16 + 16 * u;
+      for (int i = c16 + 48; i < n; i += 16) out[i] = bgn + i;
     }
   }
 }
 
+// HPW: heads per workgroup.  4: a wave each.  1: the four waves of a workgroup search the same head and share
+// the writing of its indices.
+template <int HPW>
 __global__ void __launch_bounds__(256, 4) k_select(SelectArgs a) {
   __shared__ __align__(16) uint8_t keep_l[4 * kWaveSent];
   __shared__ int slots[8];
@@ -294,20 +332,26 @@ __global__ void __launch_bounds__(256, 4) k_select(SelectArgs a) {
   const int n_heads = a.n_lh * a.batch;
   Exchange x{slots, 0};
 
-  {  // every wave takes one head of its own if the head is small enough
-    const int lhb = blockIdx.x * 4 + wave;
+  {  // heads that one wave can rank
+    const int lhb = HPW == 4 ? blockIdx.x * 4 + wave : blockIdx.x;
     if (lhb < n_heads) {
       const HeadShape hs = head_shape(a, lhb);
-      if (hs.n_sent <= kWaveSent) select_head<1>(a, lhb, hs, lane, 0, keep_l + wave * kWaveSent, x);
+      uint8_t *kl = keep_l + wave * kWaveSent;
+      const int part = HPW == 4 ? 0 : wave, parts = HPW == 4 ? 1 : 4;
+      if (hs.n_sent <= 128) select_head<1, 2>(a, lhb, hs, lane, 0, part, parts, kl, x);
+      else if (hs.n_sent <= 256) select_head<1, 4>(a, lhb, hs, lane, 0, part, parts, kl, x);
+      else if (hs.n_sent <= 512) select_head<1, 8>(a, lhb, hs, lane, 0, part, parts, kl, x);
+      else if (hs.n_sent <= kWaveSent) select_head<1, kEPL>(a, lhb, hs, lane, 0, part, parts, kl, x);
     }
   }
-  for (int w = 0; w < 4; ++w) {  // the larger heads, one after the other, by the whole workgroup
-    const int lhb = blockIdx.x * 4 + w;
+  for (int w = 0; w < HPW; ++w) {  // the larger heads, one after the other, by the whole workgroup
+    const int lhb = blockIdx.x * HPW + w;
     if (lhb >= n_heads) break;
     const HeadShape hs = head_shape(a, lhb);
     if (hs.n_sent <= kWaveSent) continue;
     __syncthreads();  // the flag buffer is free: every wave is done with its own head (or the previous large one)
-    select_head<4>(a, lhb, hs, tid, wave, keep_l, x);  // more than SKIPKV_MAX_SENTENCES: flagged by head_shape, keeps everything
+    if (hs.n_sent <= 2 * kWaveSent) select_head<4, 8>(a, lhb, hs, tid, wave, 0, 1, keep_l, x);
+    else select_head<4, kEPL>(a, lhb, hs, tid, wave, 0, 1, keep_l, x);  // more than SKIPKV_MAX_SENTENCES: flagged by head_shape, keeps everything
   }
 }
 
@@ -541,7 +585,15 @@ hipError_t launch_select_tokens(const TokSelectArgs &a, hipStream_t st) {
 hipError_t launch_select(const SelectArgs &a, hipStream_t st) {
   const int heads = a.n_lh * a.batch;
   if (heads == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_select, dim3((heads + 3) / 4), dim3(256), 0, st, a);
+  // Four waves per head while that leaves no wave waiting for a slot (1024 heads), and for heads of more than 1024
+  // sentences, which a workgroup ranks together anyway (four of them one after the other otherwise).  us, four heads /
+  // one head per workgroup:  300 sentences, 256 heads: 23.6 / 14.3, 1024: 24.2 / 21.1, 1536: 26.5 / 28.0, 2048: 27.3 / 33.3;
+  // 58 sentences, 4096 heads: 16.4 / 30.8;  1200 sentences, 1536 heads: 126.8 / 55.6.  (Before there were fewer sentences
+  // per lane than 16, and one run at a time: 33.4, 34.1, 38.3, 39.6; 36.3; 263.6.)
+  if (heads <= 1024 || (int64_t)a.total_sentences > (int64_t)a.batch * kWaveSent)
+    hipLaunchKernelGGL(k_select<1>, dim3(heads), dim3(256), 0, st, a);
+  else
+    hipLaunchKernelGGL(k_select<4>, dim3((heads + 3) / 4), dim3(256), 0, st, a);
   return hipGetLastError();
 }
 

@@ -501,3 +501,39 @@ def test_compact_rows_in_slices(dtype, n_layers, paged):
     for (l, h, b), r in rows.items():
         t0, idx = int(st.seq_off[b]), torch.from_numpy(r).long().cuda() + int(st.seq_off[b])
         assert torch.equal(k[l, h, t0:t0 + len(r)], k0[l, h, idx]) and torch.equal(v[l, h, t0:t0 + len(r)], v0[l, h, idx])
+
+
+def test_select_gives_the_same_with_few_heads_and_with_many():
+    # up to 1024 heads a workgroup's four waves share one head, above that every wave has its own; the number of
+    # sentences per lane is 2, 4, 8 or 16
+    rng = np.random.default_rng(3)
+    n_sents = [1, 127, 128, 129, 256, 257, 512, 513, 1024, 1025, 2048, 2049, 4096]
+    st = _structure([np.concatenate([[0], np.cumsum(rng.integers(1, 70, size=n) if n < 300 else rng.integers(1, 5, size=n))]).tolist() for n in n_sents])
+    Bn, S, T = len(n_sents), st.total_sentences, st.total_tokens
+    score = np.round(rng.standard_normal((2, S)), 1).astype(np.float32)  # ties
+    budget = torch.from_numpy(np.maximum(16, (st.seq_len * rng.uniform(0.05, 0.95, size=Bn)).astype(np.int32))).cuda()
+    stride = int(budget.max())
+    got = {}
+    for L in (1, 40):
+        k = torch.zeros((L, 2, T, 128), dtype=torch.bfloat16, device="cuda")
+        cfg = W.Config("select-many", 9, Bn, L, 2, 8, "bf16", 0, 0, 0, 8, 16, 4.0, 0.0)
+        status = torch.zeros(1, dtype=torch.int32, device="cuda")
+        params = B.Params(8, 16, budget, max_budget=stride, dev_status=status)
+        out = [torch.full((L, 2, S), 7, dtype=torch.uint8, device="cuda")] + [torch.full(s, -1, dtype=torch.int32, device="cuda")
+               for s in ((L, 2, Bn, stride), (L, 2, Bn), (L, 2, S + Bn), (L, 2, Bn))]
+        B.skipkv_select(make_cache(cfg, st, k, k.clone()), params, torch.from_numpy(score).cuda().expand(L, 2, S).contiguous(), *out, stride)
+        torch.cuda.synchronize()
+        assert int(status.item()) == 0
+        got[L] = out
+    for few, many in zip(got[1], got[40]):
+        assert torch.equal(few.expand_as(many), many)
+    for h in range(2):
+        for b in range(Bn):
+            off = st.offsets(b).astype(np.int64)
+            sb, ns, p = st.sent_base(b), int(st.n_sent[b]), int(off[-1]) - min(16, int(off[-1]))
+            cand = np.clip(np.minimum(off[1:], p) - off[:-1], 0, None)
+            ora = oracle.select_sentences(np.where(cand > 0, score[h, sb:sb + ns].astype(np.float64), np.inf), cand, off, int(budget[b]), 16)
+            nl = int(got[1][2][0, h, b])
+            assert nl == ora["new_len"]
+            np.testing.assert_array_equal(got[1][1][0, h, b, :nl].cpu().numpy(), ora["kept_idx"])
+            np.testing.assert_array_equal(got[1][0][0, h, sb:sb + ns].cpu().numpy().astype(bool), ora["keep"])
