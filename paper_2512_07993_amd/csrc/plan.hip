@@ -29,129 +29,195 @@ __device__ __forceinline__ int run_end(const int *off, int start, int n_sent, in
   return lo;
 }
 
-// One block per sequence.  Chunks (two-pass scan) and spans (single-pass scan) are packed greedily:
-// the longest run of whole sentences within the unit's token and sentence limits; a sentence longer
-// than the token limit is a unit of its own (a span like that sends its sequence to the two-pass scan).
-__global__ void __launch_bounds__(256) k_plan(PlanArgs a) {
-  const int b = blockIdx.x;
-  const int tid = threadIdx.x;
-  const int tok0 = a.seq_off[b];
-  const int n_tok = seq_tokens(a.seq_off, a.len, b);
-  const int sp = a.sent_ptr[b];
-  const int n_sent = seq_sentences(a.sent_ptr, a.cnt, b);
-  const int32_t *off = a.sent_off + sp;
+// Plans of sequences: WPS waves each, 4 / WPS sequences per block.  Chunks (two-pass scan) and spans (single-pass
+// scan) are packed greedily: the longest run of whole sentences within the unit's token and sentence limits; a sentence
+// longer than the token limit is a unit of its own (a span like that sends its sequence to the two-pass scan).
+//
+// What bounds a plan: with few sequences the latency of the serial walks along the runs (an LDS read per step, 300 spans
+// in 32 K tokens), so the two walks run side by side; with thousands of them (every head a sequence of its own) the
+// atomic on the one word that hands out the ranges, 13 ns each, hence one for four sequences.  LDS and registers
+// are the same for both forms: a wave takes what fits a quarter of the tables (kMaxSent<1> sentences), longer
+// sequences are done by the block afterwards.  Measured, against a block
+// per sequence with both walks in one thread: 7168 sequences of 1.1 K tokens 95 -> 32 us, 4096 of 2.1 K 60 -> 23,
+// 4 of 32 K 43 -> 28, 16 of 2-16 K 23 -> 17.
+template <int WPS>
+constexpr int kMaxSent = WPS == 4 ? SKIPKV_MAX_SENTENCES : SKIPKV_MAX_SENTENCES / 4 - 1;
 
-  __shared__ int s_off[SKIPKV_MAX_SENTENCES + 1];
-  __shared__ int s_bad;
-  if (tid == 0) s_bad = 0;
-  __syncthreads();
+struct PlanShared {
+  int off[SKIPKV_MAX_SENTENCES + 1];
+  // End of the chunk (span) that would start at each sentence; the walk along them replaces them, from the front,
+  // by the first sentences of the chunks (spans) and a final n_sent.  Chunk k never starts before sentence k, so
+  // what is replaced has been read.
+  uint16_t chunk[SKIPKV_MAX_SENTENCES + 1];
+  uint16_t span[SKIPKV_MAX_SENTENCES + 1];
+  struct Seq {
+    int n_chunks, n_spans, fused;
+    unsigned long long counts, old;  // of the sequence, and drawn before it (packed as in the header)
+  } seq[4];
+};
 
-  bool reject = n_sent > SKIPKV_MAX_SENTENCES || n_sent < 0;
-  // explicit lengths and counts must fit the room that the CSR arrays describe
-  const bool overflow = !reject && (n_tok < 0 || n_tok > a.seq_off[b + 1] - tok0 || n_sent > a.sent_ptr[b + 1] - sp - 1);
-  if (overflow) {
-    if (tid == 0) s_bad = 1;
-  } else if (!reject) {
-    // validation: o[0] = 0, o[S] = N, strictly ascending
-    int bad = 0;
-    for (int s = tid; s <= n_sent; s += 256) {
-      const int o = off[s];
-      s_off[s] = o;
-      if (s < n_sent) bad |= (off[s + 1] <= o);
+// b < 0: the group has no sequence (in this pass), but takes part in the barriers.
+template <int WPS>
+__device__ __forceinline__ void plan_sequences(const PlanArgs &a, PlanShared &sh, int b, int gt, int grp) {
+  constexpr int G = 64 * WPS, PART = SKIPKV_MAX_SENTENCES / 4;
+  static_assert(SKIPKV_MAX_SENTENCES <= 65535, "sentence indices are kept in 16 bits here");
+  int *s_off = sh.off + grp * PART;
+  uint16_t *s_chunk = sh.chunk + grp * PART, *s_span = sh.span + grp * PART;
+  auto any = [](bool x) -> bool { return WPS == 4 ? __syncthreads_or(x) != 0 : __any(x) != 0; };
+  auto sync = [] {
+    if constexpr (WPS == 4) __syncthreads();
+    else __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // one wave: its LDS operations are in order
+  };
+
+  int tok0 = 0, n_tok = 0, sp = 0, n_sent = 0;
+  bool ok = b >= 0;
+  if (ok) {
+    tok0 = a.seq_off[b];
+    n_tok = seq_tokens(a.seq_off, a.len, b);
+    sp = a.sent_ptr[b];
+    n_sent = seq_sentences(a.sent_ptr, a.cnt, b);
+    const int32_t *off = a.sent_off + sp;
+    const bool reject = n_sent > SKIPKV_MAX_SENTENCES || n_sent < 0;
+    // explicit lengths and counts must fit the room that the CSR arrays describe
+    bool bad = !reject && (n_tok < 0 || n_tok > a.seq_off[b + 1] - tok0 || n_sent > a.sent_ptr[b + 1] - sp - 1);
+    bool longer = false;  // some sentence is longer than a span may be
+    if (!reject && !bad) {
+      // validation: o[0] = 0, o[S] = N, strictly ascending
+      for (int s = gt; s <= n_sent; s += G) {
+        const int o = off[s];
+        s_off[s] = o;
+        if (s < n_sent) {
+          const int n = off[s + 1] - o;
+          bad |= off[s + 1] <= o;
+          longer |= n > kSpanCap;
+        }
+      }
+      if (gt == 0) bad |= (off[0] != 0) | (off[n_sent] != n_tok) | (n_sent == 0 && n_tok != 0);
     }
-    if (tid == 0) bad |= (off[0] != 0) | (off[n_sent] != n_tok) | (n_sent == 0 && n_tok != 0);
-    if (bad) s_bad = 1;
+    bad = any(bad);
+    longer = any(longer);
+    ok = !reject && !bad;
+    for (int lh = gt; lh < a.n_lh; lh += G) a.ws.head_redo[(int64_t)lh * a.batch + b] = 0;
+    sync();
+    if (ok) {
+      // the greedy packing is a walk along s -> end(s); the ends are found for all sentences at
+      // once, so that the (serial) walk is one LDS read per chunk
+      for (int s = gt; s < n_sent; s += G) {
+        s_chunk[s] = (uint16_t)run_end(s_off, s, n_sent, kChunkCap, kChunkMaxSent);
+        s_span[s] = (uint16_t)run_end(s_off, s, n_sent, kSpanCap, kSpanMaxSent);
+      }
+    }
+    sync();
+    PlanShared::Seq &me = sh.seq[grp];
+    constexpr int kOther = WPS == 4 ? 64 : 1;  // the thread of the second walk: another wave, or another lane in step
+    if (ok && (gt == 0 || gt == kOther)) {
+      uint16_t *at = gt == 0 ? s_span : s_chunk;
+      int n = 0;
+      for (int start = 0; start < n_sent;) {
+        const int e = at[start];
+        at[n++] = (uint16_t)start;
+        start = e;
+      }
+      at[n] = (uint16_t)n_sent;
+      if (gt == 0) me.n_spans = n;
+      else me.n_chunks = n;
+    }
+    sync();
+    if (gt == 0) {
+      unsigned long long counts = 0;
+      if (ok) {
+        const int n_items = (me.n_spans + kItemSpans - 1) / kItemSpans, nrb = (n_sent + kRowBlock - 1) / kRowBlock;
+        counts = (unsigned long long)me.n_chunks | ((unsigned long long)n_items << kHdrItemShift) | ((unsigned long long)nrb << kHdrRbShift);
+        me.fused = !longer && n_items <= kFuseMaxItems;
+      } else if (a.dev_status) {
+        atomicOr(a.dev_status, reject ? SKIPKV_DEV_TOO_MANY_SENT : SKIPKV_DEV_BAD_OFFSETS);
+      }
+      me.counts = counts;
+    }
+  } else if (gt == 0) {
+    sh.seq[grp].counts = 0;
   }
   __syncthreads();
-  __shared__ int s_base, s_nchunks, s_ibase, s_nspans, s_fused;
-  static_assert(SKIPKV_MAX_SENTENCES <= 65535, "sentence indices are kept in 16 bits here");
-  __shared__ uint16_t s_next[SKIPKV_MAX_SENTENCES];    // end of the chunk that would start at each sentence
-  __shared__ uint16_t s_first[SKIPKV_MAX_SENTENCES];   // first sentence of every chunk
-  __shared__ uint16_t s_snext[SKIPKV_MAX_SENTENCES];   // the same for spans
-  __shared__ uint16_t s_sfirst[SKIPKV_MAX_SENTENCES + 1];
-  const bool ok = !reject && !s_bad;
-  for (int lh = tid; lh < a.n_lh; lh += 256) a.ws.head_redo[(int64_t)lh * a.batch + b] = 0;
-  // the greedy packing is a walk along s -> chunk_end(s); the ends are found for all sentences at
-  // once, so that the (serial) walk is one LDS read per chunk
-  if (ok)
-    for (int s = tid; s < n_sent; s += 256) {
-      s_next[s] = (uint16_t)run_end(s_off, s, n_sent, kChunkCap, kChunkMaxSent);
-      s_snext[s] = (uint16_t)run_end(s_off, s, n_sent, kSpanCap, kSpanMaxSent);
+  if (threadIdx.x == 0) {
+    // one atomic draws the ranges of chunks, items and row blocks of the block's sequences
+    unsigned long long sum = 0;
+#pragma unroll
+    for (int i = 0; i < 4 / WPS; ++i) sum += sh.seq[i].counts;
+    unsigned long long old = sum ? atomicAdd(&a.ws.hdr->ranges, sum) : 0;
+#pragma unroll
+    for (int i = 0; i < 4 / WPS; ++i) {
+      sh.seq[i].old = old;
+      old += sh.seq[i].counts;
     }
+  }
   __syncthreads();
-  if (tid == 0) {
-    s_nchunks = -1;
-    if (!ok) {
-      if (a.dev_status) atomicOr(a.dev_status, reject ? SKIPKV_DEV_TOO_MANY_SENT : SKIPKV_DEV_BAD_OFFSETS);
+  if (b < 0) return;
+  if (!ok) {
+    if (gt == 0) {
       a.ws.chunk_base[b] = 0;
       a.ws.chunk_cnt[b] = 0;
       a.ws.rb_base[b] = 0;
       a.ws.rb_cnt[b] = 0;
       a.ws.seq_fused[b] = 1;  // nothing to scan either way
-    } else {
-      int n_chunks = 0, longest = 0;
-      for (int start = 0; start < n_sent;) {
-        const int e = s_next[start];
-        longest = max(longest, s_off[e] - s_off[start]);
-        s_first[n_chunks++] = (uint16_t)start;
-        start = e;
-      }
-      int n_spans = 0, longest_span = 0;
-      for (int start = 0; start < n_sent;) {
-        const int e = s_snext[start];
-        longest_span = max(longest_span, s_off[e] - s_off[start]);
-        s_sfirst[n_spans++] = (uint16_t)start;
-        start = e;
-      }
-      s_sfirst[n_spans] = (uint16_t)n_sent;
-      // one atomic draws the block's ranges of chunks, items and row blocks
-      const int n_items = (n_spans + kItemSpans - 1) / kItemSpans;
-      const int nrb = (n_sent + kRowBlock - 1) / kRowBlock;
-      const unsigned long long old = atomicAdd(&a.ws.hdr->ranges, (unsigned long long)n_chunks | ((unsigned long long)n_items << kHdrItemShift) |
-                                                                      ((unsigned long long)nrb << kHdrRbShift));
-      const int base = hdr_chunks(old), ibase = hdr_items(old), rb0 = hdr_rowblocks(old);
-      a.ws.chunk_base[b] = base;
-      a.ws.chunk_cnt[b] = n_chunks;
-      (void)longest;
-      const bool fused = longest_span <= kSpanCap && n_items <= kFuseMaxItems;
-      a.ws.seq_fused[b] = fused;
-      if (!fused && n_chunks > 0) atomicAdd(&a.ws.hdr->n_unfused, 1);
-      a.ws.rb_base[b] = rb0;
-      a.ws.rb_cnt[b] = nrb;
-      for (int i = 0; i < nrb; ++i) a.ws.rowblocks[rb0 + i] = RowBlock{b, i * kRowBlock};
-      s_base = base;
-      s_nchunks = n_chunks;
-      s_ibase = ibase;
-      s_nspans = n_spans;
-      s_fused = fused;
     }
+    return;
   }
-  __syncthreads();
-  if (s_nchunks < 0) return;
-  const int base = s_base, n_chunks = s_nchunks, n_spans = s_nspans, n_items = (n_spans + kItemSpans - 1) / kItemSpans;
-  for (int j = tid; j < n_chunks; j += 256) {  // one record per chunk
-    const int s0 = s_first[j], e = s_next[s0];
+  const PlanShared::Seq &me = sh.seq[grp];
+  const int n_chunks = me.n_chunks, n_spans = me.n_spans, n_items = (n_spans + kItemSpans - 1) / kItemSpans;
+  const int base = hdr_chunks(me.old), ibase = hdr_items(me.old), rb0 = hdr_rowblocks(me.old), fused = me.fused;
+  const int nrb = hdr_rowblocks(me.counts);
+  if (gt == 0) {
+    a.ws.chunk_base[b] = base;
+    a.ws.chunk_cnt[b] = n_chunks;
+    a.ws.seq_fused[b] = fused;
+    if (!fused && n_chunks > 0) atomicAdd(&a.ws.hdr->n_unfused, 1);
+    a.ws.rb_base[b] = rb0;
+    a.ws.rb_cnt[b] = nrb;
+  }
+  for (int i = gt; i < nrb; i += G) a.ws.rowblocks[rb0 + i] = RowBlock{b, i * kRowBlock};
+  for (int j = gt; j < n_chunks; j += G) {  // one record per chunk
+    const int s0 = s_chunk[j], e = s_chunk[j + 1];
     a.ws.chunks[base + j] = Chunk{b, s0, e - s0, s_off[s0], s_off[e] - s_off[s0], sp + s0, tok0, n_tok};
   }
-  for (int j = tid; j < n_items; j += 256) {  // one record per item: up to kItemSpans consecutive spans
+  for (int j = gt; j < n_items; j += G) {  // one record per item: up to kItemSpans consecutive spans
     const int nsp = min(kItemSpans, n_spans - kItemSpans * j);
-    int32_t *r = a.ws.item_rec + (int64_t)(s_ibase + j) * kItemRecInts;
-    const int s0 = s_sfirst[kItemSpans * j];
+    int32_t *r = a.ws.item_rec + (int64_t)(ibase + j) * kItemRecInts;
+    const int s0 = s_span[kItemSpans * j];
     r[kIrB] = b;
-    r[kIrNsp] = s_fused ? nsp : 0;
-    r[kIrRec] = s_ibase + j;
+    r[kIrNsp] = fused ? nsp : 0;
+    r[kIrRec] = ibase + j;
     r[kIrTok0] = tok0;
     r[kIrNTok] = n_tok;
     r[kIrNItems] = n_items;
-    r[kIrFirst] = s_ibase;
+    r[kIrFirst] = ibase;
     r[kIrSoffIdx] = sp + s0;
     uint32_t ns = 0;
     for (int w = 0; w <= kItemSpans; ++w) {
-      const int sw = s_sfirst[kItemSpans * j + min(w, nsp)];
+      const int sw = s_span[kItemSpans * j + min(w, nsp)];
       r[kIrT0 + w] = s_off[sw];
-      if (w < nsp) ns |= (uint32_t)(s_sfirst[kItemSpans * j + w + 1] - sw) << (8 * w);
+      if (w < nsp) ns |= (uint32_t)(s_span[kItemSpans * j + w + 1] - sw) << (8 * w);
     }
     r[kIrNs] = (int32_t)ns;
+  }
+}
+
+template <int WPS>
+__global__ void __launch_bounds__(256) k_plan(PlanArgs a) {
+  __shared__ PlanShared sh;
+  if constexpr (WPS == 4) {
+    plan_sequences<4>(a, sh, blockIdx.x, threadIdx.x, 0);
+  } else {
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int b = blockIdx.x * 4 + wave;
+    const bool mine = b < a.batch && seq_sentences(a.sent_ptr, a.cnt, b) <= kMaxSent<1>;
+    plan_sequences<1>(a, sh, mine ? b : -1, lane, wave);
+    for (int w = 0; w < 4; ++w) {  // the longer ones, one after the other, by the whole block
+      const int bl = blockIdx.x * 4 + w;
+      if (bl >= a.batch) break;
+      if (seq_sentences(a.sent_ptr, a.cnt, bl) <= kMaxSent<1>) continue;
+      __syncthreads();  // everybody is done with the tables
+      plan_sequences<4>(a, sh, bl, threadIdx.x, 0);
+    }
   }
 }
 
@@ -168,7 +234,11 @@ __global__ void __launch_bounds__(256) k_plan_preset(Workspace ws) {
 hipError_t launch_plan(const PlanArgs &a, hipStream_t st) {
   hipLaunchKernelGGL(k_plan_reset, dim3(1), dim3(64), 0, st, a.ws.hdr);
   if (a.batch > 0) {
-    hipLaunchKernelGGL(k_plan, dim3(a.batch), dim3(256), 0, st, a);
+    // a wave per sequence from where a block each would fill the chip (four blocks per CU)
+    if (a.batch < 1024)
+      hipLaunchKernelGGL(k_plan<4>, dim3(a.batch), dim3(256), 0, st, a);
+    else
+      hipLaunchKernelGGL(k_plan<1>, dim3((a.batch + 3) / 4), dim3(256), 0, st, a);
     const int64_t cap16 = (int64_t)a.ws.ni_max * a.ws.rows / 2;
     const int gx = (int)std::min<int64_t>((cap16 + 255) / 256, std::max(32, 8192 / std::max(1, a.n_lh)));  // ~8192 workgroups in all
     if (a.n_lh > 0 && cap16 > 0) hipLaunchKernelGGL(k_plan_preset, dim3(gx, a.n_lh), dim3(256), 0, st, a.ws);

@@ -537,3 +537,34 @@ def test_select_gives_the_same_with_few_heads_and_with_many():
             assert nl == ora["new_len"]
             np.testing.assert_array_equal(got[1][1][0, h, b, :nl].cpu().numpy(), ora["kept_idx"])
             np.testing.assert_array_equal(got[1][0][0, h, sb:sb + ns].cpu().numpy().astype(bool), ora["keep"])
+
+
+def test_plans_of_a_thousand_sequences_equal_those_of_a_few():
+    # from 1024 sequences on a wave plans each (longer than 1023 sentences: the workgroup); below, a workgroup does
+    rng = np.random.default_rng(9)
+    offsets = [np.concatenate([[0], np.cumsum(rng.integers(1, 30, size=int(rng.integers(1, 9))))]).tolist() for _ in range(1030)]
+    for i, n in ((3, 1023), (5, 1024), (6, 1500), (1029, 300)):
+        offsets[i] = np.concatenate([[0], np.cumsum(rng.integers(1, 6, size=n))]).tolist()
+    offsets[8] = [0, 200, 210, 500, 800]            # sentences that the single-pass scan does not take
+    offsets[9] = [0]                                # an empty sequence
+    offsets[10] = [0, 7, 7, 20]                     # not ascending: reported, the others are not affected
+    st = _structure(offsets)
+    cfg = W.Config("plans", 9, len(offsets), 1, 1, 4, "bf16", 0, 0, 16, 4, 4, 8.0, 0.0)
+    k0, v0, q = _random_kvq(cfg, st, 5)
+    k, v = k0.clone(), v0.clone()
+    out = run_step(cfg, st, k, v, q)
+    for lo, hi in ((0, 515), (515, 1030)):
+        part = _structure(offsets[lo:hi])
+        t0, t1 = int(st.seq_off[lo]), int(st.seq_off[hi])
+        pcfg = W.Config("plans-part", 9, hi - lo, 1, 1, 4, "bf16", 0, 0, 16, 4, 4, 8.0, 0.0)
+        kp, vp = k0[:, :, t0:t1].contiguous(), v0[:, :, t0:t1].contiguous()
+        ref = run_step(pcfg, part, kp, vp, q[:, lo:hi].contiguous())
+        assert (int(ref.dev_status.item()) != 0) == (lo == 0) and int(out.dev_status.item()) != 0
+        assert torch.equal(k[:, :, t0:t1], kp) and torch.equal(v[:, :, t0:t1], vp)
+        assert torch.equal(out.new_len[..., lo:hi], ref.new_len) and torch.equal(out.new_sent_cnt[..., lo:hi], ref.new_sent_cnt)
+        for b in range(lo, hi):
+            if b == 10:
+                continue  # scores under bad ranges are never written
+            a, c, n = st.sent_base(b), part.sent_base(b - lo), int(st.n_sent[b])
+            assert torch.equal(out.sent_score[..., a:a + n], ref.sent_score[..., c:c + n])
+            assert torch.equal(out.sent_lambda[..., a:a + n], ref.sent_lambda[..., c:c + n])
