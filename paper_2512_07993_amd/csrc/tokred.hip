@@ -11,13 +11,22 @@
 // RAW keys (exact products, fp32 accumulation; fp32 caches are rounded to bf16 first) and the
 // scale factors are applied to the accumulators.
 //
-// Only the blocks at and right of the diagonal are computed.  One workgroup owns 256 rows (64 per
+// Only the blocks at and right of the diagonal are computed.  One workgroup owns 256 rows (32 per
 // wave: the A operands stay in registers) and walks the 64-column blocks from its own rows to the
-// end of the sequence, staged through LDS and shared by the 4 waves; the next block is fetched
-// into registers while the current one is multiplied.  The 256 x 256 square on the diagonal is
-// computed in full and gives row sums only; every block right of it gives e_ij both to row i
+// end of the sequence, staged through LDS and shared by the 8 waves; the next block is fetched
+// into registers while the current one is multiplied.  The 64 x 64 squares on the diagonal are
+// computed in full and give row sums only; every block right of them gives e_ij both to row i
 // (weighted with column j's factor) and, by symmetry, to row j (weighted with row i's factor):
 // the column sums of a block are reduced over the workgroup's rows and added to the row's total.
+//
+// What bounds a sweep: vector instructions.  An entry costs a matrix instruction's 16 cycles for four, and per lane
+// two scale multiplies, an exponential (two issue slots) and two fmas; counters show the vector pipe issuing for
+// 66 % and the matrix pipe busy for 30 % of a SIMD's cycles, and the two hardly overlap.  So: 32 rows per wave in 125
+// registers, which lets four waves share a SIMD (64 rows took 237: two waves); one barrier per column block and two LDS
+// buffers; column sums of four column tiles reduced over the lane groups together (three permutes); squares of
+// 64 instead of 256 on the diagonal; and waves that can issue matrix instructions first.  32 layers x 8
+// heads, 4 x 2-4 K tokens: a sweep takes 1970 us, with 64 rows per wave it took 2376 (without the priority 2030; with
+// branches between the column tiles, and their spills, 2190).
 // Totals are accumulated across workgroups as 64-bit FIXED-POINT integers (integer addition is
 // associative: the result does not depend on the order in which workgroups arrive, and the
 // conversion of an fp32 partial sum is exact at the chosen scale for all but negligible terms),
@@ -32,9 +41,10 @@ namespace skipkv {
 namespace {
 
 constexpr int kRows = kTokredRows;  // rows per workgroup
-constexpr int kTW = kRows / 64;      // 16-row tiles per wave
-constexpr int kCols = 64;      // columns per staged block
-constexpr int LSTR = 272;      // bytes per staged key row (256 + 16: 16-byte reads of 8 rows hit distinct banks)
+constexpr int kWaves = 8;            // waves per workgroup
+constexpr int kTW = kRows / 16 / kWaves;  // 16-row tiles per wave
+constexpr int kCols = 64;            // columns per staged block
+constexpr int LSTR = 272;            // bytes per staged key row (256 + 16: 16-byte reads of 8 rows hit distinct banks)
 constexpr float kSqrtLog2e = 1.2011224087864498f;
 // fixed-point scales of the two accumulations: row sums l <= e * N (2^40: room for N up to 2^21 tokens,
 // resolution 1e-12 against terms >= 0.37), and R <= e^2 / N... <= 8 (2^50: resolution 1e-15 against R ~ 1/N)
@@ -102,15 +112,26 @@ __global__ void __launch_bounds__(256) k_key_scale(TokRedArgs a) {
   }
 }
 
+// Sums of four columns' partial sums over the four lane groups: lane (g, c16) gets the total of v_g's column.
+// The first swap leaves (v0 | v2) and (v1 | v3) in the wave's halves, the second one sorts the rows.
+__device__ __forceinline__ float sum_lane_groups(float v0, float v1, float v2, float v3) {
+  typedef __attribute__((__vector_size__(2 * sizeof(uint32_t)))) uint32_t u32x2;
+  auto swap32 = [](float x, float y) {
+    const u32x2 r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+  };
+  const u32x2 r = __builtin_amdgcn_permlane16_swap(__float_as_uint(swap32(v0, v2)), __float_as_uint(swap32(v1, v3)), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
 // SWEEP 1: adds every row's sum of e_ij into acc (scale kFix1).  SWEEP 2: adds R (scale kFix2).
 template <int DT, int SWEEP>
-__global__ void __launch_bounds__(256, kTW == 4 ? 2 : 3) k_tokred_sweep(TokRedArgs a) {
+__global__ void __launch_bounds__(64 * kWaves, 4) k_tokred_sweep(TokRedArgs a) {
   constexpr int ESZ = DT == SKIPKV_BF16 ? 2 : 4;
   constexpr float kFix = SWEEP == 1 ? kFix1 : kFix2;
-  __shared__ __align__(16) char cols[kCols * LSTR];
-  __shared__ float col_c[kCols];     // scale factor of each staged column
-  __shared__ float col_w[kCols];     // weight of each staged column in a row's sum: 1 (sweep 1), 1 / l (sweep 2)
-  __shared__ float cpart[2][4][kCols];  // [block parity]: column sums of a block over each wave's rows
+  __shared__ __align__(16) char cols[2][kCols * LSTR];
+  __shared__ float col_cw[2][2][kCols];  // of each staged column: scale factor; weight in a row's sum: 1 (sweep 1), 1 / l (sweep 2)
+  __shared__ float cpart[2][kWaves][kCols];  // [block parity]: column sums of a block over each wave's rows
 
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, c16 = lane & 15, g = lane >> 4;
   // ---- which (head, sequence, row block) is this?
@@ -137,8 +158,8 @@ __global__ void __launch_bounds__(256, kTW == 4 ? 2 : 3) k_tokred_sweep(TokRedAr
   auto slot_of = [&](int row) -> int64_t { return rmap ? (int64_t)rmap[row] : (int64_t)row; };
   const int64_t col0 = (int64_t)lh * a.total_tokens + tok0;  // index of the sequence's first token in the per-token arrays
 
-  // ---- A operands: this wave's 64 rows (4 tiles), lane (row c16 of a tile, head-dim slice g)
-  const int rw0 = r0 + 16 * kTW * wave;
+  // ---- A operands: this wave's rows, lane (row c16 of a tile, head-dim slice g)
+  const int rw0 = __builtin_amdgcn_readfirstlane(r0 + 16 * kTW * wave);
   bf16x8 af[kTW][4];
   float row_c[kTW][4];  // scale factors of the lane's output rows (rows 4g+j of every tile)
   float row_w[kTW][4];  // their weights in a column's sum (0 for rows past the end)
@@ -162,14 +183,15 @@ __global__ void __launch_bounds__(256, kTW == 4 ? 2 : 3) k_tokred_sweep(TokRedAr
     for (int jj = 0; jj < 4; ++jj) rsum[t][jj] = 0.f;
   const float inv_n = SWEEP == 1 ? 1.f : 1.f / (float)n_tok;
 
-  // a column block is 64 rows x 16 pieces of 16 bytes: 4 pieces per thread
-  uint4 pre[4];
+  // a column block is 64 rows x 16 pieces of 16 bytes: kPieces pieces per thread
+  constexpr int kPieces = kCols * 16 / (64 * kWaves), kRowStep = 4 * kWaves;
+  uint4 pre[kPieces];
   float pre_c = 0.f, pre_w = 0.f;
   auto fetch = [&](int jb) {
 #pragma unroll
-    for (int it = 0; it < 4; ++it) {
-      const int idx = it * 256 + tid, row = min(jb + (idx >> 4), n_tok - 1), piece = idx & 15;
-      pre[it] = load_piece_bf16<DT>(kbase + slot_of(row) * pitch, piece);
+    for (int it = 0; it < kPieces; ++it) {
+      const int row = min(jb + it * kRowStep + (tid >> 4), n_tok - 1);
+      pre[it] = load_piece_bf16<DT>(kbase + slot_of(row) * pitch, tid & 15);
     }
     if (tid < kCols) {
       const int col = jb + tid;
@@ -177,80 +199,80 @@ __global__ void __launch_bounds__(256, kTW == 4 ? 2 : 3) k_tokred_sweep(TokRedAr
       pre_w = col < n_tok ? (SWEEP == 1 ? 1.f : a.inv_l[col0 + col]) : 0.f;  // weight 0 drops columns past the end
     }
   };
-  auto commit = [&]() {
+  auto commit = [&](int buf) {
 #pragma unroll
-    for (int it = 0; it < 4; ++it) {
-      const int idx = it * 256 + tid, row = idx >> 4, piece = idx & 15;
-      *reinterpret_cast<uint4 *>(cols + row * LSTR + piece * 16) = pre[it];
-    }
+    for (int it = 0; it < kPieces; ++it)
+      *reinterpret_cast<uint4 *>(cols[buf] + (it * kRowStep + (tid >> 4)) * LSTR + (tid & 15) * 16) = pre[it];
     if (tid < kCols) {
-      col_c[tid] = pre_c;
-      col_w[tid] = pre_w;
+      col_cw[0][buf][tid] = pre_c;
+      col_cw[1][buf][tid] = pre_w;
     }
   };
 
   // The column sums of block jb are added to the totals one block later, right after the next fetch has
-  // been issued: the atomics then travel during that block's products, and the wait for the fetched
-  // columns (which waits for everything this thread has in flight) finds them done.
+  // been issued: the atomics then travel during that block's products.  The waves take turns.
   auto emit = [&](int jb, int buf) {
-    if (jb >= r0 + kRows && tid < kCols && jb + tid < n_tok) {
-      const float tot = ((cpart[buf][0][tid] + cpart[buf][1][tid]) + cpart[buf][2][tid]) + cpart[buf][3][tid];
-      add_fixed(a.acc + col0 + jb + tid, tot * inv_n, kFix);
+    if (wave == ((jb / kCols) & (kWaves - 1)) && jb + lane < n_tok) {
+      float tot = 0.f;
+#pragma unroll
+      for (int w = 0; w < kWaves; ++w) tot += cpart[buf][w][lane];
+      add_fixed(a.acc + col0 + jb + lane, tot * inv_n, kFix);
     }
   };
   fetch(r0);
   int buf = 0;
   for (int jb = r0; jb < n_tok; jb += kCols, buf ^= 1) {
-    commit();
+    commit(buf);
+    // One barrier per block: a buffer is written again two blocks later, when every wave has passed the barrier
+    // of the block in between and with it the end of its own reads.
     __syncthreads();
     if (jb + kCols < n_tok) fetch(jb + kCols);  // lands while this block is multiplied
-    if (jb > r0) emit(jb - kCols, buf ^ 1);
-    const bool mirror = jb >= r0 + kRows;       // right of the diagonal square: the block also stands for its transpose
+    if (jb > r0 + kCols) emit(jb - kCols, buf ^ 1);  // the first block has no mirror image
     auto products = [&](auto mirror_c) {
       constexpr bool MIRROR = decltype(mirror_c)::value;
+      float csum[kCols / 16];  // the lane's columns over the wave's rows
+      const char *tile = cols[buf] + c16 * LSTR + g * 64;
+      const float *wts = &col_cw[0][buf][c16];
 #pragma unroll
       for (int ct = 0; ct < kCols / 16; ++ct) {
-        const int cbase = jb + 16 * ct;
-        if (cbase >= n_tok) continue;
         bf16x8 bfr[4];
 #pragma unroll
-        for (int kk = 0; kk < 4; ++kk) bfr[kk] = *reinterpret_cast<const bf16x8 *>(cols + (16 * ct + c16) * LSTR + (4 * g + kk) * 16);
-        const float cc = col_c[16 * ct + c16];
-        const float cw = col_w[16 * ct + c16];
-        float csum[4] = {0.f, 0.f, 0.f, 0.f};  // the lane's column over the wave's rows: four independent chains
+        for (int kk = 0; kk < 4; ++kk) bfr[kk] = *reinterpret_cast<const bf16x8 *>(tile + ct * (16 * LSTR) + kk * 16);
+        const float cc = wts[16 * ct];
+        const float cw = wts[2 * kCols + 16 * ct];
+        float cs[2] = {0.f, 0.f};
 #pragma unroll
         for (int t = 0; t < kTW; ++t) {
           f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+          __builtin_amdgcn_s_setprio(1);  // a wave that can feed the matrix cores goes first, the others' exponentials fill in
 #pragma unroll
           for (int kk = 0; kk < 4; ++kk) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[t][kk], bfr[kk], acc, 0, 0, 0);
+          __builtin_amdgcn_s_setprio(0);
 #pragma unroll
           for (int jj = 0; jj < 4; ++jj) {
             const float e = __builtin_amdgcn_exp2f(acc[jj] * (row_c[t][jj] * cc));
             rsum[t][jj] = fmaf(e, cw, rsum[t][jj]);
-            if constexpr (MIRROR) csum[jj] = fmaf(e, row_w[t][jj], csum[jj]);
+            if constexpr (MIRROR) cs[jj & 1] = fmaf(e, row_w[t][jj], cs[jj & 1]);
           }
         }
-        if constexpr (MIRROR) {
-          // the four lane groups hold different rows of the same column
-          float v = (csum[0] + csum[1]) + (csum[2] + csum[3]);
-          v += __shfl_xor(v, 16);
-          v += __shfl_xor(v, 32);
-          if (g == 0) cpart[buf][wave][16 * ct + c16] = v;
-        }
+        csum[ct] = cs[0] + cs[1];
+        __builtin_amdgcn_sched_barrier(0);  // no fragments of the next columns in registers yet: there are none to spare
       }
+      if constexpr (MIRROR) cpart[buf][wave][lane] = sum_lane_groups(csum[0], csum[1], csum[2], csum[3]);
     };
-    if (rw0 < n_tok) {
-      if (mirror) products(std::true_type{});
-      else products(std::false_type{});
-    } else if (mirror && g == 0) {  // a wave without rows adds nothing to the columns
-#pragma unroll
-      for (int ct = 0; ct < kCols / 16; ++ct) cpart[buf][wave][16 * ct + c16] = 0.f;
+    // 64 x 64 squares on the diagonal are computed in full, blocks right of them stand for their transposes
+    // too, blocks left of them are the transposes
+    const bool square = (jb & -kCols) == (rw0 & -kCols);
+    if (rw0 < n_tok && jb > rw0 && !square) products(std::true_type{});
+    else {
+      cpart[buf][wave][lane] = 0.f;
+      if (rw0 < n_tok && square) products(std::false_type{});
     }
-    __syncthreads();  // (a cpart buffer is written again two blocks later, behind two more barriers)
   }
+  __syncthreads();
   {
     const int last = r0 + (n_tok - 1 - r0) / kCols * kCols;
-    emit(last, ((last - r0) / kCols) & 1);
+    if (last > r0) emit(last, ((last - r0) / kCols) & 1);
   }
 
   // ---- sums across the 16 column lanes, then the rows' share of their totals
@@ -294,15 +316,15 @@ hipError_t launch_token_redundancy(const TokRedArgs &a, hipStream_t st) {
   const unsigned g2 = (unsigned)std::min<int64_t>((rows + 255) / 256, 1 << 16);
   if (a.dtype == SKIPKV_BF16) {
     hipLaunchKernelGGL(k_key_scale<SKIPKV_BF16>, dim3(g0), dim3(256), 0, st, a);
-    hipLaunchKernelGGL((k_tokred_sweep<SKIPKV_BF16, 1>), dim3(g1), dim3(256), 0, st, a);
+    hipLaunchKernelGGL((k_tokred_sweep<SKIPKV_BF16, 1>), dim3(g1), dim3(64 * kWaves), 0, st, a);
     hipLaunchKernelGGL(k_tokred_finish<1>, dim3(g2), dim3(256), 0, st, a);
-    hipLaunchKernelGGL((k_tokred_sweep<SKIPKV_BF16, 2>), dim3(g1), dim3(256), 0, st, a);
+    hipLaunchKernelGGL((k_tokred_sweep<SKIPKV_BF16, 2>), dim3(g1), dim3(64 * kWaves), 0, st, a);
     hipLaunchKernelGGL(k_tokred_finish<2>, dim3(g2), dim3(256), 0, st, a);
   } else {
     hipLaunchKernelGGL(k_key_scale<SKIPKV_F32>, dim3(g0), dim3(256), 0, st, a);
-    hipLaunchKernelGGL((k_tokred_sweep<SKIPKV_F32, 1>), dim3(g1), dim3(256), 0, st, a);
+    hipLaunchKernelGGL((k_tokred_sweep<SKIPKV_F32, 1>), dim3(g1), dim3(64 * kWaves), 0, st, a);
     hipLaunchKernelGGL(k_tokred_finish<1>, dim3(g2), dim3(256), 0, st, a);
-    hipLaunchKernelGGL((k_tokred_sweep<SKIPKV_F32, 2>), dim3(g1), dim3(256), 0, st, a);
+    hipLaunchKernelGGL((k_tokred_sweep<SKIPKV_F32, 2>), dim3(g1), dim3(64 * kWaves), 0, st, a);
     hipLaunchKernelGGL(k_tokred_finish<2>, dim3(g2), dim3(256), 0, st, a);
   }
   return hipGetLastError();

@@ -53,6 +53,18 @@ def test_ragged_batch_all_heads(dtype):
     _check(cfg, st, k, out, heads, 1e-3 if dtype == "f32" else 1e-4)
 
 
+def test_lengths_around_wave_rows_and_diagonal_squares():
+    # a wave has 32 rows, the squares on the diagonal 64: lengths that leave waves empty, half a square, and
+    # column blocks right of the workgroup's own 256 rows with 1 to 64 columns
+    lens = [31, 32, 33, 95, 96, 97, 127, 129, 191, 193, 287, 289, 319, 320, 321, 511, 513, 575, 577]
+    st = _structure([[0, n] for n in lens])
+    cfg = W.Config("tokred-edges", 9, len(lens), 1, 1, 4, "bf16", 0, 0, 64, 8, 16, 16.0, 0.0)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(78)
+    k = torch.randn((1, 1, st.total_tokens, 128), generator=g, device="cuda").to(torch.bfloat16)
+    _check(cfg, st, k, _run(cfg, st, k), [(0, 0, b) for b in range(len(lens))], 1e-4)
+
+
 def test_structured_keys_duplicates_and_scaling():
     # clusters of exact duplicates with wildly different norms (cosines are scale-free), plus noise rows
     rng = np.random.default_rng(3)
