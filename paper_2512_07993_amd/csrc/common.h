@@ -94,6 +94,7 @@ struct Workspace {
   uint16_t *vhat_lo;     // [LH, S_total, 128] bf16 low part (residual)
   float *sent_imp;       // [LH, S_total]    mean token importance over the candidate span
   float *sent_red;       // [LH, S_total]    mean token redundancy over the candidate span
+  int32_t span_cap;               // tokens per span, at most kSpanCap
   int32_t nc_max, ni_max, nrb_max, rows, rows2;  // rows = R, padded query rows per head; rows2 = R2, the same for the two-pass scan
   bool fits;                      // the counts fit the packed range counters of the plan header
   size_t bytes;
@@ -172,6 +173,8 @@ struct PlanArgs {
   Workspace ws;
   int32_t *dev_status;
   const int32_t *len, *cnt;  // nullable [batch]: explicit lengths and sentence counts (then seq_off / sent_ptr only give capacities)
+  bool alone = false;        // one block in all: it writes the header itself (set by launch_plan, as the next one)
+  bool preset = false;       // the blocks mark the statistics records of their sequences
 };
 hipError_t launch_plan(const PlanArgs &a, hipStream_t st);
 

@@ -568,3 +568,28 @@ def test_plans_of_a_thousand_sequences_equal_those_of_a_few():
             a, c, n = st.sent_base(b), part.sent_base(b - lo), int(st.n_sent[b])
             assert torch.equal(out.sent_score[..., a:a + n], ref.sent_score[..., c:c + n])
             assert torch.equal(out.sent_lambda[..., a:a + n], ref.sent_lambda[..., c:c + n])
+
+
+@pytest.mark.parametrize("kind", ["short", "long sentence", "bad offsets", "empty"])
+@pytest.mark.parametrize("n_layers", [1, 60])
+def test_a_sequence_alone_gives_what_it_gives_in_a_batch(kind, n_layers):
+    # a plan of one sequence writes the header itself; with few heads it marks the statistics records too
+    rng = np.random.default_rng(4)
+    first = {"short": np.concatenate([[0], np.cumsum(rng.integers(1, 40, size=30))]).tolist(), "long sentence": [0, 10, 300, 340],
+             "bad offsets": [0, 10, 10, 40], "empty": [0]}[kind]
+    pair = _structure([first, [0, 9, 30, 77, 100]])
+    one = _structure([first])
+    cfg = W.Config("pair", 9, 2, n_layers, 8, 32, "bf16", 0, 0, 24, 8, 8, 8.0, 0.0)
+    cfg1 = W.Config("alone", 9, 1, n_layers, 8, 32, "bf16", 0, 0, 24, 8, 8, 8.0, 0.0)
+    k0, v0, q = _random_kvq(cfg, pair, 6)
+    n, ns = int(one.seq_len[0]), int(one.n_sent[0])
+    ref = run_step(cfg, pair, k0.clone(), v0.clone(), q)
+    for _ in range(2):
+        k, v = k0[:, :, :n].contiguous(), v0[:, :, :n].contiguous()
+        out = run_step(cfg1, one, k, v, q[:, :1].contiguous())
+        assert int(out.dev_status.item()) == int(ref.dev_status.item()) and (int(out.dev_status.item()) != 0) == (kind == "bad offsets")
+        assert torch.equal(out.new_len[..., 0], ref.new_len[..., 0])
+        if kind != "bad offsets":
+            assert torch.equal(out.sent_score[..., :ns], ref.sent_score[..., :ns])
+            nl = int(out.new_len.max()) if ns else 0
+            assert torch.equal(out.kept_idx[:, :, 0, :min(nl, 1)], ref.kept_idx[:, :, 0, :min(nl, 1)])
