@@ -69,14 +69,19 @@ Workspace carve(const skipkv_cache *c, const RowLayout &rl, void *base) {
   const size_t B = (size_t)c->batch, LH = (size_t)c->n_layers * c->n_kv_heads;
   const size_t T = (size_t)c->total_tokens, S = (size_t)c->total_sentences;
   // two consecutive chunks of a sequence together exceed kChunkCap tokens or kChunkMaxSent sentences
-  w.nc_max = (int32_t)(2 * ((T + kChunkCap - 1) / kChunkCap + (S + kChunkMaxSent - 1) / kChunkMaxSent) + B);
+  const size_t nc = 2 * ((T + kChunkCap - 1) / kChunkCap + (S + kChunkMaxSent - 1) / kChunkMaxSent) + B;
+  // ... and each sequence's share of the chunk list is rounded up to whole runs, as far as the list may go
+  const size_t want = (size_t)scan_run_chunks(c->dtype, (int64_t)LH, (int64_t)T), end = std::max<size_t>(nc, (size_t)kHdrMaxChunks);
+  const size_t rc = std::min(want, 1 + (end - nc) / std::max<size_t>(B, 1));
+  w.run_chunks = (int32_t)rc;
+  w.nr_max = (int32_t)((nc + B * (rc - 1)) / rc);
   w.nrb_max = (int32_t)((S + kRowBlock - 1) / kRowBlock + B);
   // two consecutive spans of a sequence together exceed span_cap tokens or kSpanMaxSent sentences
   w.span_cap = span_cap_of(c->dtype, LH * T);
   const size_t cap = (size_t)w.span_cap;
   const size_t spans_max = 2 * ((T + cap - 1) / cap + (S + kSpanMaxSent - 1) / kSpanMaxSent) + B;
   w.ni_max = (int32_t)std::min<size_t>(spans_max / kItemSpans + B + 1, (size_t)0x7FFFFFFF);
-  w.fits = w.nc_max <= kHdrMaxChunks && spans_max / kItemSpans + B + 1 <= (size_t)kHdrMaxItems && w.nrb_max <= kHdrMaxRowBlocks;
+  w.fits = nc <= (size_t)kHdrMaxChunks && spans_max / kItemSpans + B + 1 <= (size_t)kHdrMaxItems && w.nrb_max <= kHdrMaxRowBlocks;
   w.rows = rl.rows;
   w.rows2 = rl.rows2;
   size_t off = 0;
@@ -94,9 +99,13 @@ Workspace carve(const skipkv_cache *c, const RowLayout &rl, void *base) {
   w.seq_fused = static_cast<int32_t *>(take(B * 4));
   w.head_redo = static_cast<int32_t *>(take(LH * B * 4));
   w.item_rec = static_cast<int32_t *>(take((size_t)w.ni_max * kItemRecInts * 4));
-  w.chunks = static_cast<Chunk *>(take((size_t)w.nc_max * sizeof(Chunk)));
+  // The list takes the places that its rounding needs from the records, of which there is one per run: together they
+  // have the room of nc of each, which grows with the cache whatever the runs' length.
+  const size_t list = align_up(std::min(end, nc + B * (want - 1)) * sizeof(Chunk)), record = LH * rl.rows2 * sizeof(float2);
+  char *const chunks = static_cast<char *>(take(std::max(align_up(nc * sizeof(Chunk)) + align_up(nc * record), list + w.nr_max * record)));
+  w.chunks = reinterpret_cast<Chunk *>(chunks);
+  w.stat_part = chunks ? reinterpret_cast<float2 *>(chunks + list) : nullptr;
   w.rowblocks = static_cast<RowBlock *>(take((size_t)w.nrb_max * sizeof(RowBlock)));
-  w.stat_part = static_cast<float2 *>(take(LH * w.nc_max * rl.rows2 * sizeof(float2)));
   w.item_stat = static_cast<float2 *>(take(LH * w.ni_max * rl.rows * sizeof(float2)));
   w.row_norm = static_cast<float *>(take(LH * B * rl.rows2 * sizeof(float)));
   w.vhat_hi = static_cast<uint16_t *>(take(LH * S * kD * 2));

@@ -85,9 +85,9 @@ struct Workspace {
   int32_t *seq_fused;    // [B] 1: the sequence goes through the single-pass scan
   int32_t *head_redo;    // [LH, B] 1: a wait of the single-pass scan ran out for this head: the two-pass scan does it again
   int32_t *item_rec;     // [ni_max][kItemRecInts] one record per item of the single-pass scan (ItemRec)
-  Chunk *chunks;         // [nc_max]
+  Chunk *chunks;         // [nr_max * run_chunks]  each sequence's chunks start at a multiple of run_chunks
   RowBlock *rowblocks;   // [nrb_max]
-  float2 *stat_part;     // [LH, nc_max, R2]  two-pass scan: per-chunk (max, sum) of every query row, log2 domain
+  float2 *stat_part;     // [LH, nr_max, R2]  two-pass scan: per run of chunks (max, sum) of every query row, log2 domain
   float2 *item_stat;     // [LH, ni_max, R]  single-pass scan: per-item (reference, sum) of every query row; the plan presets .x of the used records to kRowNormUnset
   float *row_norm;       // [LH, B, R2]      two-pass scan: log2 of the softmax normaliser of every query row
   uint16_t *vhat_hi;     // [LH, S_total, 128] bf16 high part of the unit sentence embedding
@@ -95,7 +95,8 @@ struct Workspace {
   float *sent_imp;       // [LH, S_total]    mean token importance over the candidate span
   float *sent_red;       // [LH, S_total]    mean token redundancy over the candidate span
   int32_t span_cap;               // tokens per span, at most kSpanCap
-  int32_t nc_max, ni_max, nrb_max, rows, rows2;  // rows = R, padded query rows per head; rows2 = R2, the same for the two-pass scan
+  int32_t run_chunks, nr_max;     // chunks per run of the two-pass scan, at most; runs
+  int32_t ni_max, nrb_max, rows, rows2;  // rows = R, padded query rows per head; rows2 = R2, the same for the two-pass scan
   bool fits;                      // the counts fit the packed range counters of the plan header
   size_t bytes;
 };
@@ -206,6 +207,7 @@ struct ScanArgs {
 };
 bool scan_fused_supported(const RowLayout &rl, int64_t row_pitch_bytes);
 hipError_t launch_scan_fused(const ScanArgs &a, hipStream_t st);    // single pass over K (sequences the plan marked fused)
+int scan_run_chunks(int dtype, int64_t n_lh, int64_t total_tokens);  // chunks that the two-pass scan takes at a time, at most
 int scan_two_pass_rows(const RowLayout &rl, int dtype);  // rows of the statistics arrays that the two-pass scan of this shape has
 hipError_t launch_scan_stats(const ScanArgs &a, hipStream_t st);    // pass A: row statistics + sentence embeddings
 hipError_t launch_row_norm(const ScanArgs &a, hipStream_t st);      // combine the records of pass A

@@ -133,7 +133,8 @@ __device__ __forceinline__ void plan_sequences(const PlanArgs &a, PlanShared &sh
       unsigned long long counts = 0;
       if (ok) {
         const int n_items = (me.n_spans + kItemSpans - 1) / kItemSpans, nrb = (n_sent + kRowBlock - 1) / kRowBlock;
-        counts = (unsigned long long)me.n_chunks | ((unsigned long long)n_items << kHdrItemShift) | ((unsigned long long)nrb << kHdrRbShift);
+        const int rc = a.ws.run_chunks;  // whole runs: the sequence's chunks start at a multiple of their length
+        counts = (unsigned long long)((me.n_chunks + rc - 1) / rc * rc) | ((unsigned long long)n_items << kHdrItemShift) | ((unsigned long long)nrb << kHdrRbShift);
         me.fused = !longer && n_items <= kFuseMaxItems;
       } else if (a.dev_status) {
         atomicOr(a.dev_status, reject ? SKIPKV_DEV_TOO_MANY_SENT : SKIPKV_DEV_BAD_OFFSETS);

@@ -290,7 +290,7 @@ __global__ void __launch_bounds__(256) k_scan(ScanArgs a) {
       float s = 0.f;
 #pragma unroll
       for (int w = 0; w < 4; ++w) s += wstat[(w * R + r) * 2 + 1] * __builtin_amdgcn_exp2f(wstat[(w * R + r) * 2] - m);
-      a.ws.stat_part[((int64_t)lh * a.ws.nc_max + c) * R + r] = make_float2(m, s);
+      a.ws.stat_part[((int64_t)lh * a.ws.nr_max + c) * R + r] = make_float2(m, s);
     }
   } else {
     if (tid < ns) {
@@ -305,7 +305,7 @@ __global__ void __launch_bounds__(256) k_scan(ScanArgs a) {
 
 template <int NP, int AL, bool PASSB>
 hipError_t launch_one(const ScanArgs &a, hipStream_t st) {
-  const int64_t items = (int64_t)a.n_layers * a.n_kv_heads * a.ws.nc_max;
+  const int64_t items = (int64_t)a.n_layers * a.n_kv_heads * a.ws.nr_max;
   if (items == 0) return hipSuccess;
   const int64_t grid = items < 4096 ? items : 4096;  // grid-stride over the items
   hipLaunchKernelGGL((k_scan<NP, AL, PASSB>), dim3((unsigned)grid), dim3(256), 0, st, a);

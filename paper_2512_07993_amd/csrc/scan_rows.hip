@@ -98,8 +98,14 @@ __device__ __forceinline__ bf16x8 join_tr(i16x4 lo, i16x4 hi) {
 enum ChunkRec : int { kChB = 0, kChS0, kChNs, kChT, kChLen, kChSoff, kChTok0, kChNTok, kChInts };
 static_assert(sizeof(Chunk) == kChInts * 4, "a chunk is read as eight words");
 
+// Chunks per run of a sequence of n chunks: the runs are of one length, the last one is not left with a short rest.
+__device__ __forceinline__ int run_length(int n, int run_chunks) {
+  const int runs = (n + run_chunks - 1) / run_chunks;
+  return (n + runs - 1) / runs;
+}
+
 template <int NP, int AL, bool PASSB, bool SIMPLE>
-__global__ void __launch_bounds__(64 * kWaves, 4) k_scan_rows(ScanArgs a, int run_chunks) {
+__global__ void __launch_bounds__(64 * kWaves, 4) k_scan_rows(ScanArgs a) {
   using SH = RowsShape<NP, AL>;
   constexpr int RS = SH::RS, TH = SH::TH, ALW = SH::ALW, SPW = SH::SPW, NTW = SH::NTW, RW = SH::RW, R = SH::R, NSUB = SH::NSUB, PG = SH::PG;
   constexpr int GT = kGroupTok;
@@ -117,11 +123,11 @@ __global__ void __launch_bounds__(64 * kWaves, 4) k_scan_rows(ScanArgs a, int ru
   // Fallback: only sequences and heads that the single-pass scan left, unless everything goes this way.
   if (!a.force_two_pass && a.ws.hdr->n_unfused == 0) return;
   const int n_lh = a.n_layers * a.n_kv_heads;
-  const int n_chunks = hdr_chunks(a.ws.hdr->ranges);
-  const int n_runs = (n_chunks + run_chunks - 1) / run_chunks;
+  const int run_chunks = a.ws.run_chunks, n_runs = hdr_chunks(a.ws.hdr->ranges) / run_chunks;
   const uint32_t n_items = (uint32_t)n_lh * (uint32_t)n_runs;
   const int n = a.n_q_heads / a.n_kv_heads;
   const ConstIntPtr chunks_c = (ConstIntPtr) reinterpret_cast<const int32_t *>(a.ws.chunks);
+  const ConstIntPtr chunk_base_c = (ConstIntPtr)a.ws.chunk_base, chunk_cnt_c = (ConstIntPtr)a.ws.chunk_cnt;
 
   // lane constants of the LDS addressing, as in the single-pass scan
   const uint32_t b_off = c16 * 256 + (((4 * g) ^ swz16(c16)) << 4);
@@ -129,19 +135,16 @@ __global__ void __launch_bounds__(64 * kWaves, 4) k_scan_rows(ScanArgs a, int ru
   const uint32_t tr_off = tr_row * 256 + (((((c16 >> 1) & 1) ^ swz16(tr_row)) & 15) << 4) + ((c16 & 1) << 3);
 
   for (uint32_t item = blockIdx.x; item < n_items; item += gridDim.x) {
-  const int lh = item / n_runs;
-  const int run_end = min(n_chunks, (int)(item % n_runs + 1) * run_chunks);
-  int c1 = (int)(item % n_runs) * run_chunks;
-  while (c1 < run_end) {
-    // ---- a segment: the run's chunks of one sequence
-    const int c0 = c1;
+    // ---- a run: chunks c0 .. c1 - 1 of a sequence, filed under the run_chunks places of the chunk list that the plan
+    // keeps for it.  Runs are counted from the sequence's first chunk, wherever its chunks stand in the list: that is up to
+    // the order in which the plan's blocks drew their ranges, and a head's sums must not depend on it.
+    const int lh = item / n_runs, run = (int)(item % n_runs);
+    const int b = chunks_c[(int64_t)run * run_chunks * kChInts + kChB];
+    const int cb = chunk_base_c[b], n_chunks = chunk_cnt_c[b], len = run_length(n_chunks, run_chunks);
+    const int c0 = cb + (run - cb / run_chunks) * len, c1 = min(c0 + len, cb + n_chunks);
     const ConstIntPtr ch0 = chunks_c + (int64_t)c0 * kChInts;
-    const int b = ch0[kChB];
     int n_tiles = 0;
-    do {
-      n_tiles += (chunks_c[(int64_t)c1 * kChInts + kChLen] + kTileRows - 1) / kTileRows;
-      ++c1;
-    } while (c1 < run_end && chunks_c[(int64_t)c1 * kChInts + kChB] == b);
+    for (int c = c0; c < c1; ++c) n_tiles += (chunks_c[(int64_t)c * kChInts + kChLen] + kTileRows - 1) / kTileRows;
     if (!a.force_two_pass && a.ws.seq_fused[b] && !a.ws.head_redo[(int64_t)lh * a.batch + b]) continue;  // done by the single-pass scan
     const int l = lh / a.n_kv_heads, h = lh % a.n_kv_heads;
     const int tok0 = ch0[kChTok0], n_tok = ch0[kChNTok], t_first = ch0[kChT];
@@ -153,10 +156,10 @@ __global__ void __launch_bounds__(64 * kWaves, 4) k_scan_rows(ScanArgs a, int ru
     kr.map_pitch = a.map_stride * 2;
     kr.page_size = (a.page_size >= 16 && (a.page_size & (a.page_size - 1)) == 0) ? a.page_size : 0;
 
-    // ---- load stream: tiles of the segment in order, chunk by chunk.  A tile's loads come in two parts (part j: rows
+    // ---- load stream: tiles of the run in order, chunk by chunk.  A tile's loads come in two parts (part j: rows
     // 4j .. 4j+3 of the wave's eight; the second one also the chunk's offsets, and on to the next tile), so that they
     // can be spread over the compute: issued in one go by all waves they queue up at the CU's address unit.  Rows past
-    // a chunk's end re-read its last row, and tiles past the segment its last tile's (nobody looks at either): no
+    // a chunk's end re-read its last row, and tiles past the run its last tile's (nobody looks at either): no
     // branch, and the same count every time.
     int lc, lt, lend, lns;
     const int32_t *lso;
@@ -201,7 +204,7 @@ __global__ void __launch_bounds__(64 * kWaves, 4) k_scan_rows(ScanArgs a, int ru
 
     // Pass A keeps a row's statistics relative to a reference fixed by the wave's first 16 tokens (mode 0: one fma,
     // one exponential, one add per logit).  Should a row's sum then lie outside what fp32 holds comfortably, the
-    // segment is done again: its row maxima (mode 1), then the sums relative to those (mode 2).
+    // run is done again: its row maxima (mode 1), then the sums relative to those (mode 2).
     [[maybe_unused]] int my_first = -1;  // becomes 0 once the wave has seen a token
     [[maybe_unused]] int t_ref = 0;      // ... and this is the first one
     for (int mode = 0;; ++mode) {
@@ -250,7 +253,7 @@ __global__ void __launch_bounds__(64 * kWaves, 4) k_scan_rows(ScanArgs a, int ru
         }
         if (i == -kAhead || i >= 0) {
           asm volatile("" ::: "memory");
-          lds_barrier();  // the tile's rows are there for all waves, and all are done with the tile (or segment) before it
+          lds_barrier();  // the tile's rows are there for all waves, and all are done with the tile (or run) before it
           asm volatile("" ::: "memory");
         }
         const int fill = slot == 0 ? kTileSlots - 1 : slot - 1;
@@ -504,8 +507,8 @@ __global__ void __launch_bounds__(64 * kWaves, 4) k_scan_rows(ScanArgs a, int ru
           for (int q = 0; q < SPW; ++q) lsum[q] = -INFINITY;
           continue;
         }
-        // ---- the segment's record, filed under its first chunk; rows of waves that shared the tokens are merged
-        float2 *out = a.ws.stat_part + ((int64_t)lh * a.ws.nc_max + c0) * R;
+        // ---- the run's record; rows of waves that shared the tokens are merged
+        float2 *out = a.ws.stat_part + ((int64_t)lh * a.ws.nr_max + run) * R;
         float *wstat = fbuf + 128;
 #pragma unroll
         for (int q = 0; q < SPW; ++q) {
@@ -532,28 +535,26 @@ __global__ void __launch_bounds__(64 * kWaves, 4) k_scan_rows(ScanArgs a, int ru
       }
     }  // modes
 
-  }  // segments
   }  // items
   wait_vm<0>();  // the loads past the last tile still write LDS that the workgroup is about to give up
 }
 
-// log2 of the softmax normaliser of every query row: merge the records of a head's segments.
-__global__ void __launch_bounds__(256) k_row_norm(ScanArgs a, int R, int run_chunks) {
+// log2 of the softmax normaliser of every query row: merge the records of a head's runs, in the sequence's order.
+__global__ void __launch_bounds__(256) k_row_norm(ScanArgs a, int R) {
   const int lhb = blockIdx.x, lh = lhb / a.batch, b = lhb % a.batch;
   if (!a.force_two_pass && a.ws.seq_fused[b] && !a.ws.head_redo[lhb]) return;  // the single-pass scan computed these itself
-  const int cb = a.ws.chunk_base[b], ce = cb + a.ws.chunk_cnt[b];
+  const int rc = a.ws.run_chunks, u0 = a.ws.chunk_base[b] / rc, u1 = u0 + (a.ws.chunk_cnt[b] + rc - 1) / rc;
   const int r = threadIdx.x;
-  if (r >= R || cb >= ce) return;
-  const float2 *recs = a.ws.stat_part + (int64_t)lh * a.ws.nc_max * R + r;
+  if (r >= R || u0 >= u1) return;
+  const float2 *recs = a.ws.stat_part + (int64_t)lh * a.ws.nr_max * R + r;
   float m = kRefInit, s = 0.f;
-  const int u1 = (ce - 1) / run_chunks;
-  for (int u = cb / run_chunks; u <= u1; u += 8) {
+  for (int u = u0; u < u1; u += 8) {
     float2 p[8];
 #pragma unroll
-    for (int k = 0; k < 8; ++k) p[k] = recs[(int64_t)max(cb, min(u + k, u1) * run_chunks) * R];
+    for (int k = 0; k < 8; ++k) p[k] = recs[(int64_t)min(u + k, u1 - 1) * R];
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
-      if (u + k > u1) break;
+      if (u + k >= u1) break;
       const float nm = fmaxf(m, p[k].x);
       s = s * __builtin_amdgcn_exp2f(m - nm) + p[k].y * __builtin_amdgcn_exp2f(p[k].x - nm);
       m = nm;
@@ -562,26 +563,17 @@ __global__ void __launch_bounds__(256) k_row_norm(ScanArgs a, int R, int run_chu
   a.ws.row_norm[(int64_t)lhb * R + r] = s > 0.f ? m + __builtin_amdgcn_logf(s) : INFINITY;
 }
 
-// Chunks per run: as many as leave every workgroup slot of the chip (512) at least eight runs, so that the last
-// ones to finish do not matter, and no more than kMaxRunChunks.  (One chunk per run, pass A at 160 rows: 4627 us;
-// sixteen: 4445 us, both with 256 threads.)
-int chunks_per_run(const ScanArgs &a) {
-  const int64_t chunks = (int64_t)a.n_layers * a.n_kv_heads * (a.total_tokens / kChunkCap + 1);
-  return (int)std::min<int64_t>(kMaxRunChunks, std::max<int64_t>(1, chunks / (8 * 512)));
-}
-
 template <int NP, int AL, bool PASSB>
 hipError_t launch_rows(const ScanArgs &a, hipStream_t st) {
   static_assert(RowsShape<NP, AL>::R <= 256, "one thread per row merges the records");
   if (a.ws.rows2 != RowsShape<NP, AL>::R) return hipErrorInvalidValue;
-  const int rc = chunks_per_run(a);
-  const int64_t items = (int64_t)a.n_layers * a.n_kv_heads * ((a.ws.nc_max + rc - 1) / rc);
+  const int64_t items = (int64_t)a.n_layers * a.n_kv_heads * a.ws.nr_max;
   if (items == 0) return hipSuccess;
   const dim3 grid((unsigned)std::min<int64_t>(items, 4096));
   if (a.row_map == nullptr && a.stride_tok * 2 < (1 << 24))  // lane offsets by a 24-bit multiply
-    hipLaunchKernelGGL((k_scan_rows<NP, AL, PASSB, true>), grid, dim3(64 * kWaves), 0, st, a, rc);
+    hipLaunchKernelGGL((k_scan_rows<NP, AL, PASSB, true>), grid, dim3(64 * kWaves), 0, st, a);
   else
-    hipLaunchKernelGGL((k_scan_rows<NP, AL, PASSB, false>), grid, dim3(64 * kWaves), 0, st, a, rc);
+    hipLaunchKernelGGL((k_scan_rows<NP, AL, PASSB, false>), grid, dim3(64 * kWaves), 0, st, a);
   return hipGetLastError();
 }
 
@@ -603,6 +595,13 @@ hipError_t dispatch(const ScanArgs &a, hipStream_t st) {
 
 }  // namespace
 
+// Chunks per run: as many as leave every workgroup slot of the chip (512) at least eight runs, so that the last
+// ones to finish do not matter, and no more than kMaxRunChunks.  The fp32 scan takes chunks one by one.
+int scan_run_chunks(int dtype, int64_t n_lh, int64_t total_tokens) {
+  if (dtype != SKIPKV_BF16) return 1;
+  return (int)std::min<int64_t>(kMaxRunChunks, std::max<int64_t>(1, n_lh * (total_tokens / kChunkCap + 1) / (8 * 512)));
+}
+
 int scan_two_pass_rows(const RowLayout &rl, int dtype) {
   if (dtype != SKIPKV_BF16) return rl.rows;
 #define SKIPKV_CASE(NP_, AL_) \
@@ -621,8 +620,7 @@ hipError_t launch_rows_scores(const ScanArgs &a, hipStream_t st) { return dispat
 hipError_t launch_row_norm(const ScanArgs &a, hipStream_t st) {
   const int blocks = a.n_layers * a.n_kv_heads * a.batch;
   if (blocks == 0) return hipSuccess;
-  const int rc = a.dtype == SKIPKV_BF16 ? chunks_per_run(a) : 1;  // the fp32 scan files a record per chunk
-  hipLaunchKernelGGL(k_row_norm, dim3(blocks), dim3(256), 0, st, a, a.ws.rows2, rc);
+  hipLaunchKernelGGL(k_row_norm, dim3(blocks), dim3(256), 0, st, a, a.ws.rows2);
   return hipGetLastError();
 }
 

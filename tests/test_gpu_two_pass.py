@@ -1,0 +1,108 @@
+"""The two-pass scan of bf16 caches where its statistics can go wrong: runs of several chunks, rows that see none of
+a chunk, sums near the end of the fp32 range, rows of very different scale, large and infinite keys."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2512_07993_amd import binding as B
+from paper_2512_07993_amd import workloads as W
+from helpers import make_cache
+from test_gpu_edges import _structure
+
+pytestmark = pytest.mark.gpu
+TWO = B.FLAG_FORCE_TWO_PASS
+
+
+def _score(cfg, st, k, q, flags=0, ranges=None):
+    """Scores, lambdas, token importance (V is not read)."""
+    cache = make_cache(cfg, st, k, k)
+    status = torch.zeros(1, dtype=torch.int32, device="cuda")
+    params = B.Params(cfg.obs_window, cfg.protect_window, max(cfg.budget, cfg.protect_window), dev_status=status, flags=flags)
+    out = [torch.full((cfg.n_layers, cfg.n_kv_heads, n), float("nan"), dtype=torch.float32, device="cuda")
+           for n in (st.total_sentences, st.total_sentences, st.total_tokens)]
+    if ranges is None:
+        ws = torch.empty(B.skipkv_workspace_bytes(cache, params), dtype=torch.uint8, device="cuda")
+        B.skipkv_score(cache, params, q, None, *out, ws)
+    else:
+        ws = torch.empty(B.skipkv_ranges_workspace_bytes(cache, params), dtype=torch.uint8, device="cuda")
+        B.skipkv_score_ranges(cache, ranges, params, q, None, *out, ws)
+    torch.cuda.synchronize()
+    assert int(status.item()) == 0
+    return out
+
+
+def _cfg(name, batch, L, H, group, alpha, protect=40):
+    return W.Config(name, 9, batch, L, H, H * group, "bf16", 0, 0, 96, alpha, max(alpha, protect), 16.0, 0.0)
+
+
+def _long_batch(L, H):
+    """Sequences of ragged lengths that make runs of more than one chunk (8 x 512 chunks of all heads for each chunk of a run)."""
+    rng = np.random.default_rng(3)
+    offsets = []
+    for n in [9500, 1500, 700, 8100, 260, 5333, 9001, 40, 7000, 3100, 6600, 9100, 4700, 2900]:
+        off = [0]
+        while off[-1] < n:
+            off.append(min(n, off[-1] + int(rng.integers(1, 50))))
+        offsets.append(off)
+    st = _structure(offsets)
+    assert L * H * (st.total_tokens // 256) >= 2 * 8 * 512
+    return offsets, st
+
+
+def _bits(t):
+    return t.view(torch.int32)
+
+
+@pytest.mark.parametrize("group,alpha", [(5, 32), (4, 16)])
+def test_runs_of_chunks_give_the_same_bits_wherever_a_sequence_stands(group, alpha):
+    # The plan's blocks draw their ranges of chunks in the order in which they arrive, and another order of the batch is
+    # another order of the ranges: a sequence's statistics must not depend on where its chunks stand.
+    L, H = 4, 8
+    offsets, st = _long_batch(L, H)
+    n = len(offsets)
+    cfg = _cfg("runs", n, L, H, group, alpha)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(1)
+    k = torch.randn((L, H, st.total_tokens, 128), generator=g, device="cuda").to(torch.bfloat16)
+    q = torch.randn((L, n, H * group, alpha, 128), generator=g, device="cuda").to(torch.bfloat16)
+    ref = _score(cfg, st, k, q, TWO)
+    for _ in range(3):
+        for x, y in zip(ref, _score(cfg, st, k, q, TWO)):
+            assert torch.equal(_bits(x), _bits(y))
+    order = list(np.random.default_rng(5).permutation(n))
+    st2 = _structure([offsets[b] for b in order])
+    k2 = torch.cat([k[:, :, st.seq_off[b]:st.seq_off[b + 1]] for b in order], 2)
+    got = _score(cfg, st2, k2, q[:, order].contiguous(), TWO)
+    for j, b in enumerate(order):
+        for x, y, per_tok in zip(ref, got, (False, False, True)):
+            a, c = (int(st.seq_off[b]), int(st2.seq_off[j])) if per_tok else (st.sent_base(b), st2.sent_base(j))
+            m = int(st.seq_len[b]) if per_tok else int(st.n_sent[b])
+            assert torch.equal(_bits(x[..., a:a + m]), _bits(y[..., c:c + m])), (b, j, per_tok)
+    # every head a sequence of its own
+    ranges = B.Ranges(*[torch.from_numpy(x.astype(np.int32)).cuda().expand(L, H, x.size).contiguous() for x in (st.seq_len, st.n_sent, st.sent_off)])
+    for _ in range(2):
+        for x, y in zip(ref, _score(cfg, st, k, q, TWO, ranges)):
+            assert torch.equal(_bits(x), _bits(y))
+
+
+def test_jumping_logits_in_runs_of_several_chunks():
+    # half of the queries see logits 200 log2 units above the first ones from some token of a run on, the other half as
+    # far below: the run's sums are done again with references that follow the logits
+    L, H, group, alpha = 4, 8, 5, 32
+    offsets, st = _long_batch(L, H)
+    n = len(offsets)
+    cfg = _cfg("run-jumps", n, L, H, group, alpha)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(2)
+    k = torch.randn((L, H, st.total_tokens, 128), generator=g, device="cuda").to(torch.bfloat16)
+    for b, t in ((0, 300), (0, 700), (3, 1000), (5, 17), (8, 5000)):
+        k[:, :, int(st.seq_off[b]) + t, 0] = 40.0
+    q = torch.randn((L, n, H * group, alpha, 128), generator=g, device="cuda").to(torch.bfloat16)
+    q[..., 0::2, :, 0] = 40.0
+    q[..., 1::2, :, 0] = -40.0
+    imp = _score(cfg, st, k, q, TWO)[2]
+    for l, h, b in ((0, 0, 0), (3, 7, 0), (1, 2, 3), (2, 5, 5), (0, 1, 8), (3, 3, 1)):
+        t0, t1 = int(st.seq_off[b]), int(st.seq_off[b + 1])
+        want = oracle.token_importance(q[l, b, h * group:(h + 1) * group].double().cpu().numpy(), k[l, h, t0:t1].double().cpu().numpy())
+        np.testing.assert_allclose(imp[l, h, t0:t1].cpu().numpy(), want, rtol=1e-3, atol=1e-12)
