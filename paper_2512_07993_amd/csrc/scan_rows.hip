@@ -17,8 +17,8 @@
 //     per tile; a chunk's sentence offsets travel with its tiles;
 //   - sentence sums are matrix products of a 0/2 indicator with the transposed key tile, 32 dimensions and 16
 //     sentences per wave, so that no wave waits for another one's sentences;
-//   - pass A's row sums are relative to a reference that the wave's first 16 tokens fix: one fma, one exponential and
-//     one add per logit, with an exact second try where that reference did not fit.
+//   - pass A's row sums are relative to a reference that the wave's first 16 tokens fix for each row: two fmas and one
+//     exponential per logit, with an exact second try where that reference did not fit.
 // Measured, pass A / pass B / k_row_norm in us, against one workgroup of 256 threads per chunk with the query tile in
 // LDS and a running maximum per row, which this replaces:
 //   48 layers x 8 heads, 4 x 32 K tokens, 160 rows (50 M keys, 12.9 GB):    7327 / 3926 / 196  ->  4189 / 3193 / 14
@@ -188,9 +188,12 @@ __global__ void __launch_bounds__(64 * kWaves, 4) k_scan_rows(ScanArgs a) {
     auto slot_aq = [&](int q) { return g + 4 * (rh * ALW + q / NP); };
     auto slot_used = [&](int q) { return q < SPW && q % NP < n && slot_aq(q) < a.alpha; };
     auto slot_row = [&](int q) { return 16 * (q >> 2) + 4 * g + (q & 3); };
-    [[maybe_unused]] float ref1 = kRefInit, lsum[SPW];  // pass A: the lane group's reference, the slots' sums
+    [[maybe_unused]] float lsum[SPW];                   // pass A: the slots' sums
     [[maybe_unused]] float cn[SPW];                     // pass B: log2 normaliser of the slot's row (+inf: unused slot)
-    float *row_ref = fbuf + 128 + 2 * kWaves * RW + wave * RW;   // pass A, mode 2: the rows' own references
+    [[maybe_unused]] float *row_ref = fbuf + 128 + 2 * kWaves * RW + wave * RW;  // pass A: the rows' references
+    if constexpr (!PASSB) {
+      if (lane < RW) row_ref[lane] = kRefInit;  // (kept by a row that sees no token of the wave)
+    }
 #pragma unroll
     for (int q = 0; q < SPW; ++q) {
       if constexpr (PASSB) {
@@ -202,8 +205,8 @@ __global__ void __launch_bounds__(64 * kWaves, 4) k_scan_rows(ScanArgs a) {
     }
     const int p_start = n_tok - min(a.protect, n_tok);  // first protected token
 
-    // Pass A keeps a row's statistics relative to a reference fixed by the wave's first 16 tokens (mode 0: one fma,
-    // one exponential, one add per logit).  Should a row's sum then lie outside what fp32 holds comfortably, the
+    // Pass A keeps a row's statistics relative to a reference of its own, its largest logit among the wave's first 16 tokens
+    // (mode 0: two fmas and one exponential per logit; a lane group's references are four LDS words per row tile).  Should a row's sum then lie outside what fp32 holds comfortably, the
     // run is done again: its row maxima (mode 1), then the sums relative to those (mode 2).
     [[maybe_unused]] int my_first = -1;  // becomes 0 once the wave has seen a token
     [[maybe_unused]] int t_ref = 0;      // ... and this is the first one
@@ -292,11 +295,18 @@ __global__ void __launch_bounds__(64 * kWaves, 4) k_scan_rows(ScanArgs a) {
               logits(s);
               if (s == 0) prefetch(0);
             }
+            float live[NSUB];  // rows past the chunk's end count nothing
 #pragma unroll
-            for (int s = 0; s < NSUB; ++s)
+            for (int s = 0; s < NSUB; ++s) live[s] = wt + 16 * s + c16 < cend ? 1.f : 0.f;
 #pragma unroll
-              for (int q = 0; q < SPW; ++q)  // rows past the chunk's end count nothing
-                lsum[q] += __builtin_amdgcn_exp2f(fmaf(acc[s][q >> 2][q & 3], kScale2, wt + 16 * s + c16 < cend ? -ref1 : -INFINITY));
+            for (int T = 0; T < NTW; ++T) {
+              const f32x4 ref = *reinterpret_cast<const f32x4 *>(row_ref + 16 * T + 4 * g);
+#pragma unroll
+              for (int s = 0; s < NSUB; ++s)
+#pragma unroll
+                for (int q = 4 * T; q < SPW && q < 4 * T + 4; ++q)
+                  lsum[q] = fmaf(__builtin_amdgcn_exp2f(fmaf(acc[s][T][q & 3], kScale2, -ref[q & 3])), live[s], lsum[q]);
+            }
           } else {
             prefetch(0);
 #pragma unroll
@@ -304,23 +314,25 @@ __global__ void __launch_bounds__(64 * kWaves, 4) k_scan_rows(ScanArgs a) {
               if (wt + 16 * s >= cend) continue;
               logits(s);
               const int t = wt + 16 * s + c16, lf = opaque(last_free);
-              float mx = -INFINITY;
 #pragma unroll
               for (int q = 0; q < SPW; ++q) {
                 float x = acc[s][q >> 2][q & 3] * kScale2;
                 if (!(t < cend && t <= lf + slot_aq(q))) x = -INFINITY;
                 acc[s][q >> 2][q & 3] = x;
-                mx = fmaxf(mx, x);
               }
-              if (mode == 0 && my_first < 0) {  // the wave's first 16 tokens fix the reference: their largest logit in the lane group
+              if (mode == 0 && my_first < 0) {  // the wave's first 16 tokens fix the references
                 my_first = 0;
                 t_ref = wt + 16 * s;
-                ref1 = fmaxf(row16_max_fast(mx), kRefInit);
+#pragma unroll
+                for (int q = 0; q < SPW; ++q) {
+                  const float m = fmaxf(row16_max_fast(acc[s][q >> 2][q & 3]), kRefInit);
+                  if (c16 == 0) row_ref[slot_row(q)] = m;
+                }
               }
 #pragma unroll
               for (int q = 0; q < SPW; ++q) {
                 const float x = acc[s][q >> 2][q & 3];
-                lsum[q] = mode == 1 ? fmaxf(lsum[q], x) : lsum[q] + __builtin_amdgcn_exp2f(x - (mode == 0 ? ref1 : row_ref[slot_row(q)]));
+                lsum[q] = mode == 1 ? fmaxf(lsum[q], x) : lsum[q] + __builtin_amdgcn_exp2f(x - row_ref[slot_row(q)]);
               }
             }
           }
@@ -512,7 +524,7 @@ __global__ void __launch_bounds__(64 * kWaves, 4) k_scan_rows(ScanArgs a) {
         float *wstat = fbuf + 128;
 #pragma unroll
         for (int q = 0; q < SPW; ++q) {
-          const float2 rec = make_float2(mode == 0 ? ref1 : row_ref[slot_row(q)], lsum[q]);
+          const float2 rec = make_float2(row_ref[slot_row(q)], lsum[q]);
           if (c16 == 0) *reinterpret_cast<float2 *>(wstat + 2 * (wave * RW + slot_row(q))) = rec;
         }
         asm volatile("" ::: "memory");

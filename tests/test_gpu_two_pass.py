@@ -106,3 +106,44 @@ def test_jumping_logits_in_runs_of_several_chunks():
         t0, t1 = int(st.seq_off[b]), int(st.seq_off[b + 1])
         want = oracle.token_importance(q[l, b, h * group:(h + 1) * group].double().cpu().numpy(), k[l, h, t0:t1].double().cpu().numpy())
         np.testing.assert_allclose(imp[l, h, t0:t1].cpu().numpy(), want, rtol=1e-3, atol=1e-12)
+
+
+def test_a_row_that_sees_none_of_a_chunk_keeps_its_own_reference():
+    # The last chunk begins inside the observation window: its first window queries see none of it, the others see logits
+    # 250 log2 units above everything before.
+    group, alpha = 5, 32
+    st = _structure([[0, 128, 256, 384, 512, 538]])
+    cfg = _cfg("hidden", 1, 1, 1, group, alpha)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+    k = torch.randn((1, 1, 538, 128), generator=g, device="cuda").to(torch.bfloat16)
+    q = torch.randn((1, 1, group, alpha, 128), generator=g, device="cuda").to(torch.bfloat16)
+    k[..., :512, 0] = 0.0
+    k[..., 512:, 0] = 50.0
+    q[..., 0] = 40.0
+    imp = _score(cfg, st, k, q)[2]
+    want = oracle.token_importance(q[0, 0].double().cpu().numpy(), k[0, 0].double().cpu().numpy())
+    np.testing.assert_allclose(imp[0, 0].cpu().numpy(), want, rtol=1e-3, atol=1e-12)
+
+
+@pytest.mark.parametrize("group,alpha", [(5, 32), (8, 32)])
+def test_normalisers_of_rows_next_to_rows_of_another_scale(group, alpha):
+    # One head of the group has logits 20 times as large as the others.  Where the others decide the maximum over the
+    # group, the importance carries the error of their normalisers, the same for all tokens of a query.  A normaliser and
+    # its difference to a logit lie between 8 and 16 log2 units: half a unit in the last place of fp32 there is 4.8e-7, two
+    # of them are a relative error of 2 x 4.8e-7 x ln 2 = 6.6e-7.
+    N = 4000
+    st = _structure([list(range(0, N + 1, 20))])
+    cfg = _cfg("scales", 1, 1, 4, group, alpha)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(4)
+    k = torch.randn((1, 4, N, 128), generator=g, device="cuda").to(torch.bfloat16)
+    q = torch.randn((1, 1, 4 * group, alpha, 128), generator=g, device="cuda").to(torch.bfloat16)
+    q[:, :, 0::group] *= 20.0
+    imp = _score(cfg, st, k, q, TWO)[2]
+    err = []
+    for h in range(4):
+        want = oracle.token_importance(q[0, 0, h * group:(h + 1) * group].double().cpu().numpy(), k[0, h].double().cpu().numpy())
+        rel = imp[0, h].double().cpu().numpy() / want - 1.0
+        err.append(abs(np.median(rel)))
+    assert max(err) < 7e-7
