@@ -6,6 +6,9 @@
 namespace skipkv {
 
 constexpr float kScale2 = 0.08838834764831845f * 1.4426950408889634f;  // log2(e) / sqrt(128)
+// A row's sum relative to a reference that its first logits fixed is taken as it is between these: further down terms
+// may be missing, further up the sums of a head's 1e5 records, which may all have that reference, need not fit any more.
+constexpr float kMinRowSum = 1e-30f, kMaxRowSum = 1e30f;
 constexpr float kRescaleSlack = 16.f;  // a lane's reference is refreshed when a logit exceeds it by this much (log2 units)
 
 template <int DT>

@@ -455,7 +455,7 @@ __global__ void __launch_bounds__(256, (DT == SKIPKV_BF16 ? 2 : 1)) k_scan_fused
 #pragma unroll
       for (int q = 0; q < SLP; ++q) {
         const bool used = q < SL && (q % NP) < n && (g + 4 * (q / NP)) < a.alpha;  // padding rows hold zero queries: whatever they sum to is never used
-        doubt = doubt || (used && !(tot[q] > 1e-30f && tot[q] < 3e38f));  // also catches NaN and infinity
+        doubt = doubt || (used && !(tot[q] > kMinRowSum && tot[q] < kMaxRowSum));  // also catches NaN and infinity
       }
       float refq[SLP];
 #pragma unroll

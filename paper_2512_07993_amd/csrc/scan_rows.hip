@@ -512,7 +512,7 @@ __global__ void __launch_bounds__(64 * kWaves, 4) k_scan_rows(ScanArgs a) {
         for (int q = 0; q < SPW; ++q) {
           lsum[q] = row16_sum_fast(lsum[q]);
           // rows of padding hold zero queries, and a window query that does not see the wave's first token sees none of its tokens
-          doubt = doubt || (slot_used(q) && my_first == 0 && t_ref <= last_free + slot_aq(q) && !(lsum[q] > 1e-30f && lsum[q] < 3e38f));  // also catches NaN and infinity
+          doubt = doubt || (slot_used(q) && my_first == 0 && t_ref <= last_free + slot_aq(q) && !(lsum[q] > kMinRowSum && lsum[q] < kMaxRowSum));  // also catches NaN and infinity
         }
         if (mode == 0 && __syncthreads_or(doubt)) {
 #pragma unroll

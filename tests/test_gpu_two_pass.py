@@ -126,6 +126,23 @@ def test_a_row_that_sees_none_of_a_chunk_keeps_its_own_reference():
     np.testing.assert_allclose(imp[0, 0].cpu().numpy(), want, rtol=1e-3, atol=1e-12)
 
 
+@pytest.mark.parametrize("flags", [0, TWO])
+@pytest.mark.parametrize("group,alpha", [(5, 32), (4, 16), (4, 32), (7, 8)])
+def test_sums_near_the_end_of_the_range_can_still_be_added(group, alpha, flags):
+    # All logits are 0 but those of two tokens, at 127.5 log2 units: either term fits fp32, their sum does not.  The
+    # tokens are in one span or chunk, in shares of different waves of a tile, or in different spans and chunks.
+    st = _structure([[0, 64, 128, 192, 256, 320, 400, 500]])
+    cfg = _cfg("range", 1, 1, 1, group, alpha)
+    for where in ((70, 100), (70, 120), (80, 96), (70, 130), (70, 300)):
+        k = torch.zeros((1, 1, 500, 128), dtype=torch.bfloat16, device="cuda")
+        q = torch.zeros((1, 1, group, alpha, 128), dtype=torch.bfloat16, device="cuda")
+        q[..., 0] = 40.0
+        k[..., list(where), 0] = 25.0
+        imp = _score(cfg, st, k, q, flags)[2]
+        want = oracle.token_importance(q[0, 0].double().cpu().numpy(), k[0, 0].double().cpu().numpy())
+        np.testing.assert_allclose(imp[0, 0].cpu().numpy(), want, rtol=1e-3, atol=1e-12)
+
+
 @pytest.mark.parametrize("group,alpha", [(5, 32), (8, 32)])
 def test_normalisers_of_rows_next_to_rows_of_another_scale(group, alpha):
     # One head of the group has logits 20 times as large as the others.  Where the others decide the maximum over the
