@@ -18,7 +18,12 @@
 //   - sentence sums are matrix products of a 0/2 indicator with the transposed key tile, 32 dimensions and 16
 //     sentences per wave, so that no wave waits for another one's sentences;
 //   - pass A's row sums are relative to a reference that the wave's first 16 tokens fix for each row: two fmas and one
-//     exponential per logit, with an exact second try where that reference did not fit.
+//     exponential per logit.  Where a later logit is too far above it (2^100) a wave does its share once more by itself,
+//     with references that follow the logits.  8 layers x 8 heads, 4 x 16 K tokens, 160 rows, whole score call: 962 us, with
+//     such a jump every 4096 / 1024 / 256 tokens 1016 / 1170 / 1338;
+//   - what the rare parts of pass A (first tile, ends of chunks, second try) need of the lane's number they compute
+//     there: held over the tiles it went to scratch, whose loads wait for the tiles
+//     in flight (whole call of the first shape below 10.6 ms instead of 10.0).
 // Measured, pass A / pass B / k_row_norm in us, against one workgroup of 256 threads per chunk with the query tile in
 // LDS and a running maximum per row, which this replaces:
 //   48 layers x 8 heads, 4 x 32 K tokens, 160 rows (50 M keys, 12.9 GB):    7327 / 3926 / 196  ->  4189 / 3193 / 14
@@ -129,11 +134,6 @@ __global__ void __launch_bounds__(64 * kWaves, 4) k_scan_rows(ScanArgs a) {
   const ConstIntPtr chunks_c = (ConstIntPtr) reinterpret_cast<const int32_t *>(a.ws.chunks);
   const ConstIntPtr chunk_base_c = (ConstIntPtr)a.ws.chunk_base, chunk_cnt_c = (ConstIntPtr)a.ws.chunk_cnt;
 
-  // lane constants of the LDS addressing, as in the single-pass scan
-  const uint32_t b_off = c16 * 256 + (((4 * g) ^ swz16(c16)) << 4);
-  const int tr_row = 4 * g + (c16 >> 2);
-  const uint32_t tr_off = tr_row * 256 + (((((c16 >> 1) & 1) ^ swz16(tr_row)) & 15) << 4) + ((c16 & 1) << 3);
-
   for (uint32_t item = blockIdx.x; item < n_items; item += gridDim.x) {
     // ---- a run: chunks c0 .. c1 - 1 of a sequence, filed under the run_chunks places of the chunk list that the plan
     // keeps for it.  Runs are counted from the sequence's first chunk, wherever its chunks stand in the list: that is up to
@@ -156,6 +156,12 @@ __global__ void __launch_bounds__(64 * kWaves, 4) k_scan_rows(ScanArgs a) {
     kr.map_pitch = a.map_stride * 2;
     kr.page_size = (a.page_size >= 16 && (a.page_size & (a.page_size - 1)) == 0) ? a.page_size : 0;
 
+    // lane constants of the LDS addressing, as in the single-pass scan (computed for each run: they need not outlive its tiles)
+    const int ol = opaque(lane), ac = ol & 15, ag = ol >> 4;
+    const uint32_t b_off = ac * 256 + (((4 * ag) ^ swz16(ac)) << 4);
+    const int tr_row = 4 * ag + (ac >> 2);
+    const uint32_t tr_off = tr_row * 256 + (((((ac >> 1) & 1) ^ swz16(tr_row)) & 15) << 4) + ((ac & 1) << 3);
+
     // ---- load stream: tiles of the run in order, chunk by chunk.  A tile's loads come in two parts (part j: rows
     // 4j .. 4j+3 of the wave's eight; the second one also the chunk's offsets, and on to the next tile), so that they
     // can be spread over the compute: issued in one go by all waves they queue up at the CU's address unit.  Rows past
@@ -163,7 +169,7 @@ __global__ void __launch_bounds__(64 * kWaves, 4) k_scan_rows(ScanArgs a) {
     // branch, and the same count every time.
     int lc, lt, lend, lns;
     const int32_t *lso;
-    const uint32_t v_piece = (uint32_t)((lane & 15) ^ swz16(8 * (wave & 1) + (lane >> 4))) << 4;
+    const uint32_t v_piece = (uint32_t)(ac ^ swz16(8 * (wave & 1) + ag)) << 4;
     auto load_chunk = [&](int c) {
       const ConstIntPtr r = chunks_c + (int64_t)c * kChInts;
       lt = r[kChT];
@@ -205,348 +211,371 @@ __global__ void __launch_bounds__(64 * kWaves, 4) k_scan_rows(ScanArgs a) {
     }
     const int p_start = n_tok - min(a.protect, n_tok);  // first protected token
 
-    // Pass A keeps a row's statistics relative to a reference of its own, its largest logit among the wave's first 16 tokens
-    // (mode 0: two fmas and one exponential per logit; a lane group's references are four LDS words per row tile).  Should a row's sum then lie outside what fp32 holds comfortably, the
-    // run is done again: its row maxima (mode 1), then the sums relative to those (mode 2).
+    // Pass A keeps a row's statistics relative to a reference of its own, its largest logit among the wave's first 16 tokens:
+    // two fmas and one exponential per logit; a lane group's references are four LDS words per row tile.  Should a row's
+    // sum then lie outside what fp32 holds comfortably, the wave does its share of the run once more (below).
     [[maybe_unused]] int my_first = -1;  // becomes 0 once the wave has seen a token
     [[maybe_unused]] int t_ref = 0;      // ... and this is the first one
-    for (int mode = 0;; ++mode) {
-      lc = c0;
-      load_chunk(c0);
-      // ---- the wave's query fragments: lane (row c16 of a tile, head-dim slice g), as the A operand wants them
-      bf16x8 afr[NTW][4];
-      {
-        const char *qbase = static_cast<const char *>(a.q);
-        // layer, KV head and sequence that address the query rows (the real ones under per-head ranges)
-        int ql = l, qh = h, qb = b, q_batch = a.batch, q_heads = a.n_q_heads;
-        if (a.virt_hk > 0) {
-          const int lh_r = b / a.virt_b;
-          qb = b % a.virt_b;
-          ql = lh_r / a.virt_hk;
-          qh = lh_r % a.virt_hk;
-          q_batch = a.virt_b;
-          q_heads = a.virt_hk * n;
-        }
+    lc = c0;
+    load_chunk(c0);
+    // ---- the wave's query fragments: lane (row c16 of a tile, head-dim slice g), as the A operand wants them
+    bf16x8 afr[NTW][4];
+    {
+      const char *qbase = static_cast<const char *>(a.q);
+      // layer, KV head and sequence that address the query rows (the real ones under per-head ranges)
+      int ql = l, qh = h, qb = b, q_batch = a.batch, q_heads = a.n_q_heads;
+      if (a.virt_hk > 0) {
+        const int lh_r = b / a.virt_b;
+        qb = b % a.virt_b;
+        ql = lh_r / a.virt_hk;
+        qh = lh_r % a.virt_hk;
+        q_batch = a.virt_b;
+        q_heads = a.virt_hk * n;
+      }
 #pragma unroll
-        for (int T = 0; T < NTW; ++T) {
-          // row c16 of a tile is register (c16 & 3) of lane group c16 / 4 in the output
-          const int slot = 4 * T + (c16 & 3), gq = c16 >> 2;
-          const int al = rh * ALW + slot / NP, i = slot % NP, aq = gq + 4 * al;
-          const bool used = slot < SPW && i < n && aq < a.alpha;
-          const int64_t row = (((int64_t)ql * q_batch + qb) * q_heads + (qh * n + (used ? i : 0))) * a.alpha + (used ? aq : 0);
+      for (int T = 0; T < NTW; ++T) {
+        // row c16 of a tile is register (c16 & 3) of lane group c16 / 4 in the output
+        const int slot = 4 * T + (c16 & 3), gq = c16 >> 2;
+        const int al = rh * ALW + slot / NP, i = slot % NP, aq = gq + 4 * al;
+        const bool used = slot < SPW && i < n && aq < a.alpha;
+        const int64_t row = (((int64_t)ql * q_batch + qb) * q_heads + (qh * n + (used ? i : 0))) * a.alpha + (used ? aq : 0);
 #pragma unroll
-          for (int kk = 0; kk < 4; ++kk) {
-            uint4 v = *reinterpret_cast<const uint4 *>(qbase + row * 256 + g * 64 + kk * 16);
-            if (!used) v = make_uint4(0, 0, 0, 0);
-            afr[T][kk] = __builtin_bit_cast(bf16x8, v);
-          }
+        for (int kk = 0; kk < 4; ++kk) {
+          uint4 v = *reinterpret_cast<const uint4 *>(qbase + row * 256 + g * 64 + kk * 16);
+          if (!used) v = make_uint4(0, 0, 0, 0);
+          afr[T][kk] = __builtin_bit_cast(bf16x8, v);
         }
       }
-      // ---- compute stream
-      int cc = c0, ct = t_first, c_t0 = t_first;
-      int cend = ct + ch0[kChLen], ns = ch0[kChNs], col = ch0[kChSoff] - b;
-      f32x4 pool[2];     // pass A: sentence key sums: slots 16 (wave / 4) + 4g + r, dimensions 16 (2 (wave % 4) + jj) + c16
-      float sum_i = 0.f, sum_r = 0.f;  // pass B: thread (sentence tid / 16, part tid % 16)
+    }
+    // ---- compute stream
+    int cc = c0, ct = t_first, c_t0 = t_first;
+    int cend = ct + ch0[kChLen], ns = ch0[kChNs], col = ch0[kChSoff] - b;
+    f32x4 pool[2];     // pass A: sentence key sums: slots 16 (wave / 4) + 4g + r, dimensions 16 (2 (wave % 4) + jj) + c16
+    float sum_i = 0.f, sum_r = 0.f;  // pass B: thread (sentence tid / 16, part tid % 16)
 #pragma unroll
-      for (int jj = 0; jj < 2; ++jj) pool[jj] = f32x4{0.f, 0.f, 0.f, 0.f};
-      int slot = 1;  // (of the first step, which loads tile 0 into slot 0)
-      for (int i = -kAhead; i < n_tiles; ++i) {
-        if (i >= 0) {
-          wait_vm<(kAhead - 1) * kTileLoads>();
-        }
-        if (i == -kAhead || i >= 0) {
-          asm volatile("" ::: "memory");
-          lds_barrier();  // the tile's rows are there for all waves, and all are done with the tile (or run) before it
-          asm volatile("" ::: "memory");
-        }
-        const int fill = slot == 0 ? kTileSlots - 1 : slot - 1;
-        auto prefetch = [&](int j) { issue(fill, j); };
-        if (i < 0) {
-          prefetch(0);
-          prefetch(1);
-          slot = slot + 1 == kTileSlots ? 0 : slot + 1;
-          continue;
-        }
-        const uint32_t tile_a = lds_addr(kt[slot]);
-        const int *soff = soffb[slot];
+    for (int jj = 0; jj < 2; ++jj) pool[jj] = f32x4{0.f, 0.f, 0.f, 0.f};
+    int slot = 1;  // (of the first step, which loads tile 0 into slot 0)
+    for (int i = -kAhead; i < n_tiles; ++i) {
+      if (i >= 0) {
+        wait_vm<(kAhead - 1) * kTileLoads>();
+      }
+      if (i == -kAhead || i >= 0) {
+        asm volatile("" ::: "memory");
+        lds_barrier();  // the tile's rows are there for all waves, and all are done with the tile (or run) before it
+        asm volatile("" ::: "memory");
+      }
+      const int fill = slot == 0 ? kTileSlots - 1 : slot - 1;
+      auto prefetch = [&](int j) { issue(fill, j); };
+      if (i < 0) {
+        prefetch(0);
+        prefetch(1);
         slot = slot + 1 == kTileSlots ? 0 : slot + 1;
-        const bool chunk_done = ct + kTileRows >= cend;
+        continue;
+      }
+      const uint32_t tile_a = lds_addr(kt[slot]);
+      const int *soff = soffb[slot];
+      slot = slot + 1 == kTileSlots ? 0 : slot + 1;
+      const bool chunk_done = ct + kTileRows >= cend;
 
-        // ---- logits: acc[s][T][j] = row 4g + j of the wave's row tile T, token c16 of its sub-tile s
-        const int wt = ct + 16 * th * NSUB;  // the wave's first token
-        const uint32_t brow = tile_a + th * NSUB * 4096 + b_off;
-        f32x4 acc[NSUB][NTW];
-        auto logits = [&](int s) {
+      // ---- logits: acc[s][T][j] = row 4g + j of the wave's row tile T, token c16 of its sub-tile s
+      const int wt = ct + 16 * th * NSUB;  // the wave's first token
+      const uint32_t brow = tile_a + th * NSUB * 4096 + b_off;
+      f32x4 acc[NSUB][NTW];
+      auto logits = [&](int s) {
 #pragma unroll
-          for (int T = 0; T < NTW; ++T) acc[s][T] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int T = 0; T < NTW; ++T) acc[s][T] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-          for (int kk = 0; kk < 4; ++kk) {
-            const bf16x8 bfr = *reinterpret_cast<const __attribute__((address_space(3))) bf16x8 *>((uintptr_t)((brow + s * 4096) ^ (kk << 4)));
+        for (int kk = 0; kk < 4; ++kk) {
+          const bf16x8 bfr = *reinterpret_cast<const __attribute__((address_space(3))) bf16x8 *>((uintptr_t)((brow + s * 4096) ^ (kk << 4)));
 #pragma unroll
-            for (int T = 0; T < NTW; ++T) acc[s][T] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(afr[T][kk], bfr, acc[s][T], 0, 0, 0);
-          }
-        };
-        const bool edge = wt + 16 * NSUB - 1 > last_free;  // some key is hidden from some window query
+          for (int T = 0; T < NTW; ++T) acc[s][T] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(afr[T][kk], bfr, acc[s][T], 0, 0, 0);
+        }
+      };
+      const bool edge = wt + 16 * NSUB - 1 > last_free;  // some key is hidden from some window query
 
-        if constexpr (!PASSB) {
-          if (!edge && (mode | my_first) == 0) {
-#pragma unroll
-            for (int s = 0; s < NSUB; ++s) {
-              logits(s);
-              if (s == 0) prefetch(0);
-            }
-            float live[NSUB];  // rows past the chunk's end count nothing
-#pragma unroll
-            for (int s = 0; s < NSUB; ++s) live[s] = wt + 16 * s + c16 < cend ? 1.f : 0.f;
-#pragma unroll
-            for (int T = 0; T < NTW; ++T) {
-              const f32x4 ref = *reinterpret_cast<const f32x4 *>(row_ref + 16 * T + 4 * g);
-#pragma unroll
-              for (int s = 0; s < NSUB; ++s)
-#pragma unroll
-                for (int q = 4 * T; q < SPW && q < 4 * T + 4; ++q)
-                  lsum[q] = fmaf(__builtin_amdgcn_exp2f(fmaf(acc[s][T][q & 3], kScale2, -ref[q & 3])), live[s], lsum[q]);
-            }
-          } else {
-            prefetch(0);
-#pragma unroll
-            for (int s = 0; s < NSUB; ++s) {
-              if (wt + 16 * s >= cend) continue;
-              logits(s);
-              const int t = wt + 16 * s + c16, lf = opaque(last_free);
-#pragma unroll
-              for (int q = 0; q < SPW; ++q) {
-                float x = acc[s][q >> 2][q & 3] * kScale2;
-                if (!(t < cend && t <= lf + slot_aq(q))) x = -INFINITY;
-                acc[s][q >> 2][q & 3] = x;
-              }
-              if (mode == 0 && my_first < 0) {  // the wave's first 16 tokens fix the references
-                my_first = 0;
-                t_ref = wt + 16 * s;
-#pragma unroll
-                for (int q = 0; q < SPW; ++q) {
-                  const float m = fmaxf(row16_max_fast(acc[s][q >> 2][q & 3]), kRefInit);
-                  if (c16 == 0) row_ref[slot_row(q)] = m;
-                }
-              }
-#pragma unroll
-              for (int q = 0; q < SPW; ++q) {
-                const float x = acc[s][q >> 2][q & 3];
-                lsum[q] = mode == 1 ? fmaxf(lsum[q], x) : lsum[q] + __builtin_amdgcn_exp2f(x - row_ref[slot_row(q)]);
-              }
-            }
-          }
-          prefetch(1);
-          // ---- sentence sums: [16 slots x 32 tokens] indicator (ones written as 2.0, a single bit; the unit
-          // normalisation removes the factor) times [32 tokens x 16 dimensions]: waves 0-3 take the chunk's first 16
-          // sentences, waves 4-7 the others (if there are any), each 32 of the 128 dimensions.  Lane group g brings
-          // tokens 4g .. 4g+3 of two 16-token stages.
-          const int pw = wave & 3, u = wave >> 2;
-          if (mode == 0 && !a.no_pool && ns > 16 * u) {
-            // offsets past the chunk's last one repeat it: empty slots
-            const int s_lo = soff[16 * u + c16] - ct, s_hi = soff[16 * u + c16 + 1] - ct;
-            bf16x8 trv[2][2];
-#pragma unroll
-            for (int w = 0; w < 2; ++w)
-#pragma unroll
-              for (int jj = 0; jj < 2; ++jj) {
-                const uint32_t ta = ((tile_a + tr_off) ^ ((2 * pw + jj) << 5)) + w * 8192;
-                trv[w][jj] = join_tr(lds_read_tr16(ta), lds_read_tr16(ta + 4096));
-              }
-#pragma unroll
-            for (int w = 0; w < 2; ++w) {
-              uint32_t ind[4];
-#pragma unroll
-              for (int s = 0; s < 2; ++s) {  // the lane's sentence over its 4 tokens of stage 2w + s
-                const int t0 = 32 * w + 16 * s;
-                const int ra = min(max(s_lo, t0), t0 + 16), rb = min(max(s_hi, t0), t0 + 16);
-                const uint32_t x = __builtin_amdgcn_ubfe(bitfield_mask(rb - ra, ra), 4 * g + 16 * s, 4);
-                ind[2 * s] = ((x << 14) | (x << 29)) & 0x40004000u;
-                ind[2 * s + 1] = ((x << 12) | (x << 27)) & 0x40004000u;
-              }
-              const bf16x8 av = __builtin_bit_cast(bf16x8, make_uint4(ind[0], ind[1], ind[2], ind[3]));
-#pragma unroll
-              for (int jj = 0; jj < 2; ++jj) pool[jj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, trv[w][jj], pool[jj], 0, 0, 0);
-            }
-          }
-          if (mode == 0 && !a.no_pool && chunk_done) {
-            // ---- unit sentence embeddings as bf16 hi + lo.  The dimensions of a row are stored as the waves
-            // hold them: position 32 pw + 2 c + jj is dimension 16 (2 pw + jj) + c; every embedding of a head
-            // is written by this kernel, so cosines are not affected.
-            float *sq = fbuf;  // [slot][pw]
-            if (ns > 16 * u) {
-#pragma unroll
-              for (int r = 0; r < 4; ++r) {
-                const float v = row16_sum_fast(fmaf(pool[0][r], pool[0][r], pool[1][r] * pool[1][r]));
-                if (c16 == 0) sq[4 * (16 * u + 4 * g + r) + pw] = v;
-              }
-            }
-            asm volatile("" ::: "memory");
-            lds_barrier();
-            asm volatile("" ::: "memory");
-            if (ns > 16 * u) {
-              float4 ss4[4];
-              int len[4];
-#pragma unroll
-              for (int r = 0; r < 4; ++r) {
-                const int si = 16 * u + 4 * g + r;
-                ss4[r] = *reinterpret_cast<const float4 *>(sq + 4 * si);
-                len[r] = soff[si + 1] - soff[si];  // 0 past the last sentence
-              }
-              const int64_t o = ((int64_t)lh * a.total_sentences + col + 16 * u) * (kD / 2) + 16 * pw;
-              uint32_t *dhi = reinterpret_cast<uint32_t *>(a.ws.vhat_hi) + o, *dlo = reinterpret_cast<uint32_t *>(a.ws.vhat_lo) + o;
-#pragma unroll
-              for (int r = 0; r < 4; ++r) {
-                const float ss = ((ss4[r].x + ss4[r].y) + ss4[r].z) + ss4[r].w;
-                // mean / (|mean| + eps) = sum / (|sum| + eps * len), sums and eps scaled by 2
-                const float inv = __builtin_amdgcn_rcpf(__builtin_amdgcn_sqrtf(ss) + 2e-12f * (float)len[r]);
-                const float u0 = pool[0][r] * inv, u1 = pool[1][r] * inv;
-                const uint32_t hi = pack_bf16x2(u0, u1);
-                const uint32_t lo = pack_bf16x2(u0 - __uint_as_float(hi << 16), u1 - __uint_as_float(hi & 0xFFFF0000u));
-                if (len[r] > 0) {
-                  dhi[(4 * g + r) * (kD / 2) + c16] = hi;
-                  dlo[(4 * g + r) * (kD / 2) + c16] = lo;
-                }
-              }
-#pragma unroll
-              for (int jj = 0; jj < 2; ++jj) pool[jj] = f32x4{0.f, 0.f, 0.f, 0.f};
-            }
-          }
-        } else {
-          // ---- token importance: max over the group's heads in registers, exp2, sum over the wave's window queries
-          float *parts = fbuf, *imp = fbuf + NPART * GT;
-          const int goff = (ct - c_t0) % GT;  // the tile's place in its group of GT tokens
+      if constexpr (!PASSB) {
+        if (!edge && my_first == 0) {
 #pragma unroll
           for (int s = 0; s < NSUB; ++s) {
             logits(s);
             if (s == 0) prefetch(0);
           }
+          float live[NSUB];  // rows past the chunk's end count nothing
+#pragma unroll
+          for (int s = 0; s < NSUB; ++s) live[s] = wt + 16 * s + c16 < cend ? 1.f : 0.f;
+#pragma unroll
+          for (int T = 0; T < NTW; ++T) {
+            const f32x4 ref = *reinterpret_cast<const f32x4 *>(row_ref + 16 * T + 4 * g);
+#pragma unroll
+            for (int s = 0; s < NSUB; ++s)
+#pragma unroll
+              for (int q = 4 * T; q < SPW && q < 4 * T + 4; ++q)
+                lsum[q] = fmaf(__builtin_amdgcn_exp2f(fmaf(acc[s][T][q & 3], kScale2, -ref[q & 3])), live[s], lsum[q]);
+          }
+        } else {
+          prefetch(0);
 #pragma unroll
           for (int s = 0; s < NSUB; ++s) {
-            float sum = 0.f;
+            if (wt + 16 * s >= cend) continue;
+            logits(s);
+            const int sl = opaque(lane), sc = sl & 15, sg = sl >> 4;  // (lane constants are not kept over the tiles for this)
+            const int t = wt + 16 * s + sc, lf = last_free + sg + 4 * rh * ALW;
 #pragma unroll
-            for (int al = 0; al < ALW; ++al) {
-              float gm = -INFINITY;
+            for (int q = 0; q < SPW; ++q) {
+              float x = acc[s][q >> 2][q & 3] * kScale2;
+              if (!(t < cend && t <= lf + 4 * (q / NP))) x = -INFINITY;
+              acc[s][q >> 2][q & 3] = x;
+            }
+            if (my_first < 0) {  // the wave's first 16 tokens fix the references
+              my_first = 0;
+              t_ref = wt + 16 * s;
 #pragma unroll
-              for (int i2 = 0; i2 < NP; ++i2) {
-                const int q = al * NP + i2;
-                gm = fmaxf(gm, fmaf(acc[s][q >> 2][q & 3], kScale2, -cn[q]));
-              }
-              if (edge && wt + 16 * s + c16 > last_free + g + 4 * (rh * ALW + al)) gm = -INFINITY;
-              sum += __builtin_amdgcn_exp2f(gm);
-            }
-            if constexpr (PG == 1) {
-              sum += __shfl_xor(sum, 16);
-              sum += __shfl_xor(sum, 32);
-              if (g == 0) parts[rh * GT + goff + 16 * (th * NSUB + s) + c16] = sum;
-            } else {
-              parts[(4 * rh + g) * GT + goff + 16 * (th * NSUB + s) + c16] = sum;
-            }
-          }
-          prefetch(1);
-          if (chunk_done || goff + kTileRows == GT) {
-            // the parts of the importance are added in a fixed order, then the sentences' sums over their
-            // unprotected part
-            const int g0 = ct - goff, g1 = min(cend, g0 + GT);
-            asm volatile("" ::: "memory");
-            lds_barrier();
-            asm volatile("" ::: "memory");
-            if (tid < GT) {
-              float tot = 0.f;
-#pragma unroll
-              for (int p = 0; p < NPART; ++p) tot += parts[p * GT + tid];
-              imp[tid] = g0 + tid < g1 ? tot / (float)a.alpha : 0.f;
-            }
-            asm volatile("" ::: "memory");
-            lds_barrier();
-            asm volatile("" ::: "memory");
-            const int64_t tok_col = (int64_t)lh * a.total_tokens + tok0;
-            static_assert(kChunkMaxSent * 16 == 64 * kWaves && GT <= 64 * kWaves, "16 lanes per sentence of a chunk, one thread per token of a group");
-            const int si = tid >> 4, sub = tid & 15;
-            if (si < ns) {
-              const int lo = max(soff[si], g0), hi = min(min(soff[si + 1], p_start), g1);
-              for (int t = lo + sub; t < hi; t += 16) {
-                sum_i += imp[t - g0];
-                if (a.tok_red) sum_r += a.tok_red[tok_col + t];
+              for (int q = 0; q < SPW; ++q) {
+                const float m = fmaxf(row16_max_fast(acc[s][q >> 2][q & 3]), kRefInit);
+                if (sc == 0) row_ref[16 * (q >> 2) + 4 * sg + (q & 3)] = m;
               }
             }
-            if (a.tok_imp && tid < GT && g0 + tid < g1) a.tok_imp[tok_col + g0 + tid] = imp[tid];
-            if (chunk_done) {
-              sum_i = row16_sum_fast(sum_i);
-              if (a.tok_red) sum_r = row16_sum_fast(sum_r);
-              if (si < ns && sub == 0) {
-                const int len = min(soff[si + 1], p_start) - soff[si];
-                const int64_t o = (int64_t)lh * a.total_sentences + col + si;
-                a.ws.sent_imp[o] = len > 0 ? sum_i / (float)len : 0.f;
-                a.ws.sent_red[o] = len > 0 ? sum_r / (float)len : 0.f;
-              }
-              sum_i = sum_r = 0.f;
-            }
+#pragma unroll
+            for (int q = 0; q < SPW; ++q) lsum[q] += __builtin_amdgcn_exp2f(acc[s][q >> 2][q & 3] - row_ref[16 * (q >> 2) + 4 * sg + (q & 3)]);
           }
         }
-        ct += kTileRows;
-        if (ct >= cend && cc + 1 < c1) {
-          ++cc;
-          const ConstIntPtr r = chunks_c + (int64_t)cc * kChInts;
-          c_t0 = ct = r[kChT];
-          cend = ct + r[kChLen];
-          ns = r[kChNs];
-          col = r[kChSoff] - b;
+        prefetch(1);
+        // ---- sentence sums: [16 slots x 32 tokens] indicator (ones written as 2.0, a single bit; the unit
+        // normalisation removes the factor) times [32 tokens x 16 dimensions]: waves 0-3 take the chunk's first 16
+        // sentences, waves 4-7 the others (if there are any), each 32 of the 128 dimensions.  Lane group g brings
+        // tokens 4g .. 4g+3 of two 16-token stages.
+        const int pw = wave & 3, u = wave >> 2;
+        if (!a.no_pool && ns > 16 * u) {
+          // offsets past the chunk's last one repeat it: empty slots
+          const int g4 = opaque(4 * g);  // (no register over the tiles for 4 g + 16)
+          const int s_lo = soff[16 * u + c16] - ct, s_hi = soff[16 * u + c16 + 1] - ct;
+          bf16x8 trv[2][2];
+#pragma unroll
+          for (int w = 0; w < 2; ++w)
+#pragma unroll
+            for (int jj = 0; jj < 2; ++jj) {
+              const uint32_t ta = ((tile_a + tr_off) ^ ((2 * pw + jj) << 5)) + w * 8192;
+              trv[w][jj] = join_tr(lds_read_tr16(ta), lds_read_tr16(ta + 4096));
+            }
+#pragma unroll
+          for (int w = 0; w < 2; ++w) {
+            uint32_t ind[4];
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {  // the lane's sentence over its 4 tokens of stage 2w + s
+              const int t0 = 32 * w + 16 * s;
+              const int ra = min(max(s_lo, t0), t0 + 16), rb = min(max(s_hi, t0), t0 + 16);
+              const uint32_t x = __builtin_amdgcn_ubfe(bitfield_mask(rb - ra, ra), g4 + 16 * s, 4);
+              ind[2 * s] = ((x << 14) | (x << 29)) & 0x40004000u;
+              ind[2 * s + 1] = ((x << 12) | (x << 27)) & 0x40004000u;
+            }
+            const bf16x8 av = __builtin_bit_cast(bf16x8, make_uint4(ind[0], ind[1], ind[2], ind[3]));
+#pragma unroll
+            for (int jj = 0; jj < 2; ++jj) pool[jj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, trv[w][jj], pool[jj], 0, 0, 0);
+          }
         }
-      }  // tiles
-
-      if constexpr (PASSB) {
-        break;
+        if (!a.no_pool && chunk_done) {
+          // ---- unit sentence embeddings as bf16 hi + lo.  The dimensions of a row are stored as the waves
+          // hold them: position 32 pw + 2 c + jj is dimension 16 (2 pw + jj) + c; every embedding of a head
+          // is written by this kernel, so cosines are not affected.
+          float *sq = fbuf;  // [slot][pw]
+          const int el = opaque(lane), ec = el & 15, eg = el >> 4;  // (lane constants are not kept over the tiles for this)
+          if (ns > 16 * u) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+              const float v = row16_sum_fast(fmaf(pool[0][r], pool[0][r], pool[1][r] * pool[1][r]));
+              if (ec == 0) sq[4 * (16 * u + 4 * eg + r) + pw] = v;
+            }
+          }
+          asm volatile("" ::: "memory");
+          lds_barrier();
+          asm volatile("" ::: "memory");
+          if (ns > 16 * u) {
+            float4 ss4[4];
+            int len[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+              const int si = 16 * u + 4 * eg + r;
+              ss4[r] = *reinterpret_cast<const float4 *>(sq + 4 * si);
+              len[r] = soff[si + 1] - soff[si];  // 0 past the last sentence
+            }
+            const int64_t o = ((int64_t)lh * a.total_sentences + col + 16 * u) * (kD / 2) + 16 * pw;
+            uint32_t *dhi = reinterpret_cast<uint32_t *>(a.ws.vhat_hi) + o, *dlo = reinterpret_cast<uint32_t *>(a.ws.vhat_lo) + o;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+              const float ss = ((ss4[r].x + ss4[r].y) + ss4[r].z) + ss4[r].w;
+              // mean / (|mean| + eps) = sum / (|sum| + eps * len), sums and eps scaled by 2
+              const float inv = __builtin_amdgcn_rcpf(__builtin_amdgcn_sqrtf(ss) + 2e-12f * (float)len[r]);
+              const float u0 = pool[0][r] * inv, u1 = pool[1][r] * inv;
+              const uint32_t hi = pack_bf16x2(u0, u1);
+              const uint32_t lo = pack_bf16x2(u0 - __uint_as_float(hi << 16), u1 - __uint_as_float(hi & 0xFFFF0000u));
+              if (len[r] > 0) {
+                dhi[(4 * eg + r) * (kD / 2) + ec] = hi;
+                dlo[(4 * eg + r) * (kD / 2) + ec] = lo;
+              }
+            }
+#pragma unroll
+            for (int jj = 0; jj < 2; ++jj) pool[jj] = f32x4{0.f, 0.f, 0.f, 0.f};
+          }
+        }
       } else {
-        if (mode == 1) {
+        // ---- token importance: max over the group's heads in registers, exp2, sum over the wave's window queries
+        float *parts = fbuf, *imp = fbuf + NPART * GT;
+        const int goff = (ct - c_t0) % GT;  // the tile's place in its group of GT tokens
 #pragma unroll
-          for (int q = 0; q < SPW; ++q) {
-            const float m = fmaxf(row16_max_fast(lsum[q]), kRefInit);
-            if (c16 == 0) row_ref[slot_row(q)] = m;
-            lsum[q] = 0.f;
-          }
-          continue;
+        for (int s = 0; s < NSUB; ++s) {
+          logits(s);
+          if (s == 0) prefetch(0);
         }
-        bool doubt = false;
+#pragma unroll
+        for (int s = 0; s < NSUB; ++s) {
+          float sum = 0.f;
+#pragma unroll
+          for (int al = 0; al < ALW; ++al) {
+            float gm = -INFINITY;
+#pragma unroll
+            for (int i2 = 0; i2 < NP; ++i2) {
+              const int q = al * NP + i2;
+              gm = fmaxf(gm, fmaf(acc[s][q >> 2][q & 3], kScale2, -cn[q]));
+            }
+            if (edge && wt + 16 * s + c16 > last_free + g + 4 * (rh * ALW + al)) gm = -INFINITY;
+            sum += __builtin_amdgcn_exp2f(gm);
+          }
+          if constexpr (PG == 1) {
+            sum += __shfl_xor(sum, 16);
+            sum += __shfl_xor(sum, 32);
+            if (g == 0) parts[rh * GT + goff + 16 * (th * NSUB + s) + c16] = sum;
+          } else {
+            parts[(4 * rh + g) * GT + goff + 16 * (th * NSUB + s) + c16] = sum;
+          }
+        }
+        prefetch(1);
+        if (chunk_done || goff + kTileRows == GT) {
+          // the parts of the importance are added in a fixed order, then the sentences' sums over their
+          // unprotected part
+          const int g0 = ct - goff, g1 = min(cend, g0 + GT);
+          asm volatile("" ::: "memory");
+          lds_barrier();
+          asm volatile("" ::: "memory");
+          if (tid < GT) {
+            float tot = 0.f;
+#pragma unroll
+            for (int p = 0; p < NPART; ++p) tot += parts[p * GT + tid];
+            imp[tid] = g0 + tid < g1 ? tot / (float)a.alpha : 0.f;
+          }
+          asm volatile("" ::: "memory");
+          lds_barrier();
+          asm volatile("" ::: "memory");
+          const int64_t tok_col = (int64_t)lh * a.total_tokens + tok0;
+          static_assert(kChunkMaxSent * 16 == 64 * kWaves && GT <= 64 * kWaves, "16 lanes per sentence of a chunk, one thread per token of a group");
+          const int si = tid >> 4, sub = tid & 15;
+          if (si < ns) {
+            const int lo = max(soff[si], g0), hi = min(min(soff[si + 1], p_start), g1);
+            for (int t = lo + sub; t < hi; t += 16) {
+              sum_i += imp[t - g0];
+              if (a.tok_red) sum_r += a.tok_red[tok_col + t];
+            }
+          }
+          if (a.tok_imp && tid < GT && g0 + tid < g1) a.tok_imp[tok_col + g0 + tid] = imp[tid];
+          if (chunk_done) {
+            sum_i = row16_sum_fast(sum_i);
+            if (a.tok_red) sum_r = row16_sum_fast(sum_r);
+            if (si < ns && sub == 0) {
+              const int len = min(soff[si + 1], p_start) - soff[si];
+              const int64_t o = (int64_t)lh * a.total_sentences + col + si;
+              a.ws.sent_imp[o] = len > 0 ? sum_i / (float)len : 0.f;
+              a.ws.sent_red[o] = len > 0 ? sum_r / (float)len : 0.f;
+            }
+            sum_i = sum_r = 0.f;
+          }
+        }
+      }
+      ct += kTileRows;
+      if (ct >= cend && cc + 1 < c1) {
+        ++cc;
+        const ConstIntPtr r = chunks_c + (int64_t)cc * kChInts;
+        c_t0 = ct = r[kChT];
+        cend = ct + r[kChLen];
+        ns = r[kChNs];
+        col = r[kChSoff] - b;
+      }
+    }  // tiles
+
+    if constexpr (!PASSB) {
+      bool doubt = false;
+#pragma unroll
+      for (int q = 0; q < SPW; ++q) {
+        lsum[q] = row16_sum_fast(lsum[q]);
+        // rows of padding hold zero queries, and a window query that does not see the wave's first token sees none of its tokens
+        doubt = doubt || (slot_used(q) && my_first == 0 && t_ref <= last_free + slot_aq(q) && !(lsum[q] > kMinRowSum && lsum[q] < kMaxRowSum));  // also catches NaN and infinity
+      }
+      if (__any(doubt)) {
+        // The wave's share of the run once more, with references that follow the logits.  Its keys come straight from
+        // memory in the layout of the matrix product: no other wave is needed (the others wait for the records).
+        const int ln = opaque(lane), lc16 = ln & 15, lg = ln >> 4;  // nothing of this is kept in registers over the tiles
+        float m[SPW];
+#pragma unroll
+        for (int q = 0; q < SPW; ++q) {
+          m[q] = kRefInit;
+          lsum[q] = 0.f;
+        }
+        for (int c = c0; c < c1; ++c) {
+          const ConstIntPtr r = chunks_c + (int64_t)c * kChInts;
+          const int e = r[kChT] + r[kChLen];
+          for (int t0 = r[kChT] + 16 * th * NSUB; t0 < e; t0 += kTileRows) {
+#pragma unroll 1
+            for (int s = 0; s < NSUB; ++s) {
+              const int t = t0 + 16 * s + lc16, row = min(t, e - 1);
+              const char *key = kr.base + (kr.map ? (int64_t)kr.map[row] * kr.map_pitch : (int64_t)row * kr.pitch) + lg * 64;
+              f32x4 x[NTW];
+#pragma unroll
+              for (int T = 0; T < NTW; ++T) x[T] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+              for (int kk = 0; kk < 4; ++kk) {
+                const bf16x8 bfr = *reinterpret_cast<const bf16x8 *>(key + kk * 16);
+#pragma unroll
+                for (int T = 0; T < NTW; ++T) x[T] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(afr[T][kk], bfr, x[T], 0, 0, 0);
+              }
+#pragma unroll
+              for (int q = 0; q < SPW; ++q) {
+                const float y = t < e && t <= last_free + lg + 4 * (rh * ALW + q / NP) ? x[q >> 2][q & 3] * kScale2 : -INFINITY;
+                const float nm = fmaxf(m[q], row16_max_fast(y));
+                lsum[q] = lsum[q] * __builtin_amdgcn_exp2f(m[q] - nm) + __builtin_amdgcn_exp2f(y - nm);
+                m[q] = nm;
+              }
+            }
+          }
+        }
 #pragma unroll
         for (int q = 0; q < SPW; ++q) {
           lsum[q] = row16_sum_fast(lsum[q]);
-          // rows of padding hold zero queries, and a window query that does not see the wave's first token sees none of its tokens
-          doubt = doubt || (slot_used(q) && my_first == 0 && t_ref <= last_free + slot_aq(q) && !(lsum[q] > kMinRowSum && lsum[q] < kMaxRowSum));  // also catches NaN and infinity
+          if (lc16 == 0) row_ref[16 * (q >> 2) + 4 * lg + (q & 3)] = m[q];
         }
-        if (mode == 0 && __syncthreads_or(doubt)) {
-#pragma unroll
-          for (int q = 0; q < SPW; ++q) lsum[q] = -INFINITY;
-          continue;
-        }
-        // ---- the run's record; rows of waves that shared the tokens are merged
-        float2 *out = a.ws.stat_part + ((int64_t)lh * a.ws.nr_max + run) * R;
-        float *wstat = fbuf + 128;
-#pragma unroll
-        for (int q = 0; q < SPW; ++q) {
-          const float2 rec = make_float2(row_ref[slot_row(q)], lsum[q]);
-          if (c16 == 0) *reinterpret_cast<float2 *>(wstat + 2 * (wave * RW + slot_row(q))) = rec;
-        }
-        asm volatile("" ::: "memory");
-        lds_barrier();
-        asm volatile("" ::: "memory");
-        if (tid < R) {  // (rows past the used slots hold whatever: nobody reads them)
-          const int w = tid / RW, r = tid % RW;
-          float m = kRefInit;
-#pragma unroll
-          for (int p = 0; p < TH; ++p) m = fmaxf(m, wstat[2 * ((w + RS * p) * RW + r)]);
-          float s = 0.f;
-#pragma unroll
-          for (int p = 0; p < TH; ++p) {
-            const float *x = wstat + 2 * ((w + RS * p) * RW + r);
-            s += x[1] * __builtin_amdgcn_exp2f(x[0] - m);
-          }
-          out[tid] = make_float2(m, s);
-        }
-        break;
       }
-    }  // modes
-
+      // ---- the run's record; rows of waves that shared the tokens are merged
+      float2 *out = a.ws.stat_part + ((int64_t)lh * a.ws.nr_max + run) * R;
+      float *wstat = fbuf + 128;
+#pragma unroll
+      for (int q = 0; q < SPW; ++q) {
+        const float2 rec = make_float2(row_ref[slot_row(q)], lsum[q]);
+        if (c16 == 0) *reinterpret_cast<float2 *>(wstat + 2 * (wave * RW + slot_row(q))) = rec;
+      }
+      asm volatile("" ::: "memory");
+      lds_barrier();
+      asm volatile("" ::: "memory");
+      if (tid < R) {  // (rows past the used slots hold whatever: nobody reads them)
+        const int w = tid / RW, r = tid % RW;
+        float m = kRefInit;
+#pragma unroll
+        for (int p = 0; p < TH; ++p) m = fmaxf(m, wstat[2 * ((w + RS * p) * RW + r)]);
+        float s = 0.f;
+#pragma unroll
+        for (int p = 0; p < TH; ++p) {
+          const float *x = wstat + 2 * ((w + RS * p) * RW + r);
+          s += x[1] * __builtin_amdgcn_exp2f(x[0] - m);
+        }
+        out[tid] = make_float2(m, s);
+      }
+    }
   }  // items
   wait_vm<0>();  // the loads past the last tile still write LDS that the workgroup is about to give up
 }

@@ -108,6 +108,27 @@ def test_jumping_logits_in_runs_of_several_chunks():
         np.testing.assert_allclose(imp[l, h, t0:t1].cpu().numpy(), want, rtol=1e-3, atol=1e-12)
 
 
+@pytest.mark.parametrize("block_size", [16, 24])
+@pytest.mark.parametrize("group,alpha", [(5, 32), (4, 16)])
+def test_jumping_logits_on_pages(group, alpha, block_size):
+    from test_gpu_paged import _run_paged, _to_pages
+    st = _structure([[0, 300, 310, 500, 777], [0, 5, 700, 1000], [0, 17]])
+    cfg = _cfg("page-jumps", 3, 1, 2, group, alpha)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(8)
+    k = torch.randn((1, 2, st.total_tokens, 128), generator=g, device="cuda").to(torch.bfloat16)
+    k[:, :, [40, 650, 800, 1500], 0] = 40.0
+    q = torch.randn((1, 3, 2 * group, alpha, 128), generator=g, device="cuda").to(torch.bfloat16)
+    q[..., 0] = 40.0
+    kp, vp, table = _to_pages(cfg, st, k, k, block_size, seed=4)
+    imp = _run_paged(cfg, st, kp, vp, table, q).tok_imp
+    for h in range(2):
+        for b in range(3):
+            t0, t1 = int(st.seq_off[b]), int(st.seq_off[b + 1])
+            want = oracle.token_importance(q[0, b, h * group:(h + 1) * group].double().cpu().numpy(), k[0, h, t0:t1].double().cpu().numpy())
+            np.testing.assert_allclose(imp[0, h, t0:t1].cpu().numpy(), want, rtol=1e-3, atol=1e-12)
+
+
 def test_a_row_that_sees_none_of_a_chunk_keeps_its_own_reference():
     # The last chunk begins inside the observation window: its first window queries see none of it, the others see logits
     # 250 log2 units above everything before.
