@@ -99,6 +99,16 @@ __device__ __forceinline__ bf16x8 join_tr(i16x4 lo, i16x4 hi) {
   return __builtin_bit_cast(bf16x8, make_uint4(l.x, l.y, h.x, h.y));
 }
 
+// The value that lane r of the lane's quad holds.
+template <class T>
+__device__ __forceinline__ T quad_lane(T v, int r) {  // (r is a constant once unrolled)
+  const int x = __builtin_bit_cast(int, v);
+  return __builtin_bit_cast(T, r == 0   ? __builtin_amdgcn_mov_dpp(x, 0x00, 0xf, 0xf, true)
+                               : r == 1 ? __builtin_amdgcn_mov_dpp(x, 0x55, 0xf, 0xf, true)
+                               : r == 2 ? __builtin_amdgcn_mov_dpp(x, 0xAA, 0xf, 0xf, true)
+                                        : __builtin_amdgcn_mov_dpp(x, 0xFF, 0xf, 0xf, true));
+}
+
 // Fields of a Chunk record as seen through ConstIntPtr.
 enum ChunkRec : int { kChB = 0, kChS0, kChNs, kChT, kChLen, kChSoff, kChTok0, kChNTok, kChInts };
 static_assert(sizeof(Chunk) == kChInts * 4, "a chunk is read as eight words");
@@ -379,9 +389,16 @@ __global__ void __launch_bounds__(64 * kWaves, 4) k_scan_rows(ScanArgs a) {
           // is written by this kernel, so cosines are not affected.
           float *sq = fbuf;  // [slot][pw]
           const int el = opaque(lane), ec = el & 15, eg = el >> 4;  // (lane constants are not kept over the tiles for this)
+          // A quad's lanes each look after one sentence of their lane group and hand its values round.  Sums are brought to
+          // the size of a mean by a power of two, so that their squares leave fp32 no sooner than a mean's.
+          const int si = 16 * u + 4 * eg + (ec & 3), len = soff[si + 1] - soff[si];  // 0 past the last sentence
+          const float scale = __builtin_amdgcn_ldexpf(1.f, __builtin_clz(len | 1) - 33);
           if (ns > 16 * u) {
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
+              const float by = quad_lane(scale, r);
+#pragma unroll
+              for (int jj = 0; jj < 2; ++jj) pool[jj][r] *= by;
               const float v = row16_sum_fast(fmaf(pool[0][r], pool[0][r], pool[1][r] * pool[1][r]));
               if (ec == 0) sq[4 * (16 * u + 4 * eg + r) + pw] = v;
             }
@@ -390,25 +407,19 @@ __global__ void __launch_bounds__(64 * kWaves, 4) k_scan_rows(ScanArgs a) {
           lds_barrier();
           asm volatile("" ::: "memory");
           if (ns > 16 * u) {
-            float4 ss4[4];
-            int len[4];
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-              const int si = 16 * u + 4 * eg + r;
-              ss4[r] = *reinterpret_cast<const float4 *>(sq + 4 * si);
-              len[r] = soff[si + 1] - soff[si];  // 0 past the last sentence
-            }
+            const float4 ss4 = *reinterpret_cast<const float4 *>(sq + 4 * si);
+            const float ss = ((ss4.x + ss4.y) + ss4.z) + ss4.w;
+            // mean / (|mean| + eps), both sides times 2 len scale (ones were written as 2.0)
+            const float inv = 1.f / (sqrtf(ss) + 2e-12f * (float)len * scale);
             const int64_t o = ((int64_t)lh * a.total_sentences + col + 16 * u) * (kD / 2) + 16 * pw;
             uint32_t *dhi = reinterpret_cast<uint32_t *>(a.ws.vhat_hi) + o, *dlo = reinterpret_cast<uint32_t *>(a.ws.vhat_lo) + o;
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-              const float ss = ((ss4[r].x + ss4[r].y) + ss4[r].z) + ss4[r].w;
-              // mean / (|mean| + eps) = sum / (|sum| + eps * len), sums and eps scaled by 2
-              const float inv = __builtin_amdgcn_rcpf(__builtin_amdgcn_sqrtf(ss) + 2e-12f * (float)len[r]);
-              const float u0 = pool[0][r] * inv, u1 = pool[1][r] * inv;
+              const float by = quad_lane(inv, r);
+              const float u0 = pool[0][r] * by, u1 = pool[1][r] * by;
               const uint32_t hi = pack_bf16x2(u0, u1);
               const uint32_t lo = pack_bf16x2(u0 - __uint_as_float(hi << 16), u1 - __uint_as_float(hi & 0xFFFF0000u));
-              if (len[r] > 0) {
+              if (quad_lane(len, r) > 0) {
                 dhi[(4 * eg + r) * (kD / 2) + ec] = hi;
                 dlo[(4 * eg + r) * (kD / 2) + ec] = lo;
               }

@@ -185,3 +185,17 @@ def test_normalisers_of_rows_next_to_rows_of_another_scale(group, alpha):
         rel = imp[0, h].double().cpu().numpy() / want - 1.0
         err.append(abs(np.median(rel)))
     assert max(err) < 7e-7
+
+
+def test_embeddings_of_large_keys():
+    # the mean of a sentence of 400 keys of 1e17 has a square that fits, their sum has not
+    st = _structure([[0, 400, 420, 820, 900]])
+    cfg = _cfg("large", 1, 1, 1, 4, 16)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(6)
+    base = torch.randn(128, generator=g, device="cuda")
+    k = ((base + 0.5 * torch.randn((1, 1, 900, 128), generator=g, device="cuda")) * 1e17).to(torch.bfloat16)
+    q = (torch.randn((1, 1, 4, 16, 128), generator=g, device="cuda") * 1e-17).to(torch.bfloat16)
+    lam = _score(cfg, st, k, q, TWO)[1][0, 0].cpu().numpy()
+    want = oracle.sentence_redundancy(oracle.sentence_embeddings(k[0, 0].double().cpu().numpy(), st.offsets(0).astype(np.int64)))
+    np.testing.assert_allclose(lam[:-1], want[:-1], rtol=1e-3, atol=1e-5)
