@@ -226,6 +226,7 @@ __global__ void __launch_bounds__(64 * kWaves, 4) k_scan_rows(ScanArgs a) {
     // sum then lie outside what fp32 holds comfortably, the wave does its share of the run once more (below).
     [[maybe_unused]] int my_first = -1;  // becomes 0 once the wave has seen a token
     [[maybe_unused]] int t_ref = 0;      // ... and this is the first one
+    [[maybe_unused]] bool not_finite = false;  // some sentence of the wave's half of the chunks has no finite sum
     lc = c0;
     load_chunk(c0);
     // ---- the wave's query fragments: lane (row c16 of a tile, head-dim slice g), as the A operand wants them
@@ -409,6 +410,7 @@ __global__ void __launch_bounds__(64 * kWaves, 4) k_scan_rows(ScanArgs a) {
           if (ns > 16 * u) {
             const float4 ss4 = *reinterpret_cast<const float4 *>(sq + 4 * si);
             const float ss = ((ss4.x + ss4.y) + ss4.z) + ss4.w;
+            not_finite = not_finite || __any(len > 0 && !(ss < INFINITY));
             // mean / (|mean| + eps), both sides times 2 len scale (ones were written as 2.0)
             const float inv = 1.f / (sqrtf(ss) + 2e-12f * (float)len * scale);
             const int64_t o = ((int64_t)lh * a.total_sentences + col + 16 * u) * (kD / 2) + 16 * pw;
@@ -512,6 +514,33 @@ __global__ void __launch_bounds__(64 * kWaves, 4) k_scan_rows(ScanArgs a) {
     }  // tiles
 
     if constexpr (!PASSB) {
+      if (not_finite) {
+        // An infinite or NaN key: 0 times it is NaN, so the products have carried it into sentences that do not hold it.
+        // The embeddings of the half are formed again from each sentence's own rows alone; every wave writes its 32 dimensions.
+        const int ln = opaque(lane), pw = wave & 3, u = wave >> 2, d0 = 32 * (ln >> 4) + (ln & 15);
+        for (int c = c0; c < c1; ++c) {
+          const ConstIntPtr r = chunks_c + (int64_t)c * kChInts;
+          const int32_t *off = a.sent_off + r[kChSoff];
+          for (int si = 16 * u; si < min(r[kChNs], 16 * u + 16); ++si) {
+            float s0 = 0.f, s1 = 0.f;
+            const int t1 = off[si + 1], len = t1 - off[si];
+            for (int t = off[si]; t < t1; ++t) {
+              const char *key = kr.base + (kr.map ? (int64_t)kr.map[t] * kr.map_pitch : (int64_t)t * kr.pitch) + d0 * 2;
+              s0 += bf16_bits_to_f32(*reinterpret_cast<const uint16_t *>(key));
+              s1 += bf16_bits_to_f32(*reinterpret_cast<const uint16_t *>(key + 32));
+            }
+            const float scale = 1.f / (float)len, m0 = s0 * scale, m1 = s1 * scale;
+            const float inv = 1.f / (sqrtf(wave_sum(fmaf(m0, m0, m1 * m1))) + 1e-12f);
+            const uint32_t hi = pack_bf16x2(m0 * inv, m1 * inv);
+            const uint32_t lo = pack_bf16x2(m0 * inv - __uint_as_float(hi << 16), m1 * inv - __uint_as_float(hi & 0xFFFF0000u));
+            const int64_t o = ((int64_t)lh * a.total_sentences + r[kChSoff] - b + si) * (kD / 2) + ln;
+            if (ln >> 4 == pw) {
+              reinterpret_cast<uint32_t *>(a.ws.vhat_hi)[o] = hi;
+              reinterpret_cast<uint32_t *>(a.ws.vhat_lo)[o] = lo;
+            }
+          }
+        }
+      }
       bool doubt = false;
 #pragma unroll
       for (int q = 0; q < SPW; ++q) {

@@ -199,3 +199,35 @@ def test_embeddings_of_large_keys():
     lam = _score(cfg, st, k, q, TWO)[1][0, 0].cpu().numpy()
     want = oracle.sentence_redundancy(oracle.sentence_embeddings(k[0, 0].double().cpu().numpy(), st.offsets(0).astype(np.int64)))
     np.testing.assert_allclose(lam[:-1], want[:-1], rtol=1e-3, atol=1e-5)
+
+
+@pytest.mark.parametrize("paged", [False, True])
+@pytest.mark.parametrize("group,alpha", [(4, 16), (5, 32)])
+@pytest.mark.parametrize("token", [305, 899, 640])
+def test_an_infinite_key_stays_in_its_sentence(group, alpha, token, paged):
+    # A key with an infinity that every query scores -inf has weight 0 and spoils the embedding of its own sentence only.
+    off = [0, 300, 310, 330, 335, 350, 620, 640, 660, 700, 900, 930, 1000]
+    st = _structure([off])
+    cfg = _cfg("inf", 1, 1, 1, group, alpha)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(7)
+    k = torch.randn((1, 1, 1000, 128), generator=g, device="cuda").to(torch.bfloat16)
+    q = torch.randn((1, 1, group, alpha, 128), generator=g, device="cuda").to(torch.bfloat16)
+    q[..., 5] = 1.0
+    k[0, 0, token, 5] = float("-inf")
+    if paged:
+        from test_gpu_paged import _run_paged, _to_pages
+        kp, vp, table = _to_pages(cfg, st, k, k, 24, seed=3)
+        out = _run_paged(cfg, st, kp, vp, table, q)
+        lam, imp = out.sent_lambda, out.tok_imp
+    else:
+        _, lam, imp = _score(cfg, st, k, q, TWO)
+    lam, imp = lam[0, 0].cpu().numpy(), imp[0, 0].cpu().numpy()
+    x = k[0, 0].double().cpu().numpy()
+    x[token, 5] = -1e30
+    np.testing.assert_allclose(imp, oracle.token_importance(q[0, 0].double().cpu().numpy(), x), rtol=1e-3, atol=1e-12)
+    bad = int(np.searchsorted(off, token, side="right")) - 1
+    emb = oracle.sentence_embeddings(x, np.asarray(off))
+    good = [s for s in range(len(off) - 1) if s != bad]
+    want = oracle.sentence_redundancy(emb[good])
+    np.testing.assert_allclose(lam[good][:-1], want[:-1], rtol=1e-3, atol=1e-5)
