@@ -343,7 +343,7 @@ __global__ void __launch_bounds__(64 * kWaves, 4) k_scan_rows(ScanArgs a) {
 #pragma unroll
               for (int q = 0; q < SPW; ++q) {
                 const float m = fmaxf(row16_max_fast(acc[s][q >> 2][q & 3]), kRefInit);
-                if (sc == 0) row_ref[16 * (q >> 2) + 4 * sg + (q & 3)] = m;
+                row_ref[16 * (q >> 2) + 4 * sg + (q & 3)] = m;  // (all 16 lanes of a row the same: no branch)
               }
             }
 #pragma unroll
@@ -401,7 +401,7 @@ __global__ void __launch_bounds__(64 * kWaves, 4) k_scan_rows(ScanArgs a) {
 #pragma unroll
               for (int jj = 0; jj < 2; ++jj) pool[jj][r] *= by;
               const float v = row16_sum_fast(fmaf(pool[0][r], pool[0][r], pool[1][r] * pool[1][r]));
-              if (ec == 0) sq[4 * (16 * u + 4 * eg + r) + pw] = v;
+              sq[4 * (16 * u + 4 * eg + r) + pw] = v;
             }
           }
           asm volatile("" ::: "memory");
@@ -588,7 +588,7 @@ __global__ void __launch_bounds__(64 * kWaves, 4) k_scan_rows(ScanArgs a) {
 #pragma unroll
         for (int q = 0; q < SPW; ++q) {
           lsum[q] = row16_sum_fast(lsum[q]);
-          if (lc16 == 0) row_ref[16 * (q >> 2) + 4 * lg + (q & 3)] = m[q];
+          row_ref[16 * (q >> 2) + 4 * lg + (q & 3)] = m[q];
         }
       }
       // ---- the run's record; rows of waves that shared the tokens are merged
@@ -597,7 +597,7 @@ __global__ void __launch_bounds__(64 * kWaves, 4) k_scan_rows(ScanArgs a) {
 #pragma unroll
       for (int q = 0; q < SPW; ++q) {
         const float2 rec = make_float2(row_ref[slot_row(q)], lsum[q]);
-        if (c16 == 0) *reinterpret_cast<float2 *>(wstat + 2 * (wave * RW + slot_row(q))) = rec;
+        *reinterpret_cast<float2 *>(wstat + 2 * (wave * RW + slot_row(q))) = rec;  // (all 16 lanes of a row the same)
       }
       asm volatile("" ::: "memory");
       lds_barrier();
