@@ -74,8 +74,11 @@ __device__ __forceinline__ float lds_read_f32(uint32_t addr) {
 
 // Row (16-lane) reductions with the DPP modifier on the arithmetic instruction itself: one
 // instruction per step.  The s_nop covers the two wait states a DPP read needs after a VALU write.
-#define SKIPKV_DPP_STEP(OP, N)                                                                          \
-  asm volatile("s_nop 1\n\t" OP " %0, %1, %1 row_ror:" #N " row_mask:0xf bank_mask:0xf" : "=v"(v) : "v"(v))
+// The result goes where the operand is, never into a register of its own: the compiler might choose one that a matrix
+// instruction in flight is still going to write (an element of its result that nobody uses), and it keeps the distance
+// that this needs for its own instructions only.  The operand has to come from an instruction of the compiler's that
+// is no matrix instruction, for the same reason.
+#define SKIPKV_DPP_STEP(OP, N) asm volatile("s_nop 1\n\t" OP " %0, %0, %0 row_ror:" #N " row_mask:0xf bank_mask:0xf" : "+v"(v))
 __device__ __forceinline__ float row16_max_fast(float v) {
   SKIPKV_DPP_STEP("v_max_f32_dpp", 8);
   SKIPKV_DPP_STEP("v_max_f32_dpp", 4);
