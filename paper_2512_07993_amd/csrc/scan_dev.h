@@ -72,12 +72,13 @@ __device__ __forceinline__ float lds_read_f32(uint32_t addr) {
   return *(const __attribute__((address_space(3))) float *)(uintptr_t)addr;
 }
 
-// Row (16-lane) reductions with the DPP modifier on the arithmetic instruction itself: one
-// instruction per step.  The s_nop covers the two wait states a DPP read needs after a VALU write.
-// The result goes where the operand is, never into a register of its own: the compiler might choose one that a matrix
-// instruction in flight is still going to write (an element of its result that nobody uses), and it keeps the distance
-// that this needs for its own instructions only.  The operand has to come from an instruction of the compiler's that
-// is no matrix instruction, for the same reason.
+// Row (16-lane) reductions with the DPP modifier on the arithmetic instruction itself: one instruction per step.  The
+// compiler folds the modifier into an addition; around a maximum it would put a second one (for signalling NaNs), so that
+// is assembly, whose s_nop covers the two wait states a DPP read needs after a VALU write.  Its result goes where the
+// operand is, never into a register of its own: the compiler might choose one that a matrix instruction in flight is
+// still going to write (an element of its result that nobody uses), and it keeps the distance that this needs for its own
+// instructions only.  The operand has to come from an instruction of the compiler's that is no matrix instruction, for
+// the same reason.
 #define SKIPKV_DPP_STEP(OP, N) asm volatile("s_nop 1\n\t" OP " %0, %0, %0 row_ror:" #N " row_mask:0xf bank_mask:0xf" : "+v"(v))
 __device__ __forceinline__ float row16_max_fast(float v) {
   SKIPKV_DPP_STEP("v_max_f32_dpp", 8);
@@ -87,10 +88,12 @@ __device__ __forceinline__ float row16_max_fast(float v) {
   return v;
 }
 __device__ __forceinline__ float row16_sum_fast(float v) {
-  SKIPKV_DPP_STEP("v_add_f32_dpp", 8);
-  SKIPKV_DPP_STEP("v_add_f32_dpp", 4);
-  SKIPKV_DPP_STEP("v_add_f32_dpp", 2);
-  SKIPKV_DPP_STEP("v_add_f32_dpp", 1);
+#define SKIPKV_DPP_ADD(N) v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x120 + N, 0xf, 0xf, true))
+  SKIPKV_DPP_ADD(8);
+  SKIPKV_DPP_ADD(4);
+  SKIPKV_DPP_ADD(2);
+  SKIPKV_DPP_ADD(1);
+#undef SKIPKV_DPP_ADD
   return v;
 }
 #undef SKIPKV_DPP_STEP
