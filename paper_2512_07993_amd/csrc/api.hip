@@ -61,7 +61,8 @@ int check_params(const skipkv_cache *c, const skipkv_params *p, RowLayout *rl) {
 // counts those of all heads, so that the answer is the same when every head is presented as a sequence.
 // Scores of 8 heads per layer, us, spans of 128 / 64 / 32 tokens:  fp32, 9 K tokens in all: 53.3 / 44.7 / 42.5, 34 K: 60.9 /
 // 52.8 / 72.5, 37 K: 54.4 / 45.5 / 56.8, 147 K: 86.6 / 97.2 / 126.8;  bf16, 9 K: 38.5 / 37.1 / 37.9, 68 K: 47.0 / 49.3 / 60.7.
-int span_cap_of(int dtype, size_t tokens) { return dtype == SKIPKV_F32 && tokens <= 48 * 1024 ? 64 : kSpanCap; }
+constexpr size_t kShortSpanTokens = 48 * 1024;
+int span_cap_of(int dtype, size_t tokens) { return dtype == SKIPKV_F32 && tokens <= kShortSpanTokens ? 64 : kSpanCap; }
 
 // Carve the workspace.  `base` may be NULL to only compute the size.
 Workspace carve(const skipkv_cache *c, const RowLayout &rl, void *base) {
@@ -71,17 +72,21 @@ Workspace carve(const skipkv_cache *c, const RowLayout &rl, void *base) {
   // two consecutive chunks of a sequence together exceed kChunkCap tokens or kChunkMaxSent sentences
   const size_t nc = 2 * ((T + kChunkCap - 1) / kChunkCap + (S + kChunkMaxSent - 1) / kChunkMaxSent) + B;
   // ... and each sequence's share of the chunk list is rounded up to whole runs, as far as the list may go
-  const size_t want = (size_t)scan_run_chunks(c->dtype, (int64_t)LH, (int64_t)T), end = std::max<size_t>(nc, (size_t)kHdrMaxChunks);
+  // (runs longer than the sequences would only be room)
+  const size_t want = std::min((size_t)scan_run_chunks(c->dtype, (int64_t)LH, (int64_t)T), std::max<size_t>(1, nc / std::max<size_t>(B, 1)));
+  const size_t end = std::max<size_t>(nc, (size_t)kHdrMaxChunks);
   const size_t rc = std::min(want, 1 + (end - nc) / std::max<size_t>(B, 1));
   w.run_chunks = (int32_t)rc;
   w.nr_max = (int32_t)((nc + B * (rc - 1)) / rc);
   w.nrb_max = (int32_t)((S + kRowBlock - 1) / kRowBlock + B);
   // two consecutive spans of a sequence together exceed span_cap tokens or kSpanMaxSent sentences
   w.span_cap = span_cap_of(c->dtype, LH * T);
-  const size_t cap = (size_t)w.span_cap;
-  const size_t spans_max = 2 * ((T + cap - 1) / cap + (S + kSpanMaxSent - 1) / kSpanMaxSent) + B;
-  w.ni_max = (int32_t)std::min<size_t>(spans_max / kItemSpans + B + 1, (size_t)0x7FFFFFFF);
-  w.fits = nc <= (size_t)kHdrMaxChunks && spans_max / kItemSpans + B + 1 <= (size_t)kHdrMaxItems && w.nrb_max <= kHdrMaxRowBlocks;
+  auto items = [&](size_t tokens, size_t cap) {
+    return (2 * ((tokens + cap - 1) / cap + (S + kSpanMaxSent - 1) / kSpanMaxSent) + B) / kItemSpans + B + 1;
+  };
+  const size_t ni = items(T, (size_t)w.span_cap);
+  w.ni_max = (int32_t)std::min<size_t>(ni, (size_t)0x7FFFFFFF);
+  w.fits = nc <= (size_t)kHdrMaxChunks && ni <= (size_t)kHdrMaxItems && w.nrb_max <= kHdrMaxRowBlocks;
   w.rows = rl.rows;
   w.rows2 = rl.rows2;
   size_t off = 0;
@@ -98,15 +103,19 @@ Workspace carve(const skipkv_cache *c, const RowLayout &rl, void *base) {
   w.rb_cnt = static_cast<int32_t *>(take(B * 4));
   w.seq_fused = static_cast<int32_t *>(take(B * 4));
   w.head_redo = static_cast<int32_t *>(take(LH * B * 4));
-  w.item_rec = static_cast<int32_t *>(take((size_t)w.ni_max * kItemRecInts * 4));
-  // The list takes the places that its rounding needs from the records, of which there is one per run: together they
-  // have the room of nc of each, which grows with the cache whatever the runs' length.
+  // The chunk list, then in one place the records of the single-pass scan and those of the two-pass scan, which is
+  // enqueued behind it and writes its own before it reads any.  So that a larger cache never needs less, there is room
+  // for a record per chunk although runs have one each, and for the most items that short spans make at any smaller size.
   const size_t list = align_up(std::min(end, nc + B * (want - 1)) * sizeof(Chunk)), record = LH * rl.rows2 * sizeof(float2);
-  char *const chunks = static_cast<char *>(take(std::max(align_up(nc * sizeof(Chunk)) + align_up(nc * record), list + w.nr_max * record)));
+  const size_t item = align_up((size_t)w.ni_max * kItemRecInts * 4);
+  auto item_room = [&](size_t n) { return align_up(n * kItemRecInts * 4) + n * LH * rl.rows * sizeof(float2); };
+  const size_t short_end = c->dtype == SKIPKV_F32 ? items(std::min(T, kShortSpanTokens / std::max<size_t>(LH, 1)), 64) : 0;
+  char *const chunks = static_cast<char *>(take(list + std::max({nc * record, item_room(items(T, kSpanCap)), item_room(short_end)})));
   w.chunks = reinterpret_cast<Chunk *>(chunks);
   w.stat_part = chunks ? reinterpret_cast<float2 *>(chunks + list) : nullptr;
+  w.item_rec = chunks ? reinterpret_cast<int32_t *>(chunks + list) : nullptr;
+  w.item_stat = chunks ? reinterpret_cast<float2 *>(chunks + list + item) : nullptr;
   w.rowblocks = static_cast<RowBlock *>(take((size_t)w.nrb_max * sizeof(RowBlock)));
-  w.item_stat = static_cast<float2 *>(take(LH * w.ni_max * rl.rows * sizeof(float2)));
   w.row_norm = static_cast<float *>(take(LH * B * rl.rows2 * sizeof(float)));
   w.vhat_hi = static_cast<uint16_t *>(take(LH * S * kD * 2));
   w.vhat_lo = static_cast<uint16_t *>(take(LH * S * kD * 2));

@@ -84,10 +84,11 @@ struct Workspace {
   int32_t *rb_cnt;       // [B]
   int32_t *seq_fused;    // [B] 1: the sequence goes through the single-pass scan
   int32_t *head_redo;    // [LH, B] 1: a wait of the single-pass scan ran out for this head: the two-pass scan does it again
-  int32_t *item_rec;     // [ni_max][kItemRecInts] one record per item of the single-pass scan (ItemRec)
   Chunk *chunks;         // [nr_max * run_chunks]  each sequence's chunks start at a multiple of run_chunks
   RowBlock *rowblocks;   // [nrb_max]
   float2 *stat_part;     // [LH, nr_max, R2]  two-pass scan: per run of chunks (max, sum) of every query row, log2 domain
+  // the next two share the place of stat_part: the single-pass scan is done with them when the two-pass scan begins
+  int32_t *item_rec;     // [ni_max][kItemRecInts] one record per item of the single-pass scan (ItemRec)
   float2 *item_stat;     // [LH, ni_max, R]  single-pass scan: per-item (reference, sum) of every query row; the plan presets .x of the used records to kRowNormUnset
   float *row_norm;       // [LH, B, R2]      two-pass scan: log2 of the softmax normaliser of every query row
   uint16_t *vhat_hi;     // [LH, S_total, 128] bf16 high part of the unit sentence embedding

@@ -73,6 +73,21 @@ def test_workspace_size_is_computed_on_the_host():
     assert rc2 == B.OK and n2 > n
 
 
+@pytest.mark.parametrize("dtype,heads,group,alpha", [(B.F32, 1, 4, 8), (B.F32, 8, 4, 16), (B.F32, 8, 4, 32), (B.F32, 48, 1, 8),
+                                                     (B.BF16, 8, 5, 32), (B.BF16, 32, 4, 16)])
+def test_a_larger_cache_never_needs_less_workspace(dtype, heads, group, alpha):
+    # spans are shorter up to 48 K tokens of all heads of an fp32 cache, runs of chunks longer from 2 M tokens on
+    at = [t // heads for t in (48 * 1024, 8192 * 256, 12288 * 256)]
+    sizes = [t + d for t in at for d in (-300, -256, -1, 0, 1, 2, 255, 256, 300)] + list(range(1, 3 * at[0], max(1, at[0] // 97)))
+    for batch in (1, 7):
+        last = 0
+        for tok in sorted(sizes):
+            rc, n = _ws_bytes(_cache(dtype=dtype, n_layers=heads, n_kv_heads=1, n_q_heads=group, batch=batch, total_tokens=tok, total_sentences=300,
+                                     stride_layer=tok * 128, stride_head=tok * 128), _params(obs_window=alpha))
+            assert rc == B.OK and n >= last, (batch, tok, n, last)
+            last = n
+
+
 @pytest.mark.parametrize("ckw,pkw,expect", [
     (dict(head_dim=64), {}, B.ECAPACITY),
     (dict(dtype=7), {}, B.EINVAL),
