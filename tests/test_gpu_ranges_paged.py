@@ -259,3 +259,42 @@ def test_paged_per_head_step_replays_from_a_hip_graph():
                 for b in range(cfg.batch):
                     t0, n2 = int(st.seq_off[b]), int(nl[l, h, b])
                     assert torch.equal(kg[l, h, t0:t0 + n2], kr[l, h, t0:t0 + n2]) and torch.equal(vg[l, h, t0:t0 + n2], vr[l, h, t0:t0 + n2]), (rep, l, h, b)
+
+
+@pytest.mark.parametrize("n_layers,n_kv_heads,batch,heads_before_slots", [(28, 3, 100, False), (28, 3, 100, True), (11, 3, 64, False), (3, 2, 5, True)])
+def test_row_maps_of_many_heads(n_layers, n_kv_heads, batch, heads_before_slots):
+    # A row map's workgroup serves up to eight heads, here 8 (the last group 4), 2 (1) and 1, across layers; one sequence
+    # is longer than a workgroup walks at a time.
+    from test_gpu_edges import _structure, _random_kvq
+    from test_gpu_ranges import shared_as_ranges
+    rng = np.random.default_rng(n_layers)
+    offsets = []
+    for n in [2500] + [int(x) for x in rng.integers(1, 40, size=batch - 1)]:
+        off = [0]
+        while off[-1] < n:
+            off.append(min(n, off[-1] + int(rng.integers(1, 30))))
+        offsets.append(off)
+    st = _structure(offsets)
+    cfg = W.Config("maps", 9, batch, n_layers, n_kv_heads, n_kv_heads, "bf16", 0, 0, 24, 4, 8, 16.0, 0.0)
+    k0, v0, q = _random_kvq(cfg, st, 4)
+    k, v = k0.clone(), v0.clone()
+    ref = run_step_ranges(cfg, st, k, v, q, shared_as_ranges(cfg, st), 24)
+    for bad in (False, True):
+        kp, vp, table = _to_pages(cfg, st, k0, v0, 16, seed=2, heads_before_slots=heads_before_slots)
+        kp0 = kp.clone()
+        if bad:
+            table[2, 0] = 1 << 20
+        out = _run_ranges_paged(cfg, st, kp, vp, table, q, shared_as_ranges(cfg, st), 24)
+        assert int(out.dev_status.item()) == (B.DEV_BAD_BLOCK_TABLE if bad else 0)
+        if bad:
+            table[2, 0] = _to_pages(cfg, st, k0, v0, 16, seed=2, heads_before_slots=heads_before_slots)[2][2, 0]
+        kc, kc0 = _from_pages(cfg, st, kp, table, 16), _from_pages(cfg, st, kp0, table, 16)
+        for b in range(batch):
+            t0, t1 = int(st.seq_off[b]), int(st.seq_off[b + 1])
+            if bad and b == 2:
+                assert torch.equal(kc[:, :, t0:t1], kc0[:, :, t0:t1])
+                continue
+            assert torch.equal(out.tok_imp[:, :, t0:t1].view(torch.int32), ref.tok_imp[:, :, t0:t1].view(torch.int32))
+            assert torch.equal(out.new_len[:, :, b], ref.new_len[:, :, b])
+            live = (torch.arange(t1 - t0, device="cuda") < ref.new_len[:, :, b, None])[..., None]
+            assert bool(((kc[:, :, t0:t1] == k[:, :, t0:t1]) | ~live).all())
