@@ -160,7 +160,7 @@ int do_score(Timer &tm, const skipkv_cache *c, const skipkv_params *p, const Row
              const float *tok_red, float *sent_score, float *sent_lambda, float *tok_imp, void *ws, hipStream_t st,
              const HeadView &hv = HeadView(), const float *shared_lambda = nullptr) {
   const Workspace w = carve(c, rl, ws);
-  PlanArgs pa{c->seq_off, c->sent_ptr, c->sent_off, c->batch, c->n_layers * c->n_kv_heads, w, p->dev_status, hv.len, hv.cnt};
+  PlanArgs pa{c->seq_off, c->sent_ptr, c->sent_off, c->batch, c->n_layers * c->n_kv_heads, w, p->dev_status, hv.len, hv.cnt, c->total_sentences};
   if (tm.run("plan", [&] { return launch_plan(pa, st); }) != hipSuccess) return SKIPKV_EHIP;
   ScanArgs sa{};
   sa.k = c->k;

@@ -175,6 +175,7 @@ struct PlanArgs {
   Workspace ws;
   int32_t *dev_status;
   const int32_t *len, *cnt;  // nullable [batch]: explicit lengths and sentence counts (then seq_off / sent_ptr only give capacities)
+  int32_t total_sentences;
   bool alone = false;        // one block in all: it writes the header itself (set by launch_plan, as the next one)
   bool preset = false;       // the blocks mark the statistics records of their sequences
 };

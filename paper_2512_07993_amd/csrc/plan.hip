@@ -261,8 +261,12 @@ hipError_t launch_plan(const PlanArgs &args, hipStream_t st) {
   a.preset = a.n_lh * cap16 <= 8192 * (int64_t)a.batch && a.batch < 1024;
   if (!a.alone) hipLaunchKernelGGL(k_plan_reset, dim3(1), dim3(64), 0, st, a.ws.hdr);
   if (a.batch > 0) {
-    // a wave per sequence from where a block each would fill the chip (four blocks per CU)
-    if (a.batch < 1024)
+    // A wave per sequence from where a block each would fill the chip (four blocks per CU), unless the sentences that
+    // there is room for are so many on average that blocks would do their sequences one after the other.  us, a wave / a
+    // block: 1024 sequences of 300 / 700 / 900 / 1100 / 3000 sentences 22 / 33 / 39 / 64 / 132, 29 / 32 / 34 / 36 / 56;  2048 of
+    // 500: 31, 46;  4096 of 300 / 1020 / 1100: 34 / 55 / 103, 70 / 91 / 100.
+    const int64_t most = a.batch < 2048 ? 640 : kMaxSent<1>;
+    if (a.batch < 1024 || a.total_sentences > a.batch * most)
       hipLaunchKernelGGL(k_plan<4>, dim3(a.batch), dim3(256), 0, st, a);
     else
       hipLaunchKernelGGL(k_plan<1>, dim3((a.batch + 3) / 4), dim3(256), 0, st, a);

@@ -539,16 +539,19 @@ def test_select_gives_the_same_with_few_heads_and_with_many():
             np.testing.assert_array_equal(got[1][0][0, h, sb:sb + ns].cpu().numpy().astype(bool), ora["keep"])
 
 
-def test_plans_of_a_thousand_sequences_equal_those_of_a_few():
-    # from 1024 sequences on a wave plans each (longer than 1023 sentences: the workgroup); below, a workgroup does
+@pytest.mark.parametrize("most", [9, 1400])
+def test_plans_of_a_thousand_sequences_equal_those_of_a_few(most):
+    # from 1024 sequences on a wave plans each (longer than 1023 sentences: the workgroup), unless they have more than 640
+    # sentences on average; below 1024 a workgroup does
     rng = np.random.default_rng(9)
-    offsets = [np.concatenate([[0], np.cumsum(rng.integers(1, 30, size=int(rng.integers(1, 9))))]).tolist() for _ in range(1030)]
+    offsets = [np.concatenate([[0], np.cumsum(rng.integers(1, 30, size=int(rng.integers(1, most))))]).tolist() for _ in range(1030)]
     for i, n in ((3, 1023), (5, 1024), (6, 1500), (1029, 300)):
         offsets[i] = np.concatenate([[0], np.cumsum(rng.integers(1, 6, size=n))]).tolist()
     offsets[8] = [0, 200, 210, 500, 800]            # sentences that the single-pass scan does not take
     offsets[9] = [0]                                # an empty sequence
     offsets[10] = [0, 7, 7, 20]                     # not ascending: reported, the others are not affected
     st = _structure(offsets)
+    assert (st.total_sentences > 640 * len(offsets)) == (most > 9)
     cfg = W.Config("plans", 9, len(offsets), 1, 1, 4, "bf16", 0, 0, 16, 4, 4, 8.0, 0.0)
     k0, v0, q = _random_kvq(cfg, st, 5)
     k, v = k0.clone(), v0.clone()
