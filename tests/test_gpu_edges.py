@@ -452,7 +452,8 @@ def test_two_pass_scan_shapes(group, alpha, block_size):
 
 
 @pytest.mark.parametrize("paged", [False, True])
-@pytest.mark.parametrize("dtype,n_layers", [("bf16", 1), ("bf16", 33), ("bf16", 65), ("f32", 1), ("f32", 17), ("f32", 33), ("f32", 65)])
+@pytest.mark.parametrize("dtype,n_layers", [("bf16", 1), ("bf16", 17), ("bf16", 32), ("bf16", 33), ("bf16", 65),
+                                            ("f32", 1), ("f32", 9), ("f32", 16), ("f32", 17), ("f32", 33), ("f32", 65)])
 def test_compact_rows_in_slices(dtype, n_layers, paged):
     # 16 streams per layer here: up to 256 / 512 of them move bf16 rows in slices of 64 / 128 bytes, up to
     # 128 / 256 / 512 fp32 rows in slices of 64 / 128 / 256.  Lengths around a tile of every slice (16 to 128 rows).
@@ -586,13 +587,26 @@ def test_a_sequence_alone_gives_what_it_gives_in_a_batch(kind, n_layers):
     cfg1 = W.Config("alone", 9, 1, n_layers, 8, 32, "bf16", 0, 0, 24, 8, 8, 8.0, 0.0)
     k0, v0, q = _random_kvq(cfg, pair, 6)
     n, ns = int(one.seq_len[0]), int(one.n_sent[0])
-    ref = run_step(cfg, pair, k0.clone(), v0.clone(), q)
+    kr, vr = k0.clone(), v0.clone()
+    ref = run_step(cfg, pair, kr, vr, q)
     for _ in range(2):
         k, v = k0[:, :, :n].contiguous(), v0[:, :, :n].contiguous()
         out = run_step(cfg1, one, k, v, q[:, :1].contiguous())
         assert int(out.dev_status.item()) == int(ref.dev_status.item()) and (int(out.dev_status.item()) != 0) == (kind == "bad offsets")
         assert torch.equal(out.new_len[..., 0], ref.new_len[..., 0])
-        if kind != "bad offsets":
-            assert torch.equal(out.sent_score[..., :ns], ref.sent_score[..., :ns])
-            nl = int(out.new_len.max()) if ns else 0
-            assert torch.equal(out.kept_idx[:, :, 0, :min(nl, 1)], ref.kept_idx[:, :, 0, :min(nl, 1)])
+        if kind == "bad offsets":  # reported, and the cache left alone
+            for got, want in ((k, k0), (v, v0), (kr, k0), (vr, v0)):
+                assert torch.equal(got[:, :, :n], want[:, :, :n])
+            continue
+        assert torch.equal(out.sent_score[..., :ns], ref.sent_score[..., :ns]) and torch.equal(out.sent_lambda[..., :ns], ref.sent_lambda[..., :ns])
+        assert torch.equal(out.sent_keep[..., :ns], ref.sent_keep[..., :ns]) and torch.equal(out.new_sent_cnt[..., 0], ref.new_sent_cnt[..., 0])
+        assert torch.equal(out.tok_imp[..., :n], ref.tok_imp[..., :n])
+        # the valid part of every head's rows: kept indices, new offsets, K and V
+        nl, nc = out.new_len[:, :, 0, None], out.new_sent_cnt[:, :, 0, None]
+        at = torch.arange(max(n, ns + 1), device="cuda")
+        w = min(out.kept_stride, ref.kept_stride)
+        assert int(nl.max()) <= w
+        assert bool(((out.kept_idx[:, :, 0, :w] == ref.kept_idx[:, :, 0, :w]) | (at[:w] >= nl)).all())
+        assert bool(((out.new_sent_off[:, :, :ns + 1] == ref.new_sent_off[:, :, :ns + 1]) | (at[:ns + 1] > nc)).all())
+        for got, want in ((k, kr), (v, vr)):
+            assert bool(((got == want[:, :, :n]).all(3) | (at[:n] >= nl)).all())
