@@ -122,7 +122,8 @@ typedef struct skipkv_params {
 } skipkv_params;
 #define SKIPKV_FLAG_FORCE_TWO_PASS 1u /* read K twice: statistics pass + score pass, no waits across workgroups */
 
-/* Bytes of device scratch that skipkv_score / skipkv_step need for this problem.         */
+/* Bytes of device scratch that skipkv_score / skipkv_step need for this problem; never fewer
+ * for a larger total_tokens.                                                               */
 int skipkv_workspace_bytes(const skipkv_cache *cache, const skipkv_params *params, size_t *out_bytes);
 
 /*

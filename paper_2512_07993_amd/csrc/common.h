@@ -62,7 +62,7 @@ static_assert(kIrNs < kItemRecInts && kSpanMaxSent < 256, "the record holds the 
 struct PlanHeader {
   // The three range counters that every plan block draws from, packed into one word so that a
   // block needs ONE atomic (with thousands of blocks the same-address atomics are what the plan
-  // costs): chunks (units of the two-pass scan) in bits 0..21, items (units of the single-pass scan)
+  // costs): chunks (units of the two-pass scan, each sequence's rounded up to whole runs) in bits 0..21, items (units of the single-pass scan)
   // in bits 22..42, row blocks in bits 43..63.
   unsigned long long ranges;
   int32_t n_unfused;  // number of sequences that take the two-pass scan

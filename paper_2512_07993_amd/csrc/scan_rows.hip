@@ -7,7 +7,7 @@
 //   pass B   the logits again, I[t] = (1/alpha) sum_a max_i softmax, and its mean over every sentence.
 //
 // What bounds it.  With 160 query rows a 256-byte key costs 41 KFLOP and 160 exponentials: both passes are bound by
-// the instructions that a SIMD can issue (pass A at 160 rows: about 1240 VALU and 205 MFMA instructions per 64-key
+// the instructions that a SIMD can issue (pass A at 160 rows: about 1320 VALU and 205 MFMA instructions per 64-key
 // tile and CU; the kernel's time is close to the sum of their issue times), not by HBM.  Hence:
 //   - a workgroup takes a RUN of up to kMaxRunChunks consecutive chunks of a sequence, so that its query fragments,
 //     loaded once, stay in registers for it (no query tile in LDS);
@@ -26,10 +26,12 @@
 //     in flight (whole call of the first shape below 10.6 ms instead of 10.0).
 // Measured, pass A / pass B / k_row_norm in us, against one workgroup of 256 threads per chunk with the query tile in
 // LDS and a running maximum per row, which this replaces:
-//   48 layers x 8 heads, 4 x 32 K tokens, 160 rows (50 M keys, 12.9 GB):    7327 / 3926 / 196  ->  4189 / 3193 / 14
-//   32 layers x 8 heads, 4 x 3-9 K tokens, 1 % long sentences, 64 rows:      995 /  711 /  23  ->   407 /  347 /  9
-// Half the waves with twice the rows each (256 threads): 4445 / 3110.  32x32x16 products with the rows in two halves:
-// 5675 / 2936, the logits of a tile no longer fit beside the fragments in pass A.
+//   48 layers x 8 heads, 4 x 32 K tokens, 160 rows (50 M keys, 12.9 GB):    7327 / 3926 / 196  ->  3980 / 3210 / 10
+//   32 layers x 8 heads, 4 x 3-9 K tokens, 1 % long sentences, 64 rows:      995 /  711 /  23  ->   412 /  338 /  7
+// The whole call of the first shape with one, four, up to sixteen chunks per run: 18.0, 11.2, 10.0 ms.  Pass B alone would be
+// a little faster in either of two other shapes that pass A is slower in, measured while both took 4189 / 3193: half the waves
+// with twice the rows each (256 threads) 4445 / 3110;  32x32x16 products with the rows in two halves 5675 / 2936, the
+// logits of a tile no longer fit beside the fragments in pass A.
 #include "scan_dev.h"
 
 #include <algorithm>
@@ -44,7 +46,7 @@ constexpr int kTileSlots = 3;           // tiles in LDS
 constexpr int kAhead = kTileSlots - 1;  // tiles that are loaded ahead of the one computed on
 constexpr int kTileLoads = 3;           // direct loads of a wave per tile: 2 x 4 rows and the chunk's offsets
 constexpr int kGroupTok = 256;    // pass B: tokens whose importance is summed over the waves at a time
-constexpr int kMaxRunChunks = 16;  // per run: the query fragments' loads and a record per run are then under 2 % of it
+constexpr int kMaxRunChunks = 16;  // a run's start (query loads, the first tiles' latency) and record cost as much as 1.4 chunks
 
 template <int NP, int AL>
 struct RowsShape {

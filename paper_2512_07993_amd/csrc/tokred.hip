@@ -21,11 +21,11 @@
 //
 // What bounds a sweep: vector instructions.  An entry costs a matrix instruction's 16 cycles for four, and per lane
 // two scale multiplies, an exponential (two issue slots) and two fmas; counters show the vector pipe issuing for
-// 66 % and the matrix pipe busy for 30 % of a SIMD's cycles, and the two hardly overlap.  So: 32 rows per wave in 125
+// 62 % and the matrix pipe busy for 31 % of a SIMD's cycles, and the two hardly overlap.  So: 32 rows per wave in 125
 // registers, which lets four waves share a SIMD (64 rows took 237: two waves); one barrier per column block and two LDS
 // buffers; column sums of four column tiles reduced over the lane groups together (three permutes); squares of
 // 64 instead of 256 on the diagonal; and waves that can issue matrix instructions first.  32 layers x 8
-// heads, 4 x 2-4 K tokens: a sweep takes 1970 us, with 64 rows per wave it took 2376 (without the priority 2030; with
+// heads, 4 x 2-4 K tokens: a sweep takes 1970 us (1800 on another box), with 64 rows per wave it took 2376 (without the priority 2030; with
 // branches between the column tiles, and their spills, 2190).
 // Totals are accumulated across workgroups as 64-bit FIXED-POINT integers (integer addition is
 // associative: the result does not depend on the order in which workgroups arrive, and the

@@ -65,8 +65,8 @@ def test_two_pass_scan_matches_oracle():
 
 
 def test_two_pass_scan_is_reproducible_bit_for_bit():
-    """The forced two-pass step run twice on the same bits: sentence key sums are accumulated in a fixed
-    order (one wave per sentence, tokens in order), so lambda, scores and kept indices repeat exactly."""
+    """The forced two-pass step run twice on the same bits: all sums are taken in a fixed order, so lambda, scores
+    and kept indices repeat exactly (runs of several chunks: test_gpu_two_pass.py)."""
     import torch
     from paper_2512_07993_amd import binding as B
     cfg = W.CONFIGS[3].scaled(n_layers=2, batch=4)

@@ -3,8 +3,8 @@ vLLM") through the C ABI.  A first step on the contiguous cache leaves every hea
 length and sentence ranges; the second step then runs twice on the same numbers, once on the
 contiguous cache (whose parity with the oracle test_gpu_ranges.py establishes) and once on pools of
 blocks that the cache was scattered into, and the two must agree: token importance, selection and
-the compacted rows bit for bit, scores bit for bit through the single-pass scan and to rounding
-through the two-pass one (whose pooling order varies from run to run)."""
+the compacted rows bit for bit, scores bit for bit through the single-pass scan and (checked) to
+rounding through the two-pass one."""
 import numpy as np
 import pytest
 import torch
