@@ -203,10 +203,11 @@ def test_embeddings_of_large_keys():
 
 @pytest.mark.parametrize("paged", [False, True])
 @pytest.mark.parametrize("group,alpha", [(4, 16), (5, 32)])
-@pytest.mark.parametrize("token", [305, 899, 640])
+@pytest.mark.parametrize("token", [305, 560, 899, 640])
 def test_an_infinite_key_stays_in_its_sentence(group, alpha, token, paged):
     # A key with an infinity that every query scores -inf has weight 0 and spoils the embedding of its own sentence only.
-    off = [0, 300, 310, 330, 335, 350, 620, 640, 660, 700, 900, 930, 1000]
+    # (One of the chunks has more than 16 sentences, which other waves sum.)
+    off = [0, 300, 310, 330, 335] + list(range(350, 621, 9)) + [640, 660, 700, 900, 930, 1000]
     st = _structure([off])
     cfg = _cfg("inf", 1, 1, 1, group, alpha)
     g = torch.Generator(device="cuda")
