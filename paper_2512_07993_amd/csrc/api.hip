@@ -73,9 +73,10 @@ Workspace carve(const skipkv_cache *c, const RowLayout &rl, void *base) {
   const size_t nc = 2 * ((T + kChunkCap - 1) / kChunkCap + (S + kChunkMaxSent - 1) / kChunkMaxSent) + B;
   // ... and each sequence's share of the chunk list is rounded up to whole runs, as far as the list may go
   // (runs longer than the sequences would only be room)
-  const size_t want = std::min((size_t)scan_run_chunks(c->dtype, (int64_t)LH, (int64_t)T), std::max<size_t>(1, nc / std::max<size_t>(B, 1)));
+  const size_t want = c->dtype == SKIPKV_BF16 ? std::min<size_t>(kMaxRunChunks, std::max<size_t>(1, nc / std::max<size_t>(B, 1))) : 1;
   const size_t end = std::max<size_t>(nc, (size_t)kHdrMaxChunks);
-  const size_t rc = std::min(want, 1 + (end - nc) / std::max<size_t>(B, 1));
+  const size_t rc = std::min({(size_t)scan_run_chunks(c->dtype, (int64_t)(LH * B), (int64_t)(T / std::max<size_t>(B, 1))), want,
+                              1 + (end - nc) / std::max<size_t>(B, 1)});
   w.run_chunks = (int32_t)rc;
   w.nr_max = (int32_t)((nc + B * (rc - 1)) / rc);
   w.nrb_max = (int32_t)((S + kRowBlock - 1) / kRowBlock + B);

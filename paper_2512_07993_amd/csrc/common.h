@@ -11,6 +11,7 @@ namespace skipkv {
 constexpr int kD = SKIPKV_HEAD_DIM;  // head dimension
 constexpr int kChunkCap = 256;       // a chunk of scan work = a maximal run of whole sentences of at most this many tokens
 constexpr int kChunkMaxSent = 32;    // ... and at most this many sentences (a single longer sentence is a chunk of its own)
+constexpr int kMaxRunChunks = 16;    // chunks that a workgroup of the bf16 two-pass scan takes at a time, at most
 // Units of the single-pass scan (scan_fused.hip): a span is a maximal run of whole sentences of at most
 // kSpanCap tokens and kSpanMaxSent sentences, the share of ONE wave; an item is up to kItemSpans
 // consecutive spans of one sequence, the share of one workgroup.  A sequence with a sentence longer than
@@ -209,7 +210,7 @@ struct ScanArgs {
 };
 bool scan_fused_supported(const RowLayout &rl, int64_t row_pitch_bytes);
 hipError_t launch_scan_fused(const ScanArgs &a, hipStream_t st);    // single pass over K (sequences the plan marked fused)
-int scan_run_chunks(int dtype, int64_t n_lh, int64_t total_tokens);  // chunks that the two-pass scan takes at a time, at most
+int scan_run_chunks(int dtype, int64_t seqs, int64_t tokens);  // chunks that the two-pass scan takes at a time, at most
 int scan_two_pass_rows(const RowLayout &rl, int dtype);  // rows of the statistics arrays that the two-pass scan of this shape has
 hipError_t launch_scan_stats(const ScanArgs &a, hipStream_t st);    // pass A: row statistics + sentence embeddings
 hipError_t launch_row_norm(const ScanArgs &a, hipStream_t st);      // combine the records of pass A

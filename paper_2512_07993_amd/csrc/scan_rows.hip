@@ -46,7 +46,6 @@ constexpr int kTileSlots = 3;           // tiles in LDS
 constexpr int kAhead = kTileSlots - 1;  // tiles that are loaded ahead of the one computed on
 constexpr int kTileLoads = 3;           // direct loads of a wave per tile: 2 x 4 rows and the chunk's offsets
 constexpr int kGroupTok = 256;    // pass B: tokens whose importance is summed over the waves at a time
-constexpr int kMaxRunChunks = 16;  // a run's start (query loads, the first tiles' latency) and record cost as much as 1.4 chunks
 
 template <int NP, int AL>
 struct RowsShape {
@@ -678,11 +677,32 @@ hipError_t dispatch(const ScanArgs &a, hipStream_t st) {
 
 }  // namespace
 
-// Chunks per run: as many as leave every workgroup slot of the chip (512) at least eight runs, so that the last
-// ones to finish do not matter, and no more than kMaxRunChunks.  The fp32 scan takes chunks one by one.
-int scan_run_chunks(int dtype, int64_t n_lh, int64_t total_tokens) {
+// Chunks per run of `seqs` sequences (of all heads) of some `tokens` tokens each: the least of
+//   the runs that a CU does one after the other x (their chunks + 0.9 for the start, which another run half hides)
+//   + 0.75 x the chunks of the last ones, when CUs run idle (+ 2 where a run has its CU to itself and hides nothing),
+// in chunks of some 240 tokens, and among those within 1 % of it the shortest; but four chunks where there is a sequence
+// for every CU, which costs nothing there and leaves short sequences whole, whatever else is in the batch.  Pass A + pass B in us with 1, 3, 6, 16
+// chunks, and with the length chosen here:
+//   384 sequences of 4096 tokens, 160 rows:          420  291  273  258    271
+//   552 of 1253, 96 rows:                            173  134  132  131    140
+//   8 of 32000, 160 rows:                             90   73   83  171     74
+//   1024 of 3000-9000, 64 rows:                     1050  753  707  763    761
+//   480 of 700-5000, 256 rows:                       389  305  327  399    286
+//   1536 of 32896, 160 rows:                       11446 7764 6960 6498   6516
+// (With eight runs for every workgroup slot of the chip instead, shortest runs for all but the largest calls, the first two
+// took 435 and 173; the kernels before, a workgroup per chunk, 365 and 148.)
+int scan_run_chunks(int dtype, int64_t seqs, int64_t tokens) {
   if (dtype != SKIPKV_BF16) return 1;
-  return (int)std::min<int64_t>(kMaxRunChunks, std::max<int64_t>(1, n_lh * (total_tokens / kChunkCap + 1) / (8 * 512)));
+  const int64_t n = std::max<int64_t>(1, (tokens + 239) / 240);
+  auto cost = [&](int64_t rc) {  // in twentieths of a chunk
+    const int64_t per_seq = (n + rc - 1) / rc, len = (n + per_seq - 1) / per_seq, runs = seqs * per_seq;
+    return (runs + 255) / 256 * (20 * len + 18) + 15 * len + (runs <= 256 ? 40 : 0);
+  };
+  int64_t best = cost(1);
+  for (int rc = 2; rc <= kMaxRunChunks; ++rc) best = std::min(best, cost(rc));
+  int rc = 1;
+  while (cost(rc) * 100 > best * 101) ++rc;
+  return seqs >= 256 ? std::max(rc, 4) : rc;
 }
 
 int scan_two_pass_rows(const RowLayout &rl, int dtype) {

@@ -37,7 +37,7 @@ def _cfg(name, batch, L, H, group, alpha, protect=40):
 
 
 def _long_batch(L, H):
-    """Sequences of ragged lengths that make runs of more than one chunk (8 x 512 chunks of all heads for each chunk of a run)."""
+    """Sequences of ragged lengths, in such numbers that runs of several chunks pay."""
     rng = np.random.default_rng(3)
     offsets = []
     for n in [9500, 1500, 700, 8100, 260, 5333, 9001, 40, 7000, 3100, 6600, 9100, 4700, 2900]:
