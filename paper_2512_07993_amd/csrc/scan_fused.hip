@@ -51,6 +51,17 @@
 // run at about 225 bytes per cycle on this chip (measured), against about 135 with swz(r) = r & 15;
 // the query tile uses the same arrangement.
 //
+// What bounds it.  Two waves per SIMD (the logits take half of the registers), each one dependent stream of instructions:
+// an item's some 120 tokens per wave cost about 35 K clocks, of which the first phase takes half, the end of an item (sums,
+// records, embeddings, second phase, means) the other half.  So what counts is how many instructions an item has besides the 50
+// per stage and 34 per stage that its exponentials need, and what they wait for:
+//   - queries and sentence offsets go straight to LDS, row sums are handed out to the lanes instead of formed in all of them,
+//     few sentences fill few registers of the key sums, divisions are scalar, paged caches have a kernel of their own: 21.6 ->
+//     15.9 vector instructions per token (32 layers x 8 heads, 16 sequences of 2-16 K tokens, 64 rows: 2815 -> 2490 us);
+//   - all record loads are waited for before the second barrier, where they have long arrived: the compiler, which does not see
+//     the key loads, otherwise waits for the records' registers in the next first phase, and so for the keys in flight
+//     (28 layers x 4 heads, 64 sequences of 4-8 K, 56 rows: 3200 -> 2860 us; 3560 before all of this).
+//
 // Paged cache.  With a row map (logical token -> block slot) and blocks of a power of two >= 16
 // slots, a stage spans at most two blocks: two scalar reads of the map give two bases per stage.
 #include "scan_dev.h"
@@ -59,7 +70,7 @@
 #define SKIPKV_FRAG_AHEAD 3  // query fragments are read this many matrix instructions ahead of their use
 #endif
 #ifndef SKIPKV_SCAN_NBUF
-#define SKIPKV_SCAN_NBUF 2   // stage buffers per wave
+#define SKIPKV_SCAN_NBUF 3   // stage buffers per wave
 #endif
 
 namespace skipkv {
@@ -70,6 +81,58 @@ constexpr int kStageRows = 16;                      // rows per pipeline stage =
 constexpr int kSpanStages = kSpanCap / kStageRows;  // stages per span
 constexpr int kMergeDepth = 8;                      // records a lane has in flight while merging
 
+// Unsigned division by a number that is constant in the kernel, for dividends below 2^31: with a scalar dividend a handful
+// of scalar instructions, where the compiler's own takes some twenty vector ones and their latency.
+struct Divisor {
+  uint32_t d, m;
+  __device__ explicit Divisor(uint32_t d_) : d(max(d_, 1u)), m((uint32_t)__builtin_amdgcn_readfirstlane((int)(0xFFFFFFFFu / d))) {}  // (into a scalar register: what follows from it stays there)
+  __device__ uint32_t div(uint32_t x) const {
+    const uint32_t q = __umulhi(x, m);  // the quotient or one less
+    return x - q * d >= d ? q + 1 : q;
+  }
+};
+
+// Sums of N values over the 16 lanes of a row (16 lanes that share lane / 16), handed out: lane c of the row gets the sum of
+// value c % N.  A step pairs each lane with another one and halves the values that a lane still looks after: 45 instructions
+// for 16 values, where the sum of every value in every lane takes 64.
+template <int CTRL>
+__device__ __forceinline__ float plus_dpp(float v) {
+  return v + __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, true));
+}
+template <int N>
+__device__ __forceinline__ float row16_sums(const float (&v)[N], int c16) {
+  static_assert(N == 8 || N == 16, "one value per lane of a half row or of a row");
+  constexpr int kRor8 = 0x128, kHalfMirror = 0x141, kXor2 = 0x4E, kXor1 = 0xB1;
+  auto pick = [](bool second, float a, float b) { return second ? b : a; };  // (by value: a choice of places would put the array into memory)
+  float x[N];  // (every sum is formed in all lanes, and only then chosen from: an inactive lane would not hand out its value)
+#pragma unroll
+  for (int q = 0; q < N; ++q) x[q] = plus_dpp<kRor8>(v[q]);
+#pragma unroll
+  for (int q = 0; q + 8 < N; ++q) x[q] = pick(c16 & 8, x[q], x[q + 8]);
+#pragma unroll
+  for (int q = 0; q < 8; ++q) x[q] = plus_dpp<kHalfMirror>(x[q]);
+#pragma unroll
+  for (int q = 0; q < 4; ++q) x[q] = pick(c16 & 4, x[q], x[q + 4]);
+#pragma unroll
+  for (int q = 0; q < 4; ++q) x[q] = plus_dpp<kXor2>(x[q]);
+#pragma unroll
+  for (int q = 0; q < 2; ++q) x[q] = pick(c16 & 2, x[q], x[q + 2]);
+  x[0] = plus_dpp<kXor1>(x[0]);
+  x[1] = plus_dpp<kXor1>(x[1]);
+  return pick(c16 & 1, x[0], x[1]);
+}
+
+// Halves of a wave: lanes below 32 get x of both halves added, the others y.  Rows likewise: even rows x of their
+// pair of rows, odd rows y.
+__device__ __forceinline__ float swap_add32(float x, float y) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float swap_add16(float x, float y) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
 struct Item {  // one item as seen by one wave
   uint32_t item;  // >= n_items: none
   int lh, b, nsp, rec, n_tok, tok0, np, first, soff_idx, ns_item;
@@ -78,7 +141,7 @@ struct Item {  // one item as seen by one wave
   int ns, sb;       // ... its sentences: count, and index of the first one among the item's sentences
 };
 
-template <int DT, int NP, int AL>
+template <int DT, int NP, int AL, bool PAGED>
 __global__ void __launch_bounds__(256, (DT == SKIPKV_BF16 ? 2 : 1)) k_scan_fused(ScanArgs a) {
   constexpr int SL = NP * AL;
   constexpr int NT = (SL + 3) / 4;
@@ -101,11 +164,11 @@ __global__ void __launch_bounds__(256, (DT == SKIPKV_BF16 ? 2 : 1)) k_scan_fused
 
   __shared__ __align__(256) char kt[4][NBUF][STAGEB];  // 256-byte aligned: the row swizzle is applied as an XOR on address bits
   __shared__ __align__(256) char qt[R * QSTR];
-  __shared__ int soff_buf[2][kItemMaxSent + 2];  // [item parity]: offsets of the item's sentences
-  __shared__ float wstat[4][R][2];               // (reference, sum) of every row over each wave's span
+  __shared__ int soff_buf[2][2 * 64];            // [item parity]: offsets of the item's sentences (64 per direct load; the last one repeated)
+  __shared__ __align__(16) float wstat[4][R][2];               // (reference, sum) of every row over each wave's span
   __shared__ float mstat[4][R][2];               // (reference, sum) of every row over each wave's quarter of the head's records
   __shared__ float imp[4][kSpanCap];             // token importance of each wave's span (private to the wave)
-  __shared__ float row_norm_l[4][R];             // every wave's own copy of the head's normalisers
+  __shared__ __align__(16) float row_norm_l[4][R];  // every wave's own copy of the head's normalisers (+inf: padding row)
   __shared__ int s_timeout[2];  // [item parity] a wait of the item ran out: its sentences get NaN means
 
   const int tid = threadIdx.x, lane = tid & 63, c16 = lane & 15, g = lane >> 4;
@@ -123,13 +186,18 @@ __global__ void __launch_bounds__(256, (DT == SKIPKV_BF16 ? 2 : 1)) k_scan_fused
   const ConstIntPtr row_map_c = (ConstIntPtr)a.row_map;  // written by an earlier kernel, constant here
 
   // ---- item descriptors: one 64-byte record per item, written by the plan ----------------------
+  const Divisor by_items(n_per_lh), by_heads(a.n_kv_heads), by_virt_b(a.virt_b);
+  // batch and KV heads that the query rows are laid out by (the real ones under per-head ranges)
+  const int q_batch = a.virt_hk > 0 ? a.virt_b : a.batch, q_heads = a.virt_hk > 0 ? a.virt_hk : a.n_kv_heads;
+  const Divisor by_q_heads(q_heads);
   auto load_item = [&](uint32_t item) -> Item {  // first fused item at or after `item` in this workgroup's sequence
     Item it{};
     for (; item < n_items; item += gridDim.x) {
-      const ConstIntPtr r = item_rec_c + (int64_t)(item % n_per_lh) * kItemRecInts;
+      const uint32_t lh = by_items.div(item);
+      const ConstIntPtr r = item_rec_c + (int64_t)(item - lh * n_per_lh) * kItemRecInts;
       const int nsp = r[kIrNsp];
       if (nsp == 0) continue;  // the sequence takes the two-pass scan
-      it.lh = item / n_per_lh;
+      it.lh = (int)lh;
       it.b = r[kIrB];
       it.nsp = nsp;
       it.rec = r[kIrRec];
@@ -146,10 +214,10 @@ __global__ void __launch_bounds__(256, (DT == SKIPKV_BF16 ? 2 : 1)) k_scan_fused
       it.w0 = r[kIrT0 + min(wave, nsp)];
       it.w1 = r[kIrT0 + min(wave + 1, nsp)];
       it.nst = (it.w1 - it.w0 + kStageRows - 1) / kStageRows;
-      const int l = it.lh / a.n_kv_heads, h = it.lh % a.n_kv_heads;
+      const int l = (int)by_heads.div(lh), h = it.lh - l * a.n_kv_heads;
       // contiguous cache: first row of the sequence; paged cache: the head's base, rows come from the row map
       it.kbase = static_cast<const char *>(a.k) +
-                 ((int64_t)l * a.stride_layer + (int64_t)h * a.stride_head + (a.row_map ? 0 : (int64_t)it.tok0 * a.stride_tok)) * ESZ;
+                 ((int64_t)l * a.stride_layer + (int64_t)h * a.stride_head + (PAGED ? 0 : (int64_t)it.tok0 * a.stride_tok)) * ESZ;
       break;
     }
     it.item = item;
@@ -162,22 +230,22 @@ __global__ void __launch_bounds__(256, (DT == SKIPKV_BF16 ? 2 : 1)) k_scan_fused
     uint4 q[NQ];
     int so;
   };
+  // The first of the query rows of the item's group (head i of the group, query a: row i * alpha + a from there).
+  auto q_rows = [&](const Item &it) -> const char * {
+    int lh_r = it.lh, qb = it.b;
+    if (a.virt_hk > 0) {
+      lh_r = (int)by_virt_b.div(it.b);
+      qb = it.b - lh_r * q_batch;
+    }
+    const int l = (int)by_q_heads.div(lh_r), h = lh_r - l * q_heads;
+    return static_cast<const char *>(a.q) + (((int64_t)l * q_batch + qb) * q_heads + h) * ((int64_t)n * a.alpha * ROWB);
+  };
   auto q_fetch = [&](const Item &it) -> QFetch {
     QFetch f;
     const int t = opaque(tid);
     f.so = 0;
     if (t <= it.ns_item) f.so = a.sent_off[it.soff_idx + t];
-    const char *qbase = static_cast<const char *>(a.q);
-    // layer, KV head and sequence that address the query rows (the real ones under per-head ranges)
-    int l = it.lh / a.n_kv_heads, h = it.lh % a.n_kv_heads, qb = it.b, q_batch = a.batch, q_heads = a.n_q_heads;
-    if (a.virt_hk > 0) {
-      const int lh_r = it.b / a.virt_b;
-      qb = it.b % a.virt_b;
-      l = lh_r / a.virt_hk;
-      h = lh_r % a.virt_hk;
-      q_batch = a.virt_b;
-      q_heads = a.virt_hk * n;
-    }
+    const char *qbase = q_rows(it);
 #pragma unroll
     for (int u = 0; u < NQ; ++u) {
       const int r = u * (256 / PPR) + t / PPR, piece = t % PPR;
@@ -185,8 +253,7 @@ __global__ void __launch_bounds__(256, (DT == SKIPKV_BF16 ? 2 : 1)) k_scan_fused
       const int al = slot / NP, i = slot % NP, aq = gq + 4 * al;
       f.q[u] = make_uint4(0, 0, 0, 0);
       if (slot < SL && i < n && aq < a.alpha) {
-        const int64_t row = (((int64_t)l * q_batch + qb) * q_heads + (h * n + i)) * a.alpha + aq;
-        f.q[u] = *reinterpret_cast<const uint4 *>(qbase + row * ROWB + piece * 16);
+        f.q[u] = *reinterpret_cast<const uint4 *>(qbase + (i * a.alpha + aq) * ROWB + piece * 16);
       }
     }
     return f;
@@ -197,8 +264,23 @@ __global__ void __launch_bounds__(256, (DT == SKIPKV_BF16 ? 2 : 1)) k_scan_fused
 #pragma unroll
     for (int u = 0; u < NQ; ++u) {
       const int r = u * (256 / PPR) + t / PPR, piece = t % PPR;
-      *reinterpret_cast<uint4 *>(qt + r * QSTR + (DT == SKIPKV_BF16 ? (piece ^ swz16(r & 15)) : piece) * 16) = f.q[u];
+      *reinterpret_cast<uint4 *>(qt + r * QSTR + piece * 16) = f.q[u];
     }
+  };
+  // bf16: both go straight to LDS, behind the barrier after which nobody reads the query tile any more.  Wave w brings row
+  // tile w (a load has four rows: register lane / 16 of lane group j) and 64 of the offsets.  Rows of padding are
+  // copies of used ones: their sums are never looked at.
+  auto q_issue = [&](const Item &it, int par) {
+    const int ln = opaque(lane), lr = ln >> 4;
+    if (wave < NT) {
+      const int slot = 4 * wave + lr, al = min(slot / NP, AL - 1), i = min(slot % NP, n - 1);
+      const uint64_t base = scalar64(q_rows(it));
+      const uint32_t head = (uint32_t)(i * a.alpha) * ROWB, piece = (uint32_t)((ln & 15) ^ swz16(lr)) << 4;
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        load_to_lds_16_sbase(base, head + (uint32_t)min(j + 4 * al, a.alpha - 1) * ROWB + (piece ^ (uint32_t)(swz16(4 * j) << 4)), qt + (16 * wave + 4 * j) * ROWB);
+    }
+    if (wave < 2) load_to_lds_4_sbase(scalar64(a.sent_off + it.soff_idx), (uint32_t)min(64 * wave + ln, it.ns_item) * 4u, &soff_buf[par][64 * wave]);
   };
 
   // ---- the wave's load stream: stages of consecutive items, NBUF-1 ahead of the compute --------
@@ -212,18 +294,25 @@ __global__ void __launch_bounds__(256, (DT == SKIPKV_BF16 ? 2 : 1)) k_scan_fused
   // The stage of 16 tokens from token `ts` of a span that ends at `w1` goes into ring slot `slot`
   // (kbase, tok0, n_tok: of the span's item).
   auto issue_stage = [&](const char *kbase, int ts, int w1, int tok0, int n_tok, uint32_t slot) {
-    char *dst = kt[wave][slot % NBUF];
+    char *dst = kt[wave][slot];
     const int last = w1 - 1 - ts;  // rows past the span re-read its last row (they only meet zero weights)
-    if (a.row_map == nullptr) {
+    if constexpr (!PAGED) {
       // scalar 64-bit base of the stage + a 32-bit offset per lane (the launcher only takes this
       // kernel for row pitches below 2^24 bytes)
       const uint64_t sbase = scalar64(kbase + (int64_t)ts * tok_pitch);
       const uint32_t ln = (uint32_t)opaque(lane);
       const uint32_t vp0 = ((ln % PPR) ^ (uint32_t)swz((int)(ln / PPR))) << 4;
+      if (last >= kStageRows - 1) {  // a whole stage: the rows of a load are one step of the base from those of the one before
+        const uint32_t row0 = __umul24(ln / PPR, pitch32);
 #pragma unroll
-      for (int j = 0; j < GL; ++j) {
-        const int row = j * RPL + (int)(ln / PPR);
-        load_to_lds_16_sbase(sbase, __umul24((uint32_t)min(row, last), pitch32) + (vp0 ^ (uint32_t)(swz(j * RPL) << 4)), dst + j * 1024);
+        for (int j = 0; j < GL; ++j)
+          load_to_lds_16_sbase(sbase + (uint64_t)(j * RPL) * pitch32, row0 + (vp0 ^ (uint32_t)(swz(j * RPL) << 4)), dst + j * 1024);
+      } else {
+#pragma unroll
+        for (int j = 0; j < GL; ++j) {
+          const int row = j * RPL + (int)(ln / PPR);
+          load_to_lds_16_sbase(sbase, __umul24((uint32_t)min(row, last), pitch32) + (vp0 ^ (uint32_t)(swz(j * RPL) << 4)), dst + j * 1024);
+        }
       }
     } else {
       // Paged cache, blocks of a power of two >= 16 slots: the stage's 16 tokens lie in at most two
@@ -261,13 +350,24 @@ __global__ void __launch_bounds__(256, (DT == SKIPKV_BF16 ? 2 : 1)) k_scan_fused
 
   Item cur = load_item(blockIdx.x);
   if (cur.item >= n_items) return;
-  static_assert(NBUF == 2, "the load stream runs exactly one stage ahead of the compute");
-  uint32_t ring = 0;   // ring slot of the stage to be computed next
-  bool primed = false;  // that stage's loads are already in flight
+  static_assert(NBUF == 3, "the load stream runs up to two stages ahead of the compute");
+  uint32_t ring = 0;  // ring slot of the stage to be computed next
+  int issued = 0;     // stages of the current item whose loads are under way, at most NBUF - 1 when it begins
+  auto ring_slot = [](uint32_t r) { return r >= NBUF ? r - NBUF : r; };
   int par = 0;           // which soff buffer holds the current item's offsets
-  q_commit(cur, q_fetch(cur), par);
+  if constexpr (DT == SKIPKV_BF16) {
+    q_issue(cur, par);
+    wait_vm<0>();
+  } else {
+    q_commit(cur, q_fetch(cur), par);
+  }
   if (tid < 2) s_timeout[tid] = 0;
   lds_barrier();
+  // the row whose statistics the lane files (lane c16 of a lane group gets the sum of slot c16), and the row whose
+  // normaliser it forms: used at all?
+  auto slot_used = [&](int slot, int gq) { return slot < SL && slot % NP < n && gq + 4 * (slot / NP) < a.alpha; };
+  const int my_slot = c16 % SLP, my_row = 16 * (my_slot >> 2) + 4 * g + (my_slot & 3);
+  const bool my_row_used = slot_used(my_slot, g), norm_used = slot_used(4 * (lane >> 4) + (lane & 3), (lane >> 2) & 3);
 
   // per-lane constants of the LDS addressing (offsets inside a stage buffer)
   // key fragment of the logits: row c16, piece (4g + kk) ^ swz(c16) (the slice index kk is an XOR on bits 4..5);
@@ -288,20 +388,27 @@ __global__ void __launch_bounds__(256, (DT == SKIPKV_BF16 ? 2 : 1)) k_scan_fused
     // item's last one, its queries and offsets are fetched at the end of the first phase.  After the
     // last item the descriptor is all zero (the fetch then reads valid memory that nobody uses).
     const Item nxt = load_item(cur.item + gridDim.x);
-    if (cur.nst > 0 && !primed) issue_stage(cur.kbase, cur.w0, cur.w1, cur.tok0, cur.n_tok, ring);  // this wave had no span in the previous item
+    // (what the previous item, short of stages or without a span for this wave, has not got under way)
+    while (issued < min(NBUF - 1, cur.nst)) {
+      issue_stage(cur.kbase, cur.w0 + issued * kStageRows, cur.w1, cur.tok0, cur.n_tok, ring_slot(ring + issued));
+      ++issued;
+    }
+    int issued_next = 0;  // the same of the next item
 
     f32x4 acc[SUBS][NT];
-    f32x4 pool[8];      // key sums: register r of pool[j] = sentence 4g + r of the span, dimension 16j + c16
+    f32x4 pool[8];      // key sums: register r of pool[j] = sentence 4r + g of the span, dimension 16j + c16
     float lsum[SLP];
     float ref1 = kRefInit;
 #pragma unroll
     for (int q = 0; q < SLP; ++q) lsum[q] = 0.f;
 #pragma unroll
     for (int j = 0; j < 8; ++j) pool[j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    // the lane's sentence of the span (slot c16): token range, empty for unused slots
-    const int s_mine = cur.sb + min(c16, max(ns - 1, 0));
+    // the sentence of the span that the lane brings the indicator of, as row c16 of the key sums: token range, empty for
+    // unused ones.  Rows 4g + r, which end up in register r of lane group g, are sentences 4r + g, so that few
+    // sentences fill few registers.
+    const int s_row = 4 * (c16 & 3) + (c16 >> 2), s_mine = cur.sb + min(s_row, max(ns - 1, 0));
     const int s_lo = soff[s_mine];
-    const int s_hi = c16 < ns ? soff[s_mine + 1] : s_lo;
+    const int s_hi = s_row < ns ? soff[s_mine + 1] : s_lo;
 
     // =============== first phase: logits, row statistics and sentence key sums =================
 #pragma unroll
@@ -310,18 +417,23 @@ __global__ void __launch_bounds__(256, (DT == SKIPKV_BF16 ? 2 : 1)) k_scan_fused
       for (int T = 0; T < NT; ++T) acc[st][T] = f32x4{0.f, 0.f, 0.f, 0.f};
       if (st < cur.nst) {
         const int ts = w0 + st * kStageRows, te = min(ts + kStageRows, w1);
-        // keep the load stream one stage ahead (into the next item behind this item's last stage),
+        // keep the load stream two stages ahead (into the next item behind this item's last one),
         // then wait for this stage's rows to land
-        const bool more = st + 1 < cur.nst;
-        if (more || nxt.nst > 0) {
-          issue_stage(more ? cur.kbase : nxt.kbase, more ? ts + kStageRows : nxt.w0, more ? w1 : nxt.w1, more ? cur.tok0 : nxt.tok0,
-                      more ? n_tok : nxt.n_tok, ring + 1);
-          wait_vm<GL>();
-        } else {
-          wait_all();
+        const bool more = issued < cur.nst;
+        if (more || issued_next < nxt.nst) {
+          const int u = more ? issued : issued_next;
+          issue_stage(more ? cur.kbase : nxt.kbase, (more ? w0 : nxt.w0) + u * kStageRows, more ? w1 : nxt.w1, more ? cur.tok0 : nxt.tok0,
+                      more ? n_tok : nxt.n_tok, ring_slot(ring + (issued - st) + issued_next));
+          issued += more;
+          issued_next += !more;
         }
-        const char *stage = kt[wave][ring % NBUF];
-        ++ring;
+        switch (issued - 1 - st + issued_next) {  // stages behind this one
+          case 0: wait_all(); break;
+          case 1: wait_vm<GL>(); break;
+          default: wait_vm<2 * GL>(); break;
+        }
+        const char *stage = kt[wave][ring];
+        ring = ring_slot(ring + 1);
         const uint32_t stage_a = lds_addr(stage);
 
         // ---- operands of the sentence key sums, fetched first so that they land behind the logits block:
@@ -443,23 +555,12 @@ __global__ void __launch_bounds__(256, (DT == SKIPKV_BF16 ? 2 : 1)) k_scan_fused
 
     // ---- the span's row statistics: (reference, sum) per row, exact if the fast path is in doubt
     {
-      float tot[SLP];
-      bool doubt = false;
       // From here until the head's records are folded the wave runs at raised priority: what it does now is
       // what the other workgroups of its head wait for, while the other wave of the SIMD is mostly in its first phase.
       __builtin_amdgcn_s_setprio(3);
-#pragma unroll
-      for (int q = 0; q < SLP; ++q) tot[q] = lsum[q];
-#pragma unroll
-      for (int q = 0; q < SLP; ++q) tot[q] = row16_sum_fast(tot[q]);
-#pragma unroll
-      for (int q = 0; q < SLP; ++q) {
-        const bool used = q < SL && (q % NP) < n && (g + 4 * (q / NP)) < a.alpha;  // padding rows hold zero queries: whatever they sum to is never used
-        doubt = doubt || (used && !(tot[q] > kMinRowSum && tot[q] < kMaxRowSum));  // also catches NaN and infinity
-      }
-      float refq[SLP];
-#pragma unroll
-      for (int q = 0; q < SLP; ++q) refq[q] = ref1;
+      float my_sum = row16_sums(lsum, c16), my_ref = ref1;
+      // padding rows: whatever they sum to is never used; the comparison also catches NaN and infinity
+      const bool doubt = my_row_used && !(my_sum > kMinRowSum && my_sum < kMaxRowSum);
       if (cur.nst > 0 && __any(doubt)) {
         // slow path (a logit far above the first stage's, a row far below its group's, rows that see
         // no key of the span): every row gets its own reference, its true maximum over the span
@@ -474,22 +575,20 @@ __global__ void __launch_bounds__(256, (DT == SKIPKV_BF16 ? 2 : 1)) k_scan_fused
 #pragma unroll
           for (int st = 0; st < SUBS; ++st)
             if (st < cur.nst) s += __builtin_amdgcn_exp2f(fmaf(acc[st][q >> 2][q & 3], kScale2, -m));
-          tot[q] = row16_sum_fast(s);
-          refq[q] = m;
+          s = row16_sum_fast(s);
+          if (my_slot == q) {
+            my_sum = s;
+            my_ref = m;
+          }
         }
       }
-      if (c16 == 0) {
-#pragma unroll
-        for (int q = 0; q < SLP; ++q) {
-          const int r = 16 * (q >> 2) + 4 * g + (q & 3);
-          wstat[wave][r][0] = cur.nst > 0 ? refq[q] : kRefInit;
-          wstat[wave][r][1] = cur.nst > 0 ? tot[q] : 0.f;
-        }
-      }
+      const float2 rec = cur.nst > 0 ? make_float2(my_ref, my_sum) : make_float2(kRefInit, 0.f);
+      *reinterpret_cast<float2 *>(wstat[wave][my_row]) = rec;
     }
-    primed = cur.nst > 0 && nxt.nst > 0;
-    // the next item's queries and offsets: fetched now, committed before the second barrier below
-    const QFetch nq = q_fetch(nxt);
+    issued = issued_next;
+    // the next item's queries and offsets: fetched now, committed before the second barrier below (bf16: behind this one)
+    [[maybe_unused]] QFetch nq;
+    if constexpr (DT == SKIPKV_F32) nq = q_fetch(nxt);
     lds_barrier();  // B1: every wave is done with the query tile and has left its statistics
 
     // ---- publish the item's row statistics: one (reference, sum) record per row, lane = query row.
@@ -507,13 +606,14 @@ __global__ void __launch_bounds__(256, (DT == SKIPKV_BF16 ? 2 : 1)) k_scan_fused
       for (int w = 0; w < 4; ++w) s += wstat[w][row][1] * __builtin_amdgcn_exp2f(wstat[w][row][0] - m);
       coherent_store2(&a.ws.item_stat[((int64_t)lh * a.ws.ni_max + cur.rec) * R + row], make_float2(m, s));
     }
+    if constexpr (DT == SKIPKV_BF16) q_issue(nxt, par ^ 1);
     // ---- the head's normalisers, first half: every wave loads a quarter of the records of the head's items
     // (wave w: items w, w + 4, ...; lane = query row), kMergeDepth coherent loads in flight per lane, and
     // lets them travel while it commits the next item's queries and writes its embeddings.
-    // (The queries are committed first: they arrived long ago, and a wait for them placed behind the
+    // (fp32: the queries are committed first: they arrived long ago, and a wait for them placed behind the
     // record loads would wait for those as well.  Always kMergeDepth loads, surplus ones on the head's last
     // record, so that the number of loads in flight is known where later code waits for older ones.)
-    q_commit(nxt, nq, par ^ 1);
+    if constexpr (DT == SKIPKV_F32) q_commit(nxt, nq, par ^ 1);
     const int np = cur.np;
     const float2 *recs = a.ws.item_stat + ((int64_t)lh * a.ws.ni_max + cur.first) * R + min(opaque(lane), R - 1);
     float2 pv[kMergeDepth];
@@ -528,19 +628,16 @@ __global__ void __launch_bounds__(256, (DT == SKIPKV_BF16 ? 2 : 1)) k_scan_fused
       // (addresses are formed here, from an opaque copy: formed early they are spilled, and a reload from
       // scratch waits for every load in flight, the record loads above included)
       const int64_t col0 = (int64_t)lh * a.total_sentences + opaque(cur.soff_idx - b + cur.sb);
-      const int g4 = 4 * opaque(g);
-      float ssq[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int j = 0; j < 8; ++j)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) ssq[r] = fmaf(pool[j][r], pool[j][r], ssq[r]);
-#pragma unroll
-      for (int r = 0; r < 4; ++r) ssq[r] = row16_sum_fast(ssq[r]);  // the 16 lanes of the group hold a sentence's 128 dimensions
+      const int og = opaque(g);
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        if (r == 2) load_records(wave);  // a second look, timed to land when the embeddings are out
-        const float ss = ssq[r];
-        const int slot = g4 + r, sl = cur.sb + min(slot, ns - 1);
+        if (r == 1) load_records(wave);  // a second look, timed to land when the embeddings are out
+        if (4 * r >= ns) continue;
+        float ss = pool[0][r] * pool[0][r];
+#pragma unroll
+        for (int j = 1; j < 8; ++j) ss = fmaf(pool[j][r], pool[j][r], ss);
+        ss = row16_sum_fast(ss);  // the 16 lanes of the group hold a sentence's 128 dimensions
+        const int slot = 4 * r + og, sl = cur.sb + min(slot, ns - 1);
         const int len = soff[sl + 1] - soff[sl];
         // mean / (|mean| + eps) = sum / (|sum| + eps * len): no division by the length.  1-ulp
         // reciprocal and square root: a common scale error of ~1e-7 on the unit vector
@@ -584,14 +681,13 @@ __global__ void __launch_bounds__(256, (DT == SKIPKV_BF16 ? 2 : 1)) k_scan_fused
           __builtin_amdgcn_s_sleep(1);
           load_records(pp);
         }
+        float nm = m;
 #pragma unroll
-        for (int u = 0; u < kMergeDepth; ++u) {
-          if (pp + 4 * u < np) {  // uniform
-            const float nm = fmaxf(m, pv[u].x);
-            s = s * __builtin_amdgcn_exp2f(m - nm) + pv[u].y * __builtin_amdgcn_exp2f(pv[u].x - nm);
-            m = nm;
-          }
-        }
+        for (int u = 0; u < kMergeDepth; ++u) nm = fmaxf(nm, pv[u].x);  // (the surplus records are the head's last one)
+        s *= __builtin_amdgcn_exp2f(m - nm);
+        m = nm;
+#pragma unroll
+        for (int u = 0; u < kMergeDepth; ++u) s = fmaf(pp + 4 * u < np ? pv[u].y : 0.f, __builtin_amdgcn_exp2f(pv[u].x - nm), s);
       }
       if (lane < R) {
         mstat[wave][lane][0] = m;
@@ -599,6 +695,7 @@ __global__ void __launch_bounds__(256, (DT == SKIPKV_BF16 ? 2 : 1)) k_scan_fused
       }
     }
     __builtin_amdgcn_s_setprio(0);
+    wait_vm<0>();  // the queries are in, and so are the records: a wave without any of its own has not waited for them (see above)
     lds_barrier();  // B2: the quarters are there; the next item's queries and offsets are committed
     if (lane < R) {  // every wave folds the four quarters into its own copy of the normalisers
       float m = kRefInit;
@@ -607,18 +704,14 @@ __global__ void __launch_bounds__(256, (DT == SKIPKV_BF16 ? 2 : 1)) k_scan_fused
       float s = 0.f;
 #pragma unroll
       for (int w = 0; w < 4; ++w) s += mstat[w][lane][1] * __builtin_amdgcn_exp2f(mstat[w][lane][0] - m);
-      row_norm_l[wave][lane] = s > 0.f ? m + __builtin_amdgcn_logf(s) : INFINITY;  // log2 of the softmax normaliser
+      row_norm_l[wave][lane] = s > 0.f && norm_used ? m + __builtin_amdgcn_logf(s) : INFINITY;  // log2 of the softmax normaliser
     }
 
     // =============== second phase: token importance from the logits still in registers =========
     if (cur.nst > 0) {
-      float cn[SLP];
+      alignas(16) float cn[SLP];
 #pragma unroll
-      for (int q = 0; q < SLP; ++q) {
-        const int al = q / NP, i = q % NP;
-        const bool used = q < SL && i < n && (g + 4 * al) < a.alpha;
-        cn[q] = used ? row_norm_l[wave][16 * (q >> 2) + 4 * g + (q & 3)] : INFINITY;
-      }
+      for (int T = 0; T < NT; ++T) *reinterpret_cast<f32x4 *>(&cn[4 * T]) = *reinterpret_cast<const f32x4 *>(&row_norm_l[wave][16 * T + 4 * g]);
       float part[SUBS];  // per stage: the lane's token, summed over the lane group's window queries
 #pragma unroll
       for (int st = 0; st < SUBS; ++st) {
@@ -636,42 +729,41 @@ __global__ void __launch_bounds__(256, (DT == SKIPKV_BF16 ? 2 : 1)) k_scan_fused
           }
         }
       }
-      // the four lane groups hold the four quarters of the window: all stages' exchanges back to back
-      float other[SUBS];
+      // The four lane groups hold the four quarters of the window; summing halves the stages that a group looks after, twice:
+      // group g ends up with stages 2g and 2g + 1.  (Masked tokens have contributed 0.)
+      static_assert(SUBS == 8, "two stages for each lane group");
 #pragma unroll
-      for (int st = 0; st < SUBS; ++st) other[st] = __shfl_xor(part[st], 16);
+      for (int k = 0; k < 4; ++k) part[k] = swap_add32(part[k], part[k + 4]);
 #pragma unroll
-      for (int st = 0; st < SUBS; ++st) part[st] += other[st];
-#pragma unroll
-      for (int st = 0; st < SUBS; ++st) other[st] = __shfl_xor(part[st], 32);
-#pragma unroll
-      for (int st = 0; st < SUBS; ++st) {
-        const int t = w0 + 16 * st + c16;
-        if (g == 0 && st < cur.nst) imp[wave][16 * st + c16] = (t < w1) ? (part[st] + other[st]) * inv_alpha : 0.f;
-      }
+      for (int k = 0; k < 2; ++k) imp[wave][32 * g + 16 * k + c16] = swap_add16(part[k], part[k + 2]) * inv_alpha;
     }
     // imp[wave] is written and read by this wave only: no barrier
     const int p_start = n_tok - min(a.protect, n_tok);
     const int64_t tok_col = (int64_t)lh * a.total_tokens + cur.tok0;
-    {  // sentence means: 4 lanes per sentence, wave w takes the sentences of span w
+    {  // sentence means: 4, 8 or 16 lanes per sentence, wave w takes the sentences of span w
       static_assert(kSpanMaxSent * 4 <= 64, "4 lanes per sentence of a span");
       const int tl = opaque(lane);
-      const int s_idx = tl >> 2, part = tl & 3;
+      const int shift = ns > 8 ? 2 : (ns > 4 ? 3 : 4), lanes = 1 << shift;
+      const int s_idx = tl >> shift, part = tl & (lanes - 1);
       const bool valid = s_idx < ns;
       float sum_i = 0.f, sum_r = 0.f;
       int lo = 0, hi = 0;
       if (valid) {
         lo = soff[cur.sb + s_idx];
         hi = min(soff[cur.sb + s_idx + 1], p_start);
-        for (int t = lo + part; t < hi; t += 4) {
+        for (int t = lo + part; t < hi; t += lanes) {
           sum_i += imp[wave][t - w0];
           if (a.tok_red) sum_r += a.tok_red[tok_col + t];
         }
       }
-      sum_i += __shfl_xor(sum_i, 1);
-      sum_r += __shfl_xor(sum_r, 1);
-      sum_i += __shfl_xor(sum_i, 2);
-      sum_r += __shfl_xor(sum_r, 2);
+      auto over_lanes = [&](float v) {
+        v = plus_dpp<0xB1>(v);
+        v = plus_dpp<0x4E>(v);
+        const float v8 = plus_dpp<0x141>(v), v16 = plus_dpp<0x128>(v8);
+        return shift == 2 ? v : (shift == 3 ? v8 : v16);
+      };
+      sum_i = over_lanes(sum_i);
+      if (a.tok_red) sum_r = over_lanes(sum_r);
       if (valid && part == 0) {
         const int64_t o = (int64_t)lh * a.total_sentences + (cur.soff_idx - b) + cur.sb + s_idx;
         const float inv = hi > lo ? 1.f / (float)(hi - lo) : 0.f;
@@ -691,18 +783,18 @@ __global__ void __launch_bounds__(256, (DT == SKIPKV_BF16 ? 2 : 1)) k_scan_fused
   }
 }
 
-template <int DT, int NP, int AL>
+template <int DT, int NP, int AL, bool PAGED>
 hipError_t launch_one(const ScanArgs &a, hipStream_t st) {
   int dev = 0, cus = 0, per_cu = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;
   e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
   if (e != hipSuccess) return e;
-  e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_scan_fused<DT, NP, AL>, 256, 0);
+  e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_scan_fused<DT, NP, AL, PAGED>, 256, 0);
   if (e != hipSuccess) return e;
   const int grid = cus * per_cu;  // persistent: every workgroup is resident at once
   if (grid < kFuseMaxItems) return hipErrorInvalidConfiguration;
-  hipLaunchKernelGGL((k_scan_fused<DT, NP, AL>), dim3(grid), dim3(256), 0, st, a);
+  hipLaunchKernelGGL((k_scan_fused<DT, NP, AL, PAGED>), dim3(grid), dim3(256), 0, st, a);
   return hipGetLastError();
 }
 
@@ -714,10 +806,11 @@ bool scan_fused_supported(const RowLayout &rl, int64_t row_pitch_bytes) {
 
 hipError_t launch_scan_fused(const ScanArgs &a, hipStream_t st) {
   if ((int64_t)a.n_layers * a.n_kv_heads * a.batch == 0 || a.force_two_pass) return hipSuccess;
-#define SKIPKV_CASE(NP_, AL_)                                                \
-  if (a.rl.np == NP_ && a.rl.al == AL_)                                      \
-    return a.dtype == SKIPKV_BF16 ? launch_one<SKIPKV_BF16, NP_, AL_>(a, st) \
-                                  : launch_one<SKIPKV_F32, NP_, AL_>(a, st);
+#define SKIPKV_CASE(NP_, AL_)                                                                                                            \
+  if (a.rl.np == NP_ && a.rl.al == AL_) {                                                                                                \
+    if (a.dtype == SKIPKV_BF16) return a.row_map ? launch_one<SKIPKV_BF16, NP_, AL_, true>(a, st) : launch_one<SKIPKV_BF16, NP_, AL_, false>(a, st); \
+    return a.row_map ? launch_one<SKIPKV_F32, NP_, AL_, true>(a, st) : launch_one<SKIPKV_F32, NP_, AL_, false>(a, st);                    \
+  }
   SKIPKV_CASE(4, 2)
   SKIPKV_CASE(4, 4)
   SKIPKV_CASE(7, 2)
