@@ -142,7 +142,7 @@ int skipkv_workspace_bytes(const skipkv_cache *cache, const skipkv_params *param
  * sent_score, sent_lambda   device out [n_layers, n_kv_heads, total_sentences] fp32.
  * tok_importance  device out [n_layers, n_kv_heads, total_tokens] fp32, or NULL.
  * The key scan reads K once where it can (query rows n * obs_window <= 64 after padding, no
- * sentence longer than 128 tokens, at most 256 work items of up to 512 tokens per sequence, i.e.
+ * sentence longer than 512 tokens, at most 256 work items of up to 512 tokens per sequence, i.e.
  * about 120000 tokens) and twice otherwise.  Its single-pass form is a persistent grid that must
  * have the GPU's compute units to itself (work of other streams running at the same time can
  * only be waited out).  It waits across workgroups; the wait is bounded (params->spin_limit): on

@@ -14,8 +14,9 @@ constexpr int kChunkMaxSent = 32;    // ... and at most this many sentences (a s
 constexpr int kMaxRunChunks = 16;    // chunks that a workgroup of the bf16 two-pass scan takes at a time, at most
 // Units of the single-pass scan (scan_fused.hip): a span is a maximal run of whole sentences of at most
 // kSpanCap tokens and kSpanMaxSent sentences, the share of ONE wave; an item is up to kItemSpans
-// consecutive spans of one sequence, the share of one workgroup.  A sequence with a sentence longer than
-// kSpanCap tokens, or with more than kFuseMaxItems items, takes the two-pass scan.
+// consecutive spans of one sequence, the share of one workgroup.  A longer sentence is cut into spans of kSpanCap tokens
+// (and a last one) within one item.  A sequence with a sentence of more than kItemSpans spans, or with more than
+// kFuseMaxItems items, takes the two-pass scan.
 constexpr int kSpanCap = 128;
 constexpr int kSpanMaxSent = 16;
 constexpr int kItemSpans = 4;
@@ -46,7 +47,7 @@ struct RowBlock {
 constexpr int kItemRecInts = 16;
 enum ItemRec : int {
   kIrB = 0,        // sequence
-  kIrNsp,          // spans in the item: 1..kItemSpans; 0 = the sequence takes the two-pass scan
+  kIrNsp,          // spans in the item: 1..kItemSpans, plus kIrCut if some sentence has several of them
   kIrRec,          // index of the item (its statistics record is filed there)
   kIrTok0,         // first token of the sequence in the packed cache
   kIrNTok,         // tokens of the sequence
@@ -54,8 +55,9 @@ enum ItemRec : int {
   kIrFirst,        // index of the sequence's first item
   kIrSoffIdx,      // index of the item's first sentence offset in sent_off
   kIrT0,           // kIrT0 + w: first token of span w, relative to the sequence; kIrT0 + nsp: end of the item
-  kIrNs = kIrT0 + kItemSpans + 1,  // sentences of the four spans, one byte each
+  kIrNs = kIrT0 + kItemSpans + 1,  // sentences of the four spans, one byte each (a sentence of several spans counts in the first one)
 };
+constexpr int kIrCut = 8;
 static_assert(kIrNs < kItemRecInts && kSpanMaxSent < 256, "the record holds the spans' bounds and sentence counts");
 
 // Device scalars at the head of the workspace.

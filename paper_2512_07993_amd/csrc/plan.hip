@@ -31,7 +31,7 @@ __device__ __forceinline__ int run_end(const int *off, int start, int n_sent, in
 
 // Plans of sequences: WPS waves each, 4 / WPS sequences per block.  Chunks (two-pass scan) and spans (single-pass
 // scan) are packed greedily: the longest run of whole sentences within the unit's token and sentence limits; a sentence
-// longer than the token limit is a unit of its own (a span like that sends its sequence to the two-pass scan).
+// longer than the token limit is a chunk of its own and as many spans as it needs.
 //
 // What bounds a plan: with few sequences the latency of the serial walks along the runs (an LDS read per step, 300 spans
 // in 32 K tokens), so the two walks run side by side; with thousands of them (every head a sequence of its own) the
@@ -50,8 +50,11 @@ struct PlanShared {
   // what is replaced has been read.
   uint16_t chunk[SKIPKV_MAX_SENTENCES + 1];
   uint16_t span[SKIPKV_MAX_SENTENCES + 1];
+  // The spans of a sequence with sentences of several spans: first sentence, number of the piece of it << 13.  (A span
+  // that is only there so that the pieces of a sentence come to lie in one item is empty: it begins where the next one does.)
+  uint16_t pieces[kItemSpans * kFuseMaxItems + 4];
   struct Seq {
-    int n_chunks, n_spans, fused;
+    int n_chunks, n_spans;
     unsigned long long counts, old;  // of the sequence, and drawn before it (packed as in the header)
   } seq[4];
 };
@@ -67,6 +70,8 @@ __device__ __forceinline__ void plan_sequences(const PlanArgs &a, PlanShared &sh
   static_assert(SKIPKV_MAX_SENTENCES <= 65535, "sentence indices are kept in 16 bits here");
   int *s_off = sh.off + grp * PART;
   uint16_t *s_chunk = sh.chunk + grp * PART, *s_span = sh.span + grp * PART;
+  constexpr int kPieces = kItemSpans * kFuseMaxItems / (4 / WPS);  // spans of a sequence that the group's part of the table holds
+  uint16_t *s_pieces = sh.pieces + grp * (kPieces + 1);
   auto any = [](bool x) -> bool { return WPS == 4 ? __syncthreads_or(x) != 0 : __any(x) != 0; };
   auto sync = [] {
     if constexpr (WPS == 4) __syncthreads();
@@ -74,6 +79,7 @@ __device__ __forceinline__ void plan_sequences(const PlanArgs &a, PlanShared &sh
   };
 
   int tok0 = 0, n_tok = 0, sp = 0, n_sent = 0;
+  bool cut = false;  // some sentence has several spans
   bool ok = b >= 0;
   if (ok) {
     tok0 = a.seq_off[b];
@@ -100,6 +106,7 @@ __device__ __forceinline__ void plan_sequences(const PlanArgs &a, PlanShared &sh
     }
     bad = any(bad);
     longer = any(longer);
+    cut = longer;
     ok = !reject && !bad;
     for (int lh = gt; lh < a.n_lh; lh += G) a.ws.head_redo[(int64_t)lh * a.batch + b] = 0;
     sync();
@@ -119,12 +126,28 @@ __device__ __forceinline__ void plan_sequences(const PlanArgs &a, PlanShared &sh
     if (ok && (gt == 0 || gt == kOther)) {
       uint16_t *at = gt == 0 ? s_span : s_chunk;
       int n = 0;
-      for (int start = 0; start < n_sent;) {
-        const int e = at[start];
-        at[n++] = (uint16_t)start;
-        start = e;
+      if (gt == 0 && longer) {
+        // (no sequence gets more items than its tokens and sentences make of ordinary spans at most: that is what there is room for)
+        const int most = min(kPieces, kItemSpans * ((2 * (n_tok / a.ws.span_cap + n_sent / kSpanMaxSent) + 1) / kItemSpans + 1));
+        bool fits = true;
+        for (int start = 0; start < n_sent && fits;) {
+          const int p = max(1, (s_off[start + 1] - s_off[start] + kSpanCap - 1) / kSpanCap);
+          while (p <= kItemSpans && n % kItemSpans + p > kItemSpans && n < most) s_pieces[n++] = (uint16_t)start;
+          fits = p <= kItemSpans && n + p <= most;
+          for (int k = 0; k < p && fits; ++k) s_pieces[n++] = (uint16_t)(start | k << 13);
+          start = at[start];
+        }
+        if (fits) s_pieces[n] = (uint16_t)n_sent;
+        else n = 0;  // the two-pass scan's
+      } else {
+        for (int start = 0; start < n_sent;) {
+          const int e = at[start];
+          at[n++] = (uint16_t)start;
+          start = e;
+        }
+        at[n] = (uint16_t)n_sent;
+        if (gt == 0 && n > kItemSpans * kFuseMaxItems) n = 0;
       }
-      at[n] = (uint16_t)n_sent;
       if (gt == 0) me.n_spans = n;
       else me.n_chunks = n;
     }
@@ -135,7 +158,6 @@ __device__ __forceinline__ void plan_sequences(const PlanArgs &a, PlanShared &sh
         const int n_items = (me.n_spans + kItemSpans - 1) / kItemSpans, nrb = (n_sent + kRowBlock - 1) / kRowBlock;
         const int rc = a.ws.run_chunks;  // whole runs: the sequence's chunks start at a multiple of their length
         counts = (unsigned long long)((me.n_chunks + rc - 1) / rc * rc) | ((unsigned long long)n_items << kHdrItemShift) | ((unsigned long long)nrb << kHdrRbShift);
-        me.fused = !longer && n_items <= kFuseMaxItems;
       } else if (a.dev_status) {
         atomicOr(a.dev_status, reject ? SKIPKV_DEV_TOO_MANY_SENT : SKIPKV_DEV_BAD_OFFSETS);
       }
@@ -153,7 +175,7 @@ __device__ __forceinline__ void plan_sequences(const PlanArgs &a, PlanShared &sh
     unsigned long long old = 0;
     if (a.alone) {
       a.ws.hdr->ranges = sum;
-      a.ws.hdr->n_unfused = sum != 0 && !sh.seq[0].fused && sh.seq[0].n_chunks > 0;
+      a.ws.hdr->n_unfused = sum != 0 && sh.seq[0].n_spans == 0 && sh.seq[0].n_chunks > 0;
       a.ws.hdr->abort = 0;
     } else if (sum) {
       old = atomicAdd(&a.ws.hdr->ranges, sum);
@@ -178,7 +200,8 @@ __device__ __forceinline__ void plan_sequences(const PlanArgs &a, PlanShared &sh
   }
   const PlanShared::Seq &me = sh.seq[grp];
   const int n_chunks = me.n_chunks, n_spans = me.n_spans, n_items = (n_spans + kItemSpans - 1) / kItemSpans;
-  const int base = hdr_chunks(me.old), ibase = hdr_items(me.old), rb0 = hdr_rowblocks(me.old), fused = me.fused;
+  const int base = hdr_chunks(me.old), ibase = hdr_items(me.old), rb0 = hdr_rowblocks(me.old);
+  const bool fused = n_spans > 0 || n_chunks == 0;
   const int nrb = hdr_rowblocks(me.counts);
   if (gt == 0) {
     a.ws.chunk_base[b] = base;
@@ -196,21 +219,27 @@ __device__ __forceinline__ void plan_sequences(const PlanArgs &a, PlanShared &sh
   for (int j = gt; j < n_items; j += G) {  // one record per item: up to kItemSpans consecutive spans
     const int nsp = min(kItemSpans, n_spans - kItemSpans * j);
     int32_t *r = a.ws.item_rec + (int64_t)(ibase + j) * kItemRecInts;
-    const int s0 = s_span[kItemSpans * j];
+    const uint16_t *at = (cut ? s_pieces : s_span) + kItemSpans * j;  // sentence, piece << 13 (s_span has no pieces)
+    const int s0 = at[0] & 0x1FFF;
     r[kIrB] = b;
-    r[kIrNsp] = fused ? nsp : 0;
     r[kIrRec] = ibase + j;
     r[kIrTok0] = tok0;
     r[kIrNTok] = n_tok;
     r[kIrNItems] = n_items;
     r[kIrFirst] = ibase;
     r[kIrSoffIdx] = sp + s0;
-    uint32_t ns = 0;
+    uint32_t ns = 0, pieces = 0;
     for (int w = 0; w <= kItemSpans; ++w) {
-      const int sw = s_span[kItemSpans * j + min(w, nsp)];
-      r[kIrT0 + w] = s_off[sw];
-      if (w < nsp) ns |= (uint32_t)(s_span[kItemSpans * j + w + 1] - sw) << (8 * w);
+      const int x = at[min(w, nsp)], sw = x & 0x1FFF, piece = x >> 13;
+      r[kIrT0 + w] = s_off[sw] + kSpanCap * piece;
+      if (w < nsp) {
+        // sentences that begin here; the next span may begin within the one that this one begins with
+        const int y = at[w + 1], next = (y & 0x1FFF) + (y >> 13 ? 1 : 0);
+        if (piece == 0) ns |= (uint32_t)(next - sw) << (8 * w);
+        pieces |= piece;
+      }
     }
+    r[kIrNsp] = nsp | (pieces ? kIrCut : 0);
     r[kIrNs] = (int32_t)ns;
   }
   if (a.preset) {

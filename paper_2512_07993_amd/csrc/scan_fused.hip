@@ -16,6 +16,12 @@
 // w, w + G, ...  The four waves only meet at two barriers per item: statistics ready -> the
 // head's normalisers ready.
 //
+// A sentence of more than 128 tokens (a table, a formula, code) is the exception: it has up to four spans of one item, alone in
+// each; the waves that go on with it leave their key sums in LDS before the first barrier, the wave of its first span adds them
+// up, and after the second phase, behind one more barrier, it sums the importance over their tokens too.  One such sentence used
+// to send its whole sequence to the two-pass scan: 32 layers x 8 heads, 4 sequences of 3-9 K tokens, 1 % of the
+// sentences longer: 735 us for its passes -> 477 here.
+//
 // Per stage a wave issues, besides the loads, three blocks of work:
 //   logits      16 v_mfma_f32_16x16x32_bf16 of the stage's key rows against the query tile in LDS;
 //   statistics  one exponential per logit relative to ONE reference per lane group, fixed after the
@@ -139,6 +145,8 @@ struct Item {  // one item as seen by one wave
   const char *kbase;
   int w0, w1, nst;  // the wave's span: token range (relative to the sequence) and number of stages
   int ns, sb;       // ... its sentences: count, and index of the first one among the item's sentences
+  bool cut;         // some sentence of the item has several spans ...
+  bool goes_on;     // ... and this wave's span is not the first one of its (only) sentence
 };
 
 template <int DT, int NP, int AL, bool PAGED>
@@ -167,7 +175,8 @@ __global__ void __launch_bounds__(256, (DT == SKIPKV_BF16 ? 2 : 1)) k_scan_fused
   __shared__ int soff_buf[2][2 * 64];            // [item parity]: offsets of the item's sentences (64 per direct load; the last one repeated)
   __shared__ __align__(16) float wstat[4][R][2];               // (reference, sum) of every row over each wave's span
   __shared__ float mstat[4][R][2];               // (reference, sum) of every row over each wave's quarter of the head's records
-  __shared__ float imp[4][kSpanCap];             // token importance of each wave's span (private to the wave)
+  __shared__ float imp[4][kSpanCap];             // token importance of each wave's span (private to the wave unless a sentence goes on in the next one)
+  __shared__ float more_sum[4][kD];              // key sum of a span that goes on with the sentence of the one before
   __shared__ __align__(16) float row_norm_l[4][R];  // every wave's own copy of the head's normalisers (+inf: padding row)
   __shared__ int s_timeout[2];  // [item parity] a wait of the item ran out: its sentences get NaN means
 
@@ -190,13 +199,13 @@ __global__ void __launch_bounds__(256, (DT == SKIPKV_BF16 ? 2 : 1)) k_scan_fused
   // batch and KV heads that the query rows are laid out by (the real ones under per-head ranges)
   const int q_batch = a.virt_hk > 0 ? a.virt_b : a.batch, q_heads = a.virt_hk > 0 ? a.virt_hk : a.n_kv_heads;
   const Divisor by_q_heads(q_heads);
-  auto load_item = [&](uint32_t item) -> Item {  // first fused item at or after `item` in this workgroup's sequence
+  auto load_item = [&](uint32_t item) -> Item {
     Item it{};
-    for (; item < n_items; item += gridDim.x) {
+    if (item < n_items) {
       const uint32_t lh = by_items.div(item);
       const ConstIntPtr r = item_rec_c + (int64_t)(item - lh * n_per_lh) * kItemRecInts;
-      const int nsp = r[kIrNsp];
-      if (nsp == 0) continue;  // the sequence takes the two-pass scan
+      const int nsp = r[kIrNsp] & ~kIrCut;
+      it.cut = (r[kIrNsp] & kIrCut) != 0;
       it.lh = (int)lh;
       it.b = r[kIrB];
       it.nsp = nsp;
@@ -218,7 +227,11 @@ __global__ void __launch_bounds__(256, (DT == SKIPKV_BF16 ? 2 : 1)) k_scan_fused
       // contiguous cache: first row of the sequence; paged cache: the head's base, rows come from the row map
       it.kbase = static_cast<const char *>(a.k) +
                  ((int64_t)l * a.stride_layer + (int64_t)h * a.stride_head + (PAGED ? 0 : (int64_t)it.tok0 * a.stride_tok)) * ESZ;
-      break;
+      it.goes_on = it.cut && it.ns == 0 && it.nst > 0;
+      if (it.goes_on) {
+        it.ns = 1;
+        it.sb -= 1;
+      }
     }
     it.item = item;
     return it;
@@ -381,6 +394,7 @@ __global__ void __launch_bounds__(256, (DT == SKIPKV_BF16 ? 2 : 1)) k_scan_fused
   while (cur.item < n_items) {
     const int lh = cur.lh, b = cur.b;
     const int n_tok = cur.n_tok;
+    const int ns_own = cur.goes_on ? 0 : cur.ns;  // sentences that the wave completes: those that begin in its span
     const int last_free = n_tok - a.alpha;  // keys t <= last_free are visible to every window query
     const int *soff = soff_buf[par];
     const int w0 = cur.w0, w1 = cur.w1, ns = cur.ns;
@@ -586,6 +600,13 @@ __global__ void __launch_bounds__(256, (DT == SKIPKV_BF16 ? 2 : 1)) k_scan_fused
       *reinterpret_cast<float2 *>(wstat[wave][my_row]) = rec;
     }
     issued = issued_next;
+    if (cur.goes_on) {  // row 0 of the key sums is the sentence
+      const int ln = opaque(lane);
+      if (ln < 16) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) more_sum[wave][16 * j + ln] = pool[j][0];
+      }
+    }
     // the next item's queries and offsets: fetched now, committed before the second barrier below (bf16: behind this one)
     [[maybe_unused]] QFetch nq;
     if constexpr (DT == SKIPKV_F32) nq = q_fetch(nxt);
@@ -624,7 +645,16 @@ __global__ void __launch_bounds__(256, (DT == SKIPKV_BF16 ? 2 : 1)) k_scan_fused
     load_records(wave);
 
     // ---- sentence embeddings of the span: unit vectors as bf16 hi + lo, four sentences at a time
-    if (!a.no_pool && ns > 0) {
+    if (!a.no_pool && ns_own > 0) {
+      if (cur.cut) {  // the sums of the spans that the wave's sentence goes on in (it is alone in its span then)
+        const int spans = (soff[cur.sb + 1] - soff[cur.sb] + kSpanCap - 1) / kSpanCap;
+        const int oc = opaque(c16);
+        for (int w = 1; w < spans; ++w) {
+#pragma unroll
+          for (int j = 0; j < 8; ++j) pool[j][0] += more_sum[(wave + w) & 3][16 * j + oc];
+        }
+      }
+      bool not_finite = false;
       // (addresses are formed here, from an opaque copy: formed early they are spilled, and a reload from
       // scratch waits for every load in flight, the record loads above included)
       const int64_t col0 = (int64_t)lh * a.total_sentences + opaque(cur.soff_idx - b + cur.sb);
@@ -650,10 +680,37 @@ __global__ void __launch_bounds__(256, (DT == SKIPKV_BF16 ? 2 : 1)) k_scan_fused
           hi[j] = pack_bf16x2(u0, u1);  // round to nearest even, both halves in one instruction
           lo[j] = pack_bf16x2(u0 - __uint_as_float(hi[j] << 16), u1 - __uint_as_float(hi[j] & 0xFFFF0000u));
         }
+        not_finite = not_finite || (slot < ns && !(ss < INFINITY));
         if (slot < ns) {
           const int64_t o = (col0 + slot) * (kD / 8) + opaque(c16);  // in 16-byte units
           reinterpret_cast<uint4 *>(a.ws.vhat_hi)[o] = make_uint4(hi[0], hi[1], hi[2], hi[3]);
           reinterpret_cast<uint4 *>(a.ws.vhat_lo)[o] = make_uint4(lo[0], lo[1], lo[2], lo[3]);
+        }
+      }
+      if (__any(not_finite)) {
+        // An infinite or NaN key: 0 times it is NaN, so the products have carried it into other sentences of its stage.  The
+        // span's embeddings are formed again from each sentence's own rows: lane l has positions 2l and 2l + 1.
+        const int ln = opaque(lane), d0 = 16 * ((2 * ln) & 7) + (ln >> 2);
+        for (int s = 0; s < ns_own; ++s) {
+          const int t0 = soff[cur.sb + s], t1 = soff[cur.sb + s + 1];
+          float s0 = 0.f, s1 = 0.f;
+          for (int t = t0; t < t1; ++t) {
+            const char *key = cur.kbase + (PAGED ? (int64_t)row_map_c[cur.tok0 + t] * (a.map_stride * ESZ) : (int64_t)t * tok_pitch) + d0 * ESZ;
+            if constexpr (DT == SKIPKV_BF16) {
+              s0 += bf16_bits_to_f32(*reinterpret_cast<const uint16_t *>(key));
+              s1 += bf16_bits_to_f32(*reinterpret_cast<const uint16_t *>(key + 16 * ESZ));
+            } else {
+              s0 += *reinterpret_cast<const float *>(key);
+              s1 += *reinterpret_cast<const float *>(key + 16 * ESZ);
+            }
+          }
+          const float scale = 1.f / (float)(t1 - t0), m0 = s0 * scale, m1 = s1 * scale;
+          const float inv = 1.f / (sqrtf(wave_sum(fmaf(m0, m0, m1 * m1))) + 1e-12f);
+          const uint32_t hi = pack_bf16x2(m0 * inv, m1 * inv);
+          const uint32_t lo = pack_bf16x2(m0 * inv - __uint_as_float(hi << 16), m1 * inv - __uint_as_float(hi & 0xFFFF0000u));
+          const int64_t o = (col0 + s) * (kD / 2) + ln;
+          reinterpret_cast<uint32_t *>(a.ws.vhat_hi)[o] = hi;
+          reinterpret_cast<uint32_t *>(a.ws.vhat_lo)[o] = lo;
         }
       }
     }
@@ -732,27 +789,29 @@ __global__ void __launch_bounds__(256, (DT == SKIPKV_BF16 ? 2 : 1)) k_scan_fused
       // The four lane groups hold the four quarters of the window; summing halves the stages that a group looks after, twice:
       // group g ends up with stages 2g and 2g + 1.  (Masked tokens have contributed 0.)
       static_assert(SUBS == 8, "two stages for each lane group");
+      const int ol = opaque(lane);
 #pragma unroll
       for (int k = 0; k < 4; ++k) part[k] = swap_add32(part[k], part[k + 4]);
 #pragma unroll
-      for (int k = 0; k < 2; ++k) imp[wave][32 * g + 16 * k + c16] = swap_add16(part[k], part[k + 2]) * inv_alpha;
+      for (int k = 0; k < 2; ++k) imp[wave][(ol & 48) * 2 + 16 * k + (ol & 15)] = swap_add16(part[k], part[k + 2]) * inv_alpha;
     }
-    // imp[wave] is written and read by this wave only: no barrier
+    // imp[wave] is written and read by this wave only: no barrier, unless one of the item's sentences has several spans
+    if (cur.cut) lds_barrier();
     const int p_start = n_tok - min(a.protect, n_tok);
     const int64_t tok_col = (int64_t)lh * a.total_tokens + cur.tok0;
     {  // sentence means: 4, 8 or 16 lanes per sentence, wave w takes the sentences of span w
       static_assert(kSpanMaxSent * 4 <= 64, "4 lanes per sentence of a span");
       const int tl = opaque(lane);
-      const int shift = ns > 8 ? 2 : (ns > 4 ? 3 : 4), lanes = 1 << shift;
+      const int shift = ns_own > 8 ? 2 : (ns_own > 4 ? 3 : 4), lanes = 1 << shift;
       const int s_idx = tl >> shift, part = tl & (lanes - 1);
-      const bool valid = s_idx < ns;
+      const bool valid = s_idx < ns_own;
       float sum_i = 0.f, sum_r = 0.f;
       int lo = 0, hi = 0;
       if (valid) {
         lo = soff[cur.sb + s_idx];
         hi = min(soff[cur.sb + s_idx + 1], p_start);
         for (int t = lo + part; t < hi; t += lanes) {
-          sum_i += imp[wave][t - w0];
+          sum_i += (&imp[wave][0])[t - w0];  // (a sentence of several spans: on into the next waves' parts, whole but the last)
           if (a.tok_red) sum_r += a.tok_red[tok_col + t];
         }
       }

@@ -48,3 +48,71 @@ def test_spans_of_every_shape(dtype, group, alpha):
     lam = torch.isfinite(two.sent_lambda)
     assert torch.equal(torch.isfinite(out.sent_lambda), lam)
     assert torch.allclose(out.sent_lambda[lam], two.sent_lambda[lam], rtol=0, atol=1e-5)
+
+
+def _cut_offsets():
+    """Sentences of several spans: every length around a span's edge, at every place within an item, alone, side by side,
+    first, last and with others too short for a stage between them."""
+    seqs = []
+    for n in (128, 129, 255, 256, 257, 384, 385, 511, 512):
+        seqs.append([0, n])
+        seqs.append([0, 40, 40 + n, 43 + n])
+    seqs.append([0, 300, 600, 900, 901, 1413, 1500])
+    seqs.append([0, 100, 200, 300, 812, 830])                      # three spans, then one that needs a whole item
+    off, rng = [0], np.random.default_rng(8)
+    while off[-1] < 6000:
+        off.append(off[-1] + int(rng.choice([5, 17, 31, 60, 129, 200, 333, 400, 512], p=[.2, .2, .2, .2, .05, .05, .05, .025, .025])))
+    seqs.append(off)
+    seqs.append([0, 20, 533, 600])                                 # 513 tokens: the two-pass scan's
+    return seqs
+
+
+@pytest.mark.parametrize("dtype,group,alpha", [("bf16", 4, 16), ("bf16", 7, 8), ("bf16", 2, 5), ("f32", 4, 8)])
+def test_sentences_of_several_spans(dtype, group, alpha):
+    st = _structure(_cut_offsets())
+    cfg = W.Config("cut", 7, len(st.seq_len), 3, 2, 2 * group, dtype, 0, 0, 700, alpha, 40, 20.0, 0.0)
+    k0, v0, q = _random_kvq(cfg, st, 6)
+    k, v = k0.clone(), v0.clone()
+    red = torch.rand((3, 2, st.total_tokens), device="cuda")
+    out = run_step(cfg, st, k, v, q, red=red)
+    assert int(out.dev_status.item()) == 0
+    stats = {}
+    for l in range(3):
+        for b in range(cfg.batch):
+            compare_head(cfg, st, out, k, v, k0, v0, oracle_head(cfg, st, k0, v0, q, l, 1, b, red=red), l, 1, b, stats)
+
+
+def test_more_cut_sentences_than_there_is_room_for_items_take_the_two_pass_scan():
+    # one token, then 385: eight spans for 386 tokens, where there is room for six
+    off = [0]
+    while off[-1] < 7000:
+        off += [off[-1] + 1, off[-1] + 386]
+    st = _structure([off, [0, 10, 395, 400]])
+    cfg = W.Config("room", 7, 2, 2, 1, 4, "bf16", 0, 0, 700, 16, 40, 20.0, 0.0)
+    k0, v0, q = _random_kvq(cfg, st, 7)
+    k, v = k0.clone(), v0.clone()
+    out = run_step(cfg, st, k, v, q)
+    for b in range(2):
+        compare_head(cfg, st, out, k, v, k0, v0, oracle_head(cfg, st, k0, v0, q, 1, 0, b), 1, 0, b, {})
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("token", [5, 40, 130, 355, 390, 560])
+def test_an_infinite_key_stays_in_its_sentence(dtype, token):
+    import oracle
+    off = [0, 9, 30, 50, 350, 360, 391, 400, 640, 700]
+    st = _structure([off])
+    cfg = W.Config("inf", 7, 1, 1, 1, 4, dtype, 0, 0, 700, 8, 40, 20.0, 0.0)
+    k, v, q = _random_kvq(cfg, st, 8)
+    q[..., 5] = 1.0
+    k[0, 0, token, 5] = float("-inf")  # every query scores it -inf: weight 0
+    out = run_step(cfg, st, k.clone(), v, q)
+    x = k[0, 0].double().cpu().numpy()
+    x[token, 5] = -1e30
+    imp = oracle.token_importance(q[0, 0].double().cpu().numpy(), x)
+    np.testing.assert_allclose(out.tok_imp[0, 0].cpu().numpy(), imp, rtol=1e-3, atol=1e-12)
+    bad = int(np.searchsorted(off, token, side="right")) - 1
+    good = [s for s in range(len(off) - 1) if s != bad]
+    want = oracle.sentence_redundancy(oracle.sentence_embeddings(x, np.asarray(off))[good])
+    lam = out.sent_lambda[0, 0].cpu().numpy()
+    np.testing.assert_allclose(lam[good][:-1], want[:-1], rtol=1e-3, atol=1e-5)
