@@ -6,11 +6,26 @@
 // loads of a tile are complete before its first store, and everything a later tile reads lies
 // behind everything already written, so no row is overwritten before it has been read.  The
 // leading rows with kept_idx[k] == k are not touched at all.
+//
+// What bounds it is memory: 5.7 TB/s read and written on large caches.
 #include "common.h"
 
 namespace skipkv {
 
 namespace {
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+// 16 bytes that nobody comes back to soon (STREAM), or ordinary ones.
+template <bool STREAM>
+__device__ __forceinline__ u32x4 load16(const char *p) {
+  if constexpr (STREAM) return __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(p));
+  return *reinterpret_cast<const u32x4 *>(p);
+}
+template <bool STREAM>
+__device__ __forceinline__ void store16(char *p, u32x4 x) {
+  if constexpr (STREAM) __builtin_nontemporal_store(x, reinterpret_cast<u32x4 *>(p));
+  else *reinterpret_cast<u32x4 *>(p) = x;
+}
 
 // Paged cache (PAGED): rows live in block slots.  Sources come pre-translated (src_rows: slot row of
 // kept_idx[k], written by k_kept_rows below), destinations are read from the row map one coalesced
@@ -20,7 +35,7 @@ namespace {
 // SL: bytes of a row that a wave moves.  The argument above holds for every byte column of a stream by
 // itself, so a stream may be split into ROWB / SL waves that know nothing of each other; launch_compact
 // says when.
-template <int ROWB, int SL, bool PAGED>
+template <int ROWB, int SL, bool PAGED, bool STREAM>
 __global__ void __launch_bounds__(256) k_compact(CompactArgs a) {
   constexpr int NS = ROWB / SL;    // waves per stream
   constexpr int PPR = SL / 16;     // 16-byte pieces per row slice
@@ -81,16 +96,16 @@ __global__ void __launch_bounds__(256) k_compact(CompactArgs a) {
   // loop end up in scratch memory with this compiler.
   static_assert(U == 8, "the tiles below are spelled out for 8 instructions");
 #define SKIPKV_EACH(X, T) X(T, 0) X(T, 1) X(T, 2) X(T, 3) X(T, 4) X(T, 5) X(T, 6) X(T, 7)
-#define SKIPKV_DECL(T, u) uint4 T##u;
+#define SKIPKV_DECL(T, u) u32x4 T##u;
   // always U loads per tile: rows past the end re-read the last kept row (index loads are clamped)
 #define SKIPKV_LOAD(T, u) \
-  T##u = *reinterpret_cast<const uint4 *>(base + (int64_t)__shfl(NI == 2 && u >= 4 ? idx2_##T : idx_##T, (u * RPI + sub) & 63) * pitch + piece * 16);
+  T##u = load16<STREAM>(base + (int64_t)__shfl(NI == 2 && u >= 4 ? idx2_##T : idx_##T, (u * RPI + sub) & 63) * pitch + piece * 16);
   // destination row of the lane's piece: position in the sequence, or (paged) its slot row; the shuffle
   // is taken by all lanes, outside any condition
 #define SKIPKV_DROW(T, u) const int64_t dr_##u = PAGED ? (int64_t)__shfl(NI == 2 && u >= 4 ? dst2_##T : dst_##T, (u * RPI + sub) & 63) : (int64_t)(ks + u * RPI + sub);
-#define SKIPKV_STORE(T, u) *reinterpret_cast<uint4 *>(base + dr_##u * pitch + piece * 16) = T##u;
+#define SKIPKV_STORE(T, u) store16<STREAM>(base + dr_##u * pitch + piece * 16, T##u);
 #define SKIPKV_STORE_TAIL(T, u) \
-  if (ks + u * RPI + sub < nl) *reinterpret_cast<uint4 *>(base + dr_##u * pitch + piece * 16) = T##u;
+  if (ks + u * RPI + sub < nl) store16<STREAM>(base + dr_##u * pitch + piece * 16, T##u);
 #define SKIPKV_STORE_TILE(T, K0)        \
   {                                     \
     const int ks = (K0);                \
@@ -157,13 +172,27 @@ __global__ void __launch_bounds__(256) k_kept_rows(CompactArgs a) {
   for (int k = lane; k < nl; k += 64) out[k] = rmap[max(0, min(kept[k], room - 1))];
 }
 
-template <int ROWB, int SL>
+template <int ROWB, int SL, bool STREAM>
 void launch_slices(const CompactArgs &a, int64_t streams, hipStream_t st) {
   const unsigned grid = (unsigned)((streams * (ROWB / SL) + 3) / 4);
   if (a.row_map)
-    hipLaunchKernelGGL((k_compact<ROWB, SL, true>), dim3(grid), dim3(256), 0, st, a);
+    hipLaunchKernelGGL((k_compact<ROWB, SL, true, STREAM>), dim3(grid), dim3(256), 0, st, a);
   else
-    hipLaunchKernelGGL((k_compact<ROWB, SL, false>), dim3(grid), dim3(256), 0, st, a);
+    hipLaunchKernelGGL((k_compact<ROWB, SL, false, STREAM>), dim3(grid), dim3(256), 0, st, a);
+}
+
+// Rows of large caches are read once and written once before anybody comes back to them: they are moved past the caches, and
+// displace neither each other nor what the next kernels need.  Small ones are found in the memory-side cache again by
+// what follows the call (the next call at the latest).  Whole call, us, ordinary / past the caches, by the rows' bytes in K and V:
+//   one sequence, 4096 rows kept:   16 MB 83 / 98   64 MB 92 / 119   128 MB 132 / 141   192 MB 153 / 153   256 MB 181 / 174
+//                                   512 MB 306 / 278
+//   per-head ranges, 1024 kept:     128 MB 109 / 106   512 MB 305 / 288   2 GB 1058 / 1015
+constexpr int64_t kStreamBytes = 192ll << 20;
+
+template <int ROWB, int SL>
+void launch_slices(const CompactArgs &a, int64_t streams, hipStream_t st) {
+  if (streams * a.kept_stride * ROWB > kStreamBytes) launch_slices<ROWB, SL, true>(a, streams, st);
+  else launch_slices<ROWB, SL, false>(a, streams, st);
 }
 
 }  // namespace
