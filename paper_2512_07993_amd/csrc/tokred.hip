@@ -14,19 +14,21 @@
 // Only the blocks at and right of the diagonal are computed.  One workgroup owns 256 rows (32 per
 // wave: the A operands stay in registers) and walks the 64-column blocks from its own rows to the
 // end of the sequence, staged through LDS and shared by the 8 waves; the next block is fetched
-// into registers while the current one is multiplied.  The 64 x 64 squares on the diagonal are
+// while the current one is multiplied.  The 64 x 64 squares on the diagonal are
 // computed in full and give row sums only; every block right of them gives e_ij both to row i
 // (weighted with column j's factor) and, by symmetry, to row j (weighted with row i's factor):
 // the column sums of a block are reduced over the workgroup's rows and added to the row's total.
 //
-// What bounds a sweep: vector instructions.  An entry costs a matrix instruction's 16 cycles for four, and per lane
-// two scale multiplies, an exponential (two issue slots) and two fmas; counters show the vector pipe issuing for
-// 62 % and the matrix pipe busy for 31 % of a SIMD's cycles, and the two hardly overlap.  So: 32 rows per wave in 125
-// registers, which lets four waves share a SIMD (64 rows took 237: two waves); one barrier per column block and two LDS
-// buffers; column sums of four column tiles reduced over the lane groups together (three permutes); squares of
-// 64 instead of 256 on the diagonal; and waves that can issue matrix instructions first.  32 layers x 8
-// heads, 4 x 2-4 K tokens: a sweep takes 1970 us (1800 on another box), with 64 rows per wave it took 2376 (without the priority 2030; with
-// branches between the column tiles, and their spills, 2190).
+// What bounds a sweep: vector instructions, and then power.  Per lane an entry costs two scale multiplies, an exponential (two
+// issue slots) and two fmas, and a matrix instruction's 16 cycles for four; counters show the vector pipe issuing for 75 % of a SIMD's
+// cycles (62 % when the products of a tile came before its exponentials instead of among those of the tile before: the two
+// hardly overlapped) and the matrix pipe busy for 36 %, at a clock that has come down from 2.25 to 2.13 GHz meanwhile.  So: the
+// products of a tile are issued among the vector instructions of the one before; 32 rows per wave in some 115 registers, which lets
+// four waves share a SIMD (64 rows took 237: two waves); column blocks go straight to LDS, their addresses a scalar base and one
+// offset per lane; one barrier per column block and two LDS buffers; column sums of four column tiles reduced over the lane
+// groups together (three permutes); squares of 64 instead of 256 on the diagonal.  32 layers x 8 heads, 4 x 2-4 K tokens:
+// the sweeps take 1640 + 1690 us (1780 + 1805 with the products first and addresses formed in 64 bits; 2376 each with 64 rows
+// per wave).
 // Totals are accumulated across workgroups as 64-bit FIXED-POINT integers (integer addition is
 // associative: the result does not depend on the order in which workgroups arrive, and the
 // conversion of an fp32 partial sum is exact at the chosen scale for all but negligible terms),
@@ -34,7 +36,7 @@
 #include <algorithm>
 #include <type_traits>
 
-#include "common.h"
+#include "scan_dev.h"
 
 namespace skipkv {
 
@@ -44,7 +46,7 @@ constexpr int kRows = kTokredRows;  // rows per workgroup
 constexpr int kWaves = 8;            // waves per workgroup
 constexpr int kTW = kRows / 16 / kWaves;  // 16-row tiles per wave
 constexpr int kCols = 64;            // columns per staged block
-constexpr int LSTR = 272;            // bytes per staged key row (256 + 16: 16-byte reads of 8 rows hit distinct banks)
+constexpr int kColB = kCols * 256;   // bytes per staged block
 constexpr float kSqrtLog2e = 1.2011224087864498f;
 // fixed-point scales of the two accumulations: row sums l <= e * N (2^40: room for N up to 2^21 tokens,
 // resolution 1e-12 against terms >= 0.37), and R <= e^2 / N... <= 8 (2^50: resolution 1e-15 against R ~ 1/N)
@@ -125,11 +127,12 @@ __device__ __forceinline__ float sum_lane_groups(float v0, float v1, float v2, f
 }
 
 // SWEEP 1: adds every row's sum of e_ij into acc (scale kFix1).  SWEEP 2: adds R (scale kFix2).
-template <int DT, int SWEEP>
+// SIMPLE: contiguous cache with a row pitch below 16 MB (32-bit offsets within a column block).
+template <int DT, int SWEEP, bool SIMPLE>
 __global__ void __launch_bounds__(64 * kWaves, 4) k_tokred_sweep(TokRedArgs a) {
   constexpr int ESZ = DT == SKIPKV_BF16 ? 2 : 4;
   constexpr float kFix = SWEEP == 1 ? kFix1 : kFix2;
-  __shared__ __align__(16) char cols[2][kCols * LSTR];
+  __shared__ __align__(256) char cols[2][kColB];  // rows of 256 bytes, swizzled (swz16)
   __shared__ float col_cw[2][2][kCols];  // of each staged column: scale factor; weight in a row's sum: 1 (sweep 1), 1 / l (sweep 2)
   __shared__ float cpart[2][kWaves][kCols];  // [block parity]: column sums of a block over each wave's rows
 
@@ -152,7 +155,7 @@ __global__ void __launch_bounds__(64 * kWaves, 4) k_tokred_sweep(TokRedArgs a) {
   if (r0 >= n_tok) return;
   const int l = lh / a.n_kv_heads, h = lh % a.n_kv_heads;
   // paged cache: rows are looked up in the row map (slot rows from the head's base), else they follow tok0
-  const int32_t *rmap = a.row_map ? a.row_map + tok0 : nullptr;
+  const int32_t *rmap = !SIMPLE && a.row_map ? a.row_map + tok0 : nullptr;
   const char *kbase = static_cast<const char *>(a.k) + ((int64_t)l * a.stride_layer + (int64_t)h * a.stride_head + (rmap ? 0 : (int64_t)tok0 * a.stride_tok)) * ESZ;
   const int64_t pitch = a.stride_tok * ESZ;
   auto slot_of = [&](int row) -> int64_t { return rmap ? (int64_t)rmap[row] : (int64_t)row; };
@@ -183,29 +186,47 @@ __global__ void __launch_bounds__(64 * kWaves, 4) k_tokred_sweep(TokRedArgs a) {
     for (int jj = 0; jj < 4; ++jj) rsum[t][jj] = 0.f;
   const float inv_n = SWEEP == 1 ? 1.f : 1.f / (float)n_tok;
 
-  // a column block is 64 rows x 16 pieces of 16 bytes: kPieces pieces per thread
-  constexpr int kPieces = kCols * 16 / (64 * kWaves), kRowStep = 4 * kWaves;
-  uint4 pre[kPieces];
+  // A column block is 64 rows x 16 pieces of 16 bytes: kPieces loads of four rows per wave.  bf16 rows go straight to LDS
+  // (no register holds them over a block's products), fp32 rows are converted on the way.
+  constexpr int kPieces = kCols * 16 / (64 * kWaves);
+  constexpr bool DIRECT = DT == SKIPKV_BF16;
+  [[maybe_unused]] uint4 pre[kPieces];
   float pre_c = 0.f, pre_w = 0.f;
-  auto fetch = [&](int jb) {
+  const int wave_u = __builtin_amdgcn_readfirstlane(wave);
+  // A whole block of a simple cache: a scalar base and one offset per lane (rows 32 further on lie 32 pitches behind it and
+  // are swizzled alike).
+  const int ld_row = 4 * wave_u + (lane >> 4), ld_piece = (lane & 15) ^ swz16(ld_row & 15);
+  [[maybe_unused]] const uint32_t ld_off = (uint32_t)ld_row * (uint32_t)pitch + (uint32_t)ld_piece * 16;
+  static_assert(kCols == 64 && 4 * kWaves % 16 == 0, "the loads of a lane have rows that are swizzled alike");
+  auto fetch = [&](int jb, int buf) {
+    const int left = n_tok - jb;
+    if (SIMPLE && DIRECT && left >= kCols) {
 #pragma unroll
-    for (int it = 0; it < kPieces; ++it) {
-      const int row = min(jb + it * kRowStep + (tid >> 4), n_tok - 1);
-      pre[it] = load_piece_bf16<DT>(kbase + slot_of(row) * pitch, tid & 15);
+      for (int it = 0; it < kPieces; ++it)
+        load_to_lds_16_sbase(scalar64(kbase + (int64_t)(jb + 4 * kWaves * it) * pitch), ld_off, cols[buf] + (it * kWaves + wave_u) * 1024);
+    } else {
+#pragma unroll
+      for (int it = 0; it < kPieces; ++it) {
+        const char *src = kbase + slot_of(jb + min(4 * kWaves * it + ld_row, left - 1)) * pitch;
+        if constexpr (DIRECT) load_to_lds_16(src + ld_piece * 16, cols[buf] + (it * kWaves + wave_u) * 1024);
+        else pre[it] = load_piece_bf16<DT>(src, ld_piece);
+      }
     }
-    if (tid < kCols) {
-      const int col = jb + tid;
-      pre_c = a.scale[col0 + min(col, n_tok - 1)];
-      pre_w = col < n_tok ? (SWEEP == 1 ? 1.f : a.inv_l[col0 + col]) : 0.f;  // weight 0 drops columns past the end
+    if (wave_u == 0) {
+      const int64_t at = col0 + jb;
+      const int col = min(lane, left - 1);
+      pre_c = a.scale[at + col];
+      pre_w = lane < left ? (SWEEP == 1 ? 1.f : a.inv_l[at + col]) : 0.f;  // weight 0 drops columns past the end
     }
   };
   auto commit = [&](int buf) {
+    if constexpr (!DIRECT) {
 #pragma unroll
-    for (int it = 0; it < kPieces; ++it)
-      *reinterpret_cast<uint4 *>(cols[buf] + (it * kRowStep + (tid >> 4)) * LSTR + (tid & 15) * 16) = pre[it];
-    if (tid < kCols) {
-      col_cw[0][buf][tid] = pre_c;
-      col_cw[1][buf][tid] = pre_w;
+      for (int it = 0; it < kPieces; ++it) *reinterpret_cast<uint4 *>(cols[buf] + (it * kWaves + wave) * 1024 + lane * 16) = pre[it];
+    }
+    if (wave_u == 0) {
+      col_cw[0][buf][lane] = pre_c;
+      col_cw[1][buf][lane] = pre_w;
     }
   };
 
@@ -219,54 +240,77 @@ __global__ void __launch_bounds__(64 * kWaves, 4) k_tokred_sweep(TokRedArgs a) {
       add_fixed(a.acc + col0 + jb + lane, tot * inv_n, kFix);
     }
   };
-  fetch(r0);
   int buf = 0;
+  fetch(r0, buf);
+#pragma unroll 1
   for (int jb = r0; jb < n_tok; jb += kCols, buf ^= 1) {
     commit(buf);
     // One barrier per block: a buffer is written again two blocks later, when every wave has passed the barrier
     // of the block in between and with it the end of its own reads.
+    wait_vm<0>();  // (the compiler does not know of the direct loads)
     __syncthreads();
-    if (jb + kCols < n_tok) fetch(jb + kCols);  // lands while this block is multiplied
+    if (jb + kCols < n_tok) fetch(jb + kCols, buf ^ 1);  // lands while this block is multiplied
     if (jb > r0 + kCols) emit(jb - kCols, buf ^ 1);  // the first block has no mirror image
-    auto products = [&](auto mirror_c) {
-      constexpr bool MIRROR = decltype(mirror_c)::value;
-      float csum[kCols / 16];  // the lane's columns over the wave's rows
-      const char *tile = cols[buf] + c16 * LSTR + g * 64;
-      const float *wts = &col_cw[0][buf][c16];
-#pragma unroll
-      for (int ct = 0; ct < kCols / 16; ++ct) {
-        bf16x8 bfr[4];
-#pragma unroll
-        for (int kk = 0; kk < 4; ++kk) bfr[kk] = *reinterpret_cast<const bf16x8 *>(tile + ct * (16 * LSTR) + kk * 16);
-        const float cc = wts[16 * ct];
-        const float cw = wts[2 * kCols + 16 * ct];
-        float cs[2] = {0.f, 0.f};
-#pragma unroll
-        for (int t = 0; t < kTW; ++t) {
-          f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-          __builtin_amdgcn_s_setprio(1);  // a wave that can feed the matrix cores goes first, the others' exponentials fill in
-#pragma unroll
-          for (int kk = 0; kk < 4; ++kk) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[t][kk], bfr[kk], acc, 0, 0, 0);
-          __builtin_amdgcn_s_setprio(0);
-#pragma unroll
-          for (int jj = 0; jj < 4; ++jj) {
-            const float e = __builtin_amdgcn_exp2f(acc[jj] * (row_c[t][jj] * cc));
-            rsum[t][jj] = fmaf(e, cw, rsum[t][jj]);
-            if constexpr (MIRROR) cs[jj & 1] = fmaf(e, row_w[t][jj], cs[jj & 1]);
-          }
-        }
-        csum[ct] = cs[0] + cs[1];
-        __builtin_amdgcn_sched_barrier(0);  // no fragments of the next columns in registers yet: there are none to spare
-      }
-      if constexpr (MIRROR) cpart[buf][wave][lane] = sum_lane_groups(csum[0], csum[1], csum[2], csum[3]);
-    };
     // 64 x 64 squares on the diagonal are computed in full, blocks right of them stand for their transposes
     // too, blocks left of them are the transposes
     const bool square = (jb & -kCols) == (rw0 & -kCols);
-    if (rw0 < n_tok && jb > rw0 && !square) products(std::true_type{});
-    else {
+    if (rw0 < n_tok && (jb > rw0 || square)) {
+      float csum[kCols / 16];  // the lane's columns over the wave's rows
+      // row 16 ct + c16, piece 4g + kk: the slice index kk is an XOR on bits 4..5
+      const uint32_t tile = lds_addr(cols[buf]) + (uint32_t)(c16 * 256 + (((4 * g) ^ swz16(c16)) << 4));
+      const float *wts = &col_cw[0][buf][c16];
+      // Tiles of 16 rows x 16 columns in the order (column tile, row tile).  The products of a tile are issued among the
+      // vector instructions of the tile before it, so that the matrix cores work while those are issued; the order is pinned.
+      constexpr int CT = kCols / 16, NTILE = CT * kTW;
+      bf16x8 bfr[4];
+      f32x4 acc[2];
+      float cc[2], cw[2];
+      auto fragments = [&](int ct) {
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk) bfr[kk] = *reinterpret_cast<const __attribute__((address_space(3))) bf16x8 *>((uintptr_t)((tile ^ (kk << 4)) + ct * 4096));
+        cc[ct & 1] = wts[16 * ct];
+        cw[ct & 1] = wts[2 * kCols + 16 * ct];
+      };
+      auto half_product = [&](int i, int half) {  // of tile i: two of the four slices of the head dimension
+        f32x4 &x = acc[i & 1];
+        if (half == 0) x = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int kk = 2 * half; kk < 2 * half + 2; ++kk) x = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[i % kTW][kk], bfr[kk], x, 0, 0, 0);
+      };
+      fragments(0);
+      half_product(0, 0);
+      half_product(0, 1);
+      float cs[2] = {0.f, 0.f};
+#pragma unroll
+      for (int i = 0; i < NTILE; ++i) {
+        const int ct = i / kTW, t = i % kTW;
+        float e[4];
+#pragma unroll
+        for (int jj = 0; jj < 4; ++jj) e[jj] = row_c[t][jj] * cc[ct & 1];
+        __builtin_amdgcn_sched_barrier(0);
+        if (i + 1 < NTILE) half_product(i + 1, 0);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int jj = 0; jj < 4; ++jj) e[jj] = __builtin_amdgcn_exp2f(acc[i & 1][jj] * e[jj]);
+        __builtin_amdgcn_sched_barrier(0);
+        if (i + 1 < NTILE) half_product(i + 1, 1);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int jj = 0; jj < 4; ++jj) {
+          rsum[t][jj] = fmaf(e[jj], cw[ct & 1], rsum[t][jj]);
+          cs[jj & 1] = fmaf(e[jj], row_w[t][jj], cs[jj & 1]);
+        }
+        if ((i + 2) % kTW == 0 && i + 2 < NTILE) fragments((i + 2) / kTW);  // the products just issued were the last ones with the old ones
+        if (t == kTW - 1) {
+          csum[ct] = cs[0] + cs[1];
+          cs[0] = cs[1] = 0.f;
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      const float sum = sum_lane_groups(csum[0], csum[1], csum[2], csum[3]);
+      cpart[buf][wave][lane] = square ? 0.f : sum;
+    } else {
       cpart[buf][wave][lane] = 0.f;
-      if (rw0 < n_tok && square) products(std::false_type{});
     }
   }
   __syncthreads();
@@ -314,19 +358,21 @@ hipError_t launch_token_redundancy(const TokRedArgs &a, hipStream_t st) {
   const int64_t items = n_lh * a.nrb_max;
   const unsigned g1 = (unsigned)((items + 7) / 8 * 8);
   const unsigned g2 = (unsigned)std::min<int64_t>((rows + 255) / 256, 1 << 16);
-  if (a.dtype == SKIPKV_BF16) {
-    hipLaunchKernelGGL(k_key_scale<SKIPKV_BF16>, dim3(g0), dim3(256), 0, st, a);
-    hipLaunchKernelGGL((k_tokred_sweep<SKIPKV_BF16, 1>), dim3(g1), dim3(64 * kWaves), 0, st, a);
+  auto sweeps = [&](auto dt, auto simple) {
+    constexpr int DT = decltype(dt)::value;
+    constexpr bool SIMPLE = decltype(simple)::value;
+    hipLaunchKernelGGL(k_key_scale<DT>, dim3(g0), dim3(256), 0, st, a);
+    hipLaunchKernelGGL((k_tokred_sweep<DT, 1, SIMPLE>), dim3(g1), dim3(64 * kWaves), 0, st, a);
     hipLaunchKernelGGL(k_tokred_finish<1>, dim3(g2), dim3(256), 0, st, a);
-    hipLaunchKernelGGL((k_tokred_sweep<SKIPKV_BF16, 2>), dim3(g1), dim3(64 * kWaves), 0, st, a);
+    hipLaunchKernelGGL((k_tokred_sweep<DT, 2, SIMPLE>), dim3(g1), dim3(64 * kWaves), 0, st, a);
     hipLaunchKernelGGL(k_tokred_finish<2>, dim3(g2), dim3(256), 0, st, a);
-  } else {
-    hipLaunchKernelGGL(k_key_scale<SKIPKV_F32>, dim3(g0), dim3(256), 0, st, a);
-    hipLaunchKernelGGL((k_tokred_sweep<SKIPKV_F32, 1>), dim3(g1), dim3(64 * kWaves), 0, st, a);
-    hipLaunchKernelGGL(k_tokred_finish<1>, dim3(g2), dim3(256), 0, st, a);
-    hipLaunchKernelGGL((k_tokred_sweep<SKIPKV_F32, 2>), dim3(g1), dim3(64 * kWaves), 0, st, a);
-    hipLaunchKernelGGL(k_tokred_finish<2>, dim3(g2), dim3(256), 0, st, a);
-  }
+  };
+  auto of_type = [&](auto dt) {
+    if (!a.row_map && a.stride_tok * (decltype(dt)::value == SKIPKV_BF16 ? 2 : 4) < (1 << 24)) sweeps(dt, std::true_type{});
+    else sweeps(dt, std::false_type{});
+  };
+  if (a.dtype == SKIPKV_BF16) of_type(std::integral_constant<int, SKIPKV_BF16>{});
+  else of_type(std::integral_constant<int, SKIPKV_F32>{});
   return hipGetLastError();
 }
 

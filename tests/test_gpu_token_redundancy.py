@@ -129,3 +129,22 @@ def test_feeds_the_sentence_scores():
         full[0, h] = red_o[0, 0]
         ora = oracle_head(cfg, st, k0, v0, q, 0, h, 0, red=full)
         compare_head(cfg, st, out, k, v, k0, v0, ora, 0, h, 0, stats)
+
+
+def test_rows_sixteen_megabytes_apart():
+    # the widest pitch that whole column blocks take 32-bit offsets for, and the first one that they do not
+    lens = [66, 5, 130]
+    st = _structure([[0, n] for n in lens])
+    cfg = W.Config("tokred-pitch", 9, len(lens), 1, 1, 4, "bf16", 0, 0, 64, 8, 16, 16.0, 0.0)
+    room = torch.empty((st.total_tokens * (1 << 23)), dtype=torch.bfloat16, device="cuda")
+    g = torch.Generator(device="cuda")
+    g.manual_seed(79)
+    rows = torch.randn((st.total_tokens, 128), generator=g, device="cuda").to(torch.bfloat16)
+    want = None
+    for pitch in (128, (1 << 23) - 8, 1 << 23):
+        k = room.as_strided((1, 1, st.total_tokens, 128), (8, 8, pitch, 1))
+        k[0, 0] = rows
+        out = _run(cfg, st, k)
+        want = out if want is None else want
+        assert torch.equal(out, want)
+    _check(cfg, st, rows.view(1, 1, -1, 128), want, [(0, 0, b) for b in range(len(lens))], 1e-4)
