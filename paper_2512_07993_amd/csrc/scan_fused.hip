@@ -68,12 +68,20 @@
 //     the key loads, otherwise waits for the records' registers in the next first phase, and so for the keys in flight
 //     (28 layers x 4 heads, 64 sequences of 4-8 K, 56 rows: 3200 -> 2860 us; 3560 before all of this).
 //
+//   - With the keys always the same few rows, which need not cross the chip, the kernel takes 2170 us of 2430: the rest is the
+//     fabric, which carries some 14 GB per call.  One look at a head's records costs 8 % of an item's keys, so there is one
+//     before the wait instead of two, waves without so many records load from one place, and only what is missing is looked for
+//     again (2480 -> 2400 us and, the second shape, 2860 -> 2770).
+// Measured without a gain: statistics of a stage issued among the products of the next one; fragments read 4, 6 or 8 products
+// ahead (6: one stream of reads for both kinds of products); the items of a head on one XCD (3 % slower to 1 % faster); keys
+// loaded past the caches (5 % slower).
+//
 // Paged cache.  With a row map (logical token -> block slot) and blocks of a power of two >= 16
 // slots, a stage spans at most two blocks: two scalar reads of the map give two bases per stage.
 #include "scan_dev.h"
 
 #ifndef SKIPKV_FRAG_AHEAD
-#define SKIPKV_FRAG_AHEAD 3  // query fragments are read this many matrix instructions ahead of their use
+#define SKIPKV_FRAG_AHEAD 6  // fragments are read this many matrix instructions ahead of their use
 #endif
 #ifndef SKIPKV_SCAN_NBUF
 #define SKIPKV_SCAN_NBUF 3   // stage buffers per wave
@@ -149,7 +157,7 @@ struct Item {  // one item as seen by one wave
   bool goes_on;     // ... and this wave's span is not the first one of its (only) sentence
 };
 
-template <int DT, int NP, int AL, bool PAGED>
+template <int DT, int NP, int AL, bool PAGED, bool POOL>
 __global__ void __launch_bounds__(256, (DT == SKIPKV_BF16 ? 2 : 1)) k_scan_fused(ScanArgs a) {
   constexpr int SL = NP * AL;
   constexpr int NT = (SL + 3) / 4;
@@ -450,47 +458,52 @@ __global__ void __launch_bounds__(256, (DT == SKIPKV_BF16 ? 2 : 1)) k_scan_fused
         ring = ring_slot(ring + 1);
         const uint32_t stage_a = lds_addr(stage);
 
-        // ---- operands of the sentence key sums, fetched first so that they land behind the logits block:
         // the indicator of the lane's sentence (slot c16) over the stage's 16 tokens as a bit mask
-        // (tokens past the span belong to no sentence), and the transposed key fragments
+        // (tokens past the span belong to no sentence)
         const int ra = min(max(s_lo - ts, 0), kStageRows), rb = min(max(s_hi - ts, 0), kStageRows);
         const uint32_t rows = (1u << rb) - (1u << ra);
-        i16x4 trv[8];
+        // ---- logits of this stage's 16 tokens against all query rows, then its part of the sentence key sums
         if constexpr (DT == SKIPKV_BF16) {
-          if (!a.no_pool) {
-            const uint32_t taddr = stage_a + tr_off;
-#pragma unroll
-            for (int j = 0; j < 8; ++j) trv[j] = lds_read_tr16(taddr ^ (j << 5));
-          }
-        }
-
-        // ---- logits of this stage's 16 tokens against all query rows
-        if constexpr (DT == SKIPKV_BF16) {
-          // Fragment reads run AHEAD matrix instructions ahead of their use (the order is pinned:
-          // the compiler would otherwise read each fragment right before its use and pay the LDS
-          // latency every time, or read all of them first and run out of registers).
-          // Step i multiplies slice i / NT of the head dimension into row tile i % NT.
-          constexpr int AHEAD = SKIPKV_FRAG_AHEAD, NSTEP = 4 * NT;
-          const uint32_t baddr = stage_a + b_off;
+          // LDS reads run AHEAD products ahead of their use, one stream for both kinds of products (the order is pinned:
+          // the compiler would otherwise read each fragment right before its use and pay the LDS latency
+          // every time, or read all of them first and run out of registers).
+          // Step i < NSTEP multiplies slice i / NT of the head dimension into row tile i % NT, step NSTEP + j the indicator of the
+          // sentences (by token) into dimensions 16 j ...
+          constexpr int AHEAD = SKIPKV_FRAG_AHEAD, NSTEP = 4 * NT, NREAD = NSTEP + (POOL ? 8 : 0);
+          const uint32_t baddr = stage_a + b_off, taddr = stage_a + tr_off;
           const uint32_t aaddr = lds_addr(qt) + b_off;  // row 16 T + c16 of the query tile: same lane pattern as the key fragment
-          auto rd_a = [&](int i) {
-            return *reinterpret_cast<const __attribute__((address_space(3))) bf16x8 *>((uintptr_t)((aaddr ^ ((i / NT) << 4)) + 16 * (i % NT) * ROWB));
-          };
-          auto rd_b = [&](int kk) {
-            return *reinterpret_cast<const __attribute__((address_space(3))) bf16x8 *>((uintptr_t)(baddr ^ (kk << 4)));
-          };
           bf16x8 bfr[4], afr[NSTEP];
-          bfr[0] = rd_b(0);
+          i16x4 trv[8];
+          auto read_step = [&](int i) {
+            if (i < NSTEP) {
+              if (i % NT == 0) bfr[i / NT] = *reinterpret_cast<const __attribute__((address_space(3))) bf16x8 *>((uintptr_t)(baddr ^ ((i / NT) << 4)));
+              afr[i] = *reinterpret_cast<const __attribute__((address_space(3))) bf16x8 *>((uintptr_t)((aaddr ^ ((i / NT) << 4)) + 16 * (i % NT) * ROWB));
+            } else if (i < NREAD) {
+              trv[i - NSTEP] = lds_read_tr16(taddr ^ ((i - NSTEP) << 5));
+            }
+          };
 #pragma unroll
-          for (int i = 0; i < AHEAD && i < NSTEP; ++i) afr[i] = rd_a(i);
+          for (int i = 0; i < AHEAD; ++i) read_step(i);
           __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
           for (int i = 0; i < NSTEP; ++i) {
-            if (i + AHEAD < NSTEP) afr[i + AHEAD] = rd_a(i + AHEAD);
-            if (i % NT == 0 && i / NT + 1 < 4) bfr[i / NT + 1] = rd_b(i / NT + 1);
+            read_step(i + AHEAD);
             __builtin_amdgcn_sched_barrier(0);
             acc[st][i % NT] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(afr[i], bfr[i / NT], acc[st][i % NT], 0, 0, 0);
             __builtin_amdgcn_sched_barrier(0);
+          }
+          if constexpr (POOL) {
+            // the lane's operand: tokens 4g .. 4g+3 as bf16 values 2.0 (= bit 14 alone) or 0; row bits
+            // 4g, 4g+1 go to bits 14 and 30 of the first word, 4g+2, 4g+3 of the second one
+            const uint32_t x = rows >> (4 * g);
+            const uint2 ind = make_uint2(((x << 14) | (x << 29)) & 0x40004000u, ((x << 12) | (x << 27)) & 0x40004000u);
+            const i16x4 av = __builtin_bit_cast(i16x4, ind);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+              read_step(NSTEP + j + AHEAD);
+              __builtin_amdgcn_sched_barrier(0);
+              pool[j] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(av, trv[j], pool[j], 0, 0, 0);
+            }
           }
         } else {
 #pragma unroll
@@ -505,20 +518,7 @@ __global__ void __launch_bounds__(256, (DT == SKIPKV_BF16 ? 2 : 1)) k_scan_fused
               acc[st][T] = __builtin_amdgcn_mfma_f32_16x16x4f32(afrag.w, bfrag.w, acc[st][T], 0, 0, 0);
             }
           }
-        }
-
-        // ---- sentence key sums over the stage's tokens (they keep the matrix cores busy while the
-        // logits drain into the statistics below)
-        if (!a.no_pool) {
-          if constexpr (DT == SKIPKV_BF16) {
-            // the lane's operand: tokens 4g .. 4g+3 as bf16 values 2.0 (= bit 14 alone) or 0; row bits
-            // 4g, 4g+1 go to bits 14 and 30 of the first word, 4g+2, 4g+3 of the second one
-            const uint32_t x = rows >> (4 * g);
-            const uint2 ind = make_uint2(((x << 14) | (x << 29)) & 0x40004000u, ((x << 12) | (x << 27)) & 0x40004000u);
-            const i16x4 av = __builtin_bit_cast(i16x4, ind);
-#pragma unroll
-            for (int j = 0; j < 8; ++j) pool[j] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(av, trv[j], pool[j], 0, 0, 0);
-          } else {
+          if constexpr (POOL) {
             // fp32 keys: 16x16x4 products, token 4 ks + g against dimension 16 j + c16
 #pragma unroll
             for (int ks = 0; ks < 4; ++ks) {
@@ -600,7 +600,7 @@ __global__ void __launch_bounds__(256, (DT == SKIPKV_BF16 ? 2 : 1)) k_scan_fused
       *reinterpret_cast<float2 *>(wstat[wave][my_row]) = rec;
     }
     issued = issued_next;
-    if (cur.goes_on) {  // row 0 of the key sums is the sentence
+    if (POOL && cur.goes_on) {  // row 0 of the key sums is the sentence
       const int ln = opaque(lane);
       if (ln < 16) {
 #pragma unroll
@@ -630,22 +630,28 @@ __global__ void __launch_bounds__(256, (DT == SKIPKV_BF16 ? 2 : 1)) k_scan_fused
     if constexpr (DT == SKIPKV_BF16) q_issue(nxt, par ^ 1);
     // ---- the head's normalisers, first half: every wave loads a quarter of the records of the head's items
     // (wave w: items w, w + 4, ...; lane = query row), kMergeDepth coherent loads in flight per lane, and
-    // lets them travel while it commits the next item's queries and writes its embeddings.
+    // lets them travel while it writes its embeddings.
     // (fp32: the queries are committed first: they arrived long ago, and a wait for them placed behind the
-    // record loads would wait for those as well.  Always kMergeDepth loads, surplus ones on the head's last
-    // record, so that the number of loads in flight is known where later code waits for older ones.)
+    // record loads would wait for those as well.)
     if constexpr (DT == SKIPKV_F32) q_commit(nxt, nq, par ^ 1);
     const int np = cur.np;
-    const float2 *recs = a.ws.item_stat + ((int64_t)lh * a.ws.ni_max + cur.first) * R + min(opaque(lane), R - 1);
+    const float2 *recs = a.ws.item_stat + ((int64_t)lh * a.ws.ni_max + cur.first) * R;
+    const int rec_row = min(opaque(lane), R - 1);
     float2 pv[kMergeDepth];
+    // (Every look crosses the chip, 512 bytes per record, which the keys' bandwidth is short of: hence a single look before the
+    // wait, surplus loads all from one place, and only what is missing looked for again.)
+    auto load_record = [&](int pp, int u) {
+      const int p = pp + 4 * u;
+      pv[u] = coherent_load2(recs + (int64_t)min(p, np - 1) * R + (p < np ? rec_row : 0));
+    };
     auto load_records = [&](int pp) {
 #pragma unroll
-      for (int u = 0; u < kMergeDepth; ++u) pv[u] = coherent_load2(recs + (int64_t)min(pp + 4 * u, np - 1) * R);
+      for (int u = 0; u < kMergeDepth; ++u) load_record(pp, u);
     };
-    load_records(wave);
+    if (!(POOL && ns_own > 0)) load_records(wave);
 
     // ---- sentence embeddings of the span: unit vectors as bf16 hi + lo, four sentences at a time
-    if (!a.no_pool && ns_own > 0) {
+    if (POOL && ns_own > 0) {
       if (cur.cut) {  // the sums of the spans that the wave's sentence goes on in (it is alone in its span then)
         const int spans = (soff[cur.sb + 1] - soff[cur.sb] + kSpanCap - 1) / kSpanCap;
         const int oc = opaque(c16);
@@ -661,7 +667,7 @@ __global__ void __launch_bounds__(256, (DT == SKIPKV_BF16 ? 2 : 1)) k_scan_fused
       const int og = opaque(g);
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        if (r == 1) load_records(wave);  // a second look, timed to land when the embeddings are out
+        if (r == 1) load_records(wave);  // timed to land when the embeddings are out
         if (4 * r >= ns) continue;
         float ss = pool[0][r] * pool[0][r];
 #pragma unroll
@@ -722,10 +728,10 @@ __global__ void __launch_bounds__(256, (DT == SKIPKV_BF16 ? 2 : 1)) k_scan_fused
       for (int pp = wave; pp < np; pp += 4 * kMergeDepth) {
         if (pp != wave) load_records(pp);
         for (int polls = 0;; ++polls) {
-          bool ok = true;
+          uint32_t missing = 0;
 #pragma unroll
-          for (int u = 0; u < kMergeDepth; ++u) ok = ok && __float_as_uint(pv[u].x) != kRowNormUnset;  // surplus loads hold a real record too
-          if (__all(ok)) break;
+          for (int u = 0; u < kMergeDepth; ++u) missing |= __any(__float_as_uint(pv[u].x) == kRowNormUnset) ? 1u << u : 0u;  // surplus loads hold a real record too
+          if (missing == 0) break;
           if (wait_expired(polls)) {
             if (lane == 0) {
               s_timeout[par] = 1;
@@ -736,15 +742,20 @@ __global__ void __launch_bounds__(256, (DT == SKIPKV_BF16 ? 2 : 1)) k_scan_fused
             break;
           }
           __builtin_amdgcn_s_sleep(1);
-          load_records(pp);
+#pragma unroll
+          for (int u = 0; u < kMergeDepth; ++u)
+            if (missing & (1u << u)) load_record(pp, u);
         }
         float nm = m;
 #pragma unroll
-        for (int u = 0; u < kMergeDepth; ++u) nm = fmaxf(nm, pv[u].x);  // (the surplus records are the head's last one)
+        for (int u = 0; u < kMergeDepth; ++u) {
+          if (pp + 4 * u >= np) pv[u] = make_float2(kRefInit, 0.f);  // (a surplus load has another row's)
+          nm = fmaxf(nm, pv[u].x);
+        }
         s *= __builtin_amdgcn_exp2f(m - nm);
         m = nm;
 #pragma unroll
-        for (int u = 0; u < kMergeDepth; ++u) s = fmaf(pp + 4 * u < np ? pv[u].y : 0.f, __builtin_amdgcn_exp2f(pv[u].x - nm), s);
+        for (int u = 0; u < kMergeDepth; ++u) s = fmaf(pv[u].y, __builtin_amdgcn_exp2f(pv[u].x - nm), s);
       }
       if (lane < R) {
         mstat[wave][lane][0] = m;
@@ -842,19 +853,25 @@ __global__ void __launch_bounds__(256, (DT == SKIPKV_BF16 ? 2 : 1)) k_scan_fused
   }
 }
 
-template <int DT, int NP, int AL, bool PAGED>
+template <int DT, int NP, int AL, bool PAGED, bool POOL>
 hipError_t launch_one(const ScanArgs &a, hipStream_t st) {
   int dev = 0, cus = 0, per_cu = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;
   e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
   if (e != hipSuccess) return e;
-  e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_scan_fused<DT, NP, AL, PAGED>, 256, 0);
+  e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_scan_fused<DT, NP, AL, PAGED, POOL>, 256, 0);
   if (e != hipSuccess) return e;
   const int grid = cus * per_cu;  // persistent: every workgroup is resident at once
   if (grid < kFuseMaxItems) return hipErrorInvalidConfiguration;
-  hipLaunchKernelGGL((k_scan_fused<DT, NP, AL, PAGED>), dim3(grid), dim3(256), 0, st, a);
+  hipLaunchKernelGGL((k_scan_fused<DT, NP, AL, PAGED, POOL>), dim3(grid), dim3(256), 0, st, a);
   return hipGetLastError();
+}
+
+template <int DT, int NP, int AL>
+hipError_t launch_type(const ScanArgs &a, hipStream_t st) {
+  if (a.row_map) return a.no_pool ? launch_one<DT, NP, AL, true, false>(a, st) : launch_one<DT, NP, AL, true, true>(a, st);
+  return a.no_pool ? launch_one<DT, NP, AL, false, false>(a, st) : launch_one<DT, NP, AL, false, true>(a, st);
 }
 
 }  // namespace
@@ -865,11 +882,9 @@ bool scan_fused_supported(const RowLayout &rl, int64_t row_pitch_bytes) {
 
 hipError_t launch_scan_fused(const ScanArgs &a, hipStream_t st) {
   if ((int64_t)a.n_layers * a.n_kv_heads * a.batch == 0 || a.force_two_pass) return hipSuccess;
-#define SKIPKV_CASE(NP_, AL_)                                                                                                            \
-  if (a.rl.np == NP_ && a.rl.al == AL_) {                                                                                                \
-    if (a.dtype == SKIPKV_BF16) return a.row_map ? launch_one<SKIPKV_BF16, NP_, AL_, true>(a, st) : launch_one<SKIPKV_BF16, NP_, AL_, false>(a, st); \
-    return a.row_map ? launch_one<SKIPKV_F32, NP_, AL_, true>(a, st) : launch_one<SKIPKV_F32, NP_, AL_, false>(a, st);                    \
-  }
+#define SKIPKV_CASE(NP_, AL_)                                                                          \
+  if (a.rl.np == NP_ && a.rl.al == AL_)                                                                \
+    return a.dtype == SKIPKV_BF16 ? launch_type<SKIPKV_BF16, NP_, AL_>(a, st) : launch_type<SKIPKV_F32, NP_, AL_>(a, st);
   SKIPKV_CASE(4, 2)
   SKIPKV_CASE(4, 4)
   SKIPKV_CASE(7, 2)
