@@ -7,8 +7,9 @@
 //   pass B   the logits again, I[t] = (1/alpha) sum_a max_i softmax, and its mean over every sentence.
 //
 // What bounds it.  With 160 query rows a 256-byte key costs 41 KFLOP and 160 exponentials: both passes are bound by
-// the instructions that a SIMD can issue (pass A at 160 rows: about 1320 VALU and 205 MFMA instructions per 64-key
-// tile and CU; the kernel's time is close to the sum of their issue times), not by HBM.  Hence:
+// the instructions that a SIMD can issue (pass A at 160 rows: about 1250 vector and 220 matrix instructions per 64-key
+// tile and CU, 70 and 37 % of a SIMD's cycles at the 1.83 GHz that the chip's power allows such a load), not by HBM.  Products
+// pinned among the exponentials of the 16 tokens before them, or fragments read three ahead, changed nothing.  Hence:
 //   - a workgroup takes a RUN of up to kMaxRunChunks consecutive chunks of a sequence, so that its query fragments,
 //     loaded once, stay in registers for it (no query tile in LDS);
 //   - 8 waves; the rows are split over RS of them (2, 4, 8 for up to 16, 40, 64 slots per lane group) and a tile's
@@ -16,7 +17,8 @@
 //   - keys go HBM -> LDS directly in tiles of 64 rows, three tiles deep, two tiles ahead of the compute, one barrier
 //     per tile; a chunk's sentence offsets travel with its tiles;
 //   - sentence sums are matrix products of a 0/2 indicator with the transposed key tile, 32 dimensions and 16
-//     sentences per wave, so that no wave waits for another one's sentences;
+//     sentences per wave, so that no wave waits for another one's sentences; the indicator's words come from two additions
+//     and a three-way bit operation each;
 //   - pass A's row sums are relative to a reference that the wave's first 16 tokens fix for each row: two fmas and one
 //     exponential per logit.  Where a later logit is too far above it (2^100) a wave does its share once more by itself,
 //     with references that follow the logits.  8 layers x 8 heads, 4 x 16 K tokens, 160 rows, whole score call: 962 us, with
@@ -27,6 +29,8 @@
 // Measured, pass A / pass B / k_row_norm in us, against one workgroup of 256 threads per chunk with the query tile in
 // LDS and a running maximum per row, which this replaces:
 //   48 layers x 8 heads, 4 x 32 K tokens, 160 rows (50 M keys, 12.9 GB):    7327 / 3926 / 196  ->  3980 / 3210 / 10
+//     ->  3830 / 3010 with the first tiles' loads in front of the loop (in it, a step without a tile made the compiler move every
+//     sum at each tile) and the indicator as it is now (it took shifts and masks, 13 instructions for two words)
 //   32 layers x 8 heads, 4 x 3-9 K tokens, 1 % long sentences, 64 rows:      995 /  711 /  23  ->   412 /  338 /  7
 // The whole call of the first shape with one, four, up to sixteen chunks per run: 18.0, 11.2, 10.0 ms.  Pass B alone would be
 // a little faster in either of two other shapes that pass A is slower in, measured while both took 4189 / 3193: half the waves
@@ -93,8 +97,6 @@ __device__ __forceinline__ void issue_rows4(const KeyRows &kr, int t0, int last,
   }
 }
 
-// ((1 << width) - 1) << offset, both taken modulo 32.
-__device__ __forceinline__ uint32_t bitfield_mask(int width, int offset) { return ((1u << (width & 31)) - 1u) << (offset & 31); }
 __device__ __forceinline__ bf16x8 join_tr(i16x4 lo, i16x4 hi) {
   const uint2 l = __builtin_bit_cast(uint2, lo), h = __builtin_bit_cast(uint2, hi);
   return __builtin_bit_cast(bf16x8, make_uint4(l.x, l.y, h.x, h.y));
@@ -266,24 +268,22 @@ __global__ void __launch_bounds__(64 * kWaves, 4) k_scan_rows(ScanArgs a) {
     float sum_i = 0.f, sum_r = 0.f;  // pass B: thread (sentence tid / 16, part tid % 16)
 #pragma unroll
     for (int jj = 0; jj < 2; ++jj) pool[jj] = f32x4{0.f, 0.f, 0.f, 0.f};
-    int slot = 1;  // (of the first step, which loads tile 0 into slot 0)
-    for (int i = -kAhead; i < n_tiles; ++i) {
-      if (i >= 0) {
-        wait_vm<(kAhead - 1) * kTileLoads>();
-      }
-      if (i == -kAhead || i >= 0) {
-        asm volatile("" ::: "memory");
-        lds_barrier();  // the tile's rows are there for all waves, and all are done with the tile (or run) before it
-        asm volatile("" ::: "memory");
-      }
+    asm volatile("" ::: "memory");
+    lds_barrier();  // all waves are done with the run before
+    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int i = 0; i < kAhead; ++i) {
+      issue(i, 0);
+      issue(i, 1);
+    }
+    int slot = 0;
+    for (int i = 0; i < n_tiles; ++i) {
+      wait_vm<(kAhead - 1) * kTileLoads>();
+      asm volatile("" ::: "memory");
+      lds_barrier();  // the tile's rows are there for all waves, and all are done with the tile before it
+      asm volatile("" ::: "memory");
       const int fill = slot == 0 ? kTileSlots - 1 : slot - 1;
       auto prefetch = [&](int j) { issue(fill, j); };
-      if (i < 0) {
-        prefetch(0);
-        prefetch(1);
-        slot = slot + 1 == kTileSlots ? 0 : slot + 1;
-        continue;
-      }
       const uint32_t tile_a = lds_addr(kt[slot]);
       const int *soff = soffb[slot];
       slot = slot + 1 == kTileSlots ? 0 : slot + 1;
@@ -358,9 +358,12 @@ __global__ void __launch_bounds__(64 * kWaves, 4) k_scan_rows(ScanArgs a) {
         // tokens 4g .. 4g+3 of two 16-token stages.
         const int pw = wave & 3, u = wave >> 2;
         if (!a.no_pool && ns > 16 * u) {
-          // offsets past the chunk's last one repeat it: empty slots
-          const int g4 = opaque(4 * g);  // (no register over the tiles for 4 g + 16)
-          const int s_lo = soff[16 * u + c16] - ct, s_hi = soff[16 * u + c16 + 1] - ct;
+          // Offsets past the chunk's last one repeat it: empty slots.  Two 16-bit fields to a word, a token each: bit 14 of
+          // 0x4000 + token - first is set from the sentence's first token on, that of 0x4000 + token - end from its end on
+          const int g4 = opaque(4 * g);  // (no register over the tiles for what follows from it)
+          const uint32_t s_lo = (uint32_t)min(max(soff[16 * u + c16] - ct, 0), kTileRows), s_hi = (uint32_t)min(max(soff[16 * u + c16 + 1] - ct, 0), kTileRows);
+          const uint32_t tok = __umul24((uint32_t)g4, 0x10001u) + 0x40014000u;  // tokens 4g, 4g + 1
+          const uint32_t from = tok - (s_lo << 16 | s_lo), past = tok - (s_hi << 16 | s_hi);
           bf16x8 trv[2][2];
 #pragma unroll
           for (int w = 0; w < 2; ++w)
@@ -373,12 +376,9 @@ __global__ void __launch_bounds__(64 * kWaves, 4) k_scan_rows(ScanArgs a) {
           for (int w = 0; w < 2; ++w) {
             uint32_t ind[4];
 #pragma unroll
-            for (int s = 0; s < 2; ++s) {  // the lane's sentence over its 4 tokens of stage 2w + s
-              const int t0 = 32 * w + 16 * s;
-              const int ra = min(max(s_lo, t0), t0 + 16), rb = min(max(s_hi, t0), t0 + 16);
-              const uint32_t x = __builtin_amdgcn_ubfe(bitfield_mask(rb - ra, ra), g4 + 16 * s, 4);
-              ind[2 * s] = ((x << 14) | (x << 29)) & 0x40004000u;
-              ind[2 * s + 1] = ((x << 12) | (x << 27)) & 0x40004000u;
+            for (int s = 0; s < 4; ++s) {  // the lane's sentence over tokens 4g + 2 (s % 2) and the next of stage 2w + s / 2
+              const uint32_t at = (uint32_t)(32 * w + 16 * (s >> 1) + 2 * (s & 1)) * 0x10001u;
+              ind[s] = (from + at) & ~(past + at) & 0x40004000u;
             }
             const bf16x8 av = __builtin_bit_cast(bf16x8, make_uint4(ind[0], ind[1], ind[2], ind[3]));
 #pragma unroll

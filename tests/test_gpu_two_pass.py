@@ -232,3 +232,29 @@ def test_an_infinite_key_stays_in_its_sentence(group, alpha, token, paged):
     good = [s for s in range(len(off) - 1) if s != bad]
     want = oracle.sentence_redundancy(emb[good])
     np.testing.assert_allclose(lam[good][:-1], want[:-1], rtol=1e-3, atol=1e-5)
+
+
+@pytest.mark.parametrize("group,alpha", [(5, 32), (4, 8)])
+def test_sentences_that_begin_and_end_anywhere_in_a_tile(group, alpha):
+    # Lengths 1, 2, ... put first and last tokens at every place of the 16-token stages and the 64-token tiles; one
+    # sentence is longer than a chunk, so that it holds whole tiles and its bounds lie far outside of others.
+    L, H = 1, 2
+    lengths = list(range(1, 40)) + [700] + list(range(40, 1, -3)) + [64, 16, 128, 1]
+    offsets = [list(np.cumsum([0] + lengths)), list(np.cumsum([0, 15, 1, 16, 32, 64, 3]))]
+    st = _structure([[int(x) for x in o] for o in offsets])
+    cfg = _cfg("bounds", 2, L, H, group, alpha)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(4)
+    k = torch.randn((L, H, st.total_tokens, 128), generator=g, device="cuda").to(torch.bfloat16)
+    q = torch.randn((L, 2, H * group, alpha, 128), generator=g, device="cuda").to(torch.bfloat16)
+    lam = _score(cfg, st, k, q, TWO)[1].double().cpu()
+    kd = k.double().cpu()
+    for b, o in enumerate(offsets):
+        t0, s0, n = int(st.seq_off[b]), st.sent_base(b), int(st.n_sent[b])
+        for h in range(H):
+            e = torch.stack([kd[0, h, t0 + x:t0 + y].mean(0) for x, y in zip(o[:-1], o[1:])])
+            e = e / e.norm(dim=1, keepdim=True)
+            want = torch.where(torch.triu(torch.ones(n, n), 1) > 0, e @ e.T, torch.tensor(-np.inf, dtype=torch.float64)).max(1).values
+            # unit components carry 16 bits: a cosine is within 2 * 2^-16 of the exact one (typically 1e-6); a token too many or
+            # too few moves an embedding of n tokens by 1 / sqrt(n) > 0.03
+            np.testing.assert_allclose(lam[0, h, s0:s0 + n - 1].numpy(), want[:-1].numpy(), rtol=0, atol=3.1e-5)
