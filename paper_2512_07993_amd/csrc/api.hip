@@ -197,7 +197,7 @@ int do_score(Timer &tm, const skipkv_cache *c, const skipkv_params *p, const Row
   sa.no_pool = shared_lambda != nullptr;
   if (tm.run("scan_fused", [&] { return launch_scan_fused(sa, st); }) != hipSuccess) return SKIPKV_EHIP;
   if (tm.run("scan_stats", [&] { return launch_scan_stats(sa, st); }) != hipSuccess) return SKIPKV_EHIP;
-  if (tm.run("row_norm", [&] { return launch_row_norm(sa, st); }) != hipSuccess) return SKIPKV_EHIP;
+  if (sa.dtype == SKIPKV_F32 && tm.run("row_norm", [&] { return launch_row_norm(sa, st); }) != hipSuccess) return SKIPKV_EHIP;
   if (tm.run("scan_scores", [&] { return launch_scan_scores(sa, st); }) != hipSuccess) return SKIPKV_EHIP;
   if (shared_lambda) {  // lambda per sequence (hidden-state similarity): no Gram matrices per head
     FuseSharedArgs fa{};

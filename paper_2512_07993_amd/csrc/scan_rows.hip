@@ -3,8 +3,7 @@
 // (more than 64 query rows) and for whatever else the single-pass scan cannot take:
 //   pass A   (reference, sum exp2) of every query row over a run of chunks, and the unit key mean of every
 //            sentence;
-//   k_row_norm   merges a head's records into log2 of each row's normaliser;
-//   pass B   the logits again, I[t] = (1/alpha) sum_a max_i softmax, and its mean over every sentence.
+//   pass B   a head's records merged into log2 of each row's normaliser (every run for itself), the logits again, I[t] = (1/alpha) sum_a max_i softmax, and its mean over every sentence.
 //
 // What bounds it.  With 160 query rows a 256-byte key costs 41 KFLOP and 160 exponentials: both passes are bound by
 // the instructions that a SIMD can issue (pass A at 160 rows: about 1250 vector and 220 matrix instructions per 64-key
@@ -29,7 +28,7 @@
 // Measured, pass A / pass B / k_row_norm in us, against one workgroup of 256 threads per chunk with the query tile in
 // LDS and a running maximum per row, which this replaces:
 //   48 layers x 8 heads, 4 x 32 K tokens, 160 rows (50 M keys, 12.9 GB):    7327 / 3926 / 196  ->  3980 / 3210 / 10
-//     ->  3830 / 3010 with the first tiles' loads in front of the loop (in it, a step without a tile made the compiler move every
+//     and where that took 4075 / 3280: 3910 / 3090 with the first tiles' loads in front of the loop (in it, a step without a tile made the compiler move every
 //     sum at each tile) and the indicator as it is now (it took shifts and masks, 13 instructions for two words)
 //   32 layers x 8 heads, 4 x 3-9 K tokens, 1 % long sentences, 64 rows:      995 /  711 /  23  ->   412 /  338 /  7
 // The whole call of the first shape with one, four, up to sixteen chunks per run: 18.0, 11.2, 10.0 ms.  Pass B alone would be
@@ -120,6 +119,27 @@ static_assert(sizeof(Chunk) == kChInts * 4, "a chunk is read as eight words");
 __device__ __forceinline__ int run_length(int n, int run_chunks) {
   const int runs = (n + run_chunks - 1) / run_chunks;
   return (n + runs - 1) / runs;
+}
+
+// log2 of the softmax normaliser of query row r of a head whose sequence has n_chunks > 0 chunks from cb on: the records
+// of the runs merged in the sequence's order.
+__device__ __forceinline__ float row_norm(const ScanArgs &a, int lh, int cb, int n_chunks, int R, int r) {
+  const int rc = a.ws.run_chunks, u0 = cb / rc, u1 = u0 + (n_chunks + rc - 1) / rc;
+  const float2 *recs = a.ws.stat_part + (int64_t)lh * a.ws.nr_max * R + r;
+  float m = kRefInit, s = 0.f;
+  for (int u = u0; u < u1; u += 8) {
+    float2 p[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) p[k] = recs[(int64_t)min(u + k, u1 - 1) * R];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      if (u + k >= u1) break;
+      const float nm = fmaxf(m, p[k].x);
+      s = s * __builtin_amdgcn_exp2f(m - nm) + p[k].y * __builtin_amdgcn_exp2f(p[k].x - nm);
+      m = nm;
+    }
+  }
+  return s > 0.f ? m + __builtin_amdgcn_logf(s) : INFINITY;
 }
 
 template <int NP, int AL, bool PASSB, bool SIMPLE>
@@ -215,12 +235,7 @@ __global__ void __launch_bounds__(64 * kWaves, 4) k_scan_rows(ScanArgs a) {
     }
 #pragma unroll
     for (int q = 0; q < SPW; ++q) {
-      if constexpr (PASSB) {
-        const float x = a.ws.row_norm[((int64_t)lh * a.batch + b) * R + rh * RW + slot_row(q)];
-        cn[q] = slot_used(q) ? x : INFINITY;
-      } else {
-        lsum[q] = 0.f;
-      }
+      if constexpr (!PASSB) lsum[q] = 0.f;
     }
     const int p_start = n_tok - min(a.protect, n_tok);  // first protected token
 
@@ -275,6 +290,20 @@ __global__ void __launch_bounds__(64 * kWaves, 4) k_scan_rows(ScanArgs a) {
     for (int i = 0; i < kAhead; ++i) {
       issue(i, 0);
       issue(i, 1);
+    }
+    if constexpr (PASSB) {
+      // log2 of the normaliser of every query row, from the records of the head's runs in the sequence's order.  Every run does
+      // this for itself, while its first tiles arrive: up to some 50 records of 8 bytes a row against 240 keys and more.  As a
+      // kernel of its own between the passes it cost every call a launch, also those that leave nothing to the
+      // two passes (one sequence of 4224 tokens, 256 heads: 232 -> 228 us; a call of 73: 70).
+      float *norm = fbuf + NPART * GT;  // (the tiles' importance takes this place behind another barrier)
+      static_assert(R <= GT, "one thread and one place per row");
+      if (tid < R) norm[tid] = row_norm(a, lh, cb, n_chunks, R, tid);
+      asm volatile("" ::: "memory");
+      lds_barrier();
+      asm volatile("" ::: "memory");
+#pragma unroll
+      for (int q = 0; q < SPW; ++q) cn[q] = slot_used(q) ? norm[rh * RW + slot_row(q)] : INFINITY;
     }
     int slot = 0;
     for (int i = 0; i < n_tiles; ++i) {
@@ -621,28 +650,13 @@ __global__ void __launch_bounds__(64 * kWaves, 4) k_scan_rows(ScanArgs a) {
   wait_vm<0>();  // the loads past the last tile still write LDS that the workgroup is about to give up
 }
 
-// log2 of the softmax normaliser of every query row: merge the records of a head's runs, in the sequence's order.
+// The same as a kernel: the fp32 passes' normalisers (their runs are single chunks).
 __global__ void __launch_bounds__(256) k_row_norm(ScanArgs a, int R) {
   const int lhb = blockIdx.x, lh = lhb / a.batch, b = lhb % a.batch;
   if (!a.force_two_pass && a.ws.seq_fused[b] && !a.ws.head_redo[lhb]) return;  // the single-pass scan computed these itself
-  const int rc = a.ws.run_chunks, u0 = a.ws.chunk_base[b] / rc, u1 = u0 + (a.ws.chunk_cnt[b] + rc - 1) / rc;
   const int r = threadIdx.x;
-  if (r >= R || u0 >= u1) return;
-  const float2 *recs = a.ws.stat_part + (int64_t)lh * a.ws.nr_max * R + r;
-  float m = kRefInit, s = 0.f;
-  for (int u = u0; u < u1; u += 8) {
-    float2 p[8];
-#pragma unroll
-    for (int k = 0; k < 8; ++k) p[k] = recs[(int64_t)min(u + k, u1 - 1) * R];
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      if (u + k >= u1) break;
-      const float nm = fmaxf(m, p[k].x);
-      s = s * __builtin_amdgcn_exp2f(m - nm) + p[k].y * __builtin_amdgcn_exp2f(p[k].x - nm);
-      m = nm;
-    }
-  }
-  a.ws.row_norm[(int64_t)lhb * R + r] = s > 0.f ? m + __builtin_amdgcn_logf(s) : INFINITY;
+  if (r >= R || a.ws.chunk_cnt[b] == 0) return;
+  a.ws.row_norm[(int64_t)lhb * R + r] = row_norm(a, lh, a.ws.chunk_base[b], a.ws.chunk_cnt[b], R, r);
 }
 
 template <int NP, int AL, bool PASSB>
@@ -651,7 +665,9 @@ hipError_t launch_rows(const ScanArgs &a, hipStream_t st) {
   if (a.ws.rows2 != RowsShape<NP, AL>::R) return hipErrorInvalidValue;
   const int64_t items = (int64_t)a.n_layers * a.n_kv_heads * a.ws.nr_max;
   if (items == 0) return hipSuccess;
-  const dim3 grid((unsigned)std::min<int64_t>(items, 4096));
+  // Where these passes are only the fallback they mostly find nothing to do, and a launch of fewer workgroups is over sooner; where
+  // there is work for them, eight to a place on the chip balance it better (pass A 1 %).
+  const dim3 grid((unsigned)std::min<int64_t>(items, a.force_two_pass ? 4096 : 1024));
   if (a.row_map == nullptr && a.stride_tok * 2 < (1 << 24))  // lane offsets by a 24-bit multiply
     hipLaunchKernelGGL((k_scan_rows<NP, AL, PASSB, true>), grid, dim3(64 * kWaves), 0, st, a);
   else
