@@ -157,6 +157,85 @@ __global__ void __launch_bounds__(256) k_compact(CompactArgs a) {
 #undef SKIPKV_STORE_TILE
 }
 
+// The same by a workgroup of eight waves per slice of a stream, which moves eight tiles at a time: all rows of a step have
+// landed in registers before the first of them is stored, so no wave overwrites what another one still has to read, and a
+// step's loads may pass the stores of the one before, which lie in front of everything they read.  For few streams,
+// whose chains of tiles would otherwise be most of the time (launch_compact says when).
+template <int ROWB, int SL, bool PAGED, bool STREAM>
+__global__ void __launch_bounds__(512) k_compact_steps(CompactArgs a) {
+  constexpr int NS = ROWB / SL;    // workgroups per stream
+  constexpr int PPR = SL / 16;     // 16-byte pieces per row slice
+  constexpr int RPI = 64 / PPR;    // rows moved by one wave-wide instruction
+  constexpr int U = 8;             // instructions per wave and step
+  constexpr int TR = U * RPI;      // rows per wave and step
+  constexpr int SCAN = 4;          // indices per thread of one look for the first row that moves
+  constexpr int ESZ = ROWB / kD;
+  __shared__ int first_s;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int64_t sid = blockIdx.x / NS, lhb = sid >> 1;
+  const int b = (int)(lhb % a.batch);
+  if (PAGED && a.seq_bad[b]) return;  // invalid block table: leave the sequence alone
+  const int lh = (int)(lhb / a.batch), l = lh / a.n_kv_heads, h = lh % a.n_kv_heads;
+  char *base = static_cast<char *>((sid & 1) ? a.v : a.k) +
+               ((int64_t)l * a.stride_layer + (int64_t)h * a.stride_head + (PAGED ? 0 : (int64_t)a.seq_off[b] * a.stride_tok)) * ESZ + (int)(blockIdx.x % NS) * SL;
+  const int64_t pitch = (PAGED ? a.map_stride : a.stride_tok) * ESZ;
+  const int32_t *kept = a.kept_idx + lhb * a.kept_stride;
+  const int32_t *srcs = PAGED ? a.src_rows + lhb * a.src_stride : kept;
+  const int32_t *rmap = PAGED ? a.row_map + a.seq_off[b] : nullptr;
+  const int nl = a.new_len[lhb];
+  if (nl > a.kept_stride || (PAGED && nl > a.src_stride)) return;  // (as in k_compact)
+  const int room = a.seq_off[b + 1] - a.seq_off[b];
+
+  int first = nl;
+  for (int k0 = 0; k0 < nl; k0 += 512 * SCAN) {
+    if (tid == 0) first_s = nl;
+    __syncthreads();
+    int mine = nl;
+#pragma unroll
+    for (int j = SCAN - 1; j >= 0; --j) {
+      const int k = k0 + 512 * j + tid;
+      if (k < nl && kept[k] != k) mine = k;
+    }
+    if (mine < nl) atomicMin(&first_s, mine);
+    __syncthreads();
+    first = first_s;
+    if (first < nl) break;
+    __syncthreads();
+  }
+
+  const int sub = lane / PPR, piece = lane % PPR;
+  int src[U], dst[U];
+  auto load_rows = [&](int k0) {  // (clamped: rows past the end are the last one)
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int k = min(k0 + wave * TR + u * RPI + sub, nl - 1);
+      src[u] = srcs[k];
+      if constexpr (PAGED) dst[u] = rmap[k];
+      else {
+        src[u] = max(0, min(src[u], room - 1));
+        dst[u] = k;
+      }
+    }
+  };
+  if (first < nl) load_rows(first);
+  for (int k0 = first; k0 < nl; k0 += 8 * TR) {
+    u32x4 x[U];
+    char *to[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      x[u] = load16<STREAM>(base + (int64_t)src[u] * pitch + piece * 16);
+      to[u] = base + (int64_t)dst[u] * pitch + piece * 16;
+    }
+    load_rows(k0 + 8 * TR);
+    asm volatile("s_waitcnt vmcnt(0)" : "+v"(x[0]), "+v"(x[1]), "+v"(x[2]), "+v"(x[3]), "+v"(x[4]), "+v"(x[5]), "+v"(x[6]), "+v"(x[7])::"memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (k0 + wave * TR + u * RPI + sub < nl) store16<STREAM>(to[u], x[u]);
+  }
+}
+
 // Paged cache: src_rows[head, k] = slot row of the head's kept token k, for k < new_len (one wave
 // per head; shared by the K and the V stream of the head).
 __global__ void __launch_bounds__(256) k_kept_rows(CompactArgs a) {
@@ -195,10 +274,41 @@ void launch_slices(const CompactArgs &a, int64_t streams, hipStream_t st) {
   else launch_slices<ROWB, SL, false>(a, streams, st);
 }
 
+template <int ROWB, bool STREAM>
+void launch_steps(const CompactArgs &a, int64_t streams, hipStream_t st) {
+  constexpr int SL = 128;
+  const dim3 grid((unsigned)(streams * (ROWB / SL)));
+  if (a.row_map)
+    hipLaunchKernelGGL((k_compact_steps<ROWB, SL, true, STREAM>), grid, dim3(512), 0, st, a);
+  else
+    hipLaunchKernelGGL((k_compact_steps<ROWB, SL, false, STREAM>), grid, dim3(512), 0, st, a);
+}
+
+template <int ROWB>
+void launch_steps(const CompactArgs &a, int64_t streams, hipStream_t st) {
+  if (streams * a.kept_stride * ROWB > kStreamBytes) launch_steps<ROWB, true>(a, streams, st);
+  else launch_steps<ROWB, false>(a, streams, st);
+}
+
 }  // namespace
 
-// A stream is a serial chain of tiles, so with few streams the chip waits for memory: rows are then split into
-// slices of 128 or 64 bytes (half a cache line: the least that a wave should take) as long as that makes no more
+// A stream is a serial chain of tiles, so with few streams the chip waits for memory.  Long chains of few streams are
+// therefore moved eight tiles at a time by workgroups of eight waves, in slices of 128 bytes.  The call alone, us, a wave
+// per slice / this, by streams and rows kept:
+//   bf16       600           1024          2500          4096           3000 (of 12000)   16000
+//     8        7.4 / 7.6     8.2 / 8.0     15.3 / 11.1   21.7 / 13.5    17.6 / 12.2       118 / 49
+//     64       7.5 / 8.6     9.4 / 9.5     24.4 / 18.1   36.1 / 24.1    28.8 / 21.8       262 / 106
+//     128      7.7 / 9.6     11.8 / 11.8   28.7 / 29.6   41.3 / 40.4    39.3 / 35.7       289 / 192
+//     256      12.9 / 13.0   21.6 / 21.7   53.8 / 53.1   97.1 / 88.1    81.6 / 70.9
+//     512      -             38.3 / 41.2   -             175 / 174
+//   paged 64   17.9 / 19.2   23.5 / 22.3   54.5 / 46.7   76.9 / 62.7    63.9 / 54.3
+//   paged 256  24.6 / 24.3   35.9 / 35.4   79.0 / 78.0   144 / 135      124 / 114
+//   fp32 rows are twice as long: 64 streams of them behave like 128 of bf16
+// Slices of 64 bytes take this up to twice as long from 64 streams on, and whole rows half as much again at 8.  Streams are
+// counted in columns of 256 bytes; the caller's row of indices bounds the rows.
+constexpr int64_t kStepColumns = 64, kStepRows = 1024, kStepColumnsLong = 256, kStepRowsLong = 2560;
+
+// Otherwise rows are split into slices of 128 or 64 bytes (half a cache line: the least that a wave should take) as long as that makes no more
 // than 1024 waves, four per CU.  More waves than that gain nothing and the smaller pieces cost: whole step of 8 heads
 // per layer and 4224 tokens, us, with rows in 1 / 2 / 4 / 8 slices:
 //   bf16   32 streams: 154 / 116 / 97    128: 208 / 165 / 148    256: 288 / 217 / 199    512: 370 / 362 / 406
@@ -209,7 +319,11 @@ hipError_t launch_compact(const CompactArgs &a, hipStream_t st) {
   if (streams == 0) return hipSuccess;
   if (a.row_map) hipLaunchKernelGGL(k_kept_rows, dim3((unsigned)((heads + 3) / 4)), dim3(256), 0, st, a);
   const int64_t fit = 1024 / streams;  // slices that make at most 1024 waves
-  if (a.dtype == SKIPKV_BF16) {
+  const int64_t columns = streams * (a.dtype == SKIPKV_BF16 ? 1 : 2);
+  if (columns <= kStepColumns ? a.kept_stride >= kStepRows : columns <= kStepColumnsLong && a.kept_stride >= kStepRowsLong) {
+    if (a.dtype == SKIPKV_BF16) launch_steps<256>(a, streams, st);
+    else launch_steps<512>(a, streams, st);
+  } else if (a.dtype == SKIPKV_BF16) {
     if (fit >= 4) launch_slices<256, 64>(a, streams, st);
     else if (fit >= 2) launch_slices<256, 128>(a, streams, st);
     else launch_slices<256, 256>(a, streams, st);
