@@ -8,29 +8,30 @@
 // (hi + lo)(hi + lo)^T without its lo*lo term (below 2^-16 of a unit cosine, i.e. fp32-grade
 // for the comparison with tau and for the ranking): three bf16 MFMAs, small terms first.
 // One workgroup owns kRowBlock = 128 rows (32 per wave, A operands in registers) and walks the
-// 64-column blocks at and to the right of the diagonal, staged through LDS and shared by the 4
-// waves; the next column block is fetched into registers while the current one is multiplied.
+// column blocks at and to the right of the diagonal, which go HBM -> LDS directly, one block ahead, and are shared by the 4
+// waves.
 //
-// Bound by instruction issue: by the counters the matrix pipe and the vector pipe take half of a SIMD's cycles each
-// and hardly overlap.  So the fetch has no branches and 32-bit offsets (4 x min, shift-or), and the masks of the
-// maxima are only there for tiles on the diagonal or at the end, by wave-uniform branches.  48 layers x 8 heads, 4 x
-// 1650 sentences: 1560 us (1710 with masked fetch, masks everywhere); 32 x 8, 16 x 460: 495 (550).
-#include "common.h"
+// Bound by instruction issue and, where it runs long, by the chip's power (1.74 GHz; matrix cores 57 % of a SIMD's cycles, vector
+// pipe 22 %).  The fetch has no branches and 32-bit offsets, and the masks of the
+// maxima are only there for tiles on the diagonal or at the end, by wave-uniform branches.  Blocks of 64 columns, fetched
+// through 32 registers and padded in LDS, left room for three waves per SIMD and met bank conflicts in 40 % of the LDS
+// cycles; blocks of 32 columns, swizzled, in two buffers (32 KB) leave room for four: 48 layers x 8 heads, 4 x 1650 sentences
+// 1590 -> 1410 us, 32 x 8, 16 x 460 500 -> 440.  The same with three buffers and three waves was 2 % slower than before.
+#include "scan_dev.h"
 
 namespace skipkv {
 
 namespace {
 
-constexpr int LSTR = 272;    // bytes per staged embedding row (256 + 16 so that 16-byte reads of 8 rows hit distinct banks)
-constexpr int kColBlock = 64;
+constexpr int kColBlock = 32;
+constexpr int kColSlots = 2;                // column blocks in LDS
+constexpr int kColAhead = kColSlots - 1;    // column blocks that are loaded ahead of the one multiplied
+constexpr int kColLoads = kColBlock * 2 / 16;  // direct loads of a wave per block: 4 rows each, hi and lo
 constexpr int kRowTiles = kRowBlock / 64;  // 16-row tiles per wave
 static_assert(kRowBlock % 64 == 0, "four waves, whole tiles");
 
-typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;  // (uint4 in arrays around a loop goes to scratch)
-
-__global__ void __launch_bounds__(256, 3) k_cosine(CosineArgs a) {
-  __shared__ __align__(16) char col_hi[kColBlock * LSTR];
-  __shared__ __align__(16) char col_lo[kColBlock * LSTR];
+__global__ void __launch_bounds__(256, 4) k_cosine(CosineArgs a) {
+  __shared__ __align__(256) char cols[kColSlots][2][kColBlock * 256];  // hi and lo rows, 16-byte pieces swizzled (swz16)
 
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, c16 = lane & 15, g = lane >> 4;
   // the grid is sized for the largest possible number of row blocks; the work items that exist
@@ -86,30 +87,33 @@ __global__ void __launch_bounds__(256, 3) k_cosine(CosineArgs a) {
 #pragma unroll
     for (int j = 0; j < 4; ++j) rmax[t][j] = -INFINITY;
 
-  // a column block is 2 x 64 rows x 16 pieces of 16 bytes: 8 pieces per thread.  Rows past the end re-read the
-  // last one (their columns are masked below): no branch, and 32-bit offsets from a scalar base.
-  u32x4 pre[8];
-  auto fetch = [&](int jb) {
+  // Column blocks go to LDS directly.  Rows past the end re-read the last one (their columns are masked below), and so do
+  // blocks past the last: no branch, the same count every time, 32-bit offsets from scalar bases.
+  const uint64_t hi_s = scalar64(hi), lo_s = scalar64(lo);
+  auto issue = [&](int slot, int jb) {
 #pragma unroll
-    for (int it = 0; it < 4; ++it) {
-      const uint32_t o = (uint32_t)min(jb + 16 * it + (tid >> 4), n_sent - 1) * 256u + (uint32_t)(tid & 15) * 16u;
-      pre[it] = *reinterpret_cast<const u32x4 *>(hi + o);
-      pre[4 + it] = *reinterpret_cast<const u32x4 *>(lo + o);
+    for (int it = 0; it < kColLoads / 2; ++it) {
+      const int row = kColBlock / 4 * wave + 4 * it + g;
+      const uint32_t o = (uint32_t)min(jb + row, n_sent - 1) * 256u + ((uint32_t)(c16 ^ swz16(row & 15)) << 4);
+      char *dst = &cols[slot][0][(kColBlock / 4 * wave + 4 * it) * 256];
+      load_to_lds_16_sbase(hi_s, o, dst);
+      load_to_lds_16_sbase(lo_s, o, dst + kColBlock * 256);
     }
   };
-  auto commit = [&]() {
-#pragma unroll
-    for (int it = 0; it < 8; ++it) {
-      const int idx = it * 256 + tid, half = idx >> 10, rem = idx & 1023, row = rem >> 4, piece = rem & 15;
-      *reinterpret_cast<u32x4 *>((half ? col_lo : col_hi) + row * LSTR + piece * 16) = pre[it];
-    }
-  };
+  const uint32_t b_off = c16 * 256 + (((4 * g) ^ swz16(c16)) << 4);  // column fragment: row c16 of a tile, piece 4g + kk
 
-  if (r0 < n_sent) fetch(r0);
+  if (r0 >= n_sent) return;
+#pragma unroll
+  for (int i = 0; i < kColAhead; ++i) issue(i, r0 + i * kColBlock);
+  int slot = 0;
   for (int jb = r0; jb < n_sent; jb += kColBlock) {
-    commit();
-    __syncthreads();
-    if (jb + kColBlock < n_sent) fetch(jb + kColBlock);  // lands while this block is multiplied
+    wait_vm<(kColAhead - 1) * kColLoads>();
+    asm volatile("" ::: "memory");
+    lds_barrier();  // the block is there for all waves, and all are done with the one before it
+    asm volatile("" ::: "memory");
+    const uint32_t block_a = lds_addr(cols[slot][0]) + b_off;
+    issue(slot == 0 ? kColSlots - 1 : slot - 1, jb + kColAhead * kColBlock);
+    slot = slot + 1 == kColSlots ? 0 : slot + 1;
 #pragma unroll
     for (int ct = 0; ct < kColBlock / 16; ++ct) {
       const int cbase = jb + 16 * ct;
@@ -121,8 +125,9 @@ __global__ void __launch_bounds__(256, 3) k_cosine(CosineArgs a) {
       for (int t = 0; t < kRowTiles; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int kk = 0; kk < 4; ++kk) {
-        const bf16x8 b_hi = *reinterpret_cast<const bf16x8 *>(col_hi + (16 * ct + c16) * LSTR + g * 64 + kk * 16);
-        const bf16x8 b_lo = *reinterpret_cast<const bf16x8 *>(col_lo + (16 * ct + c16) * LSTR + g * 64 + kk * 16);
+        const uint32_t b_a = (block_a + ct * 4096) ^ (kk << 4);
+        const bf16x8 b_hi = *reinterpret_cast<const __attribute__((address_space(3))) bf16x8 *>((uintptr_t)b_a);
+        const bf16x8 b_lo = *reinterpret_cast<const __attribute__((address_space(3))) bf16x8 *>((uintptr_t)(b_a + kColBlock * 256));
 #pragma unroll
         for (int t = 0; t < kRowTiles; ++t) {
           acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a_lo[t][kk], b_hi, acc[t], 0, 0, 0);
@@ -147,8 +152,8 @@ __global__ void __launch_bounds__(256, 3) k_cosine(CosineArgs a) {
         }
       }
     }
-    __syncthreads();
   }
+  wait_vm<0>();  // the loads past the last block still write LDS that the workgroup is about to give up
 
   // row maxima across the 16 column lanes, then the fused score of Eq. 6: lane c16 = 4t + j of
   // a lane group finishes row (tile t, register j), with the inputs it fetched at the start
