@@ -159,9 +159,9 @@ struct Timer {
 
 int do_score(Timer &tm, const skipkv_cache *c, const skipkv_params *p, const RowLayout &rl, const void *q_obs,
              const float *tok_red, float *sent_score, float *sent_lambda, float *tok_imp, void *ws, hipStream_t st,
-             const HeadView &hv = HeadView(), const float *shared_lambda = nullptr) {
+             const HeadView &hv, const float *shared_lambda, bool hdr_reset) {
   const Workspace w = carve(c, rl, ws);
-  PlanArgs pa{c->seq_off, c->sent_ptr, c->sent_off, c->batch, c->n_layers * c->n_kv_heads, w, p->dev_status, hv.len, hv.cnt, c->total_sentences};
+  PlanArgs pa{c->seq_off, c->sent_ptr, c->sent_off, c->batch, c->n_layers * c->n_kv_heads, w, p->dev_status, hv.len, hv.cnt, c->total_sentences, hdr_reset};
   if (tm.run("plan", [&] { return launch_plan(pa, st); }) != hipSuccess) return SKIPKV_EHIP;
   ScanArgs sa{};
   sa.k = c->k;
@@ -577,26 +577,29 @@ int run_call(const Call &k) {
   Timer tm(p->profile, st);
   char *ws = static_cast<char *>(k.ws);
   const int32_t n_lh = c->n_layers * c->n_kv_heads;
+  char *step_ws = ws + L.head_bytes;
+  // the plan's header, for the kernel that comes before the plan (if one does) to reset
+  PlanHeader *hdr = (k.stages & kScore) && (k.per_head || (k.paged && c->batch > 0 && n_lh > 0)) ? carve(&L.c, L.rl, step_ws).hdr : nullptr;
+  int32_t *bad = k.paged ? reinterpret_cast<int32_t *>(step_ws + L.step_bytes + L.map_bytes) : nullptr;
   if (k.per_head &&
       launch_virtual_layout(c->seq_off, c->sent_ptr, c->batch, n_lh, c->total_tokens, c->total_sentences, L.v_seq_off,
-                            L.v_sent_ptr, st) != hipSuccess)
+                            L.v_sent_ptr, bad, hdr, st) != hipSuccess)
     return SKIPKV_EHIP;
-  char *step_ws = ws + L.head_bytes;
   int32_t *row_map = nullptr, *seq_bad = nullptr, *src_rows = nullptr;
   if (k.paged) {
     row_map = reinterpret_cast<int32_t *>(step_ws + L.step_bytes);
-    seq_bad = reinterpret_cast<int32_t *>(step_ws + L.step_bytes + L.map_bytes);
+    seq_bad = bad;
     src_rows = reinterpret_cast<int32_t *>(step_ws + L.step_bytes + L.map_bytes + L.bad_bytes);
     const skipkv_paging *pg = k.paging;
     RowMapArgs ra{c->seq_off, pg->block_table, c->batch, pg->table_stride, pg->block_size, pg->n_blocks,
                   k.per_head ? n_lh : 1, k.per_head ? c->n_kv_heads : 1, c->total_tokens, L.unit_layer, L.unit_head,
-                  L.unit_block, L.unit_tok, row_map, seq_bad, p->dev_status};
+                  L.unit_block, L.unit_tok, row_map, seq_bad, p->dev_status, k.per_head, k.per_head ? nullptr : hdr};
     if (tm.run("row_map", [&] { return launch_row_map(ra, st); }) != hipSuccess) return SKIPKV_EHIP;
     L.hv.row_map = row_map;
   }
   if (k.stages & kScore) {
     rc = do_score(tm, &L.c, p, L.rl, k.q_obs, k.tok_red, k.sent_score, k.sent_lambda, k.tok_imp, step_ws, st, L.hv,
-                  k.shared ? k.shared_lambda : nullptr);
+                  k.shared ? k.shared_lambda : nullptr, hdr != nullptr);
     if (rc) return rc;
   }
   if (k.stages & kSelect) {

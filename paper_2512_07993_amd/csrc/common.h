@@ -162,7 +162,7 @@ struct RangesIdsArgs {
 hipError_t launch_ranges_ids_select(const RangesIdsArgs &a, hipStream_t st);
 hipError_t launch_ranges_ids_append(const RangesIdsArgs &a, hipStream_t st);
 hipError_t launch_virtual_layout(const int32_t *seq_off, const int32_t *sent_ptr, int32_t batch, int32_t n_lh, int32_t total_tokens,
-                                 int32_t total_sentences, int32_t *v_seq_off, int32_t *v_sent_ptr, hipStream_t st);
+                                 int32_t total_sentences, int32_t *v_seq_off, int32_t *v_sent_ptr, int32_t *seq_bad, PlanHeader *hdr, hipStream_t st);
 
 // Length and sentence count of sequence b: explicit where given, else from the CSR arrays.
 __device__ __forceinline__ int seq_tokens(const int32_t *seq_off, const int32_t *len, int b) {
@@ -179,6 +179,7 @@ struct PlanArgs {
   int32_t *dev_status;
   const int32_t *len, *cnt;  // nullable [batch]: explicit lengths and sentence counts (then seq_off / sent_ptr only give capacities)
   int32_t total_sentences;
+  bool hdr_reset = false;    // an earlier kernel of the call has reset the header
   bool alone = false;        // one block in all: it writes the header itself (set by launch_plan, as the next one)
   bool preset = false;       // the blocks mark the statistics records of their sequences
 };
@@ -282,6 +283,8 @@ struct RowMapArgs {
   int32_t n_lh, n_kv_heads, total_tokens;
   int64_t unit_layer, unit_head, unit_block, unit_tok;
   int32_t *row_map, *seq_bad, *dev_status;
+  bool flags_reset = false;   // an earlier kernel of the call has cleared seq_bad
+  PlanHeader *hdr = nullptr;  // reset together with seq_bad
 };
 hipError_t launch_row_map(const RowMapArgs &a, hipStream_t st);
 
@@ -343,6 +346,13 @@ hipError_t launch_steer_strength(const int32_t *n_nonexec, float alpha0, float g
 
 // ---- device helpers -----------------------------------------------------------------------
 #if defined(__HIPCC__)
+// What the plan draws its ranges from, and what the scans count in, at the start of a call.
+__device__ __forceinline__ void reset_header(PlanHeader *hdr) {
+  hdr->ranges = 0;
+  hdr->n_unfused = 0;
+  hdr->abort = 0;
+}
+
 __device__ __forceinline__ float bf16_bits_to_f32(uint32_t b) { return __uint_as_float(b << 16); }
 
 // fp32 -> bf16 bits, round to nearest even (finite inputs).

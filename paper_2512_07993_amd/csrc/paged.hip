@@ -7,8 +7,9 @@
 
 namespace skipkv {
 
-__global__ void k_row_map_reset(int32_t *seq_bad, int n) {
+__global__ void k_row_map_reset(int32_t *seq_bad, int n, PlanHeader *hdr) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i == 0 && hdr) reset_header(hdr);
   if (i < n) seq_bad[i] = 0;
 }
 
@@ -50,7 +51,7 @@ __global__ void __launch_bounds__(256) k_row_map(RowMapArgs a, int heads) {
 hipError_t launch_row_map(const RowMapArgs &a, hipStream_t st) {
   if (a.batch == 0 || a.n_lh == 0) return hipSuccess;
   const int n_flags = a.n_lh * a.batch;
-  hipLaunchKernelGGL(k_row_map_reset, dim3((n_flags + 255) / 256), dim3(256), 0, st, a.seq_bad, n_flags);
+  if (!a.flags_reset) hipLaunchKernelGGL(k_row_map_reset, dim3((n_flags + 255) / 256), dim3(256), 0, st, a.seq_bad, n_flags, a.hdr);
   // Maps per head: eight workgroups per sequence, each for as many heads, up to eight, as leave some 8192 in all: with one
   // for every head they are bound by their number.  They are not dealt out by the mean length: one sequence may be much
   // longer than the others.  With their reset, us, one head / the heads of this rule each:

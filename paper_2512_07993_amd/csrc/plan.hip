@@ -9,11 +9,7 @@
 namespace skipkv {
 
 __global__ void k_plan_reset(PlanHeader *hdr) {
-  if (threadIdx.x == 0) {
-    hdr->ranges = 0;
-    hdr->n_unfused = 0;
-    hdr->abort = 0;
-  }
+  if (threadIdx.x == 0) reset_header(hdr);
 }
 
 // End (exclusive sentence index) of the run of whole sentences that starts at sentence `start` and
@@ -288,7 +284,7 @@ hipError_t launch_plan(const PlanArgs &args, hipStream_t st) {
   // up to about 32 records' pieces per thread of a plan block: cheaper than a launch of their own (us, whole
   // score call of 8 heads and 1152 tokens: bf16 38.5 -> 34.5, fp32 44.7 -> 40.1 without the two launches)
   a.preset = a.n_lh * cap16 <= 8192 * (int64_t)a.batch && a.batch < 1024;
-  if (!a.alone) hipLaunchKernelGGL(k_plan_reset, dim3(1), dim3(64), 0, st, a.ws.hdr);
+  if (!a.alone && !a.hdr_reset) hipLaunchKernelGGL(k_plan_reset, dim3(1), dim3(64), 0, st, a.ws.hdr);
   if (a.batch > 0) {
     // A wave per sequence from where a block each would fill the chip (four blocks per CU), unless the sentences that
     // there is room for are so many on average that blocks would do their sequences one after the other.  us, a wave / a
