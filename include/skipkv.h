@@ -143,7 +143,8 @@ int skipkv_workspace_bytes(const skipkv_cache *cache, const skipkv_params *param
  * tok_importance  device out [n_layers, n_kv_heads, total_tokens] fp32, or NULL.
  * The key scan reads K once where it can (query rows n * obs_window <= 64 after padding, no
  * sentence longer than 512 tokens, at most 256 work items of up to 512 tokens per sequence, i.e.
- * about 120000 tokens) and twice otherwise.  Its single-pass form is a persistent grid that must
+ * about 120000 tokens; and where sentences of more than 128 tokens, which are cut into spans of 128
+ * within one item, do not leave the items less than about 45 % full) and twice otherwise.  Its single-pass form is a persistent grid that must
  * have the GPU's compute units to itself (work of other streams running at the same time can
  * only be waited out).  It waits across workgroups; the wait is bounded (params->spin_limit): on
  * expiry SKIPKV_DEV_TIMEOUT is OR-ed into dev_status, every later wait of the call gives up at

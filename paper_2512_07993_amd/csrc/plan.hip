@@ -32,7 +32,8 @@ __device__ __forceinline__ int run_end(const int *off, int start, int n_sent, in
 // What bounds a plan: with few sequences the latency of the serial walks along the runs (an LDS read per step, 300 spans
 // in 32 K tokens), so the two walks run side by side; with thousands of them (every head a sequence of its own) the
 // atomic on the one word that hands out the ranges, 13 ns each, hence one for four sequences.  LDS and registers
-// are the same for both forms: a wave takes what fits a quarter of the tables (kMaxSent<1> sentences), longer
+// are the same for both forms: a wave takes what fits a quarter of the tables (kMaxSent<1> sentences; with cut sentences as
+// many spans as a quarter holds, so that a sequence takes the same scan in every batch), longer
 // sequences are done by the block afterwards.  Measured, against a block
 // per sequence with both walks in one thread: 7168 sequences of 1.1 K tokens 95 -> 32 us, 4096 of 2.1 K 60 -> 23,
 // 4 of 32 K 43 -> 28, 16 of 2-16 K 23 -> 17.
@@ -53,6 +54,7 @@ struct PlanShared {
     int n_chunks, n_spans;
     unsigned long long counts, old;  // of the sequence, and drawn before it (packed as in the header)
   } seq[4];
+  int later[4];  // a wave's sequence is left to the whole block
 };
 
 // b < 0: the group has no sequence (in this pass), but takes part in the barriers.
@@ -63,7 +65,7 @@ struct PlanShared {
 template <int WPS>
 __device__ __forceinline__ void plan_sequences(const PlanArgs &a, PlanShared &sh, int b, int gt, int grp) {
   constexpr int G = 64 * WPS, PART = SKIPKV_MAX_SENTENCES / 4;
-  static_assert(SKIPKV_MAX_SENTENCES <= 65535, "sentence indices are kept in 16 bits here");
+  static_assert(SKIPKV_MAX_SENTENCES < 1 << 13, "sentence indices are kept in 16 bits here, in 13 beside the number of a piece");
   int *s_off = sh.off + grp * PART;
   uint16_t *s_chunk = sh.chunk + grp * PART, *s_span = sh.span + grp * PART;
   constexpr int kPieces = kItemSpans * kFuseMaxItems / (4 / WPS);  // spans of a sequence that the group's part of the table holds
@@ -76,6 +78,7 @@ __device__ __forceinline__ void plan_sequences(const PlanArgs &a, PlanShared &sh
 
   int tok0 = 0, n_tok = 0, sp = 0, n_sent = 0;
   bool cut = false;  // some sentence has several spans
+  int most = 0;      // spans of a sequence like that, at most
   bool ok = b >= 0;
   if (ok) {
     tok0 = a.seq_off[b];
@@ -104,6 +107,11 @@ __device__ __forceinline__ void plan_sequences(const PlanArgs &a, PlanShared &sh
     longer = any(longer);
     cut = longer;
     ok = !reject && !bad;
+    // (no sequence gets more items than its tokens and sentences make of ordinary spans at most: that is what there is room for)
+    if (ok && cut) most = min(kItemSpans * kFuseMaxItems, kItemSpans * ((2 * (n_tok / a.ws.span_cap + n_sent / kSpanMaxSent) + 1) / kItemSpans + 1));
+    const bool later = most > kPieces;
+    if (WPS == 1 && gt == 0) sh.later[grp] = later;
+    ok = ok && !later;
     for (int lh = gt; lh < a.n_lh; lh += G) a.ws.head_redo[(int64_t)lh * a.batch + b] = 0;
     sync();
     if (ok) {
@@ -123,8 +131,6 @@ __device__ __forceinline__ void plan_sequences(const PlanArgs &a, PlanShared &sh
       uint16_t *at = gt == 0 ? s_span : s_chunk;
       int n = 0;
       if (gt == 0 && longer) {
-        // (no sequence gets more items than its tokens and sentences make of ordinary spans at most: that is what there is room for)
-        const int most = min(kPieces, kItemSpans * ((2 * (n_tok / a.ws.span_cap + n_sent / kSpanMaxSent) + 1) / kItemSpans + 1));
         bool fits = true;
         for (int start = 0; start < n_sent && fits;) {
           const int p = max(1, (s_off[start + 1] - s_off[start] + kSpanCap - 1) / kSpanCap);
@@ -154,13 +160,14 @@ __device__ __forceinline__ void plan_sequences(const PlanArgs &a, PlanShared &sh
         const int n_items = (me.n_spans + kItemSpans - 1) / kItemSpans, nrb = (n_sent + kRowBlock - 1) / kRowBlock;
         const int rc = a.ws.run_chunks;  // whole runs: the sequence's chunks start at a multiple of their length
         counts = (unsigned long long)((me.n_chunks + rc - 1) / rc * rc) | ((unsigned long long)n_items << kHdrItemShift) | ((unsigned long long)nrb << kHdrRbShift);
-      } else if (a.dev_status) {
+      } else if (a.dev_status && !later) {
         atomicOr(a.dev_status, reject ? SKIPKV_DEV_TOO_MANY_SENT : SKIPKV_DEV_BAD_OFFSETS);
       }
       me.counts = counts;
     }
   } else if (gt == 0) {
     sh.seq[grp].counts = 0;
+    if (WPS == 1) sh.later[grp] = 0;
   }
   __syncthreads();
   if (threadIdx.x == 0) {
@@ -257,10 +264,10 @@ __global__ void __launch_bounds__(256) k_plan(PlanArgs a) {
     const int b = blockIdx.x * 4 + wave;
     const bool mine = b < a.batch && seq_sentences(a.sent_ptr, a.cnt, b) <= kMaxSent<1>;
     plan_sequences<1>(a, sh, mine ? b : -1, lane, wave);
-    for (int w = 0; w < 4; ++w) {  // the longer ones, one after the other, by the whole block
+    for (int w = 0; w < 4; ++w) {  // those that were left, one after the other, by the whole block
       const int bl = blockIdx.x * 4 + w;
       if (bl >= a.batch) break;
-      if (seq_sentences(a.sent_ptr, a.cnt, bl) <= kMaxSent<1>) continue;
+      if (seq_sentences(a.sent_ptr, a.cnt, bl) <= kMaxSent<1> && !sh.later[w]) continue;
       __syncthreads();  // everybody is done with the tables
       plan_sequences<4>(a, sh, bl, threadIdx.x, 0);
     }

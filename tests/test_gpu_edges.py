@@ -548,7 +548,8 @@ def test_plans_of_a_thousand_sequences_equal_those_of_a_few(most):
     offsets = [np.concatenate([[0], np.cumsum(rng.integers(1, 30, size=int(rng.integers(1, most))))]).tolist() for _ in range(1030)]
     for i, n in ((3, 1023), (5, 1024), (6, 1500), (1029, 300)):
         offsets[i] = np.concatenate([[0], np.cumsum(rng.integers(1, 6, size=n))]).tolist()
-    offsets[8] = [0, 200, 210, 500, 800]            # sentences that the single-pass scan does not take
+    offsets[7] = np.concatenate([[0], np.cumsum([40] * 500 + [300] + [40] * 500)]).tolist()  # cut, and more spans than a wave's share of the table
+    offsets[8] = [0, 200, 210, 500, 800]            # cut
     offsets[9] = [0]                                # an empty sequence
     offsets[10] = [0, 7, 7, 20]                     # not ascending: reported, the others are not affected
     st = _structure(offsets)
