@@ -53,7 +53,8 @@ __global__ void __launch_bounds__(256) k_scan(ScanArgs a) {
   const uint32_t n_items = (uint32_t)n_lh * (uint32_t)n_chunks;
   const int n = a.n_q_heads / a.n_kv_heads;
   for (uint32_t item = blockIdx.x; item < n_items; item += gridDim.x) {
-  const int lh = item / n_chunks, c = item % n_chunks;
+  int lh, c;
+  two_pass_item(item, n_chunks, lh, c);
   const Chunk ch = a.ws.chunks[c];
   const int b = ch.b, ns = ch.ns;
   if (!a.force_two_pass && a.ws.seq_fused[b] && !a.ws.head_redo[(int64_t)lh * a.batch + b]) continue;  // done by the single-pass scan

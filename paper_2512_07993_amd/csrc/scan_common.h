@@ -11,6 +11,17 @@ constexpr float kScale2 = 0.08838834764831845f * 1.4426950408889634f;  // log2(e
 constexpr float kMinRowSum = 1e-30f, kMaxRowSum = 1e30f;
 constexpr float kRescaleSlack = 16.f;  // a lane's reference is refreshed when a logit exceeds it by this much (log2 units)
 
+// Item `item` of a two-pass scan: the head, and which of the units (runs, chunks) of all sequences.  Each head's units are
+// taken from another place on, a golden ratio of them further than the head's before: the number of workgroups is often a multiple
+// of the units, and a workgroup would meet the same ones in every head it comes to, all of them or none left by the single-pass
+// scan.  (Bf16, 32 layers x 8 heads, us, both passes, all heads from the first unit on / like this: 16 sequences of 4 K tokens, one of
+// them left: 1237 / 217; 8 of 4 K, four left: 807 / 347; everything left or forced: the same.)
+__device__ __forceinline__ void two_pass_item(uint32_t item, uint32_t units, int &lh, int &unit) {
+  const uint32_t head = item / units, x = item - head * units + (uint32_t)(((uint64_t)(head * 0x9E3779B9u) * units) >> 32);
+  lh = (int)head;
+  unit = (int)(x >= units ? x - units : x);
+}
+
 template <int DT>
 struct Tr;
 template <>

@@ -171,7 +171,8 @@ __global__ void __launch_bounds__(64 * kWaves, 4) k_scan_rows(ScanArgs a) {
     // ---- a run: chunks c0 .. c1 - 1 of a sequence, filed under the run_chunks places of the chunk list that the plan
     // keeps for it.  Runs are counted from the sequence's first chunk, wherever its chunks stand in the list: that is up to
     // the order in which the plan's blocks drew their ranges, and a head's sums must not depend on it.
-    const int lh = item / n_runs, run = (int)(item % n_runs);
+    int lh, run;
+    two_pass_item(item, n_runs, lh, run);
     const int b = chunks_c[(int64_t)run * run_chunks * kChInts + kChB];
     const int cb = chunk_base_c[b], n_chunks = chunk_cnt_c[b], len = run_length(n_chunks, run_chunks);
     const int c0 = cb + (run - cb / run_chunks) * len, c1 = min(c0 + len, cb + n_chunks);

@@ -258,3 +258,34 @@ def test_sentences_that_begin_and_end_anywhere_in_a_tile(group, alpha):
             # unit components carry 16 bits: a cosine is within 2 * 2^-16 of the exact one (typically 1e-6); a token too many or
             # too few moves an embedding of n tokens by 1 / sqrt(n) > 0.03
             np.testing.assert_allclose(lam[0, h, s0:s0 + n - 1].numpy(), want[:-1].numpy(), rtol=0, atol=3.1e-5)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("L,H", [(1, 1), (1, 3), (8, 8), (43, 6)])
+def test_sequences_that_the_single_pass_scan_leaves_get_what_the_two_pass_scan_alone_gives(dtype, L, H):
+    # A head's runs (fp32: chunks) are taken from another one on than the head's before: each of them once, whatever their number
+    # and that of the workgroups.  Here two to five of eight sequences are left, for a sentence that no item holds.
+    rng = np.random.default_rng(L + H)
+    offsets = []
+    for i, n in enumerate([900, 2048, 300, 1500, 700, 2600, 40, 1025]):
+        off = [0] if i % 2 and n < 1026 + 500 * (L % 3) else [0, 600]
+        while off[-1] < n:
+            off.append(min(n, off[-1] + int(rng.integers(1, 50))))
+        offsets.append(off)
+    st = _structure(offsets)
+    cfg = W.Config("left", 9, 8, L, H, 4 * H, dtype, 0, 0, 96, 8, 40, 16.0, 0.0)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(L)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    k = torch.randn((L, H, st.total_tokens, 128), generator=g, device="cuda").to(dt)
+    q = torch.randn((L, 8, 4 * H, 8, 128), generator=g, device="cuda").to(dt)
+    got, two = _score(cfg, st, k, q), _score(cfg, st, k, q, TWO)
+    assert not any(torch.isnan(x).any() for x in got)
+    for b, off in enumerate(offsets):
+        s = slice(st.sent_base(b), st.sent_base(b) + int(st.n_sent[b]))
+        t = slice(int(st.seq_off[b]), int(st.seq_off[b + 1]))
+        for x, y, at in zip(got, two, (s, s, t)):
+            if off[1] == 600:
+                assert torch.equal(_bits(x[..., at]), _bits(y[..., at]))
+            else:  # fp32 sums in another order
+                assert torch.allclose(x[..., at], y[..., at], rtol=1e-5, atol=1e-5)
