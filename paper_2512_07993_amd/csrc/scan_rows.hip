@@ -666,9 +666,13 @@ hipError_t launch_rows(const ScanArgs &a, hipStream_t st) {
   if (a.ws.rows2 != RowsShape<NP, AL>::R) return hipErrorInvalidValue;
   const int64_t items = (int64_t)a.n_layers * a.n_kv_heads * a.ws.nr_max;
   if (items == 0) return hipSuccess;
-  // Where these passes are only the fallback they mostly find nothing to do, and a launch of fewer workgroups is over sooner; where
-  // there is work for them, eight to a place on the chip balance it better (pass A 1 %).
-  const dim3 grid((unsigned)std::min<int64_t>(items, a.force_two_pass ? 4096 : 1024));
+  // Eight workgroups to a place on the chip balance the passes where there is work for them.  Where they are only the fallback they
+  // mostly find nothing to do, and a launch of fewer workgroups is over sooner, which small calls notice.  Whole score call, us, 1024 /
+  // 4096 workgroups, 128 tokens to a sentence at most / sequences with longer ones: one sequence of 4224 tokens, 256 heads (1.1 M keys)
+  // 101.3 / 102.4, of 8192 (2.1 M) - and 318.9 / 319.5;  4 of 4224 (4.3 M) 352.4 / 354.9;  16 of 3000, 128 heads (6.1 M) - and 823 / 776;
+  // 4 of 8192, 256 heads (8.4 M) - and 1009 / 962;  16 of 4096 (16.8 M) 1236 / 1241 and 1901 / 1777.
+  const bool many = a.force_two_pass || (int64_t)a.n_layers * a.n_kv_heads * a.total_tokens >= 6000000;
+  const dim3 grid((unsigned)std::min<int64_t>(items, many ? 4096 : 1024));
   if (a.row_map == nullptr && a.stride_tok * 2 < (1 << 24))  // lane offsets by a 24-bit multiply
     hipLaunchKernelGGL((k_scan_rows<NP, AL, PASSB, true>), grid, dim3(64 * kWaves), 0, st, a);
   else

@@ -261,7 +261,7 @@ def test_sentences_that_begin_and_end_anywhere_in_a_tile(group, alpha):
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
-@pytest.mark.parametrize("L,H", [(1, 1), (1, 3), (8, 8), (43, 6)])
+@pytest.mark.parametrize("L,H", [(1, 1), (1, 3), (8, 8), (43, 6), (96, 8)])  # the last one: 4096 workgroups instead of 1024
 def test_sequences_that_the_single_pass_scan_leaves_get_what_the_two_pass_scan_alone_gives(dtype, L, H):
     # A head's runs (fp32: chunks) are taken from another one on than the head's before: each of them once, whatever their number
     # and that of the workgroups.  Here two to five of eight sequences are left, for a sentence that no item holds.
