@@ -195,9 +195,10 @@ int do_score(Timer &tm, const skipkv_cache *c, const skipkv_params *p, const Row
   sa.virt_hk = hv.virt_hk;
   sa.virt_b = hv.virt_b;
   sa.no_pool = shared_lambda != nullptr;
+  sa.norms_apart = scan_norms_apart(sa);
   if (tm.run("scan_fused", [&] { return launch_scan_fused(sa, st); }) != hipSuccess) return SKIPKV_EHIP;
   if (tm.run("scan_stats", [&] { return launch_scan_stats(sa, st); }) != hipSuccess) return SKIPKV_EHIP;
-  if (sa.dtype == SKIPKV_F32 && tm.run("row_norm", [&] { return launch_row_norm(sa, st); }) != hipSuccess) return SKIPKV_EHIP;
+  if (sa.norms_apart && tm.run("row_norm", [&] { return launch_row_norm(sa, st); }) != hipSuccess) return SKIPKV_EHIP;
   if (tm.run("scan_scores", [&] { return launch_scan_scores(sa, st); }) != hipSuccess) return SKIPKV_EHIP;
   if (shared_lambda) {  // lambda per sequence (hidden-state similarity): no Gram matrices per head
     FuseSharedArgs fa{};

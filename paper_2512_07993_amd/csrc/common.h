@@ -93,7 +93,7 @@ struct Workspace {
   // the next two share the place of stat_part: the single-pass scan is done with them when the two-pass scan begins
   int32_t *item_rec;     // [ni_max][kItemRecInts] one record per item of the single-pass scan (ItemRec)
   float2 *item_stat;     // [LH, ni_max, R]  single-pass scan: per-item (reference, sum) of every query row; the plan presets .x of the used records to kRowNormUnset
-  float *row_norm;       // [LH, B, R2]      two-pass scan of fp32 caches: log2 of the softmax normaliser of every query row
+  float *row_norm;       // [LH, B, R2]      two-pass scan whose records are merged by a kernel of their own: log2 of the softmax normaliser of every query row
   uint16_t *vhat_hi;     // [LH, S_total, 128] bf16 high part of the unit sentence embedding
   uint16_t *vhat_lo;     // [LH, S_total, 128] bf16 low part (residual)
   float *sent_imp;       // [LH, S_total]    mean token importance over the candidate span
@@ -203,6 +203,7 @@ struct ScanArgs {
   // sequence of its own of ONE layer with ONE KV head (v = (l * H_k + h) * B + b); only the query
   // rows are still laid out by the real (l, b, h).  virt_hk = real H_k (0: off), virt_b = real B.
   int32_t virt_hk, virt_b;
+  int32_t norms_apart;  // 1: a kernel between the two passes merges the heads' records; 0: every run of the second pass does it for itself
   int32_t no_pool;  // 1: sentence embeddings are not needed (lambda comes from elsewhere): skip the key pooling
   // Paged cache: row_map[seq_off[b] + t] = slot row of logical token t, in units of map_stride elements
   // from the head's base (consecutive slots of a block are still stride_tok apart); null for a
@@ -215,8 +216,9 @@ bool scan_fused_supported(const RowLayout &rl, int64_t row_pitch_bytes);
 hipError_t launch_scan_fused(const ScanArgs &a, hipStream_t st);    // single pass over K (sequences the plan marked fused)
 int scan_run_chunks(int dtype, int64_t seqs, int64_t tokens);  // chunks that the two-pass scan takes at a time, at most
 int scan_two_pass_rows(const RowLayout &rl, int dtype);  // rows of the statistics arrays that the two-pass scan of this shape has
+bool scan_norms_apart(const ScanArgs &a);
 hipError_t launch_scan_stats(const ScanArgs &a, hipStream_t st);    // pass A: row statistics + sentence embeddings
-hipError_t launch_row_norm(const ScanArgs &a, hipStream_t st);      // combine the records of pass A (fp32; pass B of bf16 caches does it itself)
+hipError_t launch_row_norm(const ScanArgs &a, hipStream_t st);      // combine the records of pass A, where pass B does not do it itself (ScanArgs::norms_apart)
 hipError_t launch_scan_scores(const ScanArgs &a, hipStream_t st);   // pass B: token importance, sentence means
 hipError_t launch_rows_stats(const ScanArgs &a, hipStream_t st);    // ... passes A and B for bf16 caches (scan_rows.hip)
 hipError_t launch_rows_scores(const ScanArgs &a, hipStream_t st);

@@ -3,7 +3,8 @@
 // (more than 64 query rows) and for whatever else the single-pass scan cannot take:
 //   pass A   (reference, sum exp2) of every query row over a run of chunks, and the unit key mean of every
 //            sentence;
-//   pass B   a head's records merged into log2 of each row's normaliser (every run for itself), the logits again, I[t] = (1/alpha) sum_a max_i softmax, and its mean over every sentence.
+//   pass B   a head's records merged into log2 of each row's normaliser (by every run for itself, or by k_row_norm before), the
+//            logits again, I[t] = (1/alpha) sum_a max_i softmax, and its mean over every sentence.
 //
 // What bounds it.  With 160 query rows a 256-byte key costs 41 KFLOP and 160 exponentials: both passes are bound by
 // the instructions that a SIMD can issue (pass A at 160 rows: about 1250 vector and 220 matrix instructions per 64-key
@@ -121,26 +122,30 @@ __device__ __forceinline__ int run_length(int n, int run_chunks) {
   return (n + runs - 1) / runs;
 }
 
-// log2 of the softmax normaliser of query row r of a head whose sequence has n_chunks > 0 chunks from cb on: the records
-// of the runs merged in the sequence's order.
-__device__ __forceinline__ float row_norm(const ScanArgs &a, int lh, int cb, int n_chunks, int R, int r) {
-  const int rc = a.ws.run_chunks, u0 = cb / rc, u1 = u0 + (n_chunks + rc - 1) / rc;
-  const float2 *recs = a.ws.stat_part + (int64_t)lh * a.ws.nr_max * R + r;
+// (reference, sum) of query row r over n > 0 runs of a head, whose records begin at recs: merged in the sequence's order.
+__device__ __forceinline__ float2 merge_records(const float2 *recs, int n, int R, int r) {
   float m = kRefInit, s = 0.f;
-  for (int u = u0; u < u1; u += 8) {
+  for (int u = 0; u < n; u += 8) {
     float2 p[8];
 #pragma unroll
-    for (int k = 0; k < 8; ++k) p[k] = recs[(int64_t)min(u + k, u1 - 1) * R];
+    for (int k = 0; k < 8; ++k) p[k] = recs[(int64_t)min(u + k, n - 1) * R + r];
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
-      if (u + k >= u1) break;
+      if (u + k >= n) break;
       const float nm = fmaxf(m, p[k].x);
       s = s * __builtin_amdgcn_exp2f(m - nm) + p[k].y * __builtin_amdgcn_exp2f(p[k].x - nm);
       m = nm;
     }
   }
-  return s > 0.f ? m + __builtin_amdgcn_logf(s) : INFINITY;
+  return make_float2(m, s);
 }
+// Records of the head of a sequence that has n_chunks > 0 chunks from cb on, and how many there are.
+__device__ __forceinline__ const float2 *head_records(const ScanArgs &a, int lh, int cb, int n_chunks, int R, int &n) {
+  const int rc = a.ws.run_chunks;
+  n = (n_chunks + rc - 1) / rc;
+  return a.ws.stat_part + ((int64_t)lh * a.ws.nr_max + cb / rc) * R;
+}
+__device__ __forceinline__ float log2_norm(float2 x) { return x.y > 0.f ? x.x + __builtin_amdgcn_logf(x.y) : INFINITY; }
 
 template <int NP, int AL, bool PASSB, bool SIMPLE>
 __global__ void __launch_bounds__(64 * kWaves, 4) k_scan_rows(ScanArgs a) {
@@ -293,13 +298,31 @@ __global__ void __launch_bounds__(64 * kWaves, 4) k_scan_rows(ScanArgs a) {
       issue(i, 1);
     }
     if constexpr (PASSB) {
-      // log2 of the normaliser of every query row, from the records of the head's runs in the sequence's order.  Every run does
-      // this for itself, while its first tiles arrive: up to some 50 records of 8 bytes a row against 240 keys and more.  As a
-      // kernel of its own between the passes it cost every call a launch, also those that leave nothing to the
-      // two passes (one sequence of 4224 tokens, 256 heads: 232 -> 228 us; a call of 73: 70).
+      // log2 of the normaliser of every query row: from the records of the head's runs, merged while the first tiles arrive, as many
+      // threads to a row as there are, unless a kernel has done that (scan_norms_apart).
+      constexpr int kParts = 64 * kWaves / R;
       float *norm = fbuf + NPART * GT;  // (the tiles' importance takes this place behind another barrier)
-      static_assert(R <= GT, "one thread and one place per row");
-      if (tid < R) norm[tid] = row_norm(a, lh, cb, n_chunks, R, tid);
+      static_assert(R <= GT && 2 * kParts * R <= NPART * GT, "a place for each row, and for each of its parts");
+      if (a.norms_apart) {
+        if (tid < R) norm[tid] = a.ws.row_norm[((int64_t)lh * a.batch + b) * R + tid];
+      } else {
+        int n_rec;
+        const float2 *recs = head_records(a, lh, cb, n_chunks, R, n_rec);
+        const int share = (n_rec + kParts - 1) / kParts, r = tid % R, p0 = tid / R * share;
+        float2 *parts = reinterpret_cast<float2 *>(fbuf);
+        if (tid < kParts * R) parts[tid] = p0 < n_rec ? merge_records(recs + (int64_t)p0 * R, min(share, n_rec - p0), R, r) : make_float2(kRefInit, 0.f);
+        asm volatile("" ::: "memory");
+        lds_barrier();
+        asm volatile("" ::: "memory");
+        if (tid < R) {
+          float m = kRefInit, s = 0.f;
+#pragma unroll
+          for (int p = 0; p < kParts; ++p) m = fmaxf(m, parts[p * R + tid].x);
+#pragma unroll
+          for (int p = 0; p < kParts; ++p) s += parts[p * R + tid].y * __builtin_amdgcn_exp2f(parts[p * R + tid].x - m);
+          norm[tid] = log2_norm(make_float2(m, s));
+        }
+      }
       asm volatile("" ::: "memory");
       lds_barrier();
       asm volatile("" ::: "memory");
@@ -651,13 +674,15 @@ __global__ void __launch_bounds__(64 * kWaves, 4) k_scan_rows(ScanArgs a) {
   wait_vm<0>();  // the loads past the last tile still write LDS that the workgroup is about to give up
 }
 
-// The same as a kernel: the fp32 passes' normalisers (their runs are single chunks).
+// log2 of the softmax normaliser of every query row of a head, for pass B to read.
 __global__ void __launch_bounds__(256) k_row_norm(ScanArgs a, int R) {
   const int lhb = blockIdx.x, lh = lhb / a.batch, b = lhb % a.batch;
   if (!a.force_two_pass && a.ws.seq_fused[b] && !a.ws.head_redo[lhb]) return;  // the single-pass scan computed these itself
   const int r = threadIdx.x;
   if (r >= R || a.ws.chunk_cnt[b] == 0) return;
-  a.ws.row_norm[(int64_t)lhb * R + r] = row_norm(a, lh, a.ws.chunk_base[b], a.ws.chunk_cnt[b], R, r);
+  int n_rec;
+  const float2 *recs = head_records(a, lh, a.ws.chunk_base[b], a.ws.chunk_cnt[b], R, n_rec);
+  a.ws.row_norm[(int64_t)lhb * R + r] = log2_norm(merge_records(recs, n_rec, R, r));
 }
 
 template <int NP, int AL, bool PASSB>
@@ -740,6 +765,18 @@ int scan_two_pass_rows(const RowLayout &rl, int dtype) {
 
 hipError_t launch_rows_stats(const ScanArgs &a, hipStream_t st) { return dispatch<false>(a, st); }
 hipError_t launch_rows_scores(const ScanArgs &a, hipStream_t st) { return dispatch<true>(a, st); }
+
+// Whether a kernel between the passes merges the records of a head.  If not, every run of pass B does it for itself, which is
+// quadratic in the runs, but hidden and done by eight threads a row (64 rows; 160 rows: three, 256: two) where all runs have a place on the
+// chip, and saves calls that leave nothing to the passes a launch.  Whole score call, us, one thread a row / all of them / a
+// kernel, by the rows, layers x heads, the tokens of one sequence (runs of a head, of the call):
+//   64    1 x 4, 33 K (135, 540): 152 / 113 / 140    2 x 8, 131 K (112, 1792): 524 / 413 / 441    8 x 8, 131 K (56, 3584): 1154 / 1111 / 1125
+//   160   1 x 4, 33 K: 167 / 149 / 157    2 x 8, 33 K (45, 720): 180 / 172 / 174    2 x 8, 131 K: 601 / 536 / 511    8 x 8, 33 K (27, 1728):
+//         431 / 422 / 419    8 x 8, 131 K: 1476 / 1432 / 1411    32 x 8, 16 K (10, 2560): 707 / 707 / 700
+// (nr_max is about 2.2 times the runs.)  The fp32 passes read the kernel's result.
+bool scan_norms_apart(const ScanArgs &a) {
+  return a.dtype == SKIPKV_F32 || (a.ws.rows2 > 64 && (int64_t)a.n_layers * a.n_kv_heads * a.ws.nr_max > 2400);
+}
 
 hipError_t launch_row_norm(const ScanArgs &a, hipStream_t st) {
   const int blocks = a.n_layers * a.n_kv_heads * a.batch;

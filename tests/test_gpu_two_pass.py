@@ -289,3 +289,26 @@ def test_sequences_that_the_single_pass_scan_leaves_get_what_the_two_pass_scan_a
                 assert torch.equal(_bits(x[..., at]), _bits(y[..., at]))
             else:  # fp32 sums in another order
                 assert torch.allclose(x[..., at], y[..., at], rtol=1e-5, atol=1e-5)
+
+
+@pytest.mark.parametrize("L,H,group,alpha,n", [(1, 1, 5, 32, 9000), (1, 3, 4, 16, 20000), (1, 2, 8, 32, 520), (3, 1, 1, 1, 250), (2, 8, 5, 32, 40000), (1, 2, 8, 32, 140000)])
+def test_records_of_few_and_many_runs(L, H, group, alpha, n):
+    # A head's records are merged by the threads that a row has, in shares (one run, fewer runs than shares, shares of several
+    # runs), or by a kernel of its own (the last two).  The normaliser and its difference to a logit are below 32 log2 units: one unit
+    # in the last place of fp32 there is 1.9e-6, two of them a relative error of 2.6e-6, which all tokens of a row share; the sums of n
+    # terms and products of 128 add some 1e-6 each.
+    st = _structure([list(range(0, n, 50)) + [n], [0, 600, 700]])
+    cfg = _cfg("records", 2, L, H, group, alpha)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n)
+    k = torch.randn((L, H, st.total_tokens, 128), generator=g, device="cuda").to(torch.bfloat16)
+    k[:, :, n // 3] *= 4.0  # (a reference of one run that the others' are far from)
+    q = torch.randn((L, 2, H * group, alpha, 128), generator=g, device="cuda").to(torch.bfloat16)
+    imp = _score(cfg, st, k, q, TWO)[2]
+    for b in range(2):
+        t0, t1 = int(st.seq_off[b]), int(st.seq_off[b + 1])
+        x = torch.einsum("qd,td->qt", q[-1, b, (H - 1) * group:].reshape(group * alpha, 128).double(), k[-1, -1, t0:t1].double()) / 128 ** 0.5
+        x = x.view(group, alpha, t1 - t0)
+        seen = torch.arange(t1 - t0, device="cuda")[None, :] <= t1 - t0 - alpha + torch.arange(alpha, device="cuda")[:, None]
+        want = torch.where(seen, x, float("-inf")).softmax(-1).amax(0).mean(0)
+        assert torch.allclose(imp[-1, -1, t0:t1].double(), want, rtol=1e-5, atol=1e-12)
