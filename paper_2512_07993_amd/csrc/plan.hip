@@ -36,7 +36,9 @@ __device__ __forceinline__ int run_end(const int *off, int start, int n_sent, in
 // many spans as a quarter holds, so that a sequence takes the same scan in every batch), longer
 // sequences are done by the block afterwards.  Measured, against a block
 // per sequence with both walks in one thread: 7168 sequences of 1.1 K tokens 95 -> 32 us, 4096 of 2.1 K 60 -> 23,
-// 4 of 32 K 43 -> 28, 16 of 2-16 K 23 -> 17.
+// 4 of 32 K 43 -> 28, 16 of 2-16 K 23 -> 17.  The walk over cut sentences has an LDS read per step too: with three, and a walk also for
+// sequences with a sentence that no item holds, the plan of 8 K tokens of sentences of 129 took 32 us, now 25 (not cut: 14),
+// of 4 K with some sentences of more than 512 18, now 8.
 template <int WPS>
 constexpr int kMaxSent = WPS == 4 ? SKIPKV_MAX_SENTENCES : SKIPKV_MAX_SENTENCES / 4 - 1;
 
@@ -46,7 +48,7 @@ struct PlanShared {
   // by the first sentences of the chunks (spans) and a final n_sent.  Chunk k never starts before sentence k, so
   // what is replaced has been read.
   uint16_t chunk[SKIPKV_MAX_SENTENCES + 1];
-  uint16_t span[SKIPKV_MAX_SENTENCES + 1];
+  uint16_t span[SKIPKV_MAX_SENTENCES + 1];  // (with cut sentences: | (spans of the sentence - 1) << 13, and not replaced)
   // The spans of a sequence with sentences of several spans: first sentence, number of the piece of it << 13.  (A span
   // that is only there so that the pieces of a sentence come to lie in one item is empty: it begins where the next one does.)
   uint16_t pieces[kItemSpans * kFuseMaxItems + 4];
@@ -89,7 +91,7 @@ __device__ __forceinline__ void plan_sequences(const PlanArgs &a, PlanShared &sh
     const bool reject = n_sent > SKIPKV_MAX_SENTENCES || n_sent < 0;
     // explicit lengths and counts must fit the room that the CSR arrays describe
     bool bad = !reject && (n_tok < 0 || n_tok > a.seq_off[b + 1] - tok0 || n_sent > a.sent_ptr[b + 1] - sp - 1);
-    bool longer = false;  // some sentence is longer than a span may be
+    bool longer = false, too_long = false;  // some sentence is longer than a span, than an item may be
     if (!reject && !bad) {
       // validation: o[0] = 0, o[S] = N, strictly ascending
       for (int s = gt; s <= n_sent; s += G) {
@@ -99,13 +101,15 @@ __device__ __forceinline__ void plan_sequences(const PlanArgs &a, PlanShared &sh
           const int n = off[s + 1] - o;
           bad |= off[s + 1] <= o;
           longer |= n > kSpanCap;
+          too_long |= n > kItemSpans * kSpanCap;
         }
       }
       if (gt == 0) bad |= (off[0] != 0) | (off[n_sent] != n_tok) | (n_sent == 0 && n_tok != 0);
     }
     bad = any(bad);
     longer = any(longer);
-    cut = longer;
+    if (longer) too_long = any(too_long);  // the two-pass scan's: spans are not even looked for
+    cut = longer && !too_long;
     ok = !reject && !bad;
     // (no sequence gets more items than its tokens and sentences make of ordinary spans at most: that is what there is room for)
     if (ok && cut) most = min(kItemSpans * kFuseMaxItems, kItemSpans * ((2 * (n_tok / a.ws.span_cap + n_sent / kSpanMaxSent) + 1) / kItemSpans + 1));
@@ -121,7 +125,7 @@ __device__ __forceinline__ void plan_sequences(const PlanArgs &a, PlanShared &sh
       const int cap = 2 * ((n_tok + a.ws.span_cap - 1) / a.ws.span_cap + (n_sent + kSpanMaxSent - 1) / kSpanMaxSent) < kItemSpans * kFuseMaxItems ? a.ws.span_cap : kSpanCap;
       for (int s = gt; s < n_sent; s += G) {
         s_chunk[s] = (uint16_t)run_end(s_off, s, n_sent, kChunkCap, kChunkMaxSent);
-        s_span[s] = (uint16_t)run_end(s_off, s, n_sent, cap, kSpanMaxSent);
+        if (!too_long) s_span[s] = (uint16_t)(run_end(s_off, s, n_sent, cap, kSpanMaxSent) | (cut ? (s_off[s + 1] - s_off[s] - 1) / kSpanCap << 13 : 0));
       }
     }
     sync();
@@ -130,17 +134,21 @@ __device__ __forceinline__ void plan_sequences(const PlanArgs &a, PlanShared &sh
     if (ok && (gt == 0 || gt == kOther)) {
       uint16_t *at = gt == 0 ? s_span : s_chunk;
       int n = 0;
-      if (gt == 0 && longer) {
+      if (gt == 0 && cut) {
         bool fits = true;
-        for (int start = 0; start < n_sent && fits;) {
-          const int p = max(1, (s_off[start + 1] - s_off[start] + kSpanCap - 1) / kSpanCap);
-          while (p <= kItemSpans && n % kItemSpans + p > kItemSpans && n < most) s_pieces[n++] = (uint16_t)start;
-          fits = p <= kItemSpans && n + p <= most;
-          for (int k = 0; k < p && fits; ++k) s_pieces[n++] = (uint16_t)(start | k << 13);
-          start = at[start];
+        for (int start = 0; start < n_sent;) {
+          const int x = at[start], more = x >> 13;  // spans of the sentence besides its first
+          if (more > 0 && n % kItemSpans + more >= kItemSpans)  // on to the next item
+            for (; n % kItemSpans != 0 && n < most; ++n) s_pieces[n] = (uint16_t)start;
+          if (!(fits = n + more < most)) break;
+          s_pieces[n++] = (uint16_t)start;
+          for (int k = 1; k <= more; ++k) s_pieces[n++] = (uint16_t)(start | k << 13);
+          start = x & 0x1FFF;
         }
         if (fits) s_pieces[n] = (uint16_t)n_sent;
         else n = 0;  // the two-pass scan's
+      } else if (gt == 0 && too_long) {
+        n = 0;
       } else {
         for (int start = 0; start < n_sent;) {
           const int e = at[start];
