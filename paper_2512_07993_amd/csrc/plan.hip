@@ -37,8 +37,8 @@ __device__ __forceinline__ int run_end(const int *off, int start, int n_sent, in
 // sequences are done by the block afterwards.  Measured, against a block
 // per sequence with both walks in one thread: 7168 sequences of 1.1 K tokens 95 -> 32 us, 4096 of 2.1 K 60 -> 23,
 // 4 of 32 K 43 -> 28, 16 of 2-16 K 23 -> 17.  The walk over cut sentences has an LDS read per step too: with three, and a walk also for
-// sequences with a sentence that no item holds, the plan of 8 K tokens of sentences of 129 took 32 us, now 25 (not cut: 14),
-// of 4 K with some sentences of more than 512 18, now 8.
+// sequences with a sentence that no item holds, the plan of 8 K tokens of sentences of 129 took 32 us, now 24 (not cut: 14),
+// of 4 K with some sentences of more than 512 17, now 10.  What only such sequences need stands behind the rest (k_plan of others 7.3 -> 6.7 us).
 template <int WPS>
 constexpr int kMaxSent = WPS == 4 ? SKIPKV_MAX_SENTENCES : SKIPKV_MAX_SENTENCES / 4 - 1;
 
@@ -91,7 +91,7 @@ __device__ __forceinline__ void plan_sequences(const PlanArgs &a, PlanShared &sh
     const bool reject = n_sent > SKIPKV_MAX_SENTENCES || n_sent < 0;
     // explicit lengths and counts must fit the room that the CSR arrays describe
     bool bad = !reject && (n_tok < 0 || n_tok > a.seq_off[b + 1] - tok0 || n_sent > a.sent_ptr[b + 1] - sp - 1);
-    bool longer = false, too_long = false;  // some sentence is longer than a span, than an item may be
+    bool longer = false;  // some sentence is longer than a span may be
     if (!reject && !bad) {
       // validation: o[0] = 0, o[S] = N, strictly ascending
       for (int s = gt; s <= n_sent; s += G) {
@@ -101,21 +101,25 @@ __device__ __forceinline__ void plan_sequences(const PlanArgs &a, PlanShared &sh
           const int n = off[s + 1] - o;
           bad |= off[s + 1] <= o;
           longer |= n > kSpanCap;
-          too_long |= n > kItemSpans * kSpanCap;
         }
       }
       if (gt == 0) bad |= (off[0] != 0) | (off[n_sent] != n_tok) | (n_sent == 0 && n_tok != 0);
     }
     bad = any(bad);
     longer = any(longer);
-    if (longer) too_long = any(too_long);  // the two-pass scan's: spans are not even looked for
-    cut = longer && !too_long;
     ok = !reject && !bad;
-    // (no sequence gets more items than its tokens and sentences make of ordinary spans at most: that is what there is room for)
-    if (ok && cut) most = min(kItemSpans * kFuseMaxItems, kItemSpans * ((2 * (n_tok / a.ws.span_cap + n_sent / kSpanMaxSent) + 1) / kItemSpans + 1));
-    const bool later = most > kPieces;
+    bool later = false;
+    if (__builtin_expect(longer && ok, false)) {
+      bool fits_items = true;
+      sync();
+      for (int s = gt; s < n_sent; s += G) fits_items &= s_off[s + 1] - s_off[s] <= kItemSpans * kSpanCap;
+      cut = !any(!fits_items);  // (else the sequence is the two-pass scan's: its spans are not looked for)
+      // (no sequence gets more items than its tokens and sentences make of ordinary spans at most: that is what there is room for)
+      most = min(kItemSpans * kFuseMaxItems, kItemSpans * ((2 * (n_tok / a.ws.span_cap + n_sent / kSpanMaxSent) + 1) / kItemSpans + 1));
+      later = cut && most > kPieces;
+      ok = !later;
+    }
     if (WPS == 1 && gt == 0) sh.later[grp] = later;
-    ok = ok && !later;
     for (int lh = gt; lh < a.n_lh; lh += G) a.ws.head_redo[(int64_t)lh * a.batch + b] = 0;
     sync();
     if (ok) {
@@ -125,8 +129,10 @@ __device__ __forceinline__ void plan_sequences(const PlanArgs &a, PlanShared &sh
       const int cap = 2 * ((n_tok + a.ws.span_cap - 1) / a.ws.span_cap + (n_sent + kSpanMaxSent - 1) / kSpanMaxSent) < kItemSpans * kFuseMaxItems ? a.ws.span_cap : kSpanCap;
       for (int s = gt; s < n_sent; s += G) {
         s_chunk[s] = (uint16_t)run_end(s_off, s, n_sent, kChunkCap, kChunkMaxSent);
-        if (!too_long) s_span[s] = (uint16_t)(run_end(s_off, s, n_sent, cap, kSpanMaxSent) | (cut ? (s_off[s + 1] - s_off[s] - 1) / kSpanCap << 13 : 0));
+        s_span[s] = (uint16_t)run_end(s_off, s, n_sent, cap, kSpanMaxSent);
       }
+      if (__builtin_expect(cut, false))
+        for (int s = gt; s < n_sent; s += G) s_span[s] |= (uint16_t)((s_off[s + 1] - s_off[s] - 1) / kSpanCap << 13);
     }
     sync();
     PlanShared::Seq &me = sh.seq[grp];
@@ -134,21 +140,18 @@ __device__ __forceinline__ void plan_sequences(const PlanArgs &a, PlanShared &sh
     if (ok && (gt == 0 || gt == kOther)) {
       uint16_t *at = gt == 0 ? s_span : s_chunk;
       int n = 0;
-      if (gt == 0 && cut) {
-        bool fits = true;
-        for (int start = 0; start < n_sent;) {
+      if (__builtin_expect(gt == 0 && longer, false)) {
+        bool fits = cut;
+        for (int start = 0; start < n_sent && fits;) {
           const int x = at[start], more = x >> 13;  // spans of the sentence besides its first
           if (more > 0 && n % kItemSpans + more >= kItemSpans)  // on to the next item
             for (; n % kItemSpans != 0 && n < most; ++n) s_pieces[n] = (uint16_t)start;
-          if (!(fits = n + more < most)) break;
-          s_pieces[n++] = (uint16_t)start;
-          for (int k = 1; k <= more; ++k) s_pieces[n++] = (uint16_t)(start | k << 13);
+          fits = n + more < most;
+          for (int k = 0; k <= more && fits; ++k) s_pieces[n++] = (uint16_t)(start | k << 13);
           start = x & 0x1FFF;
         }
         if (fits) s_pieces[n] = (uint16_t)n_sent;
         else n = 0;  // the two-pass scan's
-      } else if (gt == 0 && too_long) {
-        n = 0;
       } else {
         for (int start = 0; start < n_sent;) {
           const int e = at[start];
