@@ -692,11 +692,14 @@ hipError_t launch_rows(const ScanArgs &a, hipStream_t st) {
   const int64_t items = (int64_t)a.n_layers * a.n_kv_heads * a.ws.nr_max;
   if (items == 0) return hipSuccess;
   // Eight workgroups to a place on the chip balance the passes where there is work for them.  Where they are only the fallback they
-  // mostly find nothing to do, and a launch of fewer workgroups is over sooner, which small calls notice.  Whole score call, us, 1024 /
-  // 4096 workgroups, 128 tokens to a sentence at most / sequences with longer ones: one sequence of 4224 tokens, 256 heads (1.1 M keys)
-  // 101.3 / 102.4, of 8192 (2.1 M) - and 318.9 / 319.5;  4 of 4224 (4.3 M) 352.4 / 354.9;  16 of 3000, 128 heads (6.1 M) - and 823 / 776;
-  // 4 of 8192, 256 heads (8.4 M) - and 1009 / 962;  16 of 4096 (16.8 M) 1236 / 1241 and 1901 / 1777.
-  const bool many = a.force_two_pass || (int64_t)a.n_layers * a.n_kv_heads * a.total_tokens >= 6000000;
+  // mostly find nothing to do, and a launch of fewer workgroups is over sooner, which all but large calls notice; unless sentences are
+  // so long on average that many do not fit the single pass.  Whole score call, us, 1024 / 4096 workgroups:
+  //   sentences of 4-64 tokens (nothing to do), 1.1 M keys 110 / 111    2.1 M 201 / 204    4.2 M 358 / 362    16.8 M 1236 / 1241
+  //   1 % of them longer than 512               1.1 M 177 / 177    2.1 M 294 / 292    8.4 M 1009 / 962    16.8 M 1901 / 1777
+  //   half of 257, half of 129                  6.1 M 823 / 776
+  //   80 % of 129, 20 % of 20                   0.5 M 137 / 136    1.5 M 279 / 254    2.1 M 326 / 291    3.6 M 520 / 460
+  const int64_t keys = (int64_t)a.n_layers * a.n_kv_heads * a.total_tokens;
+  const bool many = a.force_two_pass || keys >= 6000000 || (keys >= 1000000 && a.total_tokens >= 64 * (int64_t)a.total_sentences);
   const dim3 grid((unsigned)std::min<int64_t>(items, many ? 4096 : 1024));
   if (a.row_map == nullptr && a.stride_tok * 2 < (1 << 24))  // lane offsets by a 24-bit multiply
     hipLaunchKernelGGL((k_scan_rows<NP, AL, PASSB, true>), grid, dim3(64 * kWaves), 0, st, a);
