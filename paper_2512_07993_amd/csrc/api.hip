@@ -64,6 +64,18 @@ int check_params(const skipkv_cache *c, const skipkv_params *p, RowLayout *rl) {
 constexpr size_t kShortSpanTokens = 48 * 1024;
 int span_cap_of(int dtype, size_t tokens) { return dtype == SKIPKV_F32 && tokens <= kShortSpanTokens ? 64 : kSpanCap; }
 
+// Tokens that the items of a sequence with cut sentences have to hold on average (of 512) for the single-pass scan to take it; 0: as
+// many as the room for items makes them hold, which is about 220 in long sequences.  A bf16 item that is less than half full is still faster
+// than the two passes over its tokens, in calls of every size.  An fp32 item has a CU to itself: where a call has more items than the chip
+// has CUs, nearly empty ones cost more than the two passes.  The single pass / the two passes, us, 8 heads:
+//   bf16   1100 sequences of 150 tokens, sentences of 129 and 21 (150 tokens an item) 214 / 299    1100 of 400, of 129 and 20 (200) 393 / 477
+//   fp32   1100 of 150 1034 / 802    1100 of 400, of 129 and 20 (200) 1978 / 1800, of 385 and 20 (200 or 400) 1479 / 1985, of 129 1986 / 1972
+//          one of 4096, of 129 and 20 (205) 60 / 77
+constexpr size_t kFewF32Keys = 400 * 1000;
+int32_t cut_item_tokens_of(const skipkv_cache *c) {
+  return c->dtype == SKIPKV_F32 && (size_t)c->n_layers * c->n_kv_heads * c->total_tokens > kFewF32Keys ? 160 : 0;
+}
+
 // Carve the workspace.  `base` may be NULL to only compute the size.
 Workspace carve(const skipkv_cache *c, const RowLayout &rl, void *base) {
   Workspace w{};
@@ -161,7 +173,7 @@ int do_score(Timer &tm, const skipkv_cache *c, const skipkv_params *p, const Row
              const float *tok_red, float *sent_score, float *sent_lambda, float *tok_imp, void *ws, hipStream_t st,
              const HeadView &hv, const float *shared_lambda, bool hdr_reset) {
   const Workspace w = carve(c, rl, ws);
-  PlanArgs pa{c->seq_off, c->sent_ptr, c->sent_off, c->batch, c->n_layers * c->n_kv_heads, w, p->dev_status, hv.len, hv.cnt, c->total_sentences, hdr_reset};
+  PlanArgs pa{c->seq_off, c->sent_ptr, c->sent_off, c->batch, c->n_layers * c->n_kv_heads, w, p->dev_status, hv.len, hv.cnt, c->total_sentences, cut_item_tokens_of(c), hdr_reset};
   if (tm.run("plan", [&] { return launch_plan(pa, st); }) != hipSuccess) return SKIPKV_EHIP;
   ScanArgs sa{};
   sa.k = c->k;

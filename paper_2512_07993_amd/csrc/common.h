@@ -179,6 +179,7 @@ struct PlanArgs {
   int32_t *dev_status;
   const int32_t *len, *cnt;  // nullable [batch]: explicit lengths and sentence counts (then seq_off / sent_ptr only give capacities)
   int32_t total_sentences;
+  int32_t cut_item_tokens = 0;  // > 0: a sequence with cut sentences takes the single-pass scan only if its items hold as many tokens on average
   bool hdr_reset = false;    // an earlier kernel of the call has reset the header
   bool alone = false;        // one block in all: it writes the header itself (set by launch_plan, as the next one)
   bool preset = false;       // the blocks mark the statistics records of their sequences

@@ -116,6 +116,7 @@ __device__ __forceinline__ void plan_sequences(const PlanArgs &a, PlanShared &sh
       cut = !any(!fits_items);  // (else the sequence is the two-pass scan's: its spans are not looked for)
       // (no sequence gets more items than its tokens and sentences make of ordinary spans at most: that is what there is room for)
       most = min(kItemSpans * kFuseMaxItems, kItemSpans * ((2 * (n_tok / a.ws.span_cap + n_sent / kSpanMaxSent) + 1) / kItemSpans + 1));
+      if (a.cut_item_tokens > 0) most = min(most, kItemSpans * (n_tok / a.cut_item_tokens));
       later = cut && most > kPieces;
       ok = !later;
     }

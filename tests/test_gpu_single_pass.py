@@ -116,3 +116,28 @@ def test_an_infinite_key_stays_in_its_sentence(dtype, token):
     want = oracle.sentence_redundancy(oracle.sentence_embeddings(x, np.asarray(off))[good])
     lam = out.sent_lambda[0, 0].cpu().numpy()
     np.testing.assert_allclose(lam[good][:-1], want[:-1], rtol=1e-3, atol=1e-5)
+
+
+@pytest.mark.parametrize("n_seqs", [40, 1000])
+def test_fp32_items_that_would_stay_nearly_empty_are_left_to_the_two_passes_in_large_calls(n_seqs):
+    # 8 heads, below and above the 400 000 keys from which on the plan looks at how full the items are: 150 and 154 tokens an item
+    # are too few, 258 and what is not cut are not
+    import oracle
+    kinds = [[129, 21], [40, 129, 10, 129], [129, 129], [129] * 4, [60, 70, 80]]
+    offsets = [[0] + [int(x) for x in np.cumsum(kinds[i % 5])] for i in range(n_seqs)]
+    st = _structure(offsets)
+    assert (8 * st.total_tokens > 400000) == (n_seqs == 1000)
+    cfg = W.Config("empty", 7, n_seqs, 1, 8, 8, "f32", 0, 0, 700, 4, 40, 20.0, 0.0)
+    k0, v0, q = _random_kvq(cfg, st, 9)
+    one = run_step(cfg, st, k0.clone(), v0.clone(), q)
+    two = run_step(cfg, st, k0.clone(), v0.clone(), q, flags=B.FLAG_FORCE_TWO_PASS)
+    assert int(one.dev_status.item()) == 0
+    same = [torch.equal(one.tok_imp[..., t0:t1], two.tok_imp[..., t0:t1]) for t0, t1 in zip(st.seq_off[:-1], st.seq_off[1:])]
+    assert same == [n_seqs == 1000 and i % 5 < 2 for i in range(n_seqs)]  # (another scan shows in the last bits)
+    assert torch.allclose(one.tok_imp, two.tok_imp, rtol=1e-5, atol=1e-9)  # fp32 sums in another order
+    lam = torch.isfinite(one.sent_lambda)
+    assert torch.equal(lam, torch.isfinite(two.sent_lambda)) and torch.allclose(one.sent_lambda[lam], two.sent_lambda[lam], rtol=0, atol=1e-5)
+    for b in (0, 1, 2, 3, n_seqs - 1):
+        t0, t1 = int(st.seq_off[b]), int(st.seq_off[b + 1])
+        want = oracle.token_importance(q[0, b, 3:4].double().cpu().numpy(), k0[0, 3, t0:t1].double().cpu().numpy())
+        np.testing.assert_allclose(one.tok_imp[0, 3, t0:t1].cpu().numpy(), want, rtol=1e-4, atol=1e-12)
