@@ -15,6 +15,14 @@ namespace skipkv {
 namespace {
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
+// Rows of large caches are read once and written once before anybody comes back to them: they are moved past the caches, and
+// displace neither each other nor what the next kernels need.  Small ones are found in the memory-side cache again by
+// what follows the call (the next call at the latest).  Whole call, us, ordinary / past the caches, by the rows' bytes in K and V:
+//   one sequence, 4096 rows kept:   16 MB 83 / 98   64 MB 92 / 119   128 MB 132 / 141   192 MB 153 / 153   256 MB 181 / 174
+//                                   512 MB 306 / 278
+//   per-head ranges, 1024 kept:     128 MB 109 / 106   512 MB 305 / 288   2 GB 1058 / 1015
+constexpr int64_t kStreamBytes = 192ll << 20;
+
 // 16 bytes that nobody comes back to soon (STREAM), or ordinary ones.
 template <bool STREAM>
 __device__ __forceinline__ u32x4 load16(const char *p) {
@@ -32,36 +40,66 @@ __device__ __forceinline__ void store16(char *p, u32x4 x) {
 // load per tile, issued right before the tile's row loads.  Logical positions still only move
 // forward and distinct logical rows are distinct slots, so the order argument above holds.
 //
+// A stream: the rows of K or of V of a head of a sequence, and where they go.
+template <int ROWB, bool PAGED>
+struct Stream {
+  int64_t sid, lhb;
+  int b;
+  const int32_t *kept;   // the head's row of indices
+  int nl;                // rows kept
+  bool valid;
+  // set by locate(), which has the waits for what it loads: called where they are needed
+  char *base;            // first row of the sequence (paged: the head's base)
+  int64_t pitch;         // paged: of the units of the row map
+  const int32_t *srcs;   // what the row loads are addressed with
+  const int32_t *rmap;   // paged: slot rows of the sequence
+  int room;              // rows of the sequence (contiguous cache: a source index is one of them)
+
+  __device__ __forceinline__ Stream(const CompactArgs &a, uint32_t sid_) : sid(sid_), lhb(sid_ >> 1), b((int)((sid_ >> 1) % (uint32_t)a.batch)) {
+    kept = a.kept_idx + lhb * a.kept_stride;
+    nl = a.new_len[lhb];
+    // An invalid block table: leave the sequence alone.  A head that kept everything because its inputs could not be trusted reports
+    // its full length, which its row of indices may not even hold: nothing to move, and nothing to read past the row.
+    valid = !(PAGED && a.seq_bad[b]) && nl <= a.kept_stride && !(PAGED && nl > a.src_stride);
+  }
+  __device__ __forceinline__ void locate(const CompactArgs &a) {
+    constexpr int ESZ = ROWB / kD;
+    const uint32_t lh = (uint32_t)lhb / (uint32_t)a.batch, l = lh / (uint32_t)a.n_kv_heads, h = lh % (uint32_t)a.n_kv_heads;
+    base = static_cast<char *>((sid & 1) ? a.v : a.k) +
+           ((int64_t)l * a.stride_layer + (int64_t)h * a.stride_head + (PAGED ? 0 : (int64_t)a.seq_off[b] * a.stride_tok)) * ESZ;
+    pitch = (PAGED ? a.map_stride : a.stride_tok) * ESZ;
+    srcs = PAGED ? a.src_rows + lhb * a.src_stride : kept;
+    rmap = PAGED ? a.row_map + a.seq_off[b] : nullptr;
+    room = a.seq_off[b + 1] - a.seq_off[b];
+  }
+};
+
+// Whether a stream's rows are moved past the caches: where the call's rows are so many (kStreamBytes).  A row of indices is often much
+// longer than what is kept, so that the host only knows that they may be.  Here: if they were with every head as long as the
+// stream's own (rows of shorter ones displace little), and are by the lengths of up to 64 heads spread over the call.  The call alone, us, by
+// the list's pitch / like this: 512 streams of 1024 rows in lists of 2000: 57 / 42, 8192 of 64: 38 / 33 (lists of as many: 42, 33).
+__device__ __forceinline__ bool past_the_caches(const CompactArgs &a, int nl, int row_bytes, int lane) {
+  const int heads = a.n_layers * a.n_kv_heads * a.batch;
+  if ((int64_t)nl * heads * 2 * row_bytes <= kStreamBytes) return false;
+  const int at = heads <= 64 ? lane : (int)(((uint64_t)((uint32_t)lane * 0x9E3779B9u) * (uint32_t)heads) >> 32);
+  int n = at < heads ? a.new_len[at] : 0;
+  n = n <= a.kept_stride ? max(n, 0) : 0;
+#pragma unroll
+  for (int m = 1; m < 64; m *= 2) n += __shfl_xor(n, m);
+  return (int64_t)n * max(heads, 64) / 64 * 2 * row_bytes > kStreamBytes;
+}
+
 // SL: bytes of a row that a wave moves.  The argument above holds for every byte column of a stream by
 // itself, so a stream may be split into ROWB / SL waves that know nothing of each other; launch_compact
 // says when.
 template <int ROWB, int SL, bool PAGED, bool STREAM>
-__global__ void __launch_bounds__(256) k_compact(CompactArgs a) {
-  constexpr int NS = ROWB / SL;    // waves per stream
+__device__ __forceinline__ void move_slice(const Stream<ROWB, PAGED> &x, char *base, int lane) {
   constexpr int PPR = SL / 16;     // 16-byte pieces per row slice
   constexpr int RPI = 64 / PPR;    // rows moved by one wave-wide instruction
   constexpr int U = 8;             // instructions in flight per tile
-  constexpr int ESZ = ROWB / kD;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int64_t wid = (int64_t)blockIdx.x * (blockDim.x >> 6) + wave;
-  const int64_t sid = wid / NS;
-  const int64_t n_lhb = (int64_t)a.n_layers * a.n_kv_heads * a.batch;
-  if (sid >= 2 * n_lhb) return;
-  const int64_t lhb = sid >> 1;
-  const int b = (int)(lhb % a.batch);
-  if (PAGED && a.seq_bad[b]) return;  // invalid block table: leave the sequence alone
-  const int lh = (int)(lhb / a.batch), l = lh / a.n_kv_heads, h = lh % a.n_kv_heads;
-  char *base = static_cast<char *>((sid & 1) ? a.v : a.k) +
-               ((int64_t)l * a.stride_layer + (int64_t)h * a.stride_head + (PAGED ? 0 : (int64_t)a.seq_off[b] * a.stride_tok)) * ESZ + (int)(wid % NS) * SL;
-  const int64_t pitch = (PAGED ? a.map_stride : a.stride_tok) * ESZ;  // paged: rows are addressed in units of the row map
-  const int32_t *kept = a.kept_idx + lhb * a.kept_stride;
-  const int32_t *srcs = PAGED ? a.src_rows + lhb * a.src_stride : kept;  // what the row loads are addressed with
-  const int32_t *rmap = PAGED ? a.row_map + a.seq_off[b] : nullptr;
-  const int nl = a.new_len[lhb];
-  // A head that kept everything because its inputs could not be trusted reports its full length,
-  // which its row of indices may not even hold: nothing to move, and nothing to read past the row.
-  if (nl > a.kept_stride || (PAGED && nl > a.src_stride)) return;
-  const int room = a.seq_off[b + 1] - a.seq_off[b];  // contiguous cache: a source index is a row of the sequence
+  const int64_t pitch = x.pitch;
+  const int32_t *kept = x.kept, *srcs = x.srcs, *rmap = x.rmap;
+  const int nl = x.nl, room = x.room;
 
   // first row that actually moves
   int first = nl;
@@ -157,44 +195,93 @@ __global__ void __launch_bounds__(256) k_compact(CompactArgs a) {
 #undef SKIPKV_STORE_TILE
 }
 
+// LARGE: the rows may be so many that they are moved past the caches.
+template <int ROWB, int SL, bool PAGED, bool LARGE>
+__global__ void __launch_bounds__(256) k_compact(CompactArgs a) {
+  constexpr int NS = ROWB / SL;  // waves per stream
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int64_t wid = (int64_t)blockIdx.x * (blockDim.x >> 6) + wave, sid = wid / NS;
+  if (sid >= 2 * (int64_t)a.n_layers * a.n_kv_heads * a.batch) return;
+  Stream<ROWB, PAGED> x(a, (uint32_t)sid);
+  if (!x.valid) return;
+  x.locate(a);
+  char *base = x.base + (int)(wid % NS) * SL;
+  if (LARGE && past_the_caches(a, x.nl, ROWB, lane)) move_slice<ROWB, SL, PAGED, true>(x, base, lane);
+  else move_slice<ROWB, SL, PAGED, false>(x, base, lane);
+}
+
 // The same by a workgroup of eight waves per slice of a stream, which moves eight tiles at a time: all rows of a step have
 // landed in registers before the first of them is stored, so no wave overwrites what another one still has to read, and a
 // step's loads may pass the stores of the one before, which lie in front of everything they read.  For few streams,
 // whose chains of tiles would otherwise be most of the time (launch_compact says when).
 template <int ROWB, int SL, bool PAGED, bool STREAM>
-__global__ void __launch_bounds__(512) k_compact_steps(CompactArgs a) {
-  constexpr int NS = ROWB / SL;    // workgroups per stream
+__device__ __forceinline__ void move_steps(const Stream<ROWB, PAGED> &x, char *base, int first, int wave, int lane) {
   constexpr int PPR = SL / 16;     // 16-byte pieces per row slice
   constexpr int RPI = 64 / PPR;    // rows moved by one wave-wide instruction
   constexpr int U = 8;             // instructions per wave and step
   constexpr int TR = U * RPI;      // rows per wave and step
-  constexpr int SCAN = 4;          // indices per thread of one look for the first row that moves
-  constexpr int ESZ = ROWB / kD;
+  const int sub = lane / PPR, piece = lane % PPR, nl = x.nl;
+  int src[U], dst[U];
+  auto load_rows = [&](int k0) {  // (clamped: rows past the end are the last one)
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int k = min(k0 + wave * TR + u * RPI + sub, nl - 1);
+      src[u] = x.srcs[k];
+      if constexpr (PAGED) dst[u] = x.rmap[k];
+      else {
+        src[u] = max(0, min(src[u], x.room - 1));
+        dst[u] = k;
+      }
+    }
+  };
+  if (first < nl) load_rows(first);
+  for (int k0 = first; k0 < nl; k0 += 8 * TR) {
+    u32x4 v[U];
+    char *to[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      v[u] = load16<STREAM>(base + (int64_t)src[u] * x.pitch + piece * 16);
+      to[u] = base + (int64_t)dst[u] * x.pitch + piece * 16;
+    }
+    load_rows(k0 + 8 * TR);
+    asm volatile("s_waitcnt vmcnt(0)" : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(v[4]), "+v"(v[5]), "+v"(v[6]), "+v"(v[7])::"memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (k0 + wave * TR + u * RPI + sub < nl) store16<STREAM>(to[u], v[u]);
+  }
+}
+
+template <int ROWB, int SL, bool PAGED, bool LARGE>
+__global__ void __launch_bounds__(512) k_compact_steps(CompactArgs a, int step_rows) {
+  constexpr int NS = ROWB / SL;  // workgroups per stream
+  constexpr int SCAN = 4;        // indices per thread of one look for the first row that moves
+  constexpr int SHORT = 64;      // slices of streams that are too short for this: of as few streams' otherwise (launch_compact)
   __shared__ int first_s;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int64_t sid = blockIdx.x / NS, lhb = sid >> 1;
-  const int b = (int)(lhb % a.batch);
-  if (PAGED && a.seq_bad[b]) return;  // invalid block table: leave the sequence alone
-  const int lh = (int)(lhb / a.batch), l = lh / a.n_kv_heads, h = lh % a.n_kv_heads;
-  char *base = static_cast<char *>((sid & 1) ? a.v : a.k) +
-               ((int64_t)l * a.stride_layer + (int64_t)h * a.stride_head + (PAGED ? 0 : (int64_t)a.seq_off[b] * a.stride_tok)) * ESZ + (int)(blockIdx.x % NS) * SL;
-  const int64_t pitch = (PAGED ? a.map_stride : a.stride_tok) * ESZ;
-  const int32_t *kept = a.kept_idx + lhb * a.kept_stride;
-  const int32_t *srcs = PAGED ? a.src_rows + lhb * a.src_stride : kept;
-  const int32_t *rmap = PAGED ? a.row_map + a.seq_off[b] : nullptr;
-  const int nl = a.new_len[lhb];
-  if (nl > a.kept_stride || (PAGED && nl > a.src_stride)) return;  // (as in k_compact)
-  const int room = a.seq_off[b + 1] - a.seq_off[b];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  Stream<ROWB, PAGED> x(a, blockIdx.x / NS);
+  if (!x.valid) return;
+  const int nl = x.nl, at_byte = (int)(blockIdx.x % NS) * SL;
+  if (__builtin_expect(nl < step_rows, false)) {
+    x.locate(a);
+    if (wave < SL / SHORT) move_slice<ROWB, SHORT, PAGED, false>(x, x.base + at_byte + wave * SHORT, lane);
+    return;
+  }
+  x.locate(a);
+  const bool stream = LARGE && past_the_caches(a, nl, ROWB, lane);
 
   int first = nl;
   for (int k0 = 0; k0 < nl; k0 += 512 * SCAN) {
     if (tid == 0) first_s = nl;
     __syncthreads();
-    int mine = nl;
+    int mine = nl, at[SCAN];
+#pragma unroll
+    for (int j = 0; j < SCAN; ++j) at[j] = x.kept[min(k0 + 512 * j + tid, nl - 1)];  // (all of them before the first is looked at)
 #pragma unroll
     for (int j = SCAN - 1; j >= 0; --j) {
       const int k = k0 + 512 * j + tid;
-      if (k < nl && kept[k] != k) mine = k;
+      if (k < nl && at[j] != k) mine = k;
     }
     if (mine < nl) atomicMin(&first_s, mine);
     __syncthreads();
@@ -202,38 +289,8 @@ __global__ void __launch_bounds__(512) k_compact_steps(CompactArgs a) {
     if (first < nl) break;
     __syncthreads();
   }
-
-  const int sub = lane / PPR, piece = lane % PPR;
-  int src[U], dst[U];
-  auto load_rows = [&](int k0) {  // (clamped: rows past the end are the last one)
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int k = min(k0 + wave * TR + u * RPI + sub, nl - 1);
-      src[u] = srcs[k];
-      if constexpr (PAGED) dst[u] = rmap[k];
-      else {
-        src[u] = max(0, min(src[u], room - 1));
-        dst[u] = k;
-      }
-    }
-  };
-  if (first < nl) load_rows(first);
-  for (int k0 = first; k0 < nl; k0 += 8 * TR) {
-    u32x4 x[U];
-    char *to[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      x[u] = load16<STREAM>(base + (int64_t)src[u] * pitch + piece * 16);
-      to[u] = base + (int64_t)dst[u] * pitch + piece * 16;
-    }
-    load_rows(k0 + 8 * TR);
-    asm volatile("s_waitcnt vmcnt(0)" : "+v"(x[0]), "+v"(x[1]), "+v"(x[2]), "+v"(x[3]), "+v"(x[4]), "+v"(x[5]), "+v"(x[6]), "+v"(x[7])::"memory");
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-      if (k0 + wave * TR + u * RPI + sub < nl) store16<STREAM>(to[u], x[u]);
-  }
+  if (LARGE && stream) move_steps<ROWB, SL, PAGED, true>(x, x.base + at_byte, first, wave, lane);
+  else move_steps<ROWB, SL, PAGED, false>(x, x.base + at_byte, first, wave, lane);
 }
 
 // Paged cache: src_rows[head, k] = slot row of the head's kept token k, for k < new_len (one wave
@@ -251,43 +308,37 @@ __global__ void __launch_bounds__(256) k_kept_rows(CompactArgs a) {
   for (int k = lane; k < nl; k += 64) out[k] = rmap[max(0, min(kept[k], room - 1))];
 }
 
-template <int ROWB, int SL, bool STREAM>
+template <int ROWB, int SL, bool LARGE>
 void launch_slices(const CompactArgs &a, int64_t streams, hipStream_t st) {
   const unsigned grid = (unsigned)((streams * (ROWB / SL) + 3) / 4);
   if (a.row_map)
-    hipLaunchKernelGGL((k_compact<ROWB, SL, true, STREAM>), dim3(grid), dim3(256), 0, st, a);
+    hipLaunchKernelGGL((k_compact<ROWB, SL, true, LARGE>), dim3(grid), dim3(256), 0, st, a);
   else
-    hipLaunchKernelGGL((k_compact<ROWB, SL, false, STREAM>), dim3(grid), dim3(256), 0, st, a);
+    hipLaunchKernelGGL((k_compact<ROWB, SL, false, LARGE>), dim3(grid), dim3(256), 0, st, a);
 }
 
-// Rows of large caches are read once and written once before anybody comes back to them: they are moved past the caches, and
-// displace neither each other nor what the next kernels need.  Small ones are found in the memory-side cache again by
-// what follows the call (the next call at the latest).  Whole call, us, ordinary / past the caches, by the rows' bytes in K and V:
-//   one sequence, 4096 rows kept:   16 MB 83 / 98   64 MB 92 / 119   128 MB 132 / 141   192 MB 153 / 153   256 MB 181 / 174
-//                                   512 MB 306 / 278
-//   per-head ranges, 1024 kept:     128 MB 109 / 106   512 MB 305 / 288   2 GB 1058 / 1015
-constexpr int64_t kStreamBytes = 192ll << 20;
-
+// The caller's row of indices bounds the rows.  (Slices of 64 bytes are for so few streams that, where the bound is beyond kStreamBytes,
+// it is beyond kStepRowsLong, too: those move in steps.)
 template <int ROWB, int SL>
 void launch_slices(const CompactArgs &a, int64_t streams, hipStream_t st) {
-  if (streams * a.kept_stride * ROWB > kStreamBytes) launch_slices<ROWB, SL, true>(a, streams, st);
+  if (SL > 64 && streams * a.kept_stride * ROWB > kStreamBytes) launch_slices<ROWB, SL, (SL > 64)>(a, streams, st);
   else launch_slices<ROWB, SL, false>(a, streams, st);
 }
 
-template <int ROWB, bool STREAM>
-void launch_steps(const CompactArgs &a, int64_t streams, hipStream_t st) {
+template <int ROWB, bool LARGE>
+void launch_steps(const CompactArgs &a, int64_t streams, int step_rows, hipStream_t st) {
   constexpr int SL = 128;
   const dim3 grid((unsigned)(streams * (ROWB / SL)));
   if (a.row_map)
-    hipLaunchKernelGGL((k_compact_steps<ROWB, SL, true, STREAM>), grid, dim3(512), 0, st, a);
+    hipLaunchKernelGGL((k_compact_steps<ROWB, SL, true, LARGE>), grid, dim3(512), 0, st, a, step_rows);
   else
-    hipLaunchKernelGGL((k_compact_steps<ROWB, SL, false, STREAM>), grid, dim3(512), 0, st, a);
+    hipLaunchKernelGGL((k_compact_steps<ROWB, SL, false, LARGE>), grid, dim3(512), 0, st, a, step_rows);
 }
 
 template <int ROWB>
-void launch_steps(const CompactArgs &a, int64_t streams, hipStream_t st) {
-  if (streams * a.kept_stride * ROWB > kStreamBytes) launch_steps<ROWB, true>(a, streams, st);
-  else launch_steps<ROWB, false>(a, streams, st);
+void launch_steps(const CompactArgs &a, int64_t streams, int step_rows, hipStream_t st) {
+  if (streams * a.kept_stride * ROWB > kStreamBytes) launch_steps<ROWB, true>(a, streams, step_rows, st);
+  else launch_steps<ROWB, false>(a, streams, step_rows, st);
 }
 
 }  // namespace
@@ -305,7 +356,9 @@ void launch_steps(const CompactArgs &a, int64_t streams, hipStream_t st) {
 //   paged 256  24.6 / 24.3   35.9 / 35.4   79.0 / 78.0   144 / 135      124 / 114
 //   fp32 rows are twice as long: 64 streams of them behave like 128 of bf16
 // Slices of 64 bytes take this up to twice as long from 64 streams on, and whole rows half as much again at 8.  Streams are
-// counted in columns of 256 bytes; the caller's row of indices bounds the rows.
+// counted in columns of 256 bytes.  The host goes by the caller's row of indices, which bounds the rows; a stream that turns out to keep
+// fewer rows than the lines below is moved by a wave per slice all the same (128 streams of 600 rows in lists of 3000, us: in steps 9.6,
+// like this 7.7, lists of 600 8.5).
 constexpr int64_t kStepColumns = 64, kStepRows = 1024, kStepColumnsLong = 256, kStepRowsLong = 2560;
 
 // Otherwise rows are split into slices of 128 or 64 bytes (half a cache line: the least that a wave should take) as long as that makes no more
@@ -320,9 +373,12 @@ hipError_t launch_compact(const CompactArgs &a, hipStream_t st) {
   if (a.row_map) hipLaunchKernelGGL(k_kept_rows, dim3((unsigned)((heads + 3) / 4)), dim3(256), 0, st, a);
   const int64_t fit = 1024 / streams;  // slices that make at most 1024 waves
   const int64_t columns = streams * (a.dtype == SKIPKV_BF16 ? 1 : 2);
-  if (columns <= kStepColumns ? a.kept_stride >= kStepRows : columns <= kStepColumnsLong && a.kept_stride >= kStepRowsLong) {
-    if (a.dtype == SKIPKV_BF16) launch_steps<256>(a, streams, st);
-    else launch_steps<512>(a, streams, st);
+  const int64_t step_rows = columns <= kStepColumns ? kStepRows : kStepRowsLong;
+  if (columns <= kStepColumnsLong && a.kept_stride >= step_rows) {
+    // (two waves of a workgroup of eight are slower at more than some 160 columns than waves by themselves: from 1024 rows on, then, rather steps)
+    const int fewest = (int)(columns > 160 ? kStepRows : step_rows);
+    if (a.dtype == SKIPKV_BF16) launch_steps<256>(a, streams, fewest, st);
+    else launch_steps<512>(a, streams, fewest, st);
   } else if (a.dtype == SKIPKV_BF16) {
     if (fit >= 4) launch_slices<256, 64>(a, streams, st);
     else if (fit >= 2) launch_slices<256, 128>(a, streams, st);

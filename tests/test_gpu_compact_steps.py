@@ -1,5 +1,6 @@
 """The compaction of long chains of few streams, which moves 512 rows of a stream at a time: lengths around that, first moved
-rows in front of and behind what one look for them covers (2048), heads that move nothing, on both kinds of caches."""
+rows in front of and behind what one look for them covers (2048), heads that move nothing or too little for steps (up to 64 columns of
+256 bytes and beyond 160: less than 1024 rows, in between: 2560), on both kinds of caches."""
 import numpy as np
 import pytest
 import torch
@@ -22,7 +23,7 @@ def _kept(rng, n_tok, first, n):
 
 
 @pytest.mark.parametrize("paged", [False, True])
-@pytest.mark.parametrize("dtype,n_layers", [("bf16", 1), ("bf16", 8), ("f32", 1), ("f32", 4)])  # up to 128 columns of 256 bytes, and 256
+@pytest.mark.parametrize("dtype,n_layers", [("bf16", 1), ("bf16", 2), ("bf16", 4), ("bf16", 8), ("f32", 1), ("f32", 2), ("f32", 4)])  # 32 to 256 columns of 256 bytes
 def test_rows_moved_eight_tiles_at_a_time(dtype, n_layers, paged):
     H, n_toks, bs = 8, [4100, 3001], 16
     st = _structure([[0, n] for n in n_toks])
@@ -34,7 +35,7 @@ def test_rows_moved_eight_tiles_at_a_time(dtype, n_layers, paged):
     v0 = torch.randn((n_layers, H, T, 128), generator=g, device="cuda").to(dt)
     rng = np.random.default_rng(11)
     shapes = [(0, 1), (0, 511), (0, 512), (0, 513), (3, 1027), (700, 701), (2047, 2500), (2048, 2049), (2100, 2900), (5, 3000), (40, 40), (0, 0),
-              (511, 1024), (1, 1536), (2049, 2560), (0, 2048)]
+              (511, 1024), (1, 1536), (2049, 2560), (0, 2048), (4, 1023), (4, 2559), (0, 2999)]
     kept = torch.full((n_layers, H, 2, STRIDE), -1, dtype=torch.int32)
     new_len = torch.zeros((n_layers, H, 2), dtype=torch.int32)
     rows = {}
