@@ -198,6 +198,19 @@ __global__ void __launch_bounds__(64 * kWaves, 4) k_tokred_sweep(TokRedArgs a) {
   const int ld_row = 4 * wave_u + (lane >> 4), ld_piece = (lane & 15) ^ swz16(ld_row & 15);
   [[maybe_unused]] const uint32_t ld_off = (uint32_t)ld_row * (uint32_t)pitch + (uint32_t)ld_piece * 16;
   static_assert(kCols == 64 && 4 * kWaves % 16 == 0, "the loads of a lane have rows that are swizzled alike");
+  // Other caches: a lane's rows of the block that is fetched next.  They are looked up a block ahead: looked up with the fetch, each
+  // of them waits for the direct loads before it, too (pages, bf16, us, both sweeps looked up with the fetch / ahead: 4096 heads of 300
+  // tokens 523 / 494, 64 of 4096 457 / 425, 7168 of 1000 5221 / 4679; fp32, 64 of 4096 577 / 520).
+  [[maybe_unused]] int ahead[kPieces];
+  auto look_up = [&](int jb) {
+    if constexpr (!SIMPLE) {
+#pragma unroll
+      for (int it = 0; it < kPieces; ++it) {
+        const int row = min(jb + 4 * kWaves * it + ld_row, n_tok - 1);
+        ahead[it] = rmap ? rmap[row] : row;
+      }
+    }
+  };
   auto fetch = [&](int jb, int buf) {
     const int left = n_tok - jb;
     if (SIMPLE && DIRECT && left >= kCols) {
@@ -207,7 +220,7 @@ __global__ void __launch_bounds__(64 * kWaves, 4) k_tokred_sweep(TokRedArgs a) {
     } else {
 #pragma unroll
       for (int it = 0; it < kPieces; ++it) {
-        const char *src = kbase + slot_of(jb + min(4 * kWaves * it + ld_row, left - 1)) * pitch;
+        const char *src = kbase + (int64_t)(SIMPLE ? jb + min(4 * kWaves * it + ld_row, left - 1) : ahead[it]) * pitch;
         if constexpr (DIRECT) load_to_lds_16(src + ld_piece * 16, cols[buf] + (it * kWaves + wave_u) * 1024);
         else pre[it] = load_piece_bf16<DT>(src, ld_piece);
       }
@@ -241,7 +254,9 @@ __global__ void __launch_bounds__(64 * kWaves, 4) k_tokred_sweep(TokRedArgs a) {
     }
   };
   int buf = 0;
+  look_up(r0);
   fetch(r0, buf);
+  look_up(r0 + kCols);
 #pragma unroll 1
   for (int jb = r0; jb < n_tok; jb += kCols, buf ^= 1) {
     commit(buf);
@@ -249,7 +264,10 @@ __global__ void __launch_bounds__(64 * kWaves, 4) k_tokred_sweep(TokRedArgs a) {
     // of the block in between and with it the end of its own reads.
     wait_vm<0>();  // (the compiler does not know of the direct loads)
     __syncthreads();
-    if (jb + kCols < n_tok) fetch(jb + kCols, buf ^ 1);  // lands while this block is multiplied
+    if (jb + kCols < n_tok) {
+      fetch(jb + kCols, buf ^ 1);  // lands while this block is multiplied
+      look_up(jb + 2 * kCols);
+    }
     if (jb > r0 + kCols) emit(jb - kCols, buf ^ 1);  // the first block has no mirror image
     // 64 x 64 squares on the diagonal are computed in full, blocks right of them stand for their transposes
     // too, blocks left of them are the transposes

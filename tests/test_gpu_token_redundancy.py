@@ -148,3 +148,25 @@ def test_rows_sixteen_megabytes_apart():
         want = out if want is None else want
         assert torch.equal(out, want)
     _check(cfg, st, rows.view(1, 1, -1, 128), want, [(0, 0, b) for b in range(len(lens))], 1e-4)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("block_size", [1, 16, 24, 128])
+def test_pages_give_the_bits_of_a_contiguous_cache(dtype, block_size):
+    # rows of a column block are looked up a block ahead: lengths around blocks of 64 columns and workgroups of 256 rows
+    from test_gpu_paged import _to_pages
+    lens = [1, 63, 64, 65, 127, 128, 129, 191, 193, 255, 256, 257, 319, 321, 700]
+    st = _structure([[0, n] for n in lens])
+    cfg = W.Config("tokred-pages", 9, len(lens), 2, 3, 12, dtype, 0, 0, 64, 8, 16, 16.0, 0.0)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(block_size)
+    k = torch.randn((2, 3, st.total_tokens, 128), generator=g, device="cuda").to(torch.bfloat16 if dtype == "bf16" else torch.float32)
+    want = _run(cfg, st, k)
+    kp, vp, table = _to_pages(cfg, st, k, k, block_size, seed=3)
+    so, sp, sf = (torch.from_numpy(x).cuda() for x in (st.seq_off, st.sent_ptr, st.sent_off))
+    cache = B.PagedCache(kp, vp, table, cfg.n_q_heads, so, sp, sf, st.total_tokens, st.total_sentences)
+    ws = torch.empty(B.skipkv_redundancy_paged_workspace_bytes(cache), dtype=torch.uint8, device="cuda")
+    got = torch.full_like(want, float("nan"))
+    B.skipkv_token_redundancy_paged(cache, got, None, ws)
+    torch.cuda.synchronize()
+    assert torch.equal(got, want)
