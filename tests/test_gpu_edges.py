@@ -422,18 +422,20 @@ def test_lengths_around_chunk_and_stage_edges(dtype, sent_hi):
     assert stats["heads"] == 2 * len(lens)
 
 
+@pytest.mark.parametrize("first", [600, 300])
 @pytest.mark.parametrize("block_size", [0, 24])
 @pytest.mark.parametrize("group,alpha", [(1, 1), (4, 16), (7, 8), (5, 32), (3, 29), (8, 32)])
-def test_two_pass_scan_shapes(group, alpha, block_size):
+def test_two_pass_scan_shapes(group, alpha, block_size, first):
     """Every split of the query rows over the waves of the two-pass bf16 scan, with odd group sizes and windows, on
     lengths one below, at and one above its tile (64 rows) and chunk (256 tokens) after a sentence that no chunk
     holds, and with up to 32 sentences per chunk: every head against the oracle, by the tolerances of the other
-    parity tests (fp32 sums of bf16 products, as everywhere)."""
+    parity tests (fp32 sums of bf16 products, as everywhere).  (First sentences of 300 tokens are cut by the
+    single-pass scan, which takes such sequences of a contiguous cache with up to 64 query rows.)"""
     from test_gpu_paged import _from_pages, _run_paged, _to_pages
     rng = np.random.default_rng(group * 33 + alpha)
     offsets = []
-    for i, n in enumerate([301, 363, 364, 365, 555, 556, 557, 900]):
-        off = [0, 300]
+    for i, n in enumerate(first + x for x in [1, 63, 64, 65, 255, 256, 257, 600]):
+        off = [0, first]
         while off[-1] < n:
             off.append(min(n, off[-1] + int(rng.integers(1, 5 if i % 2 else 20))))
         offsets.append(off)
@@ -551,6 +553,9 @@ def test_plans_of_a_thousand_sequences_equal_those_of_a_few(most):
     offsets[7] = np.concatenate([[0], np.cumsum([40] * 500 + [300] + [40] * 500)]).tolist()  # cut, and more spans than a wave's share of the table
     offsets[8] = [0, 200, 210, 500, 800]            # cut
     offsets[9] = [0]                                # an empty sequence
+    # sentences that the single-pass scan does not take; of one chunk, since the runs of chunks that records stand for are chosen by
+    # the lengths in the whole batch, and where they end shows in the last bits
+    offsets[11], offsets[1028] = [0, 600], [0, 513]
     offsets[10] = [0, 7, 7, 20]                     # not ascending: reported, the others are not affected
     st = _structure(offsets)
     assert (st.total_sentences > 640 * len(offsets)) == (most > 9)
@@ -575,13 +580,13 @@ def test_plans_of_a_thousand_sequences_equal_those_of_a_few(most):
             assert torch.equal(out.sent_lambda[..., a:a + n], ref.sent_lambda[..., c:c + n])
 
 
-@pytest.mark.parametrize("kind", ["short", "long sentence", "bad offsets", "empty"])
+@pytest.mark.parametrize("kind", ["short", "cut sentence", "long sentence", "bad offsets", "empty"])
 @pytest.mark.parametrize("n_layers", [1, 60])
 def test_a_sequence_alone_gives_what_it_gives_in_a_batch(kind, n_layers):
     # a plan of one sequence writes the header itself; with few heads it marks the statistics records too
     rng = np.random.default_rng(4)
-    first = {"short": np.concatenate([[0], np.cumsum(rng.integers(1, 40, size=30))]).tolist(), "long sentence": [0, 10, 300, 340],
-             "bad offsets": [0, 10, 10, 40], "empty": [0]}[kind]
+    first = {"short": np.concatenate([[0], np.cumsum(rng.integers(1, 40, size=30))]).tolist(), "cut sentence": [0, 10, 300, 340],
+             "long sentence": [0, 10, 600, 640], "bad offsets": [0, 10, 10, 40], "empty": [0]}[kind]
     pair = _structure([first, [0, 9, 30, 77, 100]])
     one = _structure([first])
     cfg = W.Config("pair", 9, 2, n_layers, 8, 32, "bf16", 0, 0, 24, 8, 8, 8.0, 0.0)

@@ -112,7 +112,7 @@ def test_jumping_logits_in_runs_of_several_chunks():
 @pytest.mark.parametrize("group,alpha", [(5, 32), (4, 16)])
 def test_jumping_logits_on_pages(group, alpha, block_size):
     from test_gpu_paged import _run_paged, _to_pages
-    st = _structure([[0, 300, 310, 500, 777], [0, 5, 700, 1000], [0, 17]])
+    st = _structure([[0, 600, 610, 680, 777], [0, 5, 700, 1000], [0, 17]])  # (sentences that the single-pass scan leaves)
     cfg = _cfg("page-jumps", 3, 1, 2, group, alpha)
     g = torch.Generator(device="cuda")
     g.manual_seed(8)
