@@ -10,6 +10,8 @@
 // What bounds it is memory: 5.7 TB/s read and written on large caches.
 #include "common.h"
 
+#include <type_traits>
+
 namespace skipkv {
 
 namespace {
@@ -43,51 +45,62 @@ __device__ __forceinline__ void store16(char *p, u32x4 x) {
 // A stream: the rows of K or of V of a head of a sequence, and where they go.
 template <int ROWB, bool PAGED>
 struct Stream {
-  int64_t sid, lhb;
-  int b;
-  const int32_t *kept;   // the head's row of indices
-  int nl;                // rows kept
-  bool valid;
-  // set by locate(), which has the waits for what it loads: called where they are needed
   char *base;            // first row of the sequence (paged: the head's base)
   int64_t pitch;         // paged: of the units of the row map
+  const int32_t *kept;   // the head's row of indices
   const int32_t *srcs;   // what the row loads are addressed with
   const int32_t *rmap;   // paged: slot rows of the sequence
-  int room;              // rows of the sequence (contiguous cache: a source index is one of them)
+  int nl, room;          // rows kept; rows of the sequence (contiguous cache: a source index is one of them)
+  bool valid;
 
-  __device__ __forceinline__ Stream(const CompactArgs &a, uint32_t sid_) : sid(sid_), lhb(sid_ >> 1), b((int)((sid_ >> 1) % (uint32_t)a.batch)) {
-    kept = a.kept_idx + lhb * a.kept_stride;
+  __device__ __forceinline__ Stream(const CompactArgs &a, uint32_t sid) {
+    constexpr int ESZ = ROWB / kD;
+    // the arguments in one go, and what they point to (else there are waits for a few of them at a time, all along the way)
+    asm volatile("" ::"s"(a.k), "s"(a.v), "s"(a.stride_layer), "s"(a.stride_head), "s"(a.stride_tok), "s"(a.seq_off), "s"(a.kept_idx), "s"(a.new_len));
+    const uint32_t lhb = sid >> 1, lh = lhb / (uint32_t)a.batch, b = lhb - lh * (uint32_t)a.batch;
     nl = a.new_len[lhb];
+    const int t0 = a.seq_off[b], t1 = a.seq_off[b + 1];
+    const bool bad = PAGED && a.seq_bad[b];
+    __builtin_amdgcn_sched_barrier(0);
+    const uint32_t l = lh / (uint32_t)a.n_kv_heads, h = lh - l * (uint32_t)a.n_kv_heads;
+    base = static_cast<char *>((sid & 1) ? a.v : a.k) + ((int64_t)l * a.stride_layer + (int64_t)h * a.stride_head + (PAGED ? 0 : (int64_t)t0 * a.stride_tok)) * ESZ;
+    pitch = (PAGED ? a.map_stride : a.stride_tok) * ESZ;
+    kept = a.kept_idx + (int64_t)lhb * a.kept_stride;
+    srcs = PAGED ? a.src_rows + (int64_t)lhb * a.src_stride : kept;
+    rmap = PAGED ? a.row_map + t0 : nullptr;
+    room = t1 - t0;
     // An invalid block table: leave the sequence alone.  A head that kept everything because its inputs could not be trusted reports
     // its full length, which its row of indices may not even hold: nothing to move, and nothing to read past the row.
-    valid = !(PAGED && a.seq_bad[b]) && nl <= a.kept_stride && !(PAGED && nl > a.src_stride);
-  }
-  __device__ __forceinline__ void locate(const CompactArgs &a) {
-    constexpr int ESZ = ROWB / kD;
-    const uint32_t lh = (uint32_t)lhb / (uint32_t)a.batch, l = lh / (uint32_t)a.n_kv_heads, h = lh % (uint32_t)a.n_kv_heads;
-    base = static_cast<char *>((sid & 1) ? a.v : a.k) +
-           ((int64_t)l * a.stride_layer + (int64_t)h * a.stride_head + (PAGED ? 0 : (int64_t)a.seq_off[b] * a.stride_tok)) * ESZ;
-    pitch = (PAGED ? a.map_stride : a.stride_tok) * ESZ;
-    srcs = PAGED ? a.src_rows + lhb * a.src_stride : kept;
-    rmap = PAGED ? a.row_map + a.seq_off[b] : nullptr;
-    room = a.seq_off[b + 1] - a.seq_off[b];
+    valid = !bad && nl <= a.kept_stride && !(PAGED && nl > a.src_stride);
   }
 };
 
 // Whether a stream's rows are moved past the caches: where the call's rows are so many (kStreamBytes).  A row of indices is often much
 // longer than what is kept, so that the host only knows that they may be.  Here: if they were with every head as long as the
-// stream's own (rows of shorter ones displace little), and are by the lengths of up to 64 heads spread over the call.  The call alone, us, by
-// the list's pitch / like this: 512 streams of 1024 rows in lists of 2000: 57 / 42, 8192 of 64: 38 / 33 (lists of as many: 42, 33).
-__device__ __forceinline__ bool past_the_caches(const CompactArgs &a, int nl, int row_bytes, int lane) {
-  const int heads = a.n_layers * a.n_kv_heads * a.batch;
-  if ((int64_t)nl * heads * 2 * row_bytes <= kStreamBytes) return false;
-  const int at = heads <= 64 ? lane : (int)(((uint64_t)((uint32_t)lane * 0x9E3779B9u) * (uint32_t)heads) >> 32);
-  int n = at < heads ? a.new_len[at] : 0;
-  n = n <= a.kept_stride ? max(n, 0) : 0;
+// stream's own (rows of shorter ones displace little), and are by the lengths of eight heads spread over the call, which are loaded
+// together with its own.  The call alone, us, by the list's pitch / like this: 512 streams of 1024 rows in lists of 2000: 57 / 42, 8192 of
+// 64: 38 / 33 (lists of as many: 42, 33).
+struct Spread {
+  int len[8];
+  __device__ __forceinline__ explicit Spread(const CompactArgs &a) {
+    typedef const __attribute__((address_space(4))) int32_t *ConstIntPtr;  // constant while the kernel runs: scalar loads
+    const ConstIntPtr new_len = (ConstIntPtr)a.new_len;
+    const uint32_t heads = (uint32_t)(a.n_layers * a.n_kv_heads * a.batch);
 #pragma unroll
-  for (int m = 1; m < 64; m *= 2) n += __shfl_xor(n, m);
-  return (int64_t)n * max(heads, 64) / 64 * 2 * row_bytes > kStreamBytes;
-}
+    for (uint32_t i = 0; i < 8; ++i) len[i] = new_len[(uint32_t)(((uint64_t)(i * 0x9E3779B9u) * heads) >> 32)];
+    __builtin_amdgcn_sched_barrier(0);  // (all of them under way, and nothing waits for them yet)
+  }
+  __device__ __forceinline__ bool past_the_caches(const CompactArgs &a, int nl, int row_bytes) const {
+    int64_t rows = 0;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) rows += len[i] <= a.kept_stride ? max(len[i], 0) : 0;
+    return min(rows, (int64_t)8 * nl) * ((int64_t)a.n_layers * a.n_kv_heads * a.batch) * 2 * row_bytes > 8 * kStreamBytes;
+  }
+};
+struct NoSpread {
+  __device__ __forceinline__ explicit NoSpread(const CompactArgs &) {}
+  __device__ __forceinline__ bool past_the_caches(const CompactArgs &, int, int) const { return false; }
+};
 
 // SL: bytes of a row that a wave moves.  The argument above holds for every byte column of a stream by
 // itself, so a stream may be split into ROWB / SL waves that know nothing of each other; launch_compact
@@ -202,11 +215,11 @@ __global__ void __launch_bounds__(256) k_compact(CompactArgs a) {
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int64_t wid = (int64_t)blockIdx.x * (blockDim.x >> 6) + wave, sid = wid / NS;
   if (sid >= 2 * (int64_t)a.n_layers * a.n_kv_heads * a.batch) return;
-  Stream<ROWB, PAGED> x(a, (uint32_t)sid);
+  const std::conditional_t<LARGE, Spread, NoSpread> all(a);
+  const Stream<ROWB, PAGED> x(a, (uint32_t)sid);
   if (!x.valid) return;
-  x.locate(a);
   char *base = x.base + (int)(wid % NS) * SL;
-  if (LARGE && past_the_caches(a, x.nl, ROWB, lane)) move_slice<ROWB, SL, PAGED, true>(x, base, lane);
+  if (LARGE && all.past_the_caches(a, x.nl, ROWB)) move_slice<ROWB, SL, PAGED, true>(x, base, lane);
   else move_slice<ROWB, SL, PAGED, false>(x, base, lane);
 }
 
@@ -260,16 +273,14 @@ __global__ void __launch_bounds__(512) k_compact_steps(CompactArgs a, int step_r
   constexpr int SHORT = 64;      // slices of streams that are too short for this: of as few streams' otherwise (launch_compact)
   __shared__ int first_s;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  Stream<ROWB, PAGED> x(a, blockIdx.x / NS);
+  const std::conditional_t<LARGE, Spread, NoSpread> all(a);
+  const Stream<ROWB, PAGED> x(a, blockIdx.x / NS);
   if (!x.valid) return;
   const int nl = x.nl, at_byte = (int)(blockIdx.x % NS) * SL;
   if (__builtin_expect(nl < step_rows, false)) {
-    x.locate(a);
-    if (wave < SL / SHORT) move_slice<ROWB, SHORT, PAGED, false>(x, x.base + at_byte + wave * SHORT, lane);
+      if (wave < SL / SHORT) move_slice<ROWB, SHORT, PAGED, false>(x, x.base + at_byte + wave * SHORT, lane);
     return;
   }
-  x.locate(a);
-  const bool stream = LARGE && past_the_caches(a, nl, ROWB, lane);
 
   int first = nl;
   for (int k0 = 0; k0 < nl; k0 += 512 * SCAN) {
@@ -289,7 +300,7 @@ __global__ void __launch_bounds__(512) k_compact_steps(CompactArgs a, int step_r
     if (first < nl) break;
     __syncthreads();
   }
-  if (LARGE && stream) move_steps<ROWB, SL, PAGED, true>(x, x.base + at_byte, first, wave, lane);
+  if (LARGE && all.past_the_caches(a, nl, ROWB)) move_steps<ROWB, SL, PAGED, true>(x, x.base + at_byte, first, wave, lane);
   else move_steps<ROWB, SL, PAGED, false>(x, x.base + at_byte, first, wave, lane);
 }
 
@@ -375,8 +386,9 @@ hipError_t launch_compact(const CompactArgs &a, hipStream_t st) {
   const int64_t columns = streams * (a.dtype == SKIPKV_BF16 ? 1 : 2);
   const int64_t step_rows = columns <= kStepColumns ? kStepRows : kStepRowsLong;
   if (columns <= kStepColumnsLong && a.kept_stride >= step_rows) {
-    // (two waves of a workgroup of eight are slower at more than some 160 columns than waves by themselves: from 1024 rows on, then, rather steps)
-    const int fewest = (int)(columns > 160 ? kStepRows : step_rows);
+    // Budgets that whole sentences fill leave a list a little short.  And two waves of a workgroup of eight are slower at more than some 160
+    // columns than waves by themselves: rather steps, there, too.
+    const int fewest = (int)(columns > 160 || step_rows == kStepRows ? kStepRows * 7 / 8 : step_rows);
     if (a.dtype == SKIPKV_BF16) launch_steps<256>(a, streams, fewest, st);
     else launch_steps<512>(a, streams, fewest, st);
   } else if (a.dtype == SKIPKV_BF16) {
