@@ -80,13 +80,6 @@
 // slots, a stage spans at most two blocks: two scalar reads of the map give two bases per stage.
 #include "scan_dev.h"
 
-#ifndef SKIPKV_FRAG_AHEAD
-#define SKIPKV_FRAG_AHEAD 6  // fragments are read this many matrix instructions ahead of their use
-#endif
-#ifndef SKIPKV_SCAN_NBUF
-#define SKIPKV_SCAN_NBUF 3   // stage buffers per wave
-#endif
-
 namespace skipkv {
 
 namespace {
@@ -94,6 +87,8 @@ namespace {
 constexpr int kStageRows = 16;                      // rows per pipeline stage = one MFMA sub-tile of tokens
 constexpr int kSpanStages = kSpanCap / kStageRows;  // stages per span
 constexpr int kMergeDepth = 8;                      // records a lane has in flight while merging
+constexpr int kStageBufs = 3;                       // stage buffers per wave: the load stream runs up to two stages ahead of the compute
+constexpr int kFragAhead = 6;                       // fragments are read this many matrix instructions ahead of their use
 
 // Unsigned division by a number that is constant in the kernel, for dividends below 2^31: with a scalar dividend a handful
 // of scalar instructions, where the compiler's own takes some twenty vector ones and their latency.
@@ -168,7 +163,7 @@ __global__ void __launch_bounds__(256, (DT == SKIPKV_BF16 ? 2 : 1)) k_scan_fused
   constexpr int PPR = ROWB / 16;                      // 16-byte pieces per row
   constexpr int GL = kStageRows * PPR / 64;           // direct loads per stage
   constexpr int RPL = 64 / PPR;                       // rows covered by one direct load
-  constexpr int NBUF = SKIPKV_SCAN_NBUF;
+  constexpr int NBUF = kStageBufs;
   constexpr int STAGEB = kStageRows * ROWB;
   // bf16 keys are pooled with an indicator whose ones are written as 2.0 (a single bit, cheap to
   // build from a row mask): all key sums of that path carry this factor, which the normalisation
@@ -184,6 +179,7 @@ __global__ void __launch_bounds__(256, (DT == SKIPKV_BF16 ? 2 : 1)) k_scan_fused
   __shared__ __align__(16) float wstat[4][R][2];               // (reference, sum) of every row over each wave's span
   __shared__ float mstat[4][R][2];               // (reference, sum) of every row over each wave's quarter of the head's records
   __shared__ float imp[4][kSpanCap];             // token importance of each wave's span (private to the wave unless a sentence goes on in the next one)
+  static_assert(kSpanCap == kSpanStages * kStageRows, "the spans of a sentence, kSpanCap tokens each but the last, lie one behind the other in imp");
   __shared__ float more_sum[4][kD];              // key sum of a span that goes on with the sentence of the one before
   __shared__ __align__(16) float row_norm_l[4][R];  // every wave's own copy of the head's normalisers (+inf: padding row)
   __shared__ int s_timeout[2];  // [item parity] a wait of the item ran out: its sentences get NaN means
@@ -371,7 +367,7 @@ __global__ void __launch_bounds__(256, (DT == SKIPKV_BF16 ? 2 : 1)) k_scan_fused
 
   Item cur = load_item(blockIdx.x);
   if (cur.item >= n_items) return;
-  static_assert(NBUF == 3, "the load stream runs up to two stages ahead of the compute");
+  static_assert(NBUF == 3, "the waits for a stage are spelled out for up to two behind it");
   uint32_t ring = 0;  // ring slot of the stage to be computed next
   int issued = 0;     // stages of the current item whose loads are under way, at most NBUF - 1 when it begins
   auto ring_slot = [](uint32_t r) { return r >= NBUF ? r - NBUF : r; };
@@ -469,7 +465,7 @@ __global__ void __launch_bounds__(256, (DT == SKIPKV_BF16 ? 2 : 1)) k_scan_fused
           // every time, or read all of them first and run out of registers).
           // Step i < NSTEP multiplies slice i / NT of the head dimension into row tile i % NT, step NSTEP + j the indicator of the
           // sentences (by token) into dimensions 16 j ...
-          constexpr int AHEAD = SKIPKV_FRAG_AHEAD, NSTEP = 4 * NT, NREAD = NSTEP + (POOL ? 8 : 0);
+          constexpr int AHEAD = kFragAhead, NSTEP = 4 * NT, NREAD = NSTEP + (POOL ? 8 : 0);
           const uint32_t baddr = stage_a + b_off, taddr = stage_a + tr_off;
           const uint32_t aaddr = lds_addr(qt) + b_off;  // row 16 T + c16 of the query tile: same lane pattern as the key fragment
           bf16x8 bfr[4], afr[NSTEP];
@@ -806,7 +802,7 @@ __global__ void __launch_bounds__(256, (DT == SKIPKV_BF16 ? 2 : 1)) k_scan_fused
 #pragma unroll
       for (int k = 0; k < 2; ++k) imp[wave][(ol & 48) * 2 + 16 * k + (ol & 15)] = swap_add16(part[k], part[k + 2]) * inv_alpha;
     }
-    // imp[wave] is written and read by this wave only: no barrier, unless one of the item's sentences has several spans
+    // the wave's part of imp is written and read by it only: no barrier, unless one of the item's sentences has several spans
     if (cur.cut) lds_barrier();
     const int p_start = n_tok - min(a.protect, n_tok);
     const int64_t tok_col = (int64_t)lh * a.total_tokens + cur.tok0;
@@ -822,7 +818,7 @@ __global__ void __launch_bounds__(256, (DT == SKIPKV_BF16 ? 2 : 1)) k_scan_fused
         lo = soff[cur.sb + s_idx];
         hi = min(soff[cur.sb + s_idx + 1], p_start);
         for (int t = lo + part; t < hi; t += lanes) {
-          sum_i += (&imp[wave][0])[t - w0];  // (a sentence of several spans: on into the next waves' parts, whole but the last)
+          sum_i += (&imp[0][0] + wave * kSpanCap)[t - w0];  // (a sentence of several spans: on into the next waves' parts)
           if (a.tok_red) sum_r += a.tok_red[tok_col + t];
         }
       }
