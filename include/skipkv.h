@@ -144,9 +144,10 @@ int skipkv_workspace_bytes(const skipkv_cache *cache, const skipkv_params *param
  * The key scan reads K once where it can (query rows n * obs_window <= 64 after padding, no
  * sentence longer than 512 tokens, at most 256 work items of up to 512 tokens per sequence, i.e.
  * about 120000 tokens; and where sentences of more than 128 tokens, which are cut into spans of 128
- * within one item, do not leave the items less than about 45 % full) and twice otherwise.  Its single-pass form is a persistent grid that must
- * have the GPU's compute units to itself (work of other streams running at the same time can
- * only be waited out).  It waits across workgroups; the wait is bounded (params->spin_limit): on
+ * within one item, leave the items of a long sequence about 45 % full or more, and those of any
+ * sequence 31 % in fp32 calls of more than 400000 keys) and twice otherwise.  Its single-pass form
+ * is a persistent grid that must have the GPU's compute units to itself (work of other streams
+ * running at the same time can only be waited out).  It waits across workgroups; the wait is bounded (params->spin_limit): on
  * expiry SKIPKV_DEV_TIMEOUT is OR-ed into dev_status, every later wait of the call gives up at
  * once, and the heads concerned are flagged and done again by the two-pass kernels that follow in
  * the stream: the call completes with valid results, only slower (the bit tells the caller that the

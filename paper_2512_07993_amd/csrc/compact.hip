@@ -278,7 +278,7 @@ __global__ void __launch_bounds__(512) k_compact_steps(CompactArgs a, int step_r
   if (!x.valid) return;
   const int nl = x.nl, at_byte = (int)(blockIdx.x % NS) * SL;
   if (__builtin_expect(nl < step_rows, false)) {
-      if (wave < SL / SHORT) move_slice<ROWB, SHORT, PAGED, false>(x, x.base + at_byte + wave * SHORT, lane);
+    if (wave < SL / SHORT) move_slice<ROWB, SHORT, PAGED, false>(x, x.base + at_byte + wave * SHORT, lane);
     return;
   }
 

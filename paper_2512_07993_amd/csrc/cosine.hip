@@ -16,7 +16,8 @@
 // maxima are only there for tiles on the diagonal or at the end, by wave-uniform branches.  Blocks of 64 columns, fetched
 // through 32 registers and padded in LDS, left room for three waves per SIMD and met bank conflicts in 40 % of the LDS
 // cycles; blocks of 32 columns, swizzled, in two buffers (32 KB) leave room for four: 48 layers x 8 heads, 4 x 1650 sentences
-// 1590 -> 1410 us, 32 x 8, 16 x 460 500 -> 440.  The same with three buffers and three waves was 2 % slower than before.
+// 1590 -> 1410 us, 32 x 8, 16 x 460 525 -> 473 on one box, 500 -> 440 on another (460 to 500 in most runs, by what ran before).  The same
+// with three buffers and three waves was 2 % slower than before.
 #include "scan_dev.h"
 
 namespace skipkv {

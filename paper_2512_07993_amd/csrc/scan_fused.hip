@@ -66,12 +66,11 @@
 //     15.9 vector instructions per token (32 layers x 8 heads, 16 sequences of 2-16 K tokens, 64 rows: 2815 -> 2490 us);
 //   - all record loads are waited for before the second barrier, where they have long arrived: the compiler, which does not see
 //     the key loads, otherwise waits for the records' registers in the next first phase, and so for the keys in flight
-//     (28 layers x 4 heads, 64 sequences of 4-8 K, 56 rows: 3200 -> 2860 us; 3560 before all of this).
-//
-//   - With the keys always the same few rows, which need not cross the chip, the kernel takes 2170 us of 2430: the rest is the
-//     fabric, which carries some 14 GB per call.  One look at a head's records costs 8 % of an item's keys, so there is one
-//     before the wait instead of two, waves without so many records load from one place, and only what is missing is looked for
-//     again (2480 -> 2400 us and, the second shape, 2860 -> 2770).
+//     (28 layers x 4 heads, 64 sequences of 4-8 K, 56 rows: 3200 -> 2860 us; 3560 before all of this);
+//   - with the keys always the same few rows, which need not cross the chip, the kernel takes 2170 us of 2430: nine tenths are its own
+//     instructions and exchanges, one tenth is what keys and records add by crossing the chip.  One look at a head's records
+//     costs 8 % of an item's keys, so there is one before the wait instead of two, waves without so many records load from
+//     one place, and only what is missing is looked for again (2480 -> 2400 us and, the second shape, 2860 -> 2770).
 // Measured without a gain: statistics of a stage issued among the products of the next one; fragments read 4, 6 or 8 products
 // ahead (6: one stream of reads for both kinds of products); the items of a head on one XCD (3 % slower to 1 % faster); keys
 // loaded past the caches (5 % slower).

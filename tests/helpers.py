@@ -1,7 +1,7 @@
 """Shared plumbing of the GPU parity tests: run the library on a workload, run the oracle on
 single heads of the same bits, and compare to the stated bar.
 
-Bar (from the benchmark spec): scores within rel 1e-3; kept-sentence sets identical
+Bar: scores within rel 1e-3; kept-sentence sets identical
 except at near-ties (relative score gap < 1e-4 at the cut, counted and reported);
 kept indices, lengths, remapped offsets and compacted K/V bit-exact."""
 from __future__ import annotations

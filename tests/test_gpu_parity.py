@@ -39,7 +39,7 @@ def test_config1_separate_calls_match_fused():
 
 
 def test_config2_llama8b_single_full_size():
-    """Config 2 as the benchmark spec gives it (all 32 layers): 16 heads against the oracle, all 256 heads against
+    """Config 2 with all 32 layers: 16 heads against the oracle, all 256 heads against
     the definition-level checks."""
     stats = _run_and_compare(W.CONFIGS[2], 16, seed=2, all_heads=True)
     assert stats["all_heads_checked"] == 256
